@@ -367,11 +367,12 @@ def tolerance(case):
     """About four times what the present kernels differ by from themselves with the model's width and its FFN width
     permuted (the same function, every sum in another order): hidden states and cached rows 3e-3 (two layers) to 8e-3
     (four), largest 4e-2; confidences, margins and probabilities 1e-3 to 2e-3, largest 1e-2; one layer 1e-3, largest 2e-2;
-    fp32 3e-6, largest 1.3e-5.  No decision differed."""
+    fp32 3e-6, largest 1.3e-5, but its confidences 2.5e-5, largest 9e-5, from the same softmax in 64 bits: a sum of 32000
+    exponentials in one order loses the ones below half a unit of the sum.  No decision differed."""
     if case["kind"] == "subgraph":
         return "exact"
     if case["dtype"] == "f32":
-        return {"rel": 1.2e-5, "max": 1e-4, "differ": 0.005}
+        return {"rel": 1e-4, "max": 4e-4, "differ": 0.005}
     if case["kind"] == "layer":
         return {"rel": 5e-3, "max": 0.08}
     if case["hidden"]:
