@@ -56,7 +56,7 @@ bool head_shape_ok(const spiffy_model_cfg* c) {
   return mfma_lmhead_partials_per_row(c->vocab) <= 2048;
 }
 
-// generic attention keeps all scores of one row in LDS
+// Limit on the cached keys of the shapes without the MFMA attention: what one row's scores may take in LDS
 size_t generic_attn_smem(const spiffy_model_cfg* c, int B, int P) {
   const int hd = c->head_dim;
   const int nchunk = 256 / hd > 0 ? 256 / hd : 1;
@@ -93,8 +93,11 @@ LayerWs carve_layer(const spiffy_model_cfg* c, int G, int B, int P, void* base, 
   w.attn = cv.take(M * (size_t)c->n_q_heads * c->head_dim * es);
   w.h = cv.take(M * c->d * es);
   w.act = cv.take(M * c->ffn * es);
-  w.attn_partial = cv.take(layer_mfma(c) ? mfma_attn_partial_bytes(G, B, c->n_q_heads, c->head_dim, P + S_seq) : 0);
-  w.attn_partial_seq = cv.take(layer_mfma(c) && S_seq ? mfma_attn_partial_bytes(1, S_seq, c->n_q_heads, c->head_dim, P + B + S_seq) : 0);
+  w.attn_partial = cv.take(layer_mfma(c) ? mfma_attn_partial_bytes(G, B, c->n_q_heads, c->head_dim, P + S_seq)
+                                         : tile_attn_scratch_bytes(B, c->head_dim));
+  w.attn_partial_seq = cv.take(!S_seq ? 0
+                               : layer_mfma(c) ? mfma_attn_partial_bytes(1, S_seq, c->n_q_heads, c->head_dim, P + B + S_seq)
+                                               : tile_attn_scratch_bytes(S_seq, c->head_dim));
   w.splitk = cv.take(layer_mfma(c) ? sizeof(float) * 4 * M * c->d : 0);   // up to 4 K slices of [M,d] fp32
   w.gat_attn = cv.take(M * (size_t)c->n_q_heads * c->head_dim * es);
   w.gat_x = cv.take(M * c->d * es);
@@ -110,7 +113,9 @@ struct HeadWs {
   TopPartial *part, *part2, *row_top;
   float* cand_val;       // top-K refinement candidates [B][SPIFFY_MAX_TOPK][SPIFFY_MAX_TOPK]
   int32_t* cand_idx;
-  int m_cap, n_part;
+  int m_cap;
+  int n_part;            // MFMA head: summaries of 128 tokens each (the top-K refinement reads them); otherwise 0
+  int n_part_tile;       // head of the other shapes: parts of the vocabulary
   size_t bytes;
 };
 HeadWs carve_head(const spiffy_model_cfg* c, int G, int B, void* base) {
@@ -122,8 +127,16 @@ HeadWs carve_head(const spiffy_model_cfg* c, int G, int B, void* base) {
   w.row_idx = (int32_t*)cv.take(sizeof(int32_t) * w.m_cap);
   w.count = (int32_t*)cv.take(sizeof(int32_t) * 4);
   w.nf = cv.take((size_t)w.m_cap * c->d * esize(c->dtype));
-  w.part = (TopPartial*)cv.take(sizeof(TopPartial) * (size_t)w.n_part * w.m_cap);
+  // Other shapes: up to 512 parts (two workgroups per CU), of at least one 64-token tile; fewer when the scratch of the
+  // allocation-free entry point, sized for heads without summaries, would not hold them: then the 16 rows of part2 serve.
+  w.n_part_tile = head_mfma(c) ? 0 : cdiv(c->vocab, 64) < 512 ? cdiv(c->vocab, 64) : 512;
+  const size_t rest = sizeof(TopPartial) * (size_t)(kLmheadCombineSlices + 1) * w.m_cap + 8 * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK + 2048;
+  const bool in_part2 = M <= SPIFFY_STATIC_MAX_ROWS && w.n_part_tile > kLmheadCombineSlices &&
+                        cv.off + rest + sizeof(TopPartial) * (size_t)w.n_part_tile * w.m_cap > (size_t)SPIFFY_STATIC_SCRATCH_BYTES;
+  if (in_part2) w.n_part_tile = kLmheadCombineSlices;
+  w.part = (TopPartial*)cv.take(in_part2 ? 0 : sizeof(TopPartial) * (size_t)(w.n_part + w.n_part_tile) * w.m_cap);
   w.part2 = (TopPartial*)cv.take(sizeof(TopPartial) * (size_t)kLmheadCombineSlices * w.m_cap);
+  if (in_part2) w.part = w.part2;
   w.row_top = (TopPartial*)cv.take(sizeof(TopPartial) * w.m_cap);
   w.cand_val = (float*)cv.take(sizeof(float) * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK);
   w.cand_idx = (int32_t*)cv.take(sizeof(int32_t) * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK);
@@ -253,7 +266,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   g.Nseg[0] = qd; g.Nseg[1] = kvd; g.Nseg[2] = kvd;
   g.N = qd + 2 * kvd; g.C = ws.qkv; g.ldc = g.N; g.scale = 1.f;
   const bool mf_qkv = mf && mfma_gemm_supported(EPI_STORE, g);
-  if ((rc = dev(mf_qkv ? mfma_rows(EPI_STORE, g) : launch_gemm_generic(dt, EPI_STORE, g, st)))) return rc;
+  if ((rc = dev(mf_qkv ? mfma_rows(EPI_STORE, g) : launch_gemm_tile(dt, EPI_STORE, g, st)))) return rc;
 
   AttnArgs a;
   a.qkv = ws.qkv; a.prefix_k = prefix->k; a.prefix_v = prefix->v; a.out = ws.attn; a.partial = ws.attn_partial;
@@ -310,7 +323,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
     }
   }
   if (!(S_seq && mfa) &&      // with rows riding along, the MFMA path runs both groups in one launch below
-      (rc = dev(mfa ? launch_attn_mfma(a, st) : launch_attn_generic(dt, a, st))))
+      (rc = dev(mfa ? launch_attn_mfma(a, st) : launch_attn_tile(dt, a, st))))
     return rc;
   if (S_seq) {      // the suffix rows: queries at positions pos0+B .., keys = cache rows 0 .. P+B+S_seq-1, no block of their own
     const size_t es = esize(dt);
@@ -325,7 +338,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
     }
     if (mfa) {       // (b differs from a in row counts and lengths only)
       if ((rc = dev(launch_attn_mfma_pair(a, b, st)))) return rc;
-    } else if ((rc = dev(launch_attn_generic(dt, b, st)))) return rc;
+    } else if ((rc = dev(launch_attn_tile(dt, b, st)))) return rc;
   }
 
   // Masked rows only (last layer): from here on row r of every matrix is row ws.rows[r] of the block rows, r < *ws.count.
@@ -360,7 +373,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
         return rc;
       normed = true;
     } else if ((rc = dev(mfma_rows(EPI_RESID, g)))) return rc;
-  } else if ((rc = dev(launch_gemm_generic(dt, EPI_RESID, g, st)))) return rc;
+  } else if ((rc = dev(launch_gemm_tile(dt, EPI_RESID, g, st)))) return rc;
 
   if (!normed && (rc = dev(launch_rmsnorm(dt, ws.h, w->norm2, cfg->rms_eps, M, d, nullptr, n_rows, ws.n, st))))
     return rc;
@@ -369,7 +382,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   g.A = ws.n; g.lda = d; g.M = M; g.M_dev = n_rows; g.K = d; g.W[0] = w->w_gate; g.W[1] = w->w_up; g.N = cfg->ffn;
   g.C = ws.act; g.ldc = cfg->ffn; g.scale = 1.f;
   if ((rc = dev(mf && mfma_gemm_supported(EPI_SWIGLU, g) ? mfma_rows(EPI_SWIGLU, g)
-                                                          : launch_gemm_generic(dt, EPI_SWIGLU, g, st))))
+                                                          : launch_gemm_tile(dt, EPI_SWIGLU, g, st))))
     return rc;
 
   // down projection + residual; compacted rows go back to their places in hidden_out (by the reduction when K is
@@ -388,7 +401,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
                                       ng ? ws.n : nullptr, M, d, st, n_rows, cm ? ws.rows : nullptr));
     }
     if ((rc = dev(mfma_rows(EPI_RESID, g)))) return rc;
-  } else if ((rc = dev(launch_gemm_generic(dt, EPI_RESID, g, st)))) return rc;
+  } else if ((rc = dev(launch_gemm_tile(dt, EPI_RESID, g, st)))) return rc;
   if (cm) return dev(launch_scatter_rows(ws.gat_x, (size_t)d * esize(dt), ws.rows, ws.count, M, hidden_out, st));
   return SPIFFY_OK;
 }
@@ -403,6 +416,7 @@ int run_head(const spiffy_model_cfg* cfg, const void* hidden, const void* final_
   if ((rc = dev(launch_compact_rows(tokens, mask, cfg->mask_id, M, ws.row_idx, ws.count, st)))) return rc;
   if ((rc = dev(launch_rmsnorm(dt, hidden, final_norm, cfg->rms_eps, M, cfg->d, ws.row_idx, ws.count, ws.nf, st))))
     return rc;
+  int n_part = ws.n_part;
   if (head_mfma(cfg)) {
     GemmArgs g;
     std::memset(&g, 0, sizeof(g));
@@ -410,12 +424,13 @@ int run_head(const spiffy_model_cfg* cfg, const void* hidden, const void* final_
     g.W[0] = w_vocab; g.Nseg[0] = cfg->vocab; g.N = cfg->vocab;
     g.C = ws.part; g.ldc = ws.m_cap; g.scale = logit_scale;
     if ((rc = dev(launch_gemm_mfma(EPI_LMHEAD, g, st)))) return rc;
-    if ((rc = dev(launch_lmhead_combine(ws.part, ws.n_part, ws.m_cap, ws.count, M, ws.part2, ws.row_top, st)))) return rc;
   } else {
-    if ((rc = dev(launch_lmhead_generic(dt, ws.nf, w_vocab, cfg->d, cfg->vocab, logit_scale, ws.count, M,
-                                        ws.row_top, st))))
+    n_part = ws.n_part_tile;
+    if ((rc = dev(launch_lmhead_tile(dt, ws.nf, w_vocab, cfg->d, cfg->vocab, logit_scale, ws.count, M, ws.m_cap, n_part,
+                                     ws.part, st))))
       return rc;
   }
+  if ((rc = dev(launch_lmhead_combine(ws.part, n_part, ws.m_cap, ws.count, M, ws.part2, ws.row_top, st)))) return rc;
   return dev(launch_head_finalize(ws.row_top, ws.row_idx, ws.count, tokens, mask, cfg->mask_id, G, B, threshold,
                                   force_one, argmax, conf, unmask, margin, target, st));
 }
@@ -589,7 +604,7 @@ int spiffy_gemm(int32_t dtype, int32_t epilogue, const void* A, const void* W0, 
       return dev(launch_splitk_reduce((const float*)workspace, ks, R, C, nullptr, 0.f, nullptr, M, N, st));
     }
   }
-  return dev(mf ? launch_gemm_mfma(epilogue, g, st) : launch_gemm_generic(dtype, epilogue, g, st));
+  return dev(mf ? launch_gemm_mfma(epilogue, g, st) : launch_gemm_tile(dtype, epilogue, g, st));
 }
 
 int spiffy_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t with_workspace,

@@ -5,14 +5,15 @@
 
 namespace spiffy {
 
-// ---- generic (any shape, T = float or bf16 storage, fp32 math) ---------------------------------
+// ---- any shape, T = float or bf16 storage -----------------------------------------------------
 hipError_t launch_embed(int dtype, const void* w_embed, const int32_t* tokens, int M, int d, int V,
                         void* out, hipStream_t st);
 // out[r,:] = rmsnorm(x[src(r),:]) * gain, src(r) = row_idx ? row_idx[r] : r, rows r < *n_rows_dev
 // (or < M when n_rows_dev is NULL).
 hipError_t launch_rmsnorm(int dtype, const void* x, const void* gain, float eps, int M, int d,
                           const int32_t* row_idx, const int32_t* n_rows_dev, void* out, hipStream_t st);
-hipError_t launch_gemm_generic(int dtype, int epi, const GemmArgs& a, hipStream_t st);
+// EPI_STORE / EPI_RESID / EPI_SWIGLU, K and lda multiples of 8 (16-byte aligned rows)
+hipError_t launch_gemm_tile(int dtype, int epi, const GemmArgs& a, hipStream_t st);
 // a_out[r,:] = a[row_idx[r],:] and b_out[r,:] = b[row_idx[r],:] for r < *count; row sizes in bytes, multiples of 16
 hipError_t launch_scatter_rows(const void* in, size_t row_bytes, const int32_t* row_idx, const int32_t* count, int M,
                                void* out, hipStream_t st);     // out[row_idx[r],:] = in[r,:] for r < *count
@@ -25,15 +26,16 @@ struct AttnArgs {
   const void* prefix_k;  // [Hkv,P,hd]
   const void* prefix_v;
   void* out;             // [M, Hq*hd]
-  void* partial;         // MFMA path: split partials (fp32)
+  void* partial;         // MFMA path: rotary table and split partials (fp32); otherwise the rotary table
   int G, B, Hq, Hkv, hd, P, pos0;
   int ldp;               // rows allocated per KV head in prefix_k / prefix_v (0 = P)
   int S;                 // dual cache: rows P+B .. P+B+S-1 of the same arrays hold the tokens after the block
   int own;               // 1: every state also attends to its own B rows (keys / values from qkv); 0: cache rows only
   float rope_base;
-  int rope_ready;        // MFMA path: the rotary table at the start of `partial` is already filled
+  int rope_ready;        // the rotary table at the start of `partial` is already filled
 };
-hipError_t launch_attn_generic(int dtype, const AttnArgs& a, hipStream_t st);
+size_t tile_attn_scratch_bytes(int B, int hd);
+hipError_t launch_attn_tile(int dtype, const AttnArgs& a, hipStream_t st);
 // Prefix-cache extension (Sec. 3.1): the K rows (rotated at positions pos0 .. pos0+B-1) and V rows of the
 // first B rows of the fused qkv activations go to rows P .. P+B-1 of every KV head of the cache
 // ([Hkv][ldp][hd]).  Must run before the attention of the same layer reads the cache only up to row P.
@@ -47,10 +49,9 @@ hipError_t launch_kv_append(int dtype, const void* qkv, int Hq, int Hkv, int hd,
 // masked-row list: row_idx[0..count) = flattened (g,b) with mask set, ascending; *count.
 hipError_t launch_compact_rows(const int32_t* tokens, const uint8_t* mask, int mask_id, int M,
                                int32_t* row_idx, int32_t* count, hipStream_t st);
-// per compacted row r: summary over the whole vocabulary of scale * (n[r,:] . w_vocab[v,:])
-hipError_t launch_lmhead_generic(int dtype, const void* n, const void* w_vocab, int d, int V,
-                                 float scale, const int32_t* count, int M, TopPartial* row_top,
-                                 hipStream_t st);
+// summaries of scale * (n[r,:] . w_vocab[v,:]) over n_part parts of the vocabulary, rows r < *count: part[n_part][m_cap]
+hipError_t launch_lmhead_tile(int dtype, const void* n, const void* w_vocab, int d, int V, float scale, const int32_t* count,
+                              int M, int m_cap, int n_part, TopPartial* part, hipStream_t st);
 // merge n_part partials per row; part is [n_part][m_cap]; tmp is [kLmheadCombineSlices][m_cap] scratch
 constexpr int kLmheadCombineSlices = 16;
 hipError_t launch_lmhead_combine(const TopPartial* part, int n_part, int m_cap, const int32_t* count, int M,

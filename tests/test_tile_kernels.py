@@ -1,0 +1,101 @@
+"""GEMM, LM head and attention of the shapes off the bf16 matrix-core path, at the edges of their tiles and remainders."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import cfg_kw, np_weights, to_np
+from paper_2509_18085_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def sp():
+    from paper_2509_18085_amd import spiffy
+    return spiffy
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (16, 16, 32), (17, 24, 40), (33, 40, 136), (64, 8, 1032), (65, 1032, 72),
+                                   (130, 6008, 264), (128, 2816, 1024)])
+def test_tile_gemm_edges(sp, M, N, K, dtype):
+    """Against the float64 product.  |fp32 sum - exact| <= (K + 16) 2^-24 sum |a w| whatever the order; the residual, the
+    activation (a few units of exp and division, |silu'| <= 1.1) and, in bf16, one final rounding of half a unit in the last of 8 significand bits, 2^-8, are added."""
+    if dtype == "bf16" and N % 64 == 0 and K % 64 == 0:
+        N += 8                                       # keep it off the MFMA kernel
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(M * 1000 + N + K)
+    A, W0, W1, R = ((torch.randn(s, generator=g) * f).to(td) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((N, K), 0.1), ((M, N), 1.0)))
+    a, w0, w1, r = to_np(A), to_np(W0), to_np(W1), to_np(R)
+    eps, out = 2.0 ** -24, 0.0 if dtype == "f32" else 1.02 * 2.0 ** -8
+    d0, d1 = (K + 16) * eps * (np.abs(a) @ np.abs(w0).T), (K + 16) * eps * (np.abs(a) @ np.abs(w1).T)
+    dev = [t.to(DEV) for t in (A, W0, W1, R)]
+    got = to_np(sp.gemm(sp.GEMM_STORE, dev[0], dev[1]))
+    ref = a @ w0.T
+    assert (np.abs(got - ref) <= d0 + (out + eps) * np.abs(ref) + 1e-30).all()
+    got = to_np(sp.gemm(sp.GEMM_RESID, dev[0], dev[1], R=dev[3]))
+    assert (np.abs(got - (ref + r)) <= d0 + (out + 2 * eps) * np.abs(ref + r) + d0 * 2 * eps + 1e-30).all()
+    got = to_np(sp.gemm(sp.GEMM_SWIGLU, dev[0], dev[1], dev[2]))
+    silu, up = ref / (1 + np.exp(-ref)), a @ w1.T
+    bound = 1.1 * d0 * np.abs(up) + d1 * np.abs(silu) + 2 * d0 * d1 + (out + (np.abs(ref) + 16) * 8 * eps) * np.abs(silu * up)
+    assert (np.abs(got - silu * up) <= bound + 1e-30).all()
+
+
+def test_tile_gemm_rows_do_not_depend_on_the_batch(sp):
+    g = torch.Generator().manual_seed(5)
+    A, W = torch.randn((200, 520), generator=g).to(DEV), torch.randn((6008, 520), generator=g).to(DEV)
+    full = sp.gemm(sp.GEMM_STORE, A, W)              # 64 x 64 tiles
+    for n in (1, 16, 40):
+        assert torch.equal(sp.gemm(sp.GEMM_STORE, A[:n].contiguous(), W), full[:n])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("hd,Hq,Hkv,B,P,S", [(8, 2, 2, 1, 0, 0), (24, 6, 2, 5, 3, 0), (64, 4, 1, 16, 15, 0), (72, 2, 1, 7, 130, 9),
+                                             (136, 1, 1, 17, 16, 0), (200, 3, 3, 3, 1, 40), (256, 2, 1, 9, 70, 1)])
+def test_tile_attention_edges(sp, hd, Hq, Hkv, B, P, S, dtype):
+    """One layer against the oracle at the head sizes and key counts where fragments and chunks are cut short."""
+    from oracle import spiffy_oracle as O
+    cfg = synth.CONFIGS["c1"].scaled(dtype=dtype, d=96, Hq=Hq, Hkv=Hkv, hd=hd, F=72, P=P, B=B, G=3)
+    w = synth.layer_weights(cfg, 0, bias=True)
+    for k in ("wq", "wk", "wv", "wo", "w_gate", "w_up", "w_down"):
+        w[k] = (w[k].float() * 4).to(w[k].dtype)
+    g = torch.Generator().manual_seed(hd)
+    k, v = (torch.randn((Hkv, P + B + S, hd), generator=g).to(w["wq"].dtype) for _ in range(2))
+    x = synth.hidden_states(cfg)
+    scfg = sp.cfg_from_synth(cfg)
+    ws = sp.alloc_workspace(scfg, cfg.G, B, P + S, DEV)
+    out = sp.verify_layer(scfg, sp.layer_weights({n: t.to(DEV) for n, t in w.items()}),
+                          sp.prefix_kv(k.to(DEV), v.to(DEV), P, S), x.to(DEV), P, ws)
+    kn, vn = to_np(k), to_np(v)
+    kw = dict(suffix_k=kn[:, P + B:], suffix_v=vn[:, P + B:]) if S else {}
+    ref = O.verify_layer(np_weights(w), kn[:, :P], vn[:, :P], to_np(x), **cfg_kw(cfg), **kw)
+    err = np.max(np.abs(to_np(out) - ref) / (np.abs(ref) + np.sqrt(np.mean(ref * ref))))
+    assert err < (1e-4 if dtype == "f32" else 2e-2), err      # the bars of test_gpu_parity
+
+
+@pytest.mark.parametrize("d,V,G,B", [(8, 63, 1, 1), (40, 65, 2, 9), (72, 64, 3, 16), (256, 1000, 5, 13), (264, 33000, 3, 24),
+                                     (16000, 3200, 4, 32)])       # the last: barely inside the static scratch
+def test_tile_head_edges(sp, d, V, G, B):
+    """fp32 head, every position masked, against a float64 softmax: logit error <= (d + 8) 2^-24 sum |x w|."""
+    cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B)
+    g = torch.Generator().manual_seed(V)
+    x, gain, w = torch.randn((G, B, d), generator=g), torch.ones(d), torch.randn((V, d), generator=g) * 0.3
+    tok = torch.full((G, B), cfg.mask_id, dtype=torch.int32)
+    scfg = sp.cfg_from_synth(cfg)
+    ws = sp.alloc_workspace(scfg, G, B, 0, DEV)
+    got = sp.decode_head(scfg, x.to(DEV), gain.to(DEV), w.to(DEV), tok.to(DEV), 0.5, ws, force_one=False)
+    if G * B <= sp.STATIC_MAX_ROWS:
+        out = {k: torch.empty_like(t) for k, t in got.items()}
+        sp.decode_head_static(scfg, x.to(DEV), gain.to(DEV), w.to(DEV), tok.to(DEV), 0.5, out, force_one=False)
+        assert torch.equal(out["argmax"], got["argmax"]) and torch.allclose(out["conf"], got["conf"], rtol=1e-5)
+    xn = to_np(x).reshape(-1, d)
+    n = xn / np.sqrt((xn ** 2).mean(-1, keepdims=True) + 1e-5)
+    logit = n @ to_np(w).T
+    tie = 2 * (d + 16) * 2.0 ** -24 * (np.abs(n) @ np.abs(to_np(w)).T).max()
+    top = np.sort(logit, -1)[:, ::-1]
+    clear = top[:, 0] - top[:, 1] > tie             # the bound is a worst case: over 16000 terms it exceeds some margins
+    am = got["argmax"].cpu().numpy().reshape(-1)
+    assert clear.mean() > 0.5 and (am[clear] == logit.argmax(-1)[clear]).all()
+    conf = 1.0 / np.exp(logit - top[:, :1]).sum(-1)
+    np.testing.assert_allclose(to_np(got["conf"]).reshape(-1), conf, rtol=tie + V * 2.0 ** -24)
