@@ -8,12 +8,14 @@
 // whose four lane groups read 64 contiguous bytes of a row, so nothing is staged in LDS: every wavefront loads fragments
 // straight into a ring of DEPTH register buffers.  Eight wavefronts share one output tile and split K (chunk c of 128
 // bytes, a whole line of each row, goes to wavefront c % 8), which puts eight times as many loads in flight per tile;
-// their sums are added in wavefront order through LDS.  The K order of an element depends on K alone, not on the tile or
+// their sums are added through LDS as a fixed tree.  The K order of an element depends on K alone, not on the tile or
 // on M, so a row's result does not depend on the rows computed with it.
 //
 // Measured, against a 64x64-tile kernel on vector FMAs with scalar loads (and, for the head, one workgroup per row that
 // streamed the whole vocabulary matrix): bf16, 128 rows, width 1024, FFN 2816: QKV 334 -> 8.8 us (three launches -> one),
 // gate/up 208 -> 14.4, down 302 -> 9.9.  fp32, 39 of 64 rows against 32000 tokens x 1024: 44 ms -> 64 us.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace spiffy {
@@ -65,13 +67,24 @@ __device__ __forceinline__ void tile_product(const T* const (&arow)[TM], const T
     load_half(buf, 0, k);
     load_half(buf, 1, k + KC);
   };
-  auto product_half = [&](int buf, int h) {
+  // fp32: a chunk's products are summed on their own and then added, so that the long sum along K is rounded once a chunk
+  // and wavefront (a layer of width 1024 against 64 bits: 5.0e-7 with one chain, 3.0e-7 so; no measurable time)
+  auto product = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = mma(acc[i][j], fa[buf][h][i], fw[buf][h][j]);
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (std::is_same<T, float>::value) {
+          f32x4 c = mma(f32x4{0.f, 0.f, 0.f, 0.f}, fa[buf][0][i], fw[buf][0][j]);
+          c = mma(c, fa[buf][1][i], fw[buf][1][j]);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[i][j][v] += c[v];
+        } else {
+          acc[i][j] = mma(acc[i][j], fa[buf][0][i], fw[buf][0][j]);
+          acc[i][j] = mma(acc[i][j], fa[buf][1][i], fw[buf][1][j]);
+        }
+      }
   };
-  auto product = [&](int buf) { product_half(buf, 0); product_half(buf, 1); };
   // whole chunks of this wavefront; every branch is wavefront-uniform
   const int whole = K / (2 * KC), n = whole > wave ? (whole - wave + NW - 1) / NW : 0;
 #pragma unroll
@@ -112,6 +125,14 @@ __device__ __forceinline__ void tile_product(const T* const (&arow)[TM], const T
     product(0);
   }
 }
+
+// the eight wavefronts' sums of one element, stride floats apart, added as a tree (fewer roundings at full size)
+__device__ __forceinline__ float wave_sums(const float* p, int stride) {
+  const float a = (p[0] + p[stride]) + (p[2 * stride] + p[3 * stride]);
+  const float b = (p[4 * stride] + p[5 * stride]) + (p[6 * stride] + p[7 * stride]);
+  return a + b;
+}
+static_assert(NW == 8, "wave_sums adds eight");
 
 // C tile of 16*TM rows x 16*TN columns (SWIGLU: TN/2 fragments of gate rows and the same rows of up)
 template <typename T, int EPI, int TM, int TN, int DEPTH>
@@ -159,13 +180,9 @@ __global__ __launch_bounds__(64 * NW) void tile_gemm_kernel(GemmArgs a) {
       const int j = e >> 8, q = e & 255, el = q & 63;
       const int m = m0 + 16 * i + 4 * (el >> 4) + (q >> 6), n = n0 + 16 * j + (el & 15);
       if (m >= m_max || n >= a.N) continue;
-      float s = red[0][j][q];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) s += red[w][j][q];
+      float s = wave_sums(&red[0][j][q], TN * RSTRIDE);
       if (EPI == EPI_SWIGLU) {
-        float u = red[0][j + NO][q];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) u += red[w][j + NO][q];
+        const float u = wave_sums(&red[0][j + NO][q], TN * RSTRIDE);
         s = s / (1.f + __expf(-s)) * u;
       }
       if (has_bias) {
@@ -212,9 +229,7 @@ __device__ __forceinline__ void head_tiles(const T* n, const T* wv, int d, int V
       for (int p = 0; p < 2; ++p) {
         const int m = wave * 2 + p;                // row within the fragment: element (m, token) of the tile
         const int q = (m & 3) * 64 + (m >> 2) * 16 + l16;
-        float l = red[(lane >> 4) * RSTRIDE + q];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) l += red[(w * TN + (lane >> 4)) * RSTRIDE + q];
+        float l = wave_sums(red + (lane >> 4) * RSTRIDE + q, TN * RSTRIDE);
         l = idx < V ? l * scale : -INFINITY;
         const float mx = wave_max(l);
         const unsigned long long at = __ballot(l == mx);
