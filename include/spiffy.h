@@ -339,7 +339,7 @@ int spiffy_verify_step_commit(const spiffy_model_cfg *cfg, int32_t n_layers, con
  * [E,2] rows (p, q): p is a parent of q (rows with an end outside 0..N-1 are ignored).  A node is connected to a
  * set if its level is 1 or 2 or one of its parents is in the set; G' is every set of D nodes all of which are
  * connected to it; the result is the set of G' with the largest summed count, equal sums going to the smaller
- * bit mask sum_q 2^q.  Every one of the C(N, D) sets is tried; more than SPIFFY_SUBGRAPH_MAX_SETS is refused
+ * bit mask sum_q 2^q.  Every one of the C(N, D) sets is accounted for; more than SPIFFY_SUBGRAPH_MAX_SETS is refused
  * (SPIFFY_ESHAPE).  Outputs: *best_mask, *best_sum, *n_connected = |G'|, nodes_out [D] (optional) the chosen
  * nodes ascending.  When G' is empty (also D > N): mask 0, sum 0, nodes -1.  |count| must stay below 2^56 so the
  * sums cannot wrap.  All arrays and outputs are device memory; workspace (256-byte aligned) of

@@ -895,7 +895,7 @@ int spiffy_subgraph_search(const int64_t* count, const int32_t* level, int32_t N
   if (!count || !level || !best_mask || !best_sum || !n_connected || !workspace || (E > 0 && !edges))
     return SPIFFY_EINVAL;
   if (N < 1 || N > 64 || D < 1 || D > 64 || E < 0) return SPIFFY_ESHAPE;
-  // C(N, D) sets are tried one by one: refuse what would run for minutes
+  // a graph whose sets have to be tried one by one: refuse what would run for minutes
   unsigned long long total = 1;
   if (D > N) {
     total = 0;

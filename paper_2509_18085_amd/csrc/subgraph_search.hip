@@ -3,8 +3,24 @@
 //   G' = all node sets Q of size D in which every node is of level 1 or 2 or has a parent in Q
 //   G* = argmax over G' of the summed counts; equal sums go to the smaller bit mask sum_q 2^q
 //
-// Every one of the C(N, D) node sets is tried (the paper's brute force), N <= 64.  A set is a 64-bit mask
-// x; with child[p] = mask of the children of p, x is connected iff  x & ~(root | OR_{p in x} child[p]) == 0.
+// Every one of the C(N, D) node sets is accounted for (the paper's brute force tries them one by one), N <= 64.  A set
+// is a 64-bit mask x; with child[p] = mask of the children of p, x is connected iff  x & ~(root | OR_{p in x} child[p]) == 0.
+//
+// First, nodes that no connected set can hold leave the graph: neither root-level nor with a parent left, repeatedly.
+// Then the nodes are of two kinds: parents (with a child that is not root-level) and leaves (the rest).  A node's
+// parents are all of the first kind, so a choice X of parents decides everything: X must cover itself, and each leaf that
+// is root-level or a child of X may join, with no further condition.  X therefore stands for C(free leaves, D - |X|)
+// connected sets, and the best of them adds the D - |X| largest counts among its free leaves (equal counts: lower node
+// first, the smaller mask).  A thread takes one X: cover and sum from four tables of 256 entries in LDS (lanes hold
+// consecutive X: the first table is read without conflicts, the others are broadcast), a zero test, one binomial; the
+// leaves are summed only where X with the largest leaf counts of all could still beat the lane's best.  Candidate graphs
+// of 45 nodes have 10 to 25 parents: 2^10 .. 2^25 choices where C(45, 10) is 3.2e9 sets.  What is left is launch latency
+// (three launches) for few parents, vector instructions for many.  Measured, 45 nodes, sets of 10, 12 parents: 1514 -> 20.5 us
+// a call against the one-by-one search (2.1e12 sets/s).
+//
+// The one-by-one search below serves graphs with many parents and small D.  Where the line lies: a choice of parents is
+// worth about 40 vector instructions a wavefront, a tried set 12, and the tables of the one-by-one search cost as much as
+// some 4e6 sets; beyond 26 parents the choices alone take longer than 50 us.
 //
 // Work split: the nodes are cut into a low part (the h = min(N, 12) lowest nodes), a middle part (the next
 // hm <= 11) and a top part (the rest).  A one-workgroup kernel tabulates every subset of the low part (sum of
@@ -35,6 +51,23 @@ constexpr int kThreads = 1024;
 constexpr int kMaxGroups = 2048;              // (a, b) size pairs, the small ones cut into runs of low entries
 constexpr int kBinomN = 65;                    // binomials C(n, k), 0 <= n, k <= 64, saturating
 constexpr unsigned long long kSat = ~0ull;
+constexpr int kMaxParents = 26;                // most parents whose choices are enumerated
+constexpr unsigned long long kFewSets = 1ull << 22;
+
+// binomial coefficients, built by the compiler; those that do not fit 64 bits stick at the maximum
+struct Binomials {
+  unsigned long long v[kBinomN * kBinomN];
+  constexpr Binomials() : v() {
+    for (int n = 0; n < kBinomN; ++n)
+      for (int k = 0; k < kBinomN; ++k) {
+        if (k == 0) { v[n * kBinomN] = 1; continue; }
+        if (n == 0) { v[k] = 0; continue; }
+        const unsigned long long a = v[(n - 1) * kBinomN + k], b = v[(n - 1) * kBinomN + k - 1], sum = a + b;
+        v[n * kBinomN + k] = (a == kSat || b == kSat || sum < a) ? kSat : sum;
+      }
+  }
+};
+__device__ const Binomials kBinom{};
 
 struct __align__(16) SgEntry {
   long long sum;
@@ -51,7 +84,12 @@ struct SgWorkspace {                           // device memory, filled by the p
   SgEntry tab[(1 << kLow) + 8];                // low subsets grouped by size; spare entries for the read-ahead
   unsigned long long child[64];
   unsigned long long root;
-  unsigned long long binom[kBinomN * kBinomN];
+  // the graph that is searched: nodes renumbered, those that cannot be connected left out
+  long long cnt[64];
+  int node_of[64];                             // the caller's number of node i
+  int n;                                       // nodes left
+  int n_parents;                               // choices of parents are enumerated: nodes 0 .. n_parents-1 are the parents,
+                                               // the leaves follow by falling count; -1: node sets are enumerated
   int off[kLow + 2];                           // first table entry of each size group
   unsigned short tab_low[1 << kLow];           // the subset itself
   // middle subsets (nodes h .. h+hm-1), grouped by size: sum of counts, cover (OR of child masks), the subset
@@ -70,50 +108,99 @@ struct SgPartial {
   unsigned long long n_connected;
 };
 
-// child masks, root mask, binomial table, table of the low subsets; one workgroup
+// The graph that is searched and how; for the one-by-one search its tables too.  One workgroup.
 __global__ __launch_bounds__(kThreads) void sg_prepare_kernel(const long long* __restrict__ count,
-                                                              const int32_t* __restrict__ level, int N,
+                                                              const int32_t* __restrict__ level, int n_nodes,
                                                               const int32_t* __restrict__ edges, int E, int D,
                                                               unsigned long long n_threads, SgWorkspace* ws) {
-  __shared__ unsigned long long s_child[64];
-  __shared__ long long s_cnt[64];
-  __shared__ unsigned long long s_binom[kBinomN * kBinomN];
-  __shared__ int s_off[kLow + 2];
+  __shared__ unsigned long long s_child[64], s_par[64], s_down[64];
+  __shared__ long long s_cnt[64], s_in[64];
+  __shared__ int s_off[kLow + 2], s_new[64], s_n, s_parents;
   __shared__ unsigned long long s_root;
+  const unsigned long long* __restrict__ s_binom = kBinom.v;
   const int tid = threadIdx.x;
-  const int h = N < kLow ? N : kLow;
   if (tid < 64) {
     s_child[tid] = 0ull;
-    s_cnt[tid] = tid < N ? count[tid] : 0;
+    s_down[tid] = 0ull;
+    s_par[tid] = 0ull;
+    s_cnt[tid] = 0;
+    s_in[tid] = tid < n_nodes ? count[tid] : 0;
   }
   __syncthreads();
   for (int e = tid; e < E; e += kThreads) {
     const int p = edges[2 * e], q = edges[2 * e + 1];
-    if (p >= 0 && p < N && q >= 0 && q < N) atomicOr(&s_child[p], 1ull << q);
+    if (p >= 0 && p < n_nodes && q >= 0 && q < n_nodes) {
+      atomicOr(&s_down[p], 1ull << q);
+      atomicOr(&s_par[q], 1ull << p);
+    }
   }
+  __syncthreads();
   if (tid < 64) {
-    const bool is_root = tid < N && (level[tid] == 1 || level[tid] == 2);
-    const unsigned long long root = __ballot(is_root);
-    if (tid == 0) s_root = root;
-    const long long c = s_cnt[tid];
+    const bool is_root = tid < n_nodes && (level[tid] == 1 || level[tid] == 2);
+    const unsigned long long root_in = __ballot(is_root);
+    unsigned long long alive = n_nodes < 64 ? (1ull << n_nodes) - 1ull : ~0ull;
+    for (;;) {                                 // a round without a change ends it: at most 64 rounds
+      const unsigned long long keep = __ballot(((alive >> tid) & 1ull) && (is_root || (s_par[tid] & alive) != 0ull));
+      if (keep == alive) break;
+      alive = keep;
+    }
+    const bool in = (alive >> tid) & 1ull;
+    const unsigned long long parents = __ballot(in && (s_down[tid] & alive & ~root_in) != 0ull);
+    const unsigned long long below = (1ull << tid) - 1ull;
+    const int n = __popcll(alive);
+    int p = __popcll(parents);
+    const unsigned long long sets = D <= n ? s_binom[n * kBinomN + D] : 0ull;
+    if (p > kMaxParents || 3ull * (1ull << p) > (sets < kSat - kFewSets ? sets + kFewSets : kSat)) p = -1;
+    int at = __popcll(alive & below);          // one by one: nodes keep their order, so masks compare as before
+    if (p >= 0) {
+      if ((parents >> tid) & 1ull) {
+        at = __popcll(parents & below);
+      } else {
+        at = p;
+        const long long c = s_in[tid];
+        for (unsigned long long m = alive & ~parents; m; m &= m - 1) {
+          const int i = __ffsll((long long)m) - 1;
+          at += (s_in[i] > c || (s_in[i] == c && i < tid)) ? 1 : 0;
+        }
+      }
+    }
+    s_new[tid] = in ? at : 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // s_new: written and read by this wavefront
+    __builtin_amdgcn_wave_barrier();
+    unsigned long long ch = 0ull;
+    for (unsigned long long m = s_down[tid] & alive; m; m &= m - 1) ch |= 1ull << s_new[__ffsll((long long)m) - 1];
+    if (in) {
+      s_child[at] = ch;
+      s_cnt[at] = s_in[tid];
+      ws->node_of[at] = tid;
+    }
+    unsigned long long root = in && is_root ? 1ull << at : 0ull;
+    for (int o = 32; o >= 1; o >>= 1) root |= __shfl_xor(root, o, 64);
+    const long long c = in ? s_in[tid] : 0;
     unsigned long long mag = (unsigned long long)(c < 0 ? -c : c);
     bool small = mag < (1ull << 30);
     if (!small) mag = 0ull;
     for (int o = 32; o >= 1; o >>= 1) mag += __shfl_xor(mag, o, 64);
     const bool all_small = __ballot(!small) == 0ull;
-    if (tid == 0) ws->narrow = (all_small && mag < (1ull << 30)) ? 1 : 0;
-  }
-  // Pascal's triangle row by row; sums that do not fit 64 bits stick at the maximum
-  for (int k = tid; k < kBinomN; k += kThreads) s_binom[k] = k == 0 ? 1ull : 0ull;
-  __syncthreads();
-  for (int n = 1; n < kBinomN; ++n) {
-    if (tid < kBinomN) {
-      const unsigned long long a = s_binom[(n - 1) * kBinomN + tid], b = tid > 0 ? s_binom[(n - 1) * kBinomN + tid - 1] : 0ull;
-      const unsigned long long sum = a + b;
-      s_binom[n * kBinomN + tid] = (a == kSat || b == kSat || sum < a) ? kSat : sum;
+    if (tid == 0) {
+      ws->narrow = (all_small && mag < (1ull << 30)) ? 1 : 0;
+      ws->root = root;
+      ws->n = n;
+      ws->n_parents = p;
+      s_root = root;
+      s_n = n;
+      s_parents = p;
     }
-    __syncthreads();
   }
+  __syncthreads();
+  if (tid < 64) {
+    ws->child[tid] = s_child[tid];
+    ws->cnt[tid] = s_cnt[tid];
+  }
+  if (s_parents >= 0) return;
+  const int N = s_n;
+  const int h = N < kLow ? N : kLow;
+  const unsigned long long root = s_root;
   if (tid == 0) {
     int o = 0;
     for (int a = 0; a <= h; ++a) {
@@ -123,11 +210,7 @@ __global__ __launch_bounds__(kThreads) void sg_prepare_kernel(const long long* _
     s_off[h + 1] = o;
   }
   __syncthreads();
-  for (int i = tid; i < kBinomN * kBinomN; i += kThreads) ws->binom[i] = s_binom[i];
-  if (tid < 64) ws->child[tid] = s_child[tid];
   if (tid < kLow + 2) ws->off[tid] = tid <= h + 1 ? s_off[tid] : 0;
-  const unsigned long long root = s_root;
-  if (tid == 0) ws->root = root;
   // Low subsets grouped by size, colexicographic inside a group.  Entry of subset A: the sum of its counts and
   // the word P: above bit h the nodes A does not cover, below it the nodes of A that neither A nor a root
   // level covers.
@@ -251,7 +334,7 @@ __device__ __forceinline__ void sg_enumerate(const SgWorkspace* __restrict__ ws,
                                              unsigned long long& n_lane_out) {
   const int h = N < kLow ? N : kLow;
   const int nH = N - h;
-  const unsigned long long* __restrict__ binom = ws->binom;
+  const unsigned long long* __restrict__ binom = kBinom.v;
   const SgEntry* __restrict__ tab = ws->tab;
   const unsigned short* __restrict__ tab_low = ws->tab_low;
   const unsigned long long root = ws->root;
@@ -390,25 +473,100 @@ __device__ __forceinline__ void sg_enumerate(const SgWorkspace* __restrict__ ws,
   n_lane_out = n_lane;
 }
 
-__global__ __launch_bounds__(kThreads) void sg_search_kernel(const long long* __restrict__ count, int N, int D,
-                                                             const SgWorkspace* __restrict__ ws,
+// Choices of parents, X = gtid, gtid + nth, ..: see the top of the file.  Node numbers are the renumbered ones; the mask
+// kept as best is in the caller's numbers, so that equal sums compare as the caller sees them.
+__device__ __forceinline__ void sg_choices(const SgWorkspace* __restrict__ ws, int D, const long long* s_cnt,
+                                           const int* s_node, const unsigned long long (*t_cov)[256],
+                                           const long long (*t_sum)[256], const long long* s_top, unsigned int gtid,
+                                           unsigned int nth, long long& best, unsigned long long& bestx,
+                                           unsigned long long& n_lane) {
+  const int p = ws->n_parents, n = ws->n;
+  const unsigned long long root = ws->root;
+  const unsigned long long leaves = (n < 64 ? (1ull << n) - 1ull : ~0ull) & ~((1ull << p) - 1ull);
+  best = (long long)(1ull << 63);
+  bestx = ~0ull;
+  n_lane = 0ull;
+  for (unsigned int X = gtid; X < (1u << p); X += nth) {      // p <= 26 and nth <= 2^20: no wrap
+    const unsigned long long cov =
+        root | t_cov[0][X & 255u] | t_cov[1][(X >> 8) & 255u] | t_cov[2][(X >> 16) & 255u] | t_cov[3][X >> 24];
+    const int k = D - __popc(X);
+    unsigned long long free = cov & leaves;
+    const int f = __popcll(free);
+    if (k < 0 || k > f || (X & ~(unsigned int)cov) != 0u) continue;
+    n_lane += kBinom.v[f * kBinomN + k];
+    long long s = t_sum[0][X & 255u] + t_sum[1][(X >> 8) & 255u] + t_sum[2][(X >> 16) & 255u] + t_sum[3][X >> 24];
+    if (s + s_top[k] < best) continue;
+    unsigned long long set = X;
+    for (int i = 0; i < k; ++i) {              // leaves are numbered by falling count: the k lowest bits
+      const unsigned long long one = free & (0ull - free);
+      set |= one;
+      s += s_cnt[__ffsll((long long)one) - 1];
+      free ^= one;
+    }
+    if (s < best) continue;
+    unsigned long long x = 0ull;
+    for (; set; set &= set - 1) x |= 1ull << s_node[__ffsll((long long)set) - 1];
+    if (better(s, x, best, bestx)) {
+      best = s;
+      bestx = x;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void sg_search_kernel(int D, const SgWorkspace* __restrict__ ws,
                                                              SgPartial* __restrict__ partial) {
   __shared__ unsigned long long s_child[64];
   __shared__ long long s_cnt[64];
+  __shared__ int s_node[64];
   __shared__ SgPartial s_red[kThreads / 64];
+  __shared__ unsigned long long t_cov[4][256];     // one entry per thread
+  __shared__ long long t_sum[4][256], s_top[65];
+  static_assert(kThreads == 4 * 256, "the tables of sg_choices");
 
   const int tid = threadIdx.x;
-  if (tid < 64) {
-    s_child[tid] = ws->child[tid];
-    s_cnt[tid] = tid < N ? count[tid] : 0;
-  }
-  __syncthreads();
+  const int p = ws->n_parents;
   const unsigned long long gtid = (unsigned long long)blockIdx.x * kThreads + tid;
   const unsigned long long nth = (unsigned long long)gridDim.x * kThreads;
   long long best;
   unsigned long long bestx, n_lane;
-  if (ws->narrow) sg_enumerate<int>(ws, N, D, s_cnt, s_child, gtid, nth, best, bestx, n_lane);
-  else sg_enumerate<long long>(ws, N, D, s_cnt, s_child, gtid, nth, best, bestx, n_lane);
+  if (p >= 0 && (unsigned long long)blockIdx.x * kThreads >= (1ull << p)) {      // no choices left for this workgroup
+    if (tid == 0) partial[blockIdx.x] = SgPartial{(long long)(1ull << 63), ~0ull, 0ull};
+    return;
+  }
+  if (tid < 64) {
+    s_child[tid] = ws->child[tid];
+    s_cnt[tid] = ws->cnt[tid];
+    s_node[tid] = tid < ws->n ? ws->node_of[tid] : 0;
+  }
+  __syncthreads();
+  if (p >= 0) {
+    const int t = tid >> 8;
+    unsigned long long cov = 0ull;
+    long long sum = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if ((tid >> i) & 1 && 8 * t + i < p) {
+        cov |= s_child[8 * t + i];
+        sum += s_cnt[8 * t + i];
+      }
+    t_cov[t][tid & 255] = cov;
+    t_sum[t][tid & 255] = sum;
+    if (tid <= 64) {                           // the k largest leaf counts added up; beyond the leaves never read
+      long long top = 0;
+      for (int i = 0; i < tid && p + i < ws->n; ++i) top += s_cnt[p + i];
+      s_top[tid] = top;
+    }
+    __syncthreads();
+    sg_choices(ws, D, s_cnt, s_node, t_cov, t_sum, s_top, (unsigned int)gtid, (unsigned int)nth, best, bestx, n_lane);
+  } else {
+    if (ws->narrow) sg_enumerate<int>(ws, ws->n, D, s_cnt, s_child, gtid, nth, best, bestx, n_lane);
+    else sg_enumerate<long long>(ws, ws->n, D, s_cnt, s_child, gtid, nth, best, bestx, n_lane);
+    if (n_lane != 0ull) {                      // back to the caller's node numbers (same order)
+      unsigned long long x = 0ull;
+      for (unsigned long long m = bestx; m; m &= m - 1) x |= 1ull << s_node[__ffsll((long long)m) - 1];
+      bestx = x;
+    }
+  }
 
   const int lane = tid & 63, wave = tid >> 6;
   unsigned long long n_conn_hi = n_lane;
@@ -515,7 +673,7 @@ hipError_t launch_subgraph_search(const SubgraphArgs& a, hipStream_t st) {
   SgPartial* partial = reinterpret_cast<SgPartial*>(w + align_up(sizeof(SgWorkspace), 256));
   sg_prepare_kernel<<<1, kThreads, 0, st>>>((const long long*)a.count, a.level, a.N, a.edges, a.E, a.D,
                                             (unsigned long long)blocks * kThreads, ws);
-  sg_search_kernel<<<blocks, kThreads, 0, st>>>((const long long*)a.count, a.N, a.D, ws, partial);
+  sg_search_kernel<<<blocks, kThreads, 0, st>>>(a.D, ws, partial);
   sg_final_kernel<<<1, 64, 0, st>>>(partial, blocks, a.D, (unsigned long long*)a.best_mask, (long long*)a.best_sum,
                                     (unsigned long long*)a.n_connected, a.nodes_out);
   return hipGetLastError();

@@ -1545,6 +1545,37 @@ def test_subgraph_search_large_counts_take_the_64_bit_path(sp, scale):
         assert got == ref, (scale, D, got, ref)
 
 
+@pytest.mark.parametrize("N,parents,D,scale", [
+    (24, 20, 4, 1), (24, 21, 4, 1), (24, 21, 4, 1 << 40),      # the line between choices of parents and single sets
+    (30, 27, 3, 1), (30, 30, 3, 1 << 31),                      # every node a parent, no leaves
+    (25, 8, 4, 1), (26, 9, 4, 1 << 50), (20, 1, 5, 1), (24, 17, 5, 1)])
+def test_subgraph_search_by_number_of_parents(sp, N, parents, D, scale):
+    """Both searches against the oracle, bit for bit, by how many nodes have a child that is not root-level: a ring of
+    parents (one in three root-level), leaves with one or two of them, nodes that no set can hold, self-loops, labels in
+    no order, equal and negative counts."""
+    r = np.random.default_rng(N * 100 + parents)
+    order = [int(q) for q in r.permutation(N)]
+    par, leaf = order[:parents], order[parents:]
+    level = np.full(N, 3, np.int32)
+    level[par[::3]] = 1 + r.integers(0, 2, len(par[::3]))
+    edges = [(a, b) for a, b in zip(par, par[1:] + par[:1])] + [(q, q) for q in par if level[q] < 3]
+    for i, q in enumerate(par):
+        if level[q] > 2 and r.random() < 0.3:
+            edges.append((par[int(r.integers(parents))], q))
+        if level[par[(i + 1) % parents]] < 3:                  # its ring child is root-level: one child that is not
+            edges.append((q, leaf[0]) if leaf else (q, next(c for c in par if level[c] > 2)))
+    for i, q in enumerate(leaf):
+        if i % 4 == 1:
+            level[q] = 2
+        elif i % 4 != 3 or scale > 1:                          # else: may be without a parent
+            edges += [(par[int(r.integers(parents))], q) for _ in range(1 + i % 2)]
+    edges = np.asarray(edges, np.int32)
+    count = r.integers(-3, 12, N).astype(np.int64) * scale
+    ref = O().subgraph_search(count, level, edges, D)
+    assert ref["n_connected"] > 0
+    assert _run_subgraph(sp, count, level, edges, D) == ref
+
+
 # ------------------------------------------------------------------ the step inside a HIP graph
 
 def test_step_replays_from_a_captured_graph(sp):
