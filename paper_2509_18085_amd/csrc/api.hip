@@ -430,8 +430,9 @@ int run_head(const spiffy_model_cfg* cfg, const void* hidden, const void* final_
                                      ws.part, st))))
       return rc;
   }
-  if ((rc = dev(launch_lmhead_combine(ws.part, n_part, ws.m_cap, ws.count, M, ws.part2, ws.row_top, st)))) return rc;
-  return dev(launch_head_finalize(ws.row_top, ws.row_idx, ws.count, tokens, mask, cfg->mask_id, G, B, threshold,
+  int n_sums = 1;                                  // 1: merged in row_top; more: slices in part2
+  if ((rc = dev(launch_lmhead_combine(ws.part, n_part, ws.m_cap, ws.count, M, ws.part2, ws.row_top, &n_sums, st)))) return rc;
+  return dev(launch_head_finalize(ws.part2, n_sums, ws.m_cap, ws.row_top, ws.row_idx, ws.count, tokens, mask, cfg->mask_id, G, B, threshold,
                                   force_one, argmax, conf, unmask, margin, target, st));
 }
 

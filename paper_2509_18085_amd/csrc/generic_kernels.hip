@@ -243,21 +243,22 @@ __global__ __launch_bounds__(256) void lmhead_combine_kernel(const TopPartial* _
 }
 
 hipError_t launch_lmhead_combine(const TopPartial* part, int n_part, int m_cap, const int32_t* count, int M,
-                                 TopPartial* tmp, TopPartial* row_top, hipStream_t st) {
+                                 TopPartial* tmp, TopPartial* row_top, int* n_sums, hipStream_t st) {
   const int slices = kLmheadCombineSlices;
-  if (n_part > 2 * slices && tmp) {
-    lmhead_combine_kernel<<<dim3(cdiv(M, 64), slices), 256, 0, st>>>(part, n_part, m_cap, count, tmp);
-    lmhead_combine_kernel<<<dim3(cdiv(M, 64), 1), 256, 0, st>>>(tmp, slices, m_cap, count, row_top);
-  } else {
-    lmhead_combine_kernel<<<dim3(cdiv(M, 64), 1), 256, 0, st>>>(part, n_part, m_cap, count, row_top);
-  }
+  *n_sums = n_part > 2 * slices && tmp ? slices : 1;
+  lmhead_combine_kernel<<<dim3(cdiv(M, 64), *n_sums), 256, 0, st>>>(part, n_part, m_cap, count,
+                                                                    *n_sums > 1 ? tmp : row_top);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------
-// decisions per state (Alg. 1 steps 2-4 + threshold rule): one wavefront per state g
+// decisions per state (Alg. 1 steps 2-4 + threshold rule): one wavefront per state g.  A row's summary comes as
+// kLmheadCombineSlices parts (SLICED), merged here: a state's rows are few and its lanes read them side by side, so the
+// merge costs one round of loads where a launch of its own took 4 us (3.8 - 4.8 by the kernel trace, 32 to 128 rows).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void head_finalize_kernel(const TopPartial* __restrict__ row_top,
+template <bool SLICED>
+__global__ __launch_bounds__(64) void head_finalize_kernel(const TopPartial* __restrict__ sums, int m_cap,
+                                                           TopPartial* __restrict__ row_top,
                                                            const int32_t* __restrict__ row_idx,
                                                            const int32_t* __restrict__ count,
                                                            const int32_t* __restrict__ tok,
@@ -293,7 +294,25 @@ __global__ __launch_bounds__(64) void head_finalize_kernel(const TopPartial* __r
       float cf = 0.f, mg = INFINITY;
       uint8_t um = 0;
       if (mk) {
-        const TopPartial p = row_top[r];
+        TopPartial p;
+        if constexpr (SLICED) {                  // four chains, then their sum: the order of lmhead_combine_kernel
+          constexpr int N = kLmheadCombineSlices;
+          TopPartial part[N];
+#pragma unroll
+          for (int i = 0; i < N; ++i) part[i] = sums[(size_t)i * m_cap + r];
+          Top a = top_empty();
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            Top t4 = top_empty();
+#pragma unroll
+            for (int i = w; i < N; i += 4) t4 = top_merge(t4, Top{part[i].m, part[i].m2, part[i].s, part[i].idx});
+            a = top_merge(a, t4);
+          }
+          p = TopPartial{a.m, a.m2, a.s, a.idx};
+          row_top[r] = p;                        // the drafting source reads it
+        } else {
+          p = sums[r];
+        }
         am = p.idx;
         cf = 1.0f / p.s;
         mg = p.m - p.m2;
@@ -325,12 +344,17 @@ __global__ __launch_bounds__(64) void head_finalize_kernel(const TopPartial* __r
   }
 }
 
-hipError_t launch_head_finalize(const TopPartial* row_top, const int32_t* row_idx, const int32_t* count,
+hipError_t launch_head_finalize(const TopPartial* tmp, int n_sums, int m_cap, TopPartial* row_top,
+                                const int32_t* row_idx, const int32_t* count,
                                 const int32_t* tok, const uint8_t* mask, int mask_id, int G, int B, float threshold,
                                 int force_one, int32_t* argmax, float* conf, uint8_t* unmask, float* margin,
                                 int32_t* target, hipStream_t st) {
-  head_finalize_kernel<<<G, 64, 0, st>>>(row_top, row_idx, count, tok, mask, mask_id, B, threshold, force_one,
-                                         argmax, conf, unmask, margin, target);
+  if (n_sums > 1)
+    head_finalize_kernel<true><<<G, 64, 0, st>>>(tmp, m_cap, row_top, row_idx, count, tok, mask, mask_id, B, threshold,
+                                                 force_one, argmax, conf, unmask, margin, target);
+  else
+    head_finalize_kernel<false><<<G, 64, 0, st>>>(row_top, m_cap, nullptr, row_idx, count, tok, mask, mask_id, B,
+                                                  threshold, force_one, argmax, conf, unmask, margin, target);
   return hipGetLastError();
 }
 

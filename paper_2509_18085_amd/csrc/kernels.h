@@ -52,12 +52,14 @@ hipError_t launch_compact_rows(const int32_t* tokens, const uint8_t* mask, int m
 // summaries of scale * (n[r,:] . w_vocab[v,:]) over n_part parts of the vocabulary, rows r < *count: part[n_part][m_cap]
 hipError_t launch_lmhead_tile(int dtype, const void* n, const void* w_vocab, int d, int V, float scale, const int32_t* count,
                               int M, int m_cap, int n_part, TopPartial* part, hipStream_t st);
-// merge n_part partials per row; part is [n_part][m_cap]; tmp is [kLmheadCombineSlices][m_cap] scratch
+// merge n_part partials per row; part is [n_part][m_cap].  *n_sums = 1: one summary per row, in row_top; otherwise
+// kLmheadCombineSlices of them, in tmp [kLmheadCombineSlices][m_cap], which launch_head_finalize merges into row_top
 constexpr int kLmheadCombineSlices = 16;
 hipError_t launch_lmhead_combine(const TopPartial* part, int n_part, int m_cap, const int32_t* count, int M,
-                                 TopPartial* tmp, TopPartial* row_top, hipStream_t st);
+                                 TopPartial* tmp, TopPartial* row_top, int* n_sums, hipStream_t st);
 // scatter row summaries to [G,B] outputs, apply threshold / force_one, build next states
-hipError_t launch_head_finalize(const TopPartial* row_top, const int32_t* row_idx, const int32_t* count,
+hipError_t launch_head_finalize(const TopPartial* tmp, int n_sums, int m_cap, TopPartial* row_top,
+                                const int32_t* row_idx, const int32_t* count,
                                 const int32_t* tokens, const uint8_t* mask, int mask_id, int G, int B,
                                 float threshold, int force_one, int32_t* argmax, float* conf,
                                 uint8_t* unmask, float* margin, int32_t* target, hipStream_t st);
