@@ -413,8 +413,8 @@ int run_head(const spiffy_model_cfg* cfg, const void* hidden, const void* final_
   const int M = G * B, dt = cfg->dtype;
   const HeadWs ws = carve_head(cfg, G, B, workspace);
   int rc;
-  if ((rc = dev(launch_compact_rows(tokens, mask, cfg->mask_id, M, ws.row_idx, ws.count, st)))) return rc;
-  if ((rc = dev(launch_rmsnorm(dt, hidden, final_norm, cfg->rms_eps, M, cfg->d, ws.row_idx, ws.count, ws.nf, st))))
+  if ((rc = dev(launch_masked_rmsnorm(dt, hidden, final_norm, cfg->rms_eps, M, cfg->d, tokens, mask, cfg->mask_id,
+                                      ws.row_idx, ws.count, ws.nf, st))))
     return rc;
   int n_part = ws.n_part;
   if (head_mfma(cfg)) {

@@ -49,6 +49,10 @@ hipError_t launch_kv_append(int dtype, const void* qkv, int Hq, int Hkv, int hd,
 // masked-row list: row_idx[0..count) = flattened (g,b) with mask set, ascending; *count.
 hipError_t launch_compact_rows(const int32_t* tokens, const uint8_t* mask, int mask_id, int M,
                                int32_t* row_idx, int32_t* count, hipStream_t st);
+// the same list, and out[r,:] = RMSNorm of row row_idx[r] of x
+hipError_t launch_masked_rmsnorm(int dtype, const void* x, const void* gain, float eps, int M, int d, const int32_t* tokens,
+                                 const uint8_t* mask, int mask_id, int32_t* row_idx, int32_t* count, void* out,
+                                 hipStream_t st);
 // summaries of scale * (n[r,:] . w_vocab[v,:]) over n_part parts of the vocabulary, rows r < *count: part[n_part][m_cap]
 hipError_t launch_lmhead_tile(int dtype, const void* n, const void* w_vocab, int d, int V, float scale, const int32_t* count,
                               int M, int m_cap, int n_part, TopPartial* part, hipStream_t st);
