@@ -18,9 +18,9 @@
 // (three launches) for few parents, vector instructions for many.  Measured, 45 nodes, sets of 10, 12 parents: 1514 -> 20.5 us
 // a call against the one-by-one search (2.1e12 sets/s).
 //
-// The one-by-one search below serves graphs with many parents and small D.  Where the line lies: a choice of parents is
-// worth about 40 vector instructions a wavefront, a tried set 12, and the tables of the one-by-one search cost as much as
-// some 4e6 sets; beyond 26 parents the choices alone take longer than 50 us.
+// The one-by-one search below serves graphs with many parents and small D.  Where the line lies: beyond the launches a
+// choice of parents takes 0.7 - 0.9 ps (2^26: 60 of 79 us, 2^27: 97 of 117 us), a tried set 0.47 ps (3.2e9: 1.5 ms), and the tables of the
+// one-by-one search as much as 8e6 sets (28 us for 780 sets, what 2^22 choices take).
 //
 // Work split: the nodes are cut into a low part (the h = min(N, 12) lowest nodes), a middle part (the next
 // hm <= 11) and a top part (the rest).  A one-workgroup kernel tabulates every subset of the low part (sum of
@@ -51,8 +51,8 @@ constexpr int kThreads = 1024;
 constexpr int kMaxGroups = 2048;              // (a, b) size pairs, the small ones cut into runs of low entries
 constexpr int kBinomN = 65;                    // binomials C(n, k), 0 <= n, k <= 64, saturating
 constexpr unsigned long long kSat = ~0ull;
-constexpr int kMaxParents = 26;                // most parents whose choices are enumerated
-constexpr unsigned long long kFewSets = 1ull << 22;
+constexpr int kMaxParents = 30;                // most parents whose choices are enumerated (choices count in 32 bits)
+constexpr unsigned long long kFewSets = 1ull << 23;
 
 // binomial coefficients, built by the compiler; those that do not fit 64 bits stick at the maximum
 struct Binomials {
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void sg_prepare_kernel(const long long* _
     const int n = __popcll(alive);
     int p = __popcll(parents);
     const unsigned long long sets = D <= n ? s_binom[n * kBinomN + D] : 0ull;
-    if (p > kMaxParents || 3ull * (1ull << p) > (sets < kSat - kFewSets ? sets + kFewSets : kSat)) p = -1;
+    if (p > kMaxParents || 2ull * (1ull << p) > (sets < kSat - kFewSets ? sets + kFewSets : kSat)) p = -1;
     int at = __popcll(alive & below);          // one by one: nodes keep their order, so masks compare as before
     if (p >= 0) {
       if ((parents >> tid) & 1ull) {
@@ -486,7 +486,7 @@ __device__ __forceinline__ void sg_choices(const SgWorkspace* __restrict__ ws, i
   best = (long long)(1ull << 63);
   bestx = ~0ull;
   n_lane = 0ull;
-  for (unsigned int X = gtid; X < (1u << p); X += nth) {      // p <= 26 and nth <= 2^20: no wrap
+  for (unsigned int X = gtid; X < (1u << p); X += nth) {      // p <= 30 and nth <= 2^20: no wrap
     const unsigned long long cov =
         root | t_cov[0][X & 255u] | t_cov[1][(X >> 8) & 255u] | t_cov[2][(X >> 16) & 255u] | t_cov[3][X >> 24];
     const int k = D - __popc(X);
@@ -513,7 +513,8 @@ __device__ __forceinline__ void sg_choices(const SgWorkspace* __restrict__ ws, i
   }
 }
 
-__global__ __launch_bounds__(kThreads) void sg_search_kernel(int D, const SgWorkspace* __restrict__ ws,
+// The first n_set_blocks workgroups share the one-by-one search; all of them the choices of parents.
+__global__ __launch_bounds__(kThreads) void sg_search_kernel(int D, int n_set_blocks, const SgWorkspace* __restrict__ ws,
                                                              SgPartial* __restrict__ partial) {
   __shared__ unsigned long long s_child[64];
   __shared__ long long s_cnt[64];
@@ -526,10 +527,10 @@ __global__ __launch_bounds__(kThreads) void sg_search_kernel(int D, const SgWork
   const int tid = threadIdx.x;
   const int p = ws->n_parents;
   const unsigned long long gtid = (unsigned long long)blockIdx.x * kThreads + tid;
-  const unsigned long long nth = (unsigned long long)gridDim.x * kThreads;
+  const unsigned long long nth = (unsigned long long)(p >= 0 ? (int)gridDim.x : n_set_blocks) * kThreads;
   long long best;
   unsigned long long bestx, n_lane;
-  if (p >= 0 && (unsigned long long)blockIdx.x * kThreads >= (1ull << p)) {      // no choices left for this workgroup
+  if (p >= 0 ? (unsigned long long)blockIdx.x * kThreads >= (1ull << p) : (int)blockIdx.x >= n_set_blocks) {   // no share
     if (tid == 0) partial[blockIdx.x] = SgPartial{(long long)(1ull << 63), ~0ull, 0ull};
     return;
   }
@@ -662,18 +663,22 @@ hipError_t launch_subgraph_search(const SubgraphArgs& a, hipStream_t st) {
     if (n_cu <= 0) n_cu = 256;
     cu_of_device[dev & 63].store(n_cu, std::memory_order_release);
   }
-  // two workgroups of 16 wavefronts per compute unit, fewer when there is little to share out
-  int blocks = 2 * n_cu < subgraph_search_max_blocks() ? 2 * n_cu : subgraph_search_max_blocks();
-  const unsigned long long per_block = 64ull * kThreads;
-  if (a.total_sets < (unsigned long long)blocks * per_block)
-    blocks = (int)((a.total_sets + per_block - 1) / per_block);
-  if (blocks < 1) blocks = 1;
+  // two workgroups of 16 wavefronts per compute unit, fewer when there is little to share out: 64 sets, or four choices
+  // of parents, to a thread
+  const int most = 2 * n_cu < subgraph_search_max_blocks() ? 2 * n_cu : subgraph_search_max_blocks();
+  auto share = [&](unsigned long long work, unsigned long long per_block) {
+    const unsigned long long b = (work + per_block - 1) / per_block;
+    return b < 1 ? 1 : b < (unsigned long long)most ? (int)b : most;
+  };
+  const int set_blocks = share(a.total_sets, 64ull * kThreads);
+  const int choice_blocks = share(1ull << (a.N < kMaxParents ? a.N : kMaxParents), 4ull * kThreads);
+  const int blocks = set_blocks > choice_blocks ? set_blocks : choice_blocks;
   unsigned char* w = reinterpret_cast<unsigned char*>(a.workspace);
   SgWorkspace* ws = reinterpret_cast<SgWorkspace*>(w);
   SgPartial* partial = reinterpret_cast<SgPartial*>(w + align_up(sizeof(SgWorkspace), 256));
   sg_prepare_kernel<<<1, kThreads, 0, st>>>((const long long*)a.count, a.level, a.N, a.edges, a.E, a.D,
-                                            (unsigned long long)blocks * kThreads, ws);
-  sg_search_kernel<<<blocks, kThreads, 0, st>>>(a.D, ws, partial);
+                                            (unsigned long long)set_blocks * kThreads, ws);
+  sg_search_kernel<<<blocks, kThreads, 0, st>>>(a.D, set_blocks, ws, partial);
   sg_final_kernel<<<1, 64, 0, st>>>(partial, blocks, a.D, (unsigned long long*)a.best_mask, (long long*)a.best_sum,
                                     (unsigned long long*)a.n_connected, a.nodes_out);
   return hipGetLastError();

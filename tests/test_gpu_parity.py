@@ -1546,8 +1546,8 @@ def test_subgraph_search_large_counts_take_the_64_bit_path(sp, scale):
 
 
 @pytest.mark.parametrize("N,parents,D,scale", [
-    (24, 20, 4, 1), (24, 21, 4, 1), (24, 21, 4, 1 << 40),      # the line between choices of parents and single sets
-    (30, 27, 3, 1), (30, 30, 3, 1 << 31),                      # every node a parent, no leaves
+    (24, 22, 4, 1), (24, 23, 4, 1), (24, 23, 4, 1 << 40),      # the line between choices of parents and single sets
+    (24, 20, 1, 1), (33, 31, 3, 1), (30, 30, 3, 1 << 31),                      # every node a parent, no leaves
     (25, 8, 4, 1), (26, 9, 4, 1 << 50), (20, 1, 5, 1), (24, 17, 5, 1)])
 def test_subgraph_search_by_number_of_parents(sp, N, parents, D, scale):
     """Both searches against the oracle, bit for bit, by how many nodes have a child that is not root-level: a ring of
