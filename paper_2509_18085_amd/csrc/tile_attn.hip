@@ -23,12 +23,18 @@ namespace {
 
 constexpr int NW = 8;
 
-template <typename T> __device__ __forceinline__ f32x4 load4(const T* p);
-template <> __device__ __forceinline__ f32x4 load4<float>(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
-template <> __device__ __forceinline__ f32x4 load4<bf16_t>(const bf16_t* p) {
-  const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
+// four values as they are stored, and as fp32: a load that is to stay in flight is kept in its stored form
+template <typename T> struct Four;
+template <> struct Four<float> { typedef f32x4 type; };
+template <> struct Four<bf16_t> { typedef bf16x4 type; };
+template <typename T> __device__ __forceinline__ typename Four<T>::type load4_raw(const T* p) {
+  return *reinterpret_cast<const typename Four<T>::type*>(p);
+}
+__device__ __forceinline__ f32x4 widen(f32x4 v) { return v; }
+__device__ __forceinline__ f32x4 widen(bf16x4 v) {
   return f32x4{static_cast<float>(v[0]), static_cast<float>(v[1]), static_cast<float>(v[2]), static_cast<float>(v[3])};
 }
+template <typename T> __device__ __forceinline__ f32x4 load4(const T* p) { return widen(load4_raw(p)); }
 
 // values k .. k+3 of a row rotated by the angles of table row `tab` [half] (k % 4 == 0, half % 4 == 0)
 template <typename T>
@@ -45,7 +51,7 @@ __device__ __forceinline__ f32x4 load4_rotated(const T* row, int k, int half, co
 }
 
 // H64 = head_dim in units of 64, rounded up; rows of Q, K, V beyond head_dim count as zero
-template <typename T, int H64>
+template <typename T, int H64, bool AHEAD>
 __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict__ qkv, const T* __restrict__ pk,
                                                             const T* __restrict__ pv, T* __restrict__ out,
                                                             const float2* __restrict__ tab, int B, int Hq, int Hkv, int hd,
@@ -61,12 +67,6 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
   const int b = row / rep, h = kvh * rep + row % rep;
   const T* qrow = qkv + (size_t)(g * B + b) * ld + h * hd;
   const float scale = 1.0f / sqrtf((float)hd);
-  f32x4 q[NQ];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const int k = 16 * i + 4 * grp;
-    q[i] = k < hd ? load4_rotated(qrow, k, half, tab + (size_t)b * half) : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
   const int n_keys = own ? P + B + S : P;           // own == 0: cache rows 0 .. P-1 only
   const int chunks = (n_keys + 15) / 16;
   float m = -INFINITY, sum = 0.f;
@@ -75,9 +75,13 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
   for (int u = 0; u < H64; ++u)
 #pragma unroll
     for (int j = 0; j < 4; ++j) o[u][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int c = wave; c < chunks; c += NW) {
-    // values first: their loads are in flight during the scores.  Lane: keys 4 * grp + v, dims 64 * u + 4 * l16 ..
-    f32x4 vv[4][H64];
+  // A chunk's keys (lane: key l16, values 16 * i + 4 * grp ..) and values (lane: keys 4 * grp + v, dims 64 * u + 4 * l16 ..)
+  typedef typename Four<T>::type four_t;
+  struct Chunk {
+    four_t k[NQ], v[4][H64];
+  };
+  auto touches_block = [&](int c) { return 16 * c < P + B && 16 * c + 16 > P && n_keys > P; };
+  auto load_values = [&](int c, Chunk& ch) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int j = 16 * c + 4 * grp + v;
@@ -86,13 +90,40 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
 #pragma unroll
       for (int u = 0; u < H64; ++u) {
         const int t = 64 * u + 4 * l16;
-        vv[v][u] = j < n_keys && t < hd ? load4(vr + t) : f32x4{0.f, 0.f, 0.f, 0.f};
+        ch.v[v][u] = j < n_keys && t < hd ? load4_raw(vr + t) : four_t{};
       }
     }
+  };
+  auto load_keys = [&](int c, Chunk& ch) {          // cached keys; own keys are rotated and read where they are used
+    const T* kr = pk + ((size_t)kvh * ldp + min(16 * c + l16, n_keys - 1)) * hd;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int k = 16 * i + 4 * grp;
+      ch.k[i] = k < hd ? load4_raw(kr + k) : four_t{};
+    }
+  };
+  auto load_chunk = [&](int c, Chunk& ch) {
+    load_values(c, ch);
+    if (!touches_block(c)) load_keys(c, ch);
+  };
+  // AHEAD: loads run one chunk ahead of the products, the first ones ahead of the queries' rotation
+  Chunk cur;
+  if (AHEAD && wave < chunks) load_chunk(wave, cur);
+  f32x4 q[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    const int k = 16 * i + 4 * grp;
+    q[i] = k < hd ? load4_rotated(qrow, k, half, tab + (size_t)b * half) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int c = wave; c < chunks; c += NW) {
+    Chunk next;
+    if (!AHEAD) load_values(c, cur);                // in flight during the scores
+    else if (c + NW < chunks) load_chunk(c + NW, next);
+    if (AHEAD) __builtin_amdgcn_sched_barrier(0);
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    const int jk = min(16 * c + l16, n_keys - 1);   // this lane's key (operand rows beyond the last key repeat it)
-    const bool in_block = jk >= P && jk < P + B;
-    if (__ballot(in_block)) {
+    if (touches_block(c)) {
+      const int jk = min(16 * c + l16, n_keys - 1);   // this lane's key (operand rows beyond the last key repeat it)
+      const bool in_block = jk >= P && jk < P + B;
       const int bb = in_block ? jk - P : 0;
       const T* kr = in_block ? qkv + (size_t)(g * B + bb) * ld + (Hq + kvh) * hd : pk + ((size_t)kvh * ldp + jk) * hd;
 #pragma unroll
@@ -107,17 +138,13 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
         for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[e], q[i][e], s, 0, 0, 0);
       }
     } else {
-      const T* kr = pk + ((size_t)kvh * ldp + jk) * hd;
-      f32x4 kk[NQ];
+      if (!AHEAD) load_keys(c, cur);
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
-        const int k = 16 * i + 4 * grp;
-        kk[i] = k < hd ? load4(kr + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+        const f32x4 kk = widen(cur.k[i]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[e], q[i][e], s, 0, 0, 0);
       }
-#pragma unroll
-      for (int i = 0; i < NQ; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[i][e], q[i][e], s, 0, 0, 0);
     }
     float mc = m;
 #pragma unroll
@@ -143,8 +170,10 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[u][j][e] *= f;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[v][u][j], s[v], o[u][j], 0, 0, 0);
+        for (int v = 0; v < 4; ++v)
+          o[u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(static_cast<float>(cur.v[v][u][j]), s[v], o[u][j], 0, 0, 0);
       }
+    if (AHEAD) cur = next;
   }
   sum += __shfl_xor(sum, 16, 64);
   sum += __shfl_xor(sum, 32, 64);
@@ -194,20 +223,33 @@ __global__ void tile_rope_kernel(float2* __restrict__ tab, int B, int half, int 
   tab[i] = make_float2((float)cos(ang), (float)sin(ang));
 }
 
-template <typename T, int H64>
-hipError_t launch_h(const AttnArgs& a, hipStream_t st) {
+template <typename T, int H64, bool AHEAD>
+hipError_t launch_k(const AttnArgs& a, int grid, hipStream_t st) {
   const size_t smem = sizeof(float) * NW * 16 * (size_t)(a.hd + 2);
   if (smem > 64 * 1024) {
     static std::atomic<unsigned long long> lds_ok{0};
-    const hipError_t e = allow_dynamic_lds((const void*)tile_attn_kernel<T, H64>, (int)(sizeof(float) * NW * 16 * (64 * H64 + 2)),
-                                           lds_ok);
+    const hipError_t e = allow_dynamic_lds((const void*)tile_attn_kernel<T, H64, AHEAD>,
+                                           (int)(sizeof(float) * NW * 16 * (64 * H64 + 2)), lds_ok);
     if (e != hipSuccess) return e;
   }
-  const int grid = a.G * a.Hkv * cdiv(a.B * (a.Hq / a.Hkv), 16);
-  tile_attn_kernel<T, H64><<<grid, 64 * NW, smem, st>>>((const T*)a.qkv, (const T*)a.prefix_k, (const T*)a.prefix_v, (T*)a.out,
-                                                        (const float2*)a.partial, a.B, a.Hq, a.Hkv, a.hd, a.P, a.S,
-                                                        a.ldp ? a.ldp : a.P, a.own);
+  tile_attn_kernel<T, H64, AHEAD><<<grid, 64 * NW, smem, st>>>((const T*)a.qkv, (const T*)a.prefix_k, (const T*)a.prefix_v,
+                                                               (T*)a.out, (const float2*)a.partial, a.B, a.Hq, a.Hkv, a.hd,
+                                                               a.P, a.S, a.ldp ? a.ldp : a.P, a.own);
   return hipGetLastError();
+}
+
+// Loads a chunk ahead where a compute unit gets one workgroup at most, so that nothing else covers a load's latency, where
+// a wavefront has more than one chunk, and where two chunks fit the registers (bf16 up to head_dim 128).  Measured: 128
+// workgroups, bf16, 16 heads of 64, 544 keys, the whole pass of two layers 185.3 -> 174.3 us; fp32 (twice the registers
+// and the same matrix time) 249.3 -> 251.1 us with 316 keys, 90.9 -> 92.4 us with 72, so fp32 loads where it uses.  With
+// more workgroups than compute units the registers of the second chunk would halve the workgroups of a unit.
+template <typename T, int H64>
+hipError_t launch_h(const AttnArgs& a, hipStream_t st) {
+  const int grid = a.G * a.Hkv * cdiv(a.B * (a.Hq / a.Hkv), 16);
+  if constexpr (sizeof(T) == 2 && H64 <= 2) {
+    if (grid <= 256 && a.P + a.B + a.S > 16 * NW) return launch_k<T, H64, true>(a, grid, st);
+  }
+  return launch_k<T, H64, false>(a, grid, st);
 }
 
 template <typename T>
