@@ -88,7 +88,7 @@ LayerWs carve_layer(const spiffy_model_cfg* c, int G, int B, int P, void* base, 
   const size_t qkv_cols = (size_t)(c->n_q_heads + 2 * c->n_kv_heads) * c->head_dim;
   Carve cv(base);
   LayerWs w;
-  w.n = cv.take(M * c->d * es);
+  w.n = cv.take(M * c->d * es);          // first: the steps' embedding kernel leaves the first layer's input here
   w.qkv = cv.take(M * qkv_cols * es);
   w.attn = cv.take(M * (size_t)c->n_q_heads * c->head_dim * es);
   w.h = cv.take(M * c->d * es);
@@ -508,7 +508,7 @@ int spiffy_embed(const spiffy_model_cfg* cfg, const void* w_embed, const int32_t
   if (!w_embed || !block_tokens || !hidden_out) return SPIFFY_EINVAL;
   if (!aligned16(w_embed) || !aligned16(hidden_out)) return SPIFFY_EALIGN;
   return dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hidden_out,
-                          (hipStream_t)stream));
+                          nullptr, 0.f, nullptr, (hipStream_t)stream));
 }
 
 int spiffy_verify_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const spiffy_prefix_kv* prefix,
@@ -719,8 +719,12 @@ int spiffy_verify_step(const spiffy_model_cfg* cfg, int32_t n_layers, const spif
   hipStream_t st = (hipStream_t)stream;
   void* hid = hidden_out ? hidden_out : ws.hidden;
   int32_t* tgt = target_states ? target_states : ws.target;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, st)))) return rc;
+  // the layer scratch starts with the first layer's normalised input
+  const void* norm1 = n_layers > 0 ? layers[0].norm1 : nullptr;
+  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, norm1, cfg->rms_eps, ws.rest, st))))
+    return rc;
   LayerChain chain;
+  chain.normed_out = true;
   chain.tokens = block_tokens;
   for (int l = 0; l < n_layers; ++l) {
     chain.normed_in = chain.normed_out;
@@ -779,12 +783,18 @@ int spiffy_verify_step_seq(const spiffy_model_cfg* cfg, int32_t n_layers, const 
   hipStream_t st = (hipStream_t)stream;
   void* hid = hidden_out ? hidden_out : ws.hidden;
   int32_t* tgt = target_states ? target_states : ws.target;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, st)))) return rc;
+  // the layer scratch starts with the first layer's normalised input
+  const void* norm1 = n_layers > 0 ? layers[0].norm1 : nullptr;
+  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, norm1, cfg->rms_eps, ws.rest, st))))
+    return rc;
   if (S > 0) {
     void* hid_seq = reinterpret_cast<char*>(hid) + (size_t)G * B * cfg->d * esize(cfg->dtype);
-    if ((rc = dev(launch_embed(cfg->dtype, w_embed, suffix_tokens, S, cfg->d, cfg->vocab, hid_seq, st)))) return rc;
+    void* n_seq = reinterpret_cast<char*>(ws.rest) + (size_t)G * B * cfg->d * esize(cfg->dtype);
+    if ((rc = dev(launch_embed(cfg->dtype, w_embed, suffix_tokens, S, cfg->d, cfg->vocab, hid_seq, norm1, cfg->rms_eps, n_seq, st))))
+      return rc;
   }
   LayerChain chain;
+  chain.normed_out = true;
   chain.seq_S = S;
   for (int l = 0; l < n_layers; ++l) {
     chain.normed_in = chain.normed_out;
@@ -838,9 +848,15 @@ int spiffy_verify_step_commit(const spiffy_model_cfg* cfg, int32_t n_layers, con
   void* hid = hidden_out ? hidden_out : ws.hidden;
   int32_t* tgt = target_states ? target_states : ws.target;
   void* hid_prev = reinterpret_cast<char*>(hid) + (size_t)G * B * cfg->d * esize(cfg->dtype);
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, st)))) return rc;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, prev_block_tokens, B, cfg->d, cfg->vocab, hid_prev, st)))) return rc;
+  // the layer scratch starts with the first layer's normalised input
+  const void* norm1 = n_layers > 0 ? layers[0].norm1 : nullptr;
+  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, norm1, cfg->rms_eps, ws.rest, st))))
+    return rc;
+  void* n_prev = reinterpret_cast<char*>(ws.rest) + (size_t)G * B * cfg->d * esize(cfg->dtype);
+  if ((rc = dev(launch_embed(cfg->dtype, w_embed, prev_block_tokens, B, cfg->d, cfg->vocab, hid_prev, norm1, cfg->rms_eps, n_prev, st))))
+    return rc;
   LayerChain chain;
+  chain.normed_out = true;
   chain.seq_S = B;
   chain.tail_is_prev_block = true;
   for (int l = 0; l < n_layers; ++l) {
@@ -876,8 +892,11 @@ int spiffy_commit_block(const spiffy_model_cfg* cfg, int32_t n_layers, const spi
   const StepWs ws = carve_step(cfg, 1, B, P_max, workspace);
   if (workspace_bytes < ws.bytes) return SPIFFY_EWORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, B, cfg->d, cfg->vocab, ws.hidden, st)))) return rc;
+  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, B, cfg->d, cfg->vocab, ws.hidden,
+                             n_layers > 0 ? layers[0].norm1 : nullptr, cfg->rms_eps, ws.rest, st))))
+    return rc;
   LayerChain chain;
+  chain.normed_out = true;
   chain.append_kv = true;
   for (int l = 0; l < n_layers; ++l) {
     chain.normed_in = chain.normed_out;

@@ -5,30 +5,6 @@
 namespace spiffy {
 
 // ---------------------------------------------------------------------------------------------
-// embedding gather: out[m,:] = w[tok[m],:]
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ w, const int32_t* __restrict__ tok,
-                                                    int d, int V, T* __restrict__ out) {
-  const int m = blockIdx.x;
-  int t = tok[m];
-  t = t < 0 ? 0 : (t >= V ? V - 1 : t);
-  const uint4* src = reinterpret_cast<const uint4*>(w + (size_t)t * d);
-  uint4* dst = reinterpret_cast<uint4*>(out + (size_t)m * d);
-  const int n16 = d * (int)sizeof(T) / 16;
-  for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = src[i];
-}
-
-hipError_t launch_embed(int dtype, const void* w, const int32_t* tok, int M, int d, int V, void* out,
-                        hipStream_t st) {
-  if (dtype == SPIFFY_F32)
-    embed_kernel<float><<<M, 256, 0, st>>>((const float*)w, tok, d, V, (float*)out);
-  else
-    embed_kernel<bf16_t><<<M, 256, 0, st>>>((const bf16_t*)w, tok, d, V, (bf16_t*)out);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------------
 // row gather of two matrices with one row list: a_out[r,:] = a[row_idx[r],:], b_out[r,:] = b[row_idx[r],:]
 // for r < *count (the masked rows of the last layer: attention output and residual stream)
 // ---------------------------------------------------------------------------------------------
@@ -153,6 +129,35 @@ hipError_t launch_rmsnorm(int dtype, const void* x, const void* gain, float eps,
   else
     rmsnorm_kernel<bf16_t><<<M, 256, 0, st>>>((const bf16_t*)x, (const bf16_t*)gain, eps, M, d, row_idx,
                                               n_rows_dev, (bf16_t*)out);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------
+// embedding gather: out[m,:] = w[tok[m],:]; with a gain also n_out[m,:] = RMSNorm of that row, which the first layer
+// starts from (a launch of its own took 2.9 - 4.2 us; the row is still in L1 here)
+// ---------------------------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ w, const int32_t* __restrict__ tok,
+                                                    int d, int V, T* __restrict__ out, const T* __restrict__ gain,
+                                                    float eps, T* __restrict__ n_out) {
+  __shared__ float red[4];
+  const int m = blockIdx.x;
+  int t = tok[m];
+  t = t < 0 ? 0 : (t >= V ? V - 1 : t);
+  const uint4* src = reinterpret_cast<const uint4*>(w + (size_t)t * d);
+  uint4* dst = reinterpret_cast<uint4*>(out + (size_t)m * d);
+  const int n16 = d * (int)sizeof(T) / 16;
+  for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = src[i];
+  if (gain) rmsnorm_row<T>(w, gain, eps, d, t, m, n_out, red);
+}
+
+hipError_t launch_embed(int dtype, const void* w, const int32_t* tok, int M, int d, int V, void* out, const void* gain,
+                        float eps, void* n_out, hipStream_t st) {
+  if (dtype == SPIFFY_F32)
+    embed_kernel<float><<<M, 256, 0, st>>>((const float*)w, tok, d, V, (float*)out, (const float*)gain, eps, (float*)n_out);
+  else
+    embed_kernel<bf16_t><<<M, 256, 0, st>>>((const bf16_t*)w, tok, d, V, (bf16_t*)out, (const bf16_t*)gain, eps,
+                                            (bf16_t*)n_out);
   return hipGetLastError();
 }
 

@@ -6,8 +6,8 @@
 namespace spiffy {
 
 // ---- any shape, T = float or bf16 storage -----------------------------------------------------
-hipError_t launch_embed(int dtype, const void* w_embed, const int32_t* tokens, int M, int d, int V,
-                        void* out, hipStream_t st);
+hipError_t launch_embed(int dtype, const void* w_embed, const int32_t* tokens, int M, int d, int V, void* out,
+                        const void* gain, float eps, void* n_out, hipStream_t st);   // gain: n_out = RMSNorm(out) too
 // out[r,:] = rmsnorm(x[src(r),:]) * gain, src(r) = row_idx ? row_idx[r] : r, rows r < *n_rows_dev
 // (or < M when n_rows_dev is NULL).
 hipError_t launch_rmsnorm(int dtype, const void* x, const void* gain, float eps, int M, int d,
