@@ -99,3 +99,30 @@ def test_tile_head_edges(sp, d, V, G, B):
     assert clear.mean() > 0.5 and (am[clear] == logit.argmax(-1)[clear]).all()
     conf = 1.0 / np.exp(logit - top[:, :1]).sum(-1)
     np.testing.assert_allclose(to_np(got["conf"]).reshape(-1), conf, rtol=tie + V * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("last_masked", [False, True])
+@pytest.mark.parametrize("G", [1, 2, 64, 65])
+def test_head_rows_do_not_depend_on_how_the_masked_rows_are_listed(sp, G, last_masked, dtype):
+    """Up to 2048 rows the norm's workgroups find their places in the row list themselves, above a list kernel runs first: every
+    output of a state equals, bit for bit, that of the state alone; masked and unmasked last rows, a state without MASK."""
+    B, d, V = 32, 256, 3000                            # bf16: the merge in slices and the matrix-core head
+    cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B, dtype=dtype)
+    g = torch.Generator().manual_seed(G)
+    td = cfg.torch_dtype()
+    x, w = torch.randn((G, B, d), generator=g).to(td).to(DEV), (torch.randn((V, d), generator=g) * 0.1).to(td).to(DEV)
+    gain = torch.ones(d).to(td).to(DEV)
+    tok = torch.randint(0, V - 1, (G, B), generator=g, dtype=torch.int32)
+    tok[torch.rand((G, B), generator=g) < 0.5] = cfg.mask_id
+    if G > 1:
+        tok[G // 2] = 1
+    tok[G - 1, B - 1] = cfg.mask_id if last_masked else 1
+    tok = tok.to(DEV)
+    scfg = sp.cfg_from_synth(cfg)
+    got = sp.decode_head(scfg, x, gain, w, tok, 0.01, sp.alloc_workspace(scfg, G, B, 0, DEV))
+    one = sp.alloc_workspace(scfg, 1, B, 0, DEV)
+    for s in sorted({0, G // 2, G - 1}):
+        ref = sp.decode_head(scfg, x[s:s + 1].contiguous(), gain, w, tok[s:s + 1].contiguous(), 0.01, one)
+        for k in ref:
+            assert torch.equal(got[k][s], ref[k][0]), (s, k)
