@@ -161,11 +161,12 @@ int spiffy_decode_head(const spiffy_model_cfg *cfg, const void *hidden, const vo
 
 /* spiffy_decode_head for callers that cannot allocate and have no workspace to pass: code recorded into a HIP
  * graph, tight serving loops, harnesses that forbid hipMalloc.  Same arguments (without the workspace), same
- * kernels and bit-identical outputs; the scratch is a device array of SPIFFY_STATIC_SCRATCH_BYTES that the library
- * holds on every GPU it runs on until the process ends.  The call allocates nothing and frees nothing.  Limits:
+ * kernels and bit-identical outputs; the scratch is a device array of SPIFFY_STATIC_SCRATCH_BYTES (and 1 MiB for the
+ * vocabulary summaries of the heads off the matrix-core path) that the library holds on every GPU it runs on until
+ * the process ends.  The call allocates nothing and frees nothing.  Limits:
  * G*B <= SPIFFY_STATIC_MAX_ROWS (the paper's operating point, four states of a 32-token block, Sec. 5) and a head
- * scratch (gathered rows G*B x d, one 16-byte summary per row and 128-token chunk of the vocabulary) within the
- * array: bf16 with d <= 8192 and vocab <= 262144 always fits.  Anything larger returns SPIFFY_ELIMIT before any
+ * scratch (gathered rows G*B x d; on the matrix-core path one 16-byte summary per row and 128-token chunk of the
+ * vocabulary) within SPIFFY_STATIC_SCRATCH_BYTES: bf16 with d <= 8192 and vocab <= 262144 always fits.  Anything larger returns SPIFFY_ELIMIT before any
  * launch.  All calls on one GPU share that GPU's array (each call overwrites what the last one left; nothing in it
  * has to be cleared), so calls that overlap on one GPU, on different streams or from different threads, race:
  * serialise them.  The first call on a device looks up the array's address (not inside a graph capture). */

@@ -12,7 +12,11 @@ using namespace spiffy;
 // Scratch of the allocation-free entry point (spiffy_decode_head_static): every GPU the library runs on holds its own
 // copy of this array until the process ends.  In host code the name is only a handle for hipGetSymbolAddress; kernels
 // get the device address that call returns.
-static __device__ __align__(256) unsigned char scratch[SPIFFY_STATIC_SCRATCH_BYTES];
+// Beside the scratch proper it has room for the vocabulary summaries of the heads off the matrix-core path.
+constexpr int kTileHeadParts = 512;     // two rounds of one workgroup a CU
+constexpr size_t kStaticSummaryBytes = sizeof(TopPartial) * kTileHeadParts * SPIFFY_STATIC_MAX_ROWS;
+static __device__ __align__(256) unsigned char scratch[SPIFFY_STATIC_SCRATCH_BYTES + kStaticSummaryBytes];
+static_assert(SPIFFY_STATIC_MAX_ROWS % 128 == 0, "rows of a summary array come in groups of 128");
 
 namespace {
 
@@ -116,7 +120,7 @@ struct HeadWs {
   int m_cap;
   int n_part;            // MFMA head: summaries of 128 tokens each (the top-K refinement reads them); otherwise 0
   int n_part_tile;       // head of the other shapes: parts of the vocabulary
-  size_t bytes;
+  size_t tile_summary_bytes, bytes;      // what their summaries take; everything
 };
 HeadWs carve_head(const spiffy_model_cfg* c, int G, int B, void* base) {
   const int M = G * B;
@@ -127,16 +131,13 @@ HeadWs carve_head(const spiffy_model_cfg* c, int G, int B, void* base) {
   w.row_idx = (int32_t*)cv.take(sizeof(int32_t) * w.m_cap);
   w.count = (int32_t*)cv.take(sizeof(int32_t) * 4);
   w.nf = cv.take((size_t)w.m_cap * c->d * esize(c->dtype));
-  // Other shapes: up to 512 parts (two workgroups per CU), of at least one 64-token tile; fewer when the scratch of the
-  // allocation-free entry point, sized for heads without summaries, would not hold them: then the 16 rows of part2 serve.
-  w.n_part_tile = head_mfma(c) ? 0 : cdiv(c->vocab, 64) < 512 ? cdiv(c->vocab, 64) : 512;
-  const size_t rest = sizeof(TopPartial) * (size_t)(kLmheadCombineSlices + 1) * w.m_cap + 8 * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK + 2048;
-  const bool in_part2 = M <= SPIFFY_STATIC_MAX_ROWS && w.n_part_tile > kLmheadCombineSlices &&
-                        cv.off + rest + sizeof(TopPartial) * (size_t)w.n_part_tile * w.m_cap > (size_t)SPIFFY_STATIC_SCRATCH_BYTES;
-  if (in_part2) w.n_part_tile = kLmheadCombineSlices;
-  w.part = (TopPartial*)cv.take(in_part2 ? 0 : sizeof(TopPartial) * (size_t)(w.n_part + w.n_part_tile) * w.m_cap);
+  // Other shapes: parts of at least one 64-token tile.  Their number depends on the vocabulary alone: it sets the order in
+  // which a row's exponentials are added.
+  w.n_part_tile = head_mfma(c) ? 0 : cdiv(c->vocab, 64) < kTileHeadParts ? cdiv(c->vocab, 64) : kTileHeadParts;
+  const size_t before = cv.off;
+  w.part = (TopPartial*)cv.take(sizeof(TopPartial) * (size_t)(w.n_part + w.n_part_tile) * w.m_cap);
+  w.tile_summary_bytes = head_mfma(c) ? 0 : cv.off - before;
   w.part2 = (TopPartial*)cv.take(sizeof(TopPartial) * (size_t)kLmheadCombineSlices * w.m_cap);
-  if (in_part2) w.part = w.part2;
   w.row_top = (TopPartial*)cv.take(sizeof(TopPartial) * w.m_cap);
   w.cand_val = (float*)cv.take(sizeof(float) * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK);
   w.cand_idx = (int32_t*)cv.take(sizeof(int32_t) * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK);
@@ -568,7 +569,8 @@ int spiffy_decode_head_static(const spiffy_model_cfg* cfg, const void* hidden, c
                             unmask)))
     return rc;
   if ((int64_t)G * B > SPIFFY_STATIC_MAX_ROWS) return SPIFFY_ELIMIT;
-  if (carve_head(cfg, G, B, nullptr).bytes > (size_t)SPIFFY_STATIC_SCRATCH_BYTES) return SPIFFY_ELIMIT;
+  const HeadWs need = carve_head(cfg, G, B, nullptr);
+  if (need.bytes - need.tile_summary_bytes > (size_t)SPIFFY_STATIC_SCRATCH_BYTES) return SPIFFY_ELIMIT;
   void* ws = nullptr;
   if ((rc = static_scratch_ptr(&ws))) return rc;
   // every kernel of the head writes what it later reads (row list and count, gathered rows, summaries): nothing in

@@ -159,6 +159,19 @@ def test_matrix_core_head_refuses_what_its_32_bit_offsets_cannot_address():
                                      DUMMY, None, None, 0x100000, 16, None) == sp.SPIFFY_EWORKSPACE
 
 
+@pytest.mark.parametrize("V,d,fits", [(2, 16280, True), (64, 16280, True), (64, 16288, False), (1000, 16240, True),
+                                      (1024, 16280, True), (1024, 16288, False), (3200, 16000, True), (126464, 16280, True)])
+def test_static_head_limit_does_not_count_the_vocabulary_summaries(V, d, fits):
+    """fp32 heads of 128 rows on either side of the 8 MiB limit, with one vocabulary tile to many."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the call would run on these addresses")
+    cfg = sp.cfg_from_synth(synth.CONFIGS["c1"].scaled(d=d, V=V))
+    rc = sp.lib.spiffy_decode_head_static(C.byref(cfg), DUMMY, DUMMY, DUMMY, DUMMY, None, 4, 32, 0.5, 1.0, 1, DUMMY, DUMMY,
+                                          DUMMY, DUMMY, DUMMY, None)
+    assert rc == (sp.SPIFFY_EDEVICE if fits else sp.SPIFFY_ELIMIT)       # every host check passed: no GPU to run on
+
+
 def test_graph_accept_argument_errors():
     call = lambda **k: sp.lib.spiffy_graph_accept(
         k.get("edges", DUMMY), k.get("E", 3), k.get("ds", DUMMY), k.get("ts", DUMMY), k.get("G", 4), 8,

@@ -126,3 +126,21 @@ def test_head_rows_do_not_depend_on_how_the_masked_rows_are_listed(sp, G, last_m
         ref = sp.decode_head(scfg, x[s:s + 1].contiguous(), gain, w, tok[s:s + 1].contiguous(), 0.01, one)
         for k in ref:
             assert torch.equal(got[k][s], ref[k][0]), (s, k)
+
+
+def test_head_rows_do_not_depend_on_the_batch_at_large_widths(sp):
+    """128 rows of 16000 are at the edge of the static scratch: the vocabulary is cut alike there and for 160 rows."""
+    d, V, G, B = 16000, 3200, 5, 32
+    cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B)
+    g = torch.Generator().manual_seed(3)
+    x, w = torch.randn((G, B, d), generator=g).to(DEV), (torch.randn((V, d), generator=g) * 0.01).to(DEV)
+    gain, tok = torch.ones(d).to(DEV), torch.full((G, B), cfg.mask_id, dtype=torch.int32).to(DEV)
+    scfg = sp.cfg_from_synth(cfg)
+    got = sp.decode_head(scfg, x, gain, w, tok, 0.01, sp.alloc_workspace(scfg, G, B, 0, DEV))
+    few = sp.decode_head(scfg, x[:4].contiguous(), gain, w, tok[:4].contiguous(), 0.01, sp.alloc_workspace(scfg, 4, B, 0, DEV))
+    for k in few:
+        assert torch.equal(got[k][:4], few[k]), k
+    out = {k: torch.empty_like(t) for k, t in few.items()}
+    sp.decode_head_static(scfg, x[:4].contiguous(), gain, w, tok[:4].contiguous(), 0.01, out)
+    for k in few:
+        assert torch.equal(out[k], few[k]), k
