@@ -129,8 +129,9 @@ def test_head_rows_do_not_depend_on_how_the_masked_rows_are_listed(sp, G, last_m
 
 
 def test_head_rows_do_not_depend_on_the_batch_at_large_widths(sp):
-    """128 rows of 16000 are at the edge of the static scratch: the vocabulary is cut alike there and for 160 rows."""
-    d, V, G, B = 16000, 3200, 5, 32
+    """128 rows of 16000 leave less of the static scratch than 100 summaries a row take: the vocabulary is cut alike there and
+    for 160 rows."""
+    d, V, G, B = 16000, 6400, 5, 32
     cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B)
     g = torch.Generator().manual_seed(3)
     x, w = torch.randn((G, B, d), generator=g).to(DEV), (torch.randn((V, d), generator=g) * 0.01).to(DEV)
