@@ -18,9 +18,7 @@
 // (three launches) for few parents, vector instructions for many.  Measured, 45 nodes, sets of 10, 12 parents: 1514 -> 20.5 us
 // a call against the one-by-one search (2.1e12 sets/s).
 //
-// The one-by-one search below serves graphs with many parents and small D.  Where the line lies: beyond the launches a
-// choice of parents takes 0.7 - 0.9 ps (2^26: 60 of 79 us, 2^27: 97 of 117 us), a tried set 0.47 ps (3.2e9: 1.5 ms), and the tables of the
-// one-by-one search as much as 8e6 sets (28 us for 780 sets, what 2^22 choices take).
+// The one-by-one search below serves graphs with many parents and small D (choices_pay has the line between the two).
 //
 // Work split: the nodes are cut into a low part (the h = min(N, 12) lowest nodes), a middle part (the next
 // hm <= 11) and a top part (the rest).  A one-workgroup kernel tabulates every subset of the low part (sum of
@@ -52,7 +50,6 @@ constexpr int kMaxGroups = 2048;              // (a, b) size pairs, the small on
 constexpr int kBinomN = 65;                    // binomials C(n, k), 0 <= n, k <= 64, saturating
 constexpr unsigned long long kSat = ~0ull;
 constexpr int kMaxParents = 30;                // most parents whose choices are enumerated (choices count in 32 bits)
-constexpr unsigned long long kFewSets = 1ull << 23;
 
 // binomial coefficients, built by the compiler; those that do not fit 64 bits stick at the maximum
 struct Binomials {
@@ -68,6 +65,30 @@ struct Binomials {
   }
 };
 __device__ const Binomials kBinom{};
+
+constexpr unsigned long long binomial(int n, int k) { return Binomials().v[n * kBinomN + k]; }
+
+// Choices of p parents or sets one by one, n nodes.  Both searches timed at the same graphs (24 to 64 nodes, sets of 2 to
+// 12, 18 to 28 parents; microseconds a call, 19.5 of them the launches that both have): 2^p choices take 0.55 ps each in small
+// sets (2^26: 57) to 0.9 ps in large ones, up to 1.4 ps where all counts are equal and no choice falls behind the best (2^26,
+// sets of 12: 131).  One by one, besides 0.45 ps a set, few sets cost what their tables and size pairs do: 25 at 990 sets, 40 at
+// 14190, 65 at 1.5e5, 76 at 8e6 (45 nodes), and more with more nodes (635376 sets: 57 of 30 nodes' size pairs, 103 of 64's),
+// which grows about with the logarithm of their number.  In units of 0.05 ps:
+constexpr bool choices_pay(int n, int p, unsigned long long sets) {
+  if (p > kMaxParents) return false;
+  int lg = 0;
+  for (unsigned long long s = sets; s > 1ull; s >>= 1) ++lg;
+  const long long lump = (5ll * lg - 50) * n / 40;                       // microseconds
+  const unsigned long long few = 20000000ull * (unsigned long long)(lump > 6 ? lump : 6);
+  return 13ull * (1ull << p) <= few + 9ull * (sets < kSat / 16 ? sets : kSat / 16);
+}
+static_assert(choices_pay(24, 22, binomial(24, 2)) && choices_pay(45, 23, binomial(45, 2)), "22 of 25 us, 25 of 27 us");
+static_assert(!choices_pay(36, 25, binomial(36, 2)) && !choices_pay(64, 26, binomial(64, 2)), "36 of 25 us, 60 of 34 us");
+static_assert(choices_pay(45, 25, binomial(45, 4)) && !choices_pay(45, 27, binomial(45, 4)), "38 of 62 us, 94 of 65 us");
+static_assert(choices_pay(64, 26, binomial(64, 4)) && !choices_pay(64, 28, binomial(64, 4)), "60 of 104 us, 171 of 102 us");
+static_assert(choices_pay(30, 25, binomial(30, 6)) && !choices_pay(30, 27, binomial(30, 6)), "38 of 53 us, 94 of 57 us");
+static_assert(choices_pay(45, 27, binomial(45, 8)) && choices_pay(45, 30, binomial(45, 10)), "108 of 255 us, 775 of 1487 us");
+static_assert(!choices_pay(36, 28, binomial(36, 8)), "183 of 105 us");
 
 struct __align__(16) SgEntry {
   long long sum;
@@ -151,7 +172,7 @@ __global__ __launch_bounds__(kThreads) void sg_prepare_kernel(const long long* _
     const int n = __popcll(alive);
     int p = __popcll(parents);
     const unsigned long long sets = D <= n ? kBinom.v[n * kBinomN + D] : 0ull;
-    if (p > kMaxParents || 2ull * (1ull << p) > (sets < kSat - kFewSets ? sets + kFewSets : kSat)) p = -1;
+    if (!choices_pay(n, p, sets)) p = -1;
     int at = __popcll(alive & below);          // one by one: nodes keep their order, so masks compare as before
     if (p >= 0) {
       if ((parents >> tid) & 1ull) {
