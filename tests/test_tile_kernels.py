@@ -107,7 +107,7 @@ def test_tile_head_edges(sp, d, V, G, B):
 def test_head_rows_do_not_depend_on_how_the_masked_rows_are_listed(sp, G, last_masked, dtype):
     """Up to 2048 rows the norm's workgroups find their places in the row list themselves, above a list kernel runs first: every
     output of a state equals, bit for bit, that of the state alone; masked and unmasked last rows, a state without MASK."""
-    B, d, V = 32, 256, 3000                            # bf16: the merge in slices and the matrix-core head
+    B, d, V = 32, 256, 3000                            # fp32: the merge in slices; bf16: one merge, and the matrix-core head
     cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B, dtype=dtype)
     g = torch.Generator().manual_seed(G)
     td = cfg.torch_dtype()
@@ -145,3 +145,74 @@ def test_head_rows_do_not_depend_on_the_batch_at_large_widths(sp):
     sp.decode_head_static(scfg, x[:4].contiguous(), gain, w, tok[:4].contiguous(), 0.01, out)
     for k in few:
         assert torch.equal(out[k], few[k]), k
+
+
+@pytest.mark.parametrize("epi", ["store", "resid", "swiglu"])
+def test_tile_gemm_rows_do_not_depend_on_the_batch_bf16(sp, epi):
+    g = torch.Generator().manual_seed(6)
+    A, W, W1, R = (torch.randn(s, generator=g).to(torch.bfloat16).to(DEV) for s in ((200, 520), (6008, 520), (6008, 520), (200, 6008)))
+
+    def run(n):                                      # 200 rows: 64 x 64 tiles; 40: 32 x 16; 16 and fewer: 16 x 16
+        a, r = A[:n].contiguous(), R[:n].contiguous()
+        if epi == "swiglu":
+            return sp.gemm(sp.GEMM_SWIGLU, a, W, W1)
+        return sp.gemm(sp.GEMM_RESID, a, W, R=r) if epi == "resid" else sp.gemm(sp.GEMM_STORE, a, W)
+
+    full = run(200)
+    for n in (1, 16, 40):
+        assert torch.equal(run(n), full[:n]), n
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("hd,Hq,Hkv,P,S", [(64, 4, 4, 300, 0), (96, 8, 4, 130, 140), (64, 4, 4, 2000, 0), (136, 4, 4, 260, 0)])
+def test_tile_attention_states_do_not_depend_on_the_batch(sp, hd, Hq, Hkv, P, S, dtype):
+    """65 states of 16 tokens are more than 256 workgroups of attention, one or 64 states are not, and from there bf16 heads of up
+    to 128 load a chunk ahead: a state's rows are the same bits; the first also against the oracle."""
+    from oracle import spiffy_oracle as O
+    B, G = 16, 65
+    cfg = synth.CONFIGS["c1"].scaled(dtype=dtype, d=96, Hq=Hq, Hkv=Hkv, hd=hd, F=72, P=P, B=B, G=G)
+    w = synth.layer_weights(cfg, 0, bias=True)
+    for k in ("wq", "wk", "wv", "wo"):
+        w[k] = (w[k].float() * 4).to(w[k].dtype)
+    g = torch.Generator().manual_seed(hd + P)
+    k, v = (torch.randn((Hkv, P + B + S, hd), generator=g).to(w["wq"].dtype) for _ in range(2))
+    x = synth.hidden_states(cfg, G=G)
+    scfg, lw, pk = sp.cfg_from_synth(cfg), sp.layer_weights({n: t.to(DEV) for n, t in w.items()}), sp.prefix_kv(k.to(DEV), v.to(DEV), P, S)
+
+    def run(a, b):
+        return sp.verify_layer(scfg, lw, pk, x[a:b].contiguous().to(DEV), P, sp.alloc_workspace(scfg, b - a, B, P + S, DEV)).clone()
+
+    full = run(0, G)
+    for a, b in ((0, 1), (G - 1, G), (1, G)):
+        assert torch.equal(run(a, b), full[a:b]), (a, b)
+    kn, vn = to_np(k), to_np(v)
+    kw = dict(suffix_k=kn[:, P + B:], suffix_v=vn[:, P + B:]) if S else {}
+    ref = O.verify_layer(np_weights(w), kn[:, :P], vn[:, :P], to_np(x[:2]), **cfg_kw(cfg), **kw)
+    err = np.max(np.abs(to_np(full[:2]) - ref) / (np.abs(ref) + np.sqrt(np.mean(ref * ref))))
+    assert err < (1e-4 if dtype == "f32" else 2e-2), err      # the bars of test_gpu_parity
+
+
+@pytest.mark.parametrize("G", [1, 2, 65])
+def test_head_merged_in_slices_does_not_depend_on_the_batch(sp, G):
+    """bf16, 34 chunk summaries a row (more than the 32 that one launch merges): every output of a state, and the drafting source's
+    tokens and probabilities, which start from the merged row, equal those of the state alone."""
+    B, d, V = 32, 256, 4352 - 56
+    cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B, dtype="bf16")
+    g = torch.Generator().manual_seed(100 + G)
+    x, w = torch.randn((G, B, d), generator=g).bfloat16().to(DEV), (torch.randn((V, d), generator=g) * 0.1).bfloat16().to(DEV)
+    gain = torch.ones(d).bfloat16().to(DEV)
+    tok = torch.randint(0, V - 1, (G, B), generator=g, dtype=torch.int32)
+    tok[torch.rand((G, B), generator=g) < 0.5] = cfg.mask_id
+    tok[0, 0] = tok[G - 1, B - 1] = cfg.mask_id
+    tok = tok.to(DEV)
+    scfg = sp.cfg_from_synth(cfg)
+    ws, one = sp.alloc_workspace(scfg, G, B, 0, DEV), sp.alloc_workspace(scfg, 1, B, 0, DEV)
+    got = sp.decode_head(scfg, x, gain, w, tok, 0.01, ws)
+    for s in sorted({0, G - 1}):
+        top = sp.head_topk(scfg, w, tok, 3, 1.0, ws, node=s)
+        ts = tok[s:s + 1].contiguous()
+        ref = sp.decode_head(scfg, x[s:s + 1].contiguous(), gain, w, ts, 0.01, one)
+        for k in ref:
+            assert torch.equal(got[k][s], ref[k][0]), (s, k)
+        for a, b in zip(top, sp.head_topk(scfg, w, ts, 3, 1.0, one, node=0)):
+            assert torch.equal(a, b), s
