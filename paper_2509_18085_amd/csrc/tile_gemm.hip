@@ -134,6 +134,32 @@ __device__ __forceinline__ float wave_sums(const float* p, int stride) {
 }
 static_assert(NW == 8, "wave_sums adds eight");
 
+// row n of the segments' weights laid one below the other, as n runs over the output columns
+template <typename T, int EPI>
+__device__ __forceinline__ const T* weight_row(const GemmArgs& a, int n) {
+  n = min(n, a.N - 1);
+  int s = 0;
+  if (n >= a.Nseg[0] && EPI == EPI_STORE) {
+    n -= a.Nseg[0];
+    s = 1;
+    if (n >= a.Nseg[1]) { n -= a.Nseg[1]; s = 2; }
+  }
+  return (const T*)(s == 0 ? a.W[0] : s == 1 ? a.W[1] : a.W[2]) + (size_t)n * a.K;
+}
+
+// output element (m, n) from its sums (SWIGLU: of gate and up)
+template <typename T, int EPI>
+__device__ __forceinline__ void store_element(const GemmArgs& a, bool has_bias, int m, int n, float s, float u) {
+  if (EPI == EPI_SWIGLU) s = s / (1.f + __expf(-s)) * u;
+  if (has_bias) {
+    const bool s0 = n < a.Nseg[0], s1 = n < a.Nseg[0] + a.Nseg[1];
+    const T* b = (const T*)(s0 ? a.bias[0] : s1 ? a.bias[1] : a.bias[2]);
+    if (b) s += to_f32(b[s0 ? n : s1 ? n - a.Nseg[0] : n - a.Nseg[0] - a.Nseg[1]]);
+  }
+  if (EPI == EPI_RESID) s += to_f32(((const T*)a.R)[(size_t)m * a.ldc + n]);
+  ((T*)a.C)[(size_t)m * a.ldc + n] = from_f32<T>(s);
+}
+
 // C tile of 16*TM rows x 16*TN columns (SWIGLU: TN/2 fragments of gate rows and the same rows of up)
 template <typename T, int EPI, int TM, int TN, int DEPTH>
 __global__ __launch_bounds__(64 * NW) void tile_gemm_kernel(GemmArgs a) {
@@ -149,20 +175,10 @@ __global__ __launch_bounds__(64 * NW) void tile_gemm_kernel(GemmArgs a) {
   const T* wrow[TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i) arow[i] = (const T*)a.A + (size_t)min(m0 + 16 * i + l16, m_max - 1) * a.lda;
-  auto weight_row = [&](int n) {
-    n = min(n, a.N - 1);
-    int s = 0;
-    if (n >= a.Nseg[0] && EPI == EPI_STORE) {
-      n -= a.Nseg[0];
-      s = 1;
-      if (n >= a.Nseg[1]) { n -= a.Nseg[1]; s = 2; }
-    }
-    return (const T*)(s == 0 ? a.W[0] : s == 1 ? a.W[1] : a.W[2]) + (size_t)n * K;
-  };
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     if (EPI == EPI_SWIGLU) wrow[j] = (const T*)a.W[j / NO] + (size_t)min(n0 + 16 * (j % NO) + l16, a.N - 1) * K;
-    else wrow[j] = weight_row(n0 + 16 * j + l16);
+    else wrow[j] = weight_row<T, EPI>(a, n0 + 16 * j + l16);
   }
   f32x4 acc[TM][TN];
   tile_product<T, TM, TN, DEPTH>(arow, wrow, K, wave, lane, acc);
@@ -180,20 +196,104 @@ __global__ __launch_bounds__(64 * NW) void tile_gemm_kernel(GemmArgs a) {
       const int j = e >> 8, q = e & 255, el = q & 63;
       const int m = m0 + 16 * i + 4 * (el >> 4) + (q >> 6), n = n0 + 16 * j + (el & 15);
       if (m >= m_max || n >= a.N) continue;
-      float s = wave_sums(&red[0][j][q], TN * RSTRIDE);
-      if (EPI == EPI_SWIGLU) {
-        const float u = wave_sums(&red[0][j + NO][q], TN * RSTRIDE);
-        s = s / (1.f + __expf(-s)) * u;
-      }
-      if (has_bias) {
-        const bool s0 = n < a.Nseg[0], s1 = n < a.Nseg[0] + a.Nseg[1];
-        const T* b = (const T*)(s0 ? a.bias[0] : s1 ? a.bias[1] : a.bias[2]);
-        if (b) s += to_f32(b[s0 ? n : s1 ? n - a.Nseg[0] : n - a.Nseg[0] - a.Nseg[1]]);
-      }
-      if (EPI == EPI_RESID) s += to_f32(((const T*)a.R)[(size_t)m * a.ldc + n]);
-      ((T*)a.C)[(size_t)m * a.ldc + n] = from_f32<T>(s);
+      const float s = wave_sums(&red[0][j][q], TN * RSTRIDE);
+      const float u = EPI == EPI_SWIGLU ? wave_sums(&red[0][j + NO][q], TN * RSTRIDE) : 0.f;
+      store_element<T, EPI>(a, has_bias, m, n, s, u);
     }
   }
+}
+
+// The same sums where K has at most six chunks: one wavefront per 32 x 32 output tile adds its chunks' products in the order
+// of wave_sums (the other chunks' are zero), in registers.  With so few chunks some of the eight wavefronts of a shared tile
+// have none, and the trip through LDS takes longer than the products.  MAX_CHUNKS: 4 (fewer registers), or 6 for five and six.
+constexpr int SW = 4;      // wavefronts of a workgroup, side by side along the columns
+
+template <typename T, int EPI, int MAX_CHUNKS>
+__global__ __launch_bounds__(64 * SW) void tile_gemm_short_kernel(GemmArgs a, int col_blocks) {
+  typedef typename Frag<T>::type frag_t;
+  constexpr int KC = Frag<T>::KC, VEC = Frag<T>::VEC, TM = 2, NO = 2, TN = EPI == EPI_SWIGLU ? 2 * NO : NO;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l16 = lane & 15;
+  const int m_max = a.M_dev ? min(*a.M_dev, a.M) : a.M;
+  const int m0 = blockIdx.x / col_blocks * 16 * TM, n0 = (blockIdx.x % col_blocks * SW + wave) * 16 * NO;
+  if (m0 >= m_max || n0 >= a.N) return;
+  const int K = a.K;
+  const T* arow[TM];
+  const T* wrow[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) arow[i] = (const T*)a.A + (size_t)min(m0 + 16 * i + l16, m_max - 1) * a.lda;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    if (EPI == EPI_SWIGLU) wrow[j] = (const T*)a.W[j / NO] + (size_t)min(n0 + 16 * (j % NO) + l16, a.N - 1) * K;
+    else wrow[j] = weight_row<T, EPI>(a, n0 + 16 * j + l16);
+  }
+  f32x4 sum[TM][TN], part[TM][TN];
+  auto add_chunk = [&](int t, f32x4 (&to)[TM][TN]) {      // K is a multiple of 8: a lane's values are all inside K or beyond it
+    frag_t fa[2][TM], fw[2][TN];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = (2 * t + h) * KC + (lane >> 4) * VEC, kk = min(k, K - VEC);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fw[h][j] = *reinterpret_cast<const frag_t*>(wrow[j] + kk);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[h][i] = *reinterpret_cast<const frag_t*>(arow[i] + kk);
+      if (k >= K) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fw[h][j] = frag_t{};
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[h][i] = frag_t{};
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const f32x4 c = mma(mma(f32x4{0.f, 0.f, 0.f, 0.f}, fa[0][i], fw[0][j]), fa[1][i], fw[1][j]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) to[i][j][v] += c[v];
+      }
+  };
+  auto clear = [&](f32x4 (&to)[TM][TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) to[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  auto add = [&](f32x4 (&to)[TM][TN], const f32x4 (&x)[TM][TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) to[i][j][v] += x[i][j][v];
+  };
+  const int chunks = (K + 2 * KC - 1) / (2 * KC);
+  clear(sum);
+  add_chunk(0, sum);
+  if (chunks > 1) add_chunk(1, sum);
+  if (chunks > 2) {
+    clear(part);
+    add_chunk(2, part);
+    if (chunks > 3) add_chunk(3, part);
+    add(sum, part);
+  }
+  if constexpr (MAX_CHUNKS > 4) {
+    static_assert(MAX_CHUNKS <= 6, "the second half of the tree is (4 + 5) + 0");
+    clear(part);
+    add_chunk(4, part);
+    if (chunks > 5) add_chunk(5, part);
+    add(sum, part);
+  }
+  const bool has_bias = EPI == EPI_STORE && (a.bias[0] || a.bias[1] || a.bias[2]);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int j = 0; j < NO; ++j) {
+        const int m = m0 + 16 * i + 4 * (lane >> 4) + v, n = n0 + 16 * j + l16;
+        if (m < m_max && n < a.N) store_element<T, EPI>(a, has_bias, m, n, sum[i][j][v], EPI == EPI_SWIGLU ? sum[i][j + NO][v] : 0.f);
+      }
 }
 
 // LM head: rows r < *count of n against vocabulary tiles of 64 tokens.  blockIdx.x = vocabulary part (tiles x, x + n_part,
@@ -268,12 +368,28 @@ __global__ __launch_bounds__(64 * NW) void tile_head_kernel(const T* __restrict_
   else head_tiles<T, 1>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, red);
 }
 
+template <typename T, int EPI, int MAX_CHUNKS>
+void launch_short(const GemmArgs& a, hipStream_t st) {
+  const int col_blocks = cdiv(a.N, 32 * SW);
+  tile_gemm_short_kernel<T, EPI, MAX_CHUNKS><<<cdiv(a.M, 32) * col_blocks, 64 * SW, 0, st>>>(a, col_blocks);
+}
+
 // Tiles of 64 x 64 (SWIGLU: 32 features) where they fill the chip: a quarter of the operand traffic per product.  Below
 // that 32 x 16 (16 x 16 with one fragment of rows): four to eight times the workgroups, each reading its operands once.
+// Measured around the line, fp32 / bf16, in us with 64 x 64 and with 32 x 16: 200 rows of 4104 columns (260 tiles of 64 x 64),
+// K = 1032: 45.4, 37.4 / 13.5, 17.9, SwiGLU 66, 58 / 22, 25; 1024 rows of 4104, 1040 tiles: 116, 150 / 46, 72; 4096 rows: 393, 578 /
+// 148, 271 (one line for both types: fp32 alone would gain from 32 x 16 tiles a little longer).  Where 64 x 64 tiles fill the chip and K has up to six chunks in fp32 (192), four in bf16 (256), a wavefront takes a
+// tile: 4096 x 4104 from K = 8 87 -> 23 / 59 -> 15, K = 136 127 -> 81 / 65 -> 32; with more chunks the shared tiles were as fast
+// or faster where they just fill the chip (1024 x 1032, SwiGLU: seven chunks fp32 23 against 25, five bf16 15 against 18).
 template <typename T, int EPI>
 hipError_t launch_epi(const GemmArgs& a, hipStream_t st) {
+  constexpr int CHUNK = 2 * Frag<T>::KC;
   const int big = cdiv(a.M, 64) * cdiv(a.N, EPI == EPI_SWIGLU ? 32 : 64);
-  if (big >= 256) {
+  if (big >= 256 && a.K <= 4 * CHUNK) {
+    launch_short<T, EPI, 4>(a, st);
+  } else if (big >= 256 && a.K <= 6 * CHUNK && sizeof(T) == 4) {
+    launch_short<float, EPI, 6>(a, st);
+  } else if (big >= 256) {
     constexpr int NO = EPI == EPI_SWIGLU ? 2 : 4;
     tile_gemm_kernel<T, EPI, 4, 4, 1><<<dim3(cdiv(a.N, 16 * NO), cdiv(a.M, 64)), 64 * NW, 0, st>>>(a);
   } else if (a.M <= 16) {

@@ -216,3 +216,42 @@ def test_head_merged_in_slices_does_not_depend_on_the_batch(sp, G):
             assert torch.equal(got[k][s], ref[k][0]), (s, k)
         for a, b in zip(top, sp.head_topk(scfg, w, ts, 3, 1.0, one, node=0)):
             assert torch.equal(a, b), s
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("K", [8, 24, 32, 40, 64, 72, 104, 128, 136, 168, 192, 200, 256, 264, 328, 376, 384, 392])
+def test_tile_gemm_short_k_rows_do_not_depend_on_the_batch(sp, K, dtype):
+    """Up to six chunks of K (128 bytes of a row each) many rows take a wavefront a tile, few rows share one: same bits, at edges
+    of the 32 x 32 tiles; and against the float64 product, |fp32 sum - exact| <= (K + 16) 2^-24 sum |a w|."""
+    M, N = 513, 2024 if dtype == "f32" else 2088      # 32 x 128 columns of workgroups cut short; bf16 off the MFMA kernel
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(K)
+    A, W, W1, R = ((torch.randn(s, generator=g) * f).to(td) for s, f in (((M, K), 1.0), ((N, K), 0.3), ((N, K), 0.3), ((M, N), 1.0)))
+    a, w, w1, r = [t.to(DEV) for t in (A, W, W1, R)]
+    full = [sp.gemm(sp.GEMM_STORE, a, w), sp.gemm(sp.GEMM_RESID, a, w, R=r), sp.gemm(sp.GEMM_SWIGLU, a, w, w1)]
+    for n in (1, 16, 33):
+        part = a[-n:].contiguous()
+        few = [sp.gemm(sp.GEMM_STORE, part, w), sp.gemm(sp.GEMM_RESID, part, w, R=r[-n:].contiguous()), sp.gemm(sp.GEMM_SWIGLU, part, w, w1)]
+        for x, y in zip(full, few):
+            assert torch.equal(x[-n:], y), n
+    ref, out = to_np(A) @ to_np(W).T, 2.0 ** -24 if dtype == "f32" else 1.02 * 2.0 ** -8
+    assert (np.abs(to_np(full[0]) - ref) <= (K + 16) * 2.0 ** -24 * (np.abs(to_np(A)) @ np.abs(to_np(W)).T) + out * np.abs(ref) + 1e-30).all()
+
+
+def test_layer_of_short_rows_with_masked_rows_only(sp):
+    """A layer 64 wide with projections of many columns (one wavefront a tile), biases, and the last layer's device row count:
+    the masked rows of the full layer, bit for bit."""
+    G, B, P = 17, 32, 20
+    cfg = synth.CONFIGS["c1"].scaled(dtype="f32", d=64, Hq=8, Hkv=8, hd=128, F=4104, P=P, B=B, G=G)
+    scfg, w = sp.cfg_from_synth(cfg), {n: t.to(DEV) for n, t in synth.layer_weights(cfg, 0, bias=True).items()}
+    g = torch.Generator().manual_seed(1)
+    k, v = (torch.randn((8, P + B, 128), generator=g).to(DEV) for _ in range(2))
+    x = synth.hidden_states(cfg, G=G).to(DEV)
+    tok = torch.where(torch.rand((G, B), generator=g) < 0.9, cfg.mask_id, 1).to(torch.int32).to(DEV)
+    lw, pk, ws = sp.layer_weights(w), sp.prefix_kv(k, v, P, 0), sp.alloc_workspace(scfg, G, B, P, DEV)
+    full = sp.verify_layer(scfg, lw, pk, x, P, ws).clone()
+    last = sp.verify_layer_last(scfg, lw, pk, x, tok, P, ws, torch.zeros_like(x))
+    masked = tok == cfg.mask_id
+    assert torch.equal(last[masked], full[masked])
+    one = sp.verify_layer(scfg, lw, pk, x[3:4].contiguous(), P, sp.alloc_workspace(scfg, 1, B, P, DEV))
+    assert torch.equal(one[0], full[3])
