@@ -12,8 +12,12 @@
 // S^T = K Q^T and then O^T = V^T P^T: accumulator element v of lane (q = lane % 16, group = lane / 16) of S^T is key
 // 4 * group + v of query q, which is exactly the P^T operand element of the second product's v-th step, so the
 // probabilities never leave their registers, and the softmax scale of a query is lane-local in both products.
+// Values are loaded in front of the scores and kept as they are stored, so that they arrive meanwhile.  Loading keys and values a
+// whole chunk ahead was measured and taken back: bf16, 128 workgroups, 17.7 us with it and 17.3 without at 544 keys of 64, 13.6 and
+// 12.5 at 232, 31.4 and 30.6 at 544 keys of 128.  Above head_dim 128 in fp32 a wavefront spills 18 to 118 registers (bf16 above 192:
+// 34), shapes that only have to run.
 // Measured against one workgroup per (row, head), which computed its own rotary angles in double precision and read K one
-// row per thread: bf16, 128 rows, 16 heads of 64, 544 keys 102 -> 23.5 us; what is left is the fp32 matrix rate on 128
+// row per thread: bf16, 128 rows, 16 heads of 64, 544 keys 102 -> 17.3 us; what is left is the fp32 matrix rate on 128
 // workgroups and the latency of a chunk.
 #include "kernels.h"
 
@@ -23,7 +27,7 @@ namespace {
 
 constexpr int NW = 8;
 
-// four values as they are stored, and as fp32: a load that is to stay in flight is kept in its stored form
+// four values as they are stored, and as fp32
 template <typename T> struct Four;
 template <> struct Four<float> { typedef f32x4 type; };
 template <> struct Four<bf16_t> { typedef bf16x4 type; };
@@ -51,7 +55,7 @@ __device__ __forceinline__ f32x4 load4_rotated(const T* row, int k, int half, co
 }
 
 // H64 = head_dim in units of 64, rounded up; rows of Q, K, V beyond head_dim count as zero
-template <typename T, int H64, bool AHEAD>
+template <typename T, int H64>
 __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict__ qkv, const T* __restrict__ pk,
                                                             const T* __restrict__ pv, T* __restrict__ out,
                                                             const float2* __restrict__ tab, int B, int Hq, int Hkv, int hd,
@@ -102,13 +106,7 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
       ch.k[i] = k < hd ? load4_raw(kr + k) : four_t{};
     }
   };
-  auto load_chunk = [&](int c, Chunk& ch) {
-    load_values(c, ch);
-    if (!touches_block(c)) load_keys(c, ch);
-  };
-  // AHEAD: loads run one chunk ahead of the products, the first ones ahead of the queries' rotation
   Chunk cur;
-  if (AHEAD && wave < chunks) load_chunk(wave, cur);
   f32x4 q[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
@@ -116,10 +114,7 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
     q[i] = k < hd ? load4_rotated(qrow, k, half, tab + (size_t)b * half) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
   for (int c = wave; c < chunks; c += NW) {
-    Chunk next;
-    if (!AHEAD) load_values(c, cur);                // in flight during the scores
-    else if (c + NW < chunks) load_chunk(c + NW, next);
-    if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+    load_values(c, cur);                            // in flight during the scores
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     if (touches_block(c)) {
       const int jk = min(16 * c + l16, n_keys - 1);   // this lane's key (operand rows beyond the last key repeat it)
@@ -138,7 +133,7 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
         for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[e], q[i][e], s, 0, 0, 0);
       }
     } else {
-      if (!AHEAD) load_keys(c, cur);
+      load_keys(c, cur);
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         const f32x4 kk = widen(cur.k[i]);
@@ -173,7 +168,6 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
         for (int v = 0; v < 4; ++v)
           o[u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(static_cast<float>(cur.v[v][u][j]), s[v], o[u][j], 0, 0, 0);
       }
-    if (AHEAD) cur = next;
   }
   sum += __shfl_xor(sum, 16, 64);
   sum += __shfl_xor(sum, 32, 64);
@@ -223,33 +217,20 @@ __global__ void tile_rope_kernel(float2* __restrict__ tab, int B, int half, int 
   tab[i] = make_float2((float)cos(ang), (float)sin(ang));
 }
 
-template <typename T, int H64, bool AHEAD>
-hipError_t launch_k(const AttnArgs& a, int grid, hipStream_t st) {
-  const size_t smem = sizeof(float) * NW * 16 * (size_t)(a.hd + 2);
-  if (smem > 64 * 1024) {
-    static std::atomic<unsigned long long> lds_ok{0};
-    const hipError_t e = allow_dynamic_lds((const void*)tile_attn_kernel<T, H64, AHEAD>,
-                                           (int)(sizeof(float) * NW * 16 * (64 * H64 + 2)), lds_ok);
-    if (e != hipSuccess) return e;
-  }
-  tile_attn_kernel<T, H64, AHEAD><<<grid, 64 * NW, smem, st>>>((const T*)a.qkv, (const T*)a.prefix_k, (const T*)a.prefix_v,
-                                                               (T*)a.out, (const float2*)a.partial, a.B, a.Hq, a.Hkv, a.hd,
-                                                               a.P, a.S, a.ldp ? a.ldp : a.P, a.own);
-  return hipGetLastError();
-}
-
-// Loads a chunk ahead where a compute unit gets one workgroup at most, so that nothing else covers a load's latency, where
-// a wavefront has more than one chunk, and where two chunks fit the registers (bf16 up to head_dim 128).  Measured: 128
-// workgroups, bf16, 16 heads of 64, 544 keys, the whole pass of two layers 185.3 -> 174.3 us; fp32 (twice the registers
-// and the same matrix time) 249.3 -> 251.1 us with 316 keys, 90.9 -> 92.4 us with 72, so fp32 loads where it uses.  With
-// more workgroups than compute units the registers of the second chunk would halve the workgroups of a unit.
 template <typename T, int H64>
 hipError_t launch_h(const AttnArgs& a, hipStream_t st) {
   const int grid = a.G * a.Hkv * cdiv(a.B * (a.Hq / a.Hkv), 16);
-  if constexpr (sizeof(T) == 2 && H64 <= 2) {
-    if (grid <= 256 && a.P + a.B + a.S > 16 * NW) return launch_k<T, H64, true>(a, grid, st);
+  const size_t smem = sizeof(float) * NW * 16 * (size_t)(a.hd + 2);
+  if (smem > 64 * 1024) {
+    static std::atomic<unsigned long long> lds_ok{0};
+    const hipError_t e = allow_dynamic_lds((const void*)tile_attn_kernel<T, H64>,
+                                           (int)(sizeof(float) * NW * 16 * (64 * H64 + 2)), lds_ok);
+    if (e != hipSuccess) return e;
   }
-  return launch_k<T, H64, false>(a, grid, st);
+  tile_attn_kernel<T, H64><<<grid, 64 * NW, smem, st>>>((const T*)a.qkv, (const T*)a.prefix_k, (const T*)a.prefix_v,
+                                                        (T*)a.out, (const float2*)a.partial, a.B, a.Hq, a.Hkv, a.hd,
+                                                        a.P, a.S, a.ldp ? a.ldp : a.P, a.own);
+  return hipGetLastError();
 }
 
 template <typename T>

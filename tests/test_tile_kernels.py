@@ -166,8 +166,8 @@ def test_tile_gemm_rows_do_not_depend_on_the_batch_bf16(sp, epi):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("hd,Hq,Hkv,P,S", [(64, 4, 4, 300, 0), (96, 8, 4, 130, 140), (64, 4, 4, 2000, 0), (136, 4, 4, 260, 0)])
 def test_tile_attention_states_do_not_depend_on_the_batch(sp, hd, Hq, Hkv, P, S, dtype):
-    """65 states of 16 tokens are more than 256 workgroups of attention, one or 64 states are not, and from there bf16 heads of up
-    to 128 load a chunk ahead: a state's rows are the same bits; the first also against the oracle."""
+    """65 states of 16 tokens are more than 256 workgroups of attention, one or 64 states are not: a state's rows are the same bits;
+    the first also against the oracle."""
     from oracle import spiffy_oracle as O
     B, G = 16, 65
     cfg = synth.CONFIGS["c1"].scaled(dtype=dtype, d=96, Hq=Hq, Hkv=Hkv, hd=hd, F=72, P=P, B=B, G=G)
