@@ -105,7 +105,7 @@ def test_tile_head_edges(sp, d, V, G, B):
 @pytest.mark.parametrize("last_masked", [False, True])
 @pytest.mark.parametrize("G", [1, 2, 64, 65])
 def test_head_rows_do_not_depend_on_how_the_masked_rows_are_listed(sp, G, last_masked, dtype):
-    """Up to 2048 rows the norm's workgroups find their places in the row list themselves, above a list kernel runs first: every
+    """Up to 8192 rows the norm's workgroups find their places in the row list themselves, above a list kernel runs first: every
     output of a state equals, bit for bit, that of the state alone; masked and unmasked last rows, a state without MASK."""
     B, d, V = 32, 256, 3000                            # fp32: the merge in slices; bf16: one merge, and the matrix-core head
     cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B, dtype=dtype)
@@ -255,3 +255,23 @@ def test_layer_of_short_rows_with_masked_rows_only(sp):
     assert torch.equal(last[masked], full[masked])
     one = sp.verify_layer(scfg, lw, pk, x[3:4].contiguous(), P, sp.alloc_workspace(scfg, 1, B, P, DEV))
     assert torch.equal(one[0], full[3])
+
+
+@pytest.mark.parametrize("G,last_masked", [(256, True), (256, False), (257, True), (257, False)])
+def test_head_rows_at_the_line_between_the_two_row_lists(sp, G, last_masked):
+    """8192 and 8224 rows: each state's outputs are those of the state alone, bit for bit."""
+    B, d, V = 32, 64, 600
+    cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B)
+    g = torch.Generator().manual_seed(G)
+    x, w = torch.randn((G, B, d), generator=g).to(DEV), (torch.randn((V, d), generator=g) * 0.1).to(DEV)
+    gain, tok = torch.ones(d).to(DEV), torch.randint(0, V - 1, (G, B), generator=g, dtype=torch.int32)
+    tok[torch.rand((G, B), generator=g) < 0.5] = cfg.mask_id
+    tok[G // 2], tok[G - 1, B - 1] = 1, cfg.mask_id if last_masked else 1
+    tok = tok.to(DEV)
+    scfg = sp.cfg_from_synth(cfg)
+    got = sp.decode_head(scfg, x, gain, w, tok, 0.01, sp.alloc_workspace(scfg, G, B, 0, DEV))
+    one = sp.alloc_workspace(scfg, 1, B, 0, DEV)
+    for s in (0, 1, G // 2, G - 2, G - 1):
+        ref = sp.decode_head(scfg, x[s:s + 1].contiguous(), gain, w, tok[s:s + 1].contiguous(), 0.01, one)
+        for k in ref:
+            assert torch.equal(got[k][s], ref[k][0]), (s, k)
