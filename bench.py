@@ -628,10 +628,16 @@ def subgraph_leg(sp, dev, seed, n_levels=15, D=10, iters=30):
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / iters
-    sets = math.comb(N, D)
-    return {"nodes": N, "edges": int(len(edges)), "D": D, "sets": sets, "ms": ms, "sets_per_s": sets / (ms * 1e-3),
-            "connected_sets": int(out["n_connected"].item()), "best_sum": int(out["best_sum"].item()),
-            "bound": "launch latency (three kernels)"}
+    # parents: nodes of some connected set with a child that is not root-level; their choices are what is enumerated
+    alive, kept = set(range(N)), None
+    while alive != kept:
+        kept = alive
+        alive = {q for q in kept if level[q] < 3 or any(b == q and a in kept for a, b in edges)}
+    parents = len({int(a) for a, b in edges if a in alive and b in alive and level[b] > 2})
+    return {"nodes": N, "edges": int(len(edges)), "D": D, "sets": math.comb(N, D), "parents": parents,
+            "choices_of_parents": 1 << parents, "ms": ms, "connected_sets": int(out["n_connected"].item()),
+            "best_sum": int(out["best_sum"].item()),
+            "bound": "launch latency (three kernels)" if parents <= 20 else "vector instructions"}
 
 
 def full_sequence_leg(sp, cfg, layers, prefix, hw, w_embed, d_states, d_edges, dev, S=224, steps=5):

@@ -10,8 +10,12 @@
  *
  * Conventions for every call
  *   - Kernel choice is by shape: bf16 with head_dim 128, d % 128 == 0, ffn % 64 == 0 runs the MFMA
- *     kernels (LM head: d % 64 == 0); anything else runs shape-agnostic fp32-math kernels.  The
+ *     kernels (LM head: d % 64 == 0); anything else runs kernels for any shape on 16 x 16 matrix
+ *     instructions: products of the stored type, fp32 sums, and fp32 throughout in the attention.  The
  *     choice depends on the arguments of the call only (no environment variable, no global state).
+ *     Off the MFMA kernels 4 * (head_dim * (1 + B + 256 / head_dim) + P + B + S) may not exceed 150 KB
+ *     (the tokens after the block count as B where they are recomputed), and an LM head takes
+ *     d <= 16384: SPIFFY_ESHAPE beyond.
  *     On the MFMA kernels a layer takes d <= 16384 (a row in fp32 is kept in 64 KB of on-chip memory by
  *     the reduction behind the output and down projections); wider models get SPIFFY_ESHAPE.
  *   - All data pointers are DEVICE pointers owned by the caller unless a parameter says "host".
@@ -102,7 +106,7 @@ typedef struct {
 
 const char *spiffy_status_str(int status);
 
-/* 1 if the cfg/B combination runs on the MFMA kernels, 0 if on the generic kernels, <0 = status. */
+/* 1 if the cfg/B combination runs on the MFMA kernels, 0 if on the kernels for any shape, <0 = status. */
 int spiffy_uses_mfma(const spiffy_model_cfg *cfg, int32_t B);
 
 /* Bytes of caller-provided scratch needed by verify_layer / decode_head / verify_step for up to
@@ -182,7 +186,7 @@ int spiffy_decode_head_static(const spiffy_model_cfg *cfg, const void *hidden, c
  * timing.  A [M,K], weights [N,K] row-major, C [M,N] (SPIFFY_GEMM_SWIGLU: W0 = gate, W1 = up,
  * both [N,K], C = silu(A W0^T) * (A W1^T)); SPIFFY_GEMM_RESID: C = R + A W0^T with R [M,N];
  * SPIFFY_GEMM_STORE: C = A W0^T.  bf16 with K % 64 == 0 and N % 64 == 0 (SWIGLU: N % 32 == 0)
- * runs the MFMA kernel, anything else the generic kernel.  workspace (256-byte aligned, at least
+ * runs the MFMA kernel, anything else the kernels for any shape.  workspace (256-byte aligned, at least
  * 4*M*N*sizeof(float) bytes) may be NULL; with it, SPIFFY_GEMM_RESID slices K exactly as
  * verify_layer does for its output and down projections (the slice count depends on N and K only). */
 enum { SPIFFY_GEMM_STORE = 0, SPIFFY_GEMM_RESID = 1, SPIFFY_GEMM_SWIGLU = 2 };

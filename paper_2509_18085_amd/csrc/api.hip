@@ -60,13 +60,14 @@ bool head_shape_ok(const spiffy_model_cfg* c) {
   return mfma_lmhead_partials_per_row(c->vocab) <= 2048;
 }
 
-// Limit on the cached keys of the shapes without the MFMA attention: what one row's scores may take in LDS
-size_t generic_attn_smem(const spiffy_model_cfg* c, int B, int P) {
+// Limit on the block and the cached rows of the shapes without the MFMA attention.  Its kernel keeps neither scores nor
+// angles of a whole row and would take more; the limit is what callers of these shapes have been refused so far.
+size_t attn_limit_bytes(const spiffy_model_cfg* c, int B, int P) {
   const int hd = c->head_dim;
   const int nchunk = 256 / hd > 0 ? 256 / hd : 1;
   return sizeof(float) * ((size_t)hd + (size_t)B * hd + (size_t)(P + B) + (size_t)nchunk * hd);
 }
-constexpr size_t kMaxGenericSmem = 150 * 1024;
+constexpr size_t kAttnLimitBytes = 150 * 1024;
 
 struct Carve {
   unsigned char* base;
@@ -183,7 +184,7 @@ int check_layer_args(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w,
                         w->bq, w->bk, w->bv, prefix->k, prefix->v};
   for (const void* p : ptrs)
     if (p && !aligned16(p)) return SPIFFY_EALIGN;
-  if (!layer_mfma(cfg) && generic_attn_smem(cfg, B, prefix->P + prefix->S) > kMaxGenericSmem) return SPIFFY_ESHAPE;
+  if (!layer_mfma(cfg) && attn_limit_bytes(cfg, B, prefix->P + prefix->S) > kAttnLimitBytes) return SPIFFY_ESHAPE;
   // the reduction behind the split-K projections keeps a row of d fp32 values in 64 KB of LDS for its RMSNorm
   if (layer_mfma(cfg) && (size_t)cfg->d * sizeof(float) > 64 * 1024) return SPIFFY_ESHAPE;
   return SPIFFY_OK;
@@ -444,7 +445,7 @@ int check_head_args(const spiffy_model_cfg* cfg, const void* hidden, const void*
   if (!(threshold >= 0.f && threshold <= 1.f) || !(logit_scale > 0.f) || !std::isfinite(logit_scale))
     return SPIFFY_EINVAL;
   if (!aligned16(hidden) || !aligned16(final_norm) || !aligned16(w_vocab)) return SPIFFY_EALIGN;
-  if ((size_t)cfg->d * sizeof(float) > 64 * 1024 && !head_mfma(cfg)) return SPIFFY_ESHAPE;
+  if ((size_t)cfg->d * sizeof(float) > 64 * 1024 && !head_mfma(cfg)) return SPIFFY_ESHAPE;   // d <= 16384, as for layers
   return head_shape_ok(cfg) ? SPIFFY_OK : SPIFFY_ESHAPE;
 }
 
@@ -770,7 +771,7 @@ int spiffy_verify_step_seq(const spiffy_model_cfg* cfg, int32_t n_layers, const 
     if (S > 0) {
       if (!prefix[l].k || !prefix[l].v) return SPIFFY_EINVAL;         // rows behind the prefix are written
       if ((int64_t)prefix[l].P + B + S > prefix[l].capacity) return SPIFFY_ESHAPE;
-      if (!layer_mfma(cfg) && generic_attn_smem(cfg, S, prefix[l].P + B + S) > kMaxGenericSmem) return SPIFFY_ESHAPE;
+      if (!layer_mfma(cfg) && attn_limit_bytes(cfg, S, prefix[l].P + B + S) > kAttnLimitBytes) return SPIFFY_ESHAPE;
     }
     if (prefix[l].P > P_max) P_max = prefix[l].P;
   }
@@ -835,7 +836,7 @@ int spiffy_verify_step_commit(const spiffy_model_cfg* cfg, int32_t n_layers, con
     if (!prefix[l].k || !prefix[l].v) return SPIFFY_EINVAL;            // the finished block's rows are written
     const int cap = prefix[l].capacity ? prefix[l].capacity : prefix[l].P;
     if ((int64_t)prefix[l].P + B > cap) return SPIFFY_ESHAPE;
-    if (!layer_mfma(cfg) && generic_attn_smem(cfg, B, prefix[l].P + B + prefix[l].S) > kMaxGenericSmem) return SPIFFY_ESHAPE;
+    if (!layer_mfma(cfg) && attn_limit_bytes(cfg, B, prefix[l].P + B + prefix[l].S) > kAttnLimitBytes) return SPIFFY_ESHAPE;
     if (prefix[l].P + prefix[l].S > P_max) P_max = prefix[l].P + prefix[l].S;
   }
   if ((rc = check_head_args(cfg, workspace, final_norm, w_vocab, block_tokens, threshold, logit_scale, argmax, conf,

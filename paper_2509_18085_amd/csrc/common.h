@@ -56,10 +56,6 @@ __device__ __forceinline__ Top top_merge(const Top& a, const Top& b) {
   r.s = sa + sb;
   return r;
 }
-__device__ __forceinline__ Top top_push(const Top& a, float l, int idx) {
-  Top b{l, -INFINITY, 1.f, idx};
-  return top_merge(a, b);
-}
 __device__ __forceinline__ Top top_shfl_xor(const Top& a, int o) {
   Top b;
   b.m = __shfl_xor(a.m, o, 64);
