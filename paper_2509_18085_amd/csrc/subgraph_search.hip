@@ -76,8 +76,7 @@ constexpr unsigned long long binomial(int n, int k) { return Binomials().v[n * k
 // which grows about with the logarithm of their number.  In units of 0.05 ps:
 constexpr bool choices_pay(int n, int p, unsigned long long sets) {
   if (p > kMaxParents) return false;
-  int lg = 0;
-  for (unsigned long long s = sets; s > 1ull; s >>= 1) ++lg;
+  const int lg = sets > 1ull ? 63 - __builtin_clzll(sets) : 0;
   const long long lump = (5ll * lg - 50) * n / 40;                       // microseconds
   const unsigned long long few = 20000000ull * (unsigned long long)(lump > 6 ? lump : 6);
   return 13ull * (1ull << p) <= few + 9ull * (sets < kSat / 16 ? sets : kSat / 16);
