@@ -15,7 +15,7 @@
 // consecutive X: the first table is read without conflicts, the others are broadcast), a zero test, one binomial; the
 // leaves are summed only where X with the largest leaf counts of all could still beat the lane's best.  Candidate graphs
 // of 45 nodes have 10 to 25 parents: 2^10 .. 2^25 choices where C(45, 10) is 3.2e9 sets.  What is left is launch latency
-// (three launches) for few parents, vector instructions for many.  Measured, 45 nodes, sets of 10, 12 parents: 1514 -> 20.5 us
+// (three launches) for few parents, vector instructions for many.  Measured, 45 nodes, sets of 10, 12 parents: 1514 -> 20.1 us
 // a call against the one-by-one search (2.1e12 sets/s).
 //
 // The one-by-one search below serves graphs with many parents and small D (choices_pay has the line between the two).
