@@ -445,7 +445,7 @@ int check_head_args(const spiffy_model_cfg* cfg, const void* hidden, const void*
   if (!(threshold >= 0.f && threshold <= 1.f) || !(logit_scale > 0.f) || !std::isfinite(logit_scale))
     return SPIFFY_EINVAL;
   if (!aligned16(hidden) || !aligned16(final_norm) || !aligned16(w_vocab)) return SPIFFY_EALIGN;
-  if ((size_t)cfg->d * sizeof(float) > 64 * 1024 && !head_mfma(cfg)) return SPIFFY_ESHAPE;   // d <= 16384, as for layers
+  if ((size_t)cfg->d * sizeof(float) > 64 * 1024 && !head_mfma(cfg)) return SPIFFY_ESHAPE;   // d <= 16384
   return head_shape_ok(cfg) ? SPIFFY_OK : SPIFFY_ESHAPE;
 }
 

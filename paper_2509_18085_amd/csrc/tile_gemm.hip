@@ -390,10 +390,11 @@ void launch_short(const GemmArgs& a, hipStream_t st) {
 // Tiles of 64 x 64 (SWIGLU: 32 features) where they fill the chip: a quarter of the operand traffic per product.  Below
 // that 32 x 16 (16 x 16 with one fragment of rows): four to eight times the workgroups, each reading its operands once.
 // Measured around the line, fp32 / bf16, in us with 64 x 64 and with 32 x 16: 200 rows of 4104 columns (260 tiles of 64 x 64),
-// K = 1032: 45.4, 37.4 / 13.5, 17.9, SwiGLU 66, 58 / 22, 25; 1024 rows of 4104, 1040 tiles: 116, 150 / 46, 72; 4096 rows: 393, 578 /
-// 148, 271 (one line for both types: fp32 alone would gain from 32 x 16 tiles a little longer).  Where 64 x 64 tiles fill the chip and K has up to six chunks in fp32 (192), four in bf16 (256), a wavefront takes a
-// tile: 4096 x 4104 from K = 8 87 -> 23 / 59 -> 15, K = 136 127 -> 81 / 65 -> 32; with more chunks the shared tiles were as fast
-// or faster where they just fill the chip (1024 x 1032, SwiGLU: seven chunks fp32 23 against 25, five bf16 15 against 18).
+// K = 1032: 45.4, 37.4 / 13.5, 17.9, SwiGLU 66, 58 / 22, 25; 1024 rows of 4104, 1040 tiles: 116, 150 / 46, 72; 4096 rows: 393,
+// 578 / 148, 271 (one line for both types: fp32 alone would gain from 32 x 16 tiles a little longer).
+// Where 64 x 64 tiles fill the chip and K has up to six chunks in fp32 (192), four in bf16 (256), a wavefront takes a tile: 4096 x
+// 4104 from K = 8 87 -> 23 / 59 -> 15, K = 136 127 -> 81 / 65 -> 32; with more chunks the shared tiles were as fast or faster
+// where they just fill the chip (1024 x 1032, SwiGLU: seven chunks fp32 23 against 25, five bf16 15 against 18).
 template <typename T, int EPI>
 hipError_t launch_epi(const GemmArgs& a, hipStream_t st) {
   constexpr int CHUNK = 2 * Frag<T>::KC;

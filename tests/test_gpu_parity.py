@@ -1534,8 +1534,8 @@ def test_subgraph_search_edge_cases(sp):
 
 @pytest.mark.parametrize("scale", [1 << 29, 1 << 30, 1 << 41])
 def test_subgraph_search_large_counts_take_the_64_bit_path(sp, scale):
-    """Counts whose magnitudes add up to 2^30 or more are summed in 64 bits; below that in 32 bits: both against
-    the oracle, with negative counts and sums beyond 2^44."""
+    """Counts up to 2^41 against the oracle, with negative counts and sums beyond 2^44.  These graphs take the choices of
+    parents, which sum in 64 bits always; test_subgraph_forests has the line of the other search, 32-bit sums below 2^30."""
     count, level, edges, _ = synth.candidate_graph(6, seed=300)
     r = np.random.default_rng(scale % 1000)
     big = (r.integers(-8, 9, len(count)) * (scale // 8)).astype(np.int64) + count
