@@ -401,7 +401,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
           const float h0 = silu_mul(__uint_as_float(s0[0]), __uint_as_float(s0[1]));   // row r + up
           const float h1 = silu_mul(__uint_as_float(s1[0]), __uint_as_float(s1[1]));   // row r + 2 + up
           const float keep = odd ? h1 : h0;
-          const float got = __shfl_xor(odd ? h0 : h1, 1, 64);
+          const float got = swap_neighbours(odd ? h0 : h1);
           bf16x2 out2;
           out2[0] = static_cast<bf16_t>(odd ? got : keep);
           out2[1] = static_cast<bf16_t>(odd ? keep : got);
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
           asm volatile("" : "+v"(a0), "+v"(a1));   // two plain selects below, not a lane-indexed element extract
           const float keep = odd ? a1 : a0;
           const float give = odd ? a0 : a1;
-          const float got = __shfl_xor(give, 1, 64);
+          const float got = swap_neighbours(give);
           float lo = odd ? got : keep, hi = odd ? keep : got;   // columns n-odd, n-odd+1 of row r+odd
           if (CHECKED && r + odd >= i_max) continue;
           const size_t o = (size_t)r * a.ldc + j * 32;
