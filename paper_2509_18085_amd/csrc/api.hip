@@ -116,12 +116,13 @@ struct HeadWs {
   int32_t *row_idx, *count;
   void* nf;
   TopPartial *part, *part2, *row_top;
-  float* cand_val;       // top-K refinement candidates [B][SPIFFY_MAX_TOPK][SPIFFY_MAX_TOPK]
-  int32_t* cand_idx;
+  float *logits, *cand_val;           // top-K of a node: with summaries the logits of each position's best chunks, else candidates
+  int32_t *chunk_id, *cand_idx;
   int m_cap;
   int n_part;            // MFMA head: summaries of 128 tokens each (the top-K refinement reads them); otherwise 0
   int n_part_tile;       // head of the other shapes: parts of the vocabulary
   size_t tile_summary_bytes, bytes;      // what their summaries take; everything
+  size_t static_bytes;   // what SPIFFY_STATIC_SCRATCH_BYTES limits: the head itself and candidate lists of the top-K
 };
 HeadWs carve_head(const spiffy_model_cfg* c, int G, int B, void* base) {
   const int M = G * B;
@@ -140,8 +141,17 @@ HeadWs carve_head(const spiffy_model_cfg* c, int G, int B, void* base) {
   w.tile_summary_bytes = head_mfma(c) ? 0 : cv.off - before;
   w.part2 = (TopPartial*)cv.take(sizeof(TopPartial) * (size_t)kLmheadCombineSlices * w.m_cap);
   w.row_top = (TopPartial*)cv.take(sizeof(TopPartial) * w.m_cap);
-  w.cand_val = (float*)cv.take(sizeof(float) * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK);
-  w.cand_idx = (int32_t*)cv.take(sizeof(int32_t) * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK);
+  const size_t lists = sizeof(float) * (size_t)B * SPIFFY_MAX_TOPK * SPIFFY_MAX_TOPK;
+  w.static_bytes = cv.off - w.tile_summary_bytes + 2 * align_up(lists, 256);
+  w.logits = w.cand_val = nullptr;
+  w.chunk_id = w.cand_idx = nullptr;
+  if (w.n_part) {
+    w.logits = (float*)cv.take(sizeof(float) * (size_t)B * SPIFFY_MAX_TOPK * 128);
+    w.chunk_id = (int32_t*)cv.take(sizeof(int32_t) * (size_t)B * SPIFFY_MAX_TOPK);
+  } else {
+    w.cand_val = (float*)cv.take(lists);
+    w.cand_idx = (int32_t*)cv.take(lists);
+  }
   w.bytes = cv.off;
   return w;
 }
@@ -571,7 +581,7 @@ int spiffy_decode_head_static(const spiffy_model_cfg* cfg, const void* hidden, c
     return rc;
   if ((int64_t)G * B > SPIFFY_STATIC_MAX_ROWS) return SPIFFY_ELIMIT;
   const HeadWs need = carve_head(cfg, G, B, nullptr);
-  if (need.bytes - need.tile_summary_bytes > (size_t)SPIFFY_STATIC_SCRATCH_BYTES) return SPIFFY_ELIMIT;
+  if (need.static_bytes > (size_t)SPIFFY_STATIC_SCRATCH_BYTES) return SPIFFY_ELIMIT;
   void* ws = nullptr;
   if ((rc = static_scratch_ptr(&ws))) return rc;
   // every kernel of the head writes what it later reads (row list and count, gathered rows, summaries): nothing in
@@ -669,7 +679,7 @@ int spiffy_head_topk(const spiffy_model_cfg* cfg, const void* w_vocab, const int
   a.dtype = cfg->dtype; a.nf = ws.nf; a.w_vocab = w_vocab; a.d = cfg->d; a.V = cfg->vocab; a.scale = logit_scale;
   a.part = ws.part; a.n_part = ws.n_part; a.m_cap = ws.m_cap; a.row_top = ws.row_top; a.row_idx = ws.row_idx;
   a.count = ws.count; a.tokens = block_tokens; a.result = result; a.node = node; a.G = G; a.B = B; a.K = K;
-  a.cand_val = ws.cand_val; a.cand_idx = ws.cand_idx; a.out_tokens = topk_tokens; a.out_probs = topk_probs;
+  a.logits = ws.logits; a.chunk_id = ws.chunk_id; a.cand_val = ws.cand_val; a.cand_idx = ws.cand_idx; a.out_tokens = topk_tokens; a.out_probs = topk_probs;
   return dev(launch_head_topk(a, (hipStream_t)stream));
 }
 

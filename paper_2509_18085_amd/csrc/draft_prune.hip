@@ -24,6 +24,7 @@ constexpr int kMaxB = 4096;
 
 __global__ __launch_bounds__(64) void draft_prune_kernel(DraftPruneArgs a) {
   __shared__ int order[kMaxB];              // order[i-1] = position of rank i
+  __shared__ float s_conf[kMaxB];           // confidence of the masked positions, NaN elsewhere
   __shared__ float s_local[64], s_score[64];
   __shared__ unsigned char s_ok[64];
   __shared__ unsigned long long s_kids[64];
@@ -36,13 +37,15 @@ __global__ __launch_bounds__(64) void draft_prune_kernel(DraftPruneArgs a) {
   if (lane == 0) s_nmasked = 0;
   s_kids[lane] = 0ull;
   __syncthreads();
+  // through LDS: the comparisons read every confidence once per position, and a chain of loads from L2 is what they cost
+  for (int b = lane; b < B; b += 64) s_conf[b] = a.state[b] == a.mask_id ? a.topk_probs[(size_t)b * K] : __builtin_nanf("");
+  __syncthreads();
   for (int b = lane; b < B; b += 64) {
     if (a.state[b] != a.mask_id) continue;
-    const float pb = a.topk_probs[(size_t)b * K];
+    const float pb = s_conf[b];
     int beat = 0;
     for (int c = 0; c < B; ++c) {
-      if (a.state[c] != a.mask_id) continue;
-      const float pc = a.topk_probs[(size_t)c * K];
+      const float pc = s_conf[c];            // NaN where the position is not masked: beats nothing
       beat += (pc > pb || (pc == pb && c < b)) ? 1 : 0;
     }
     order[beat] = b;

@@ -6,13 +6,16 @@
 // best tokens of a row lie in the K chunks with the largest chunk maxima (a token outside them is beaten by
 // the K maxima; equal logits go to the lower token id and chunks are contiguous id ranges), so only those
 // K x 128 logits are recomputed - 1/250 of a second pass over the vocabulary matrix at V = 126k:
-//   topk_refine_kernel   workgroup (position b, k): picks the k-th best chunk of the row, recomputes its 128
-//                        logits (one wavefront per vocabulary row), keeps the chunk's K best
+//   topk_refine_kernel   workgroup (position b, k, slice): picks the k-th best chunk of the row and recomputes
+//                        kRefineRows of its 128 logits, four vocabulary rows a wavefront at a time
 //   topk_full_kernel     path without chunk summaries (fp32 / shapes the MFMA head does not take): one
-//                        workgroup per position scans the whole vocabulary
-//   topk_merge_kernel    one wavefront per position: K best of the K x K candidates, probabilities from the
-//                        row's (top logit, sum of exponentials); the row's argmax stays first with exactly the
-//                        confidence the head reported
+//                        workgroup per position scans the whole vocabulary, K best candidates
+//   topk_merge_kernel    one wavefront per position: K best of the K x 128 logits (of the K candidates),
+//                        probabilities from the row's (top logit, sum of exponentials); the row's argmax stays
+//                        first with exactly the confidence the head reported
+//
+// The refinement is bound by what a compute unit can fetch (25 - 50 GB/s: a chunk of 4096-wide bf16 rows is 1 MB), so a
+// chunk is shared by eight workgroups, each of which picks the chunk again (a few loads from L2).
 #include "kernels.h"
 
 namespace spiffy {
@@ -71,6 +74,7 @@ template <>
 __device__ __forceinline__ void dot_rows4<bf16_t>(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, int d, int lane,
                                                   float (&out)[4]) {
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
   for (int e = lane * 8; e < d; e += 512) {
     const bf16x8 a = *reinterpret_cast<const bf16x8*>(x + e);
     bf16x8 b[4];
@@ -91,22 +95,19 @@ __device__ __forceinline__ void dot_rows4<float>(const float* __restrict__ x, co
   for (int u = 0; u < 4; ++u) out[u] = dot_row<float>(x, w + (size_t)u * d, d, lane);
 }
 
+// vocabulary rows of a chunk that one workgroup of the refinement takes: 16, four per wavefront.  24 positions, 2 chunks each
+// of 4096 bf16 columns (50 MB): 55.9 us with a workgroup a chunk (48 at work), 14.9 us with eight.
+constexpr int kRefineRows = 16;
+
 template <typename T>
 __global__ __launch_bounds__(256) void topk_refine_kernel(HeadTopkArgs a) {
-  __shared__ float s_val[4];
-  __shared__ int s_idx[4];
-  __shared__ float s_logit[128];
-  __shared__ int s_chunk;
+  __shared__ float s_val[2][4];
+  __shared__ int s_idx[2][4];
   const int b = blockIdx.x, k = blockIdx.y;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int node = a.result ? a.result->node : a.node;
-  float* cv = a.cand_val + ((size_t)b * KMAX + k) * KMAX;
-  int32_t* ci = a.cand_idx + ((size_t)b * KMAX + k) * KMAX;
   const int r = (node >= 0 && node < a.G) ? find_row(a.row_idx, min(*a.count, a.G * a.B), node * a.B + b) : -1;
-  if (r < 0) {
-    if (tid < a.K) { cv[tid] = -INFINITY; ci[tid] = -1; }
-    return;
-  }
+  if (r < 0) return;                                // the merge sees the same and reads nothing of this position
   // ---- the k-th best chunk of the row: k+1 rounds of a workgroup-wide best, each excluding the winners so far
   float mine[8];
   const int per = (a.n_part + 255) / 256;          // <= 8 (n_part <= 2048)
@@ -125,64 +126,42 @@ __global__ __launch_bounds__(256) void topk_refine_kernel(HeadTopkArgs a) {
       if (better(mine[q], p, v, i)) { v = mine[q]; i = p; }
     }
     wave_best(v, i);
-    if (lane == 0) { s_val[w] = v; s_idx[w] = i; }
+    float* sv = s_val[round & 1];                   // two sets in turn: one barrier a round
+    int* si = s_idx[round & 1];
+    if (lane == 0) { sv[w] = v; si[w] = i; }
     __syncthreads();
-    if (tid == 0) {
-      float bv = s_val[0];
-      int bi = s_idx[0];
-      for (int x = 1; x < 4; ++x)
-        if (better(s_val[x], s_idx[x], bv, bi)) { bv = s_val[x]; bi = s_idx[x]; }
-      s_chunk = (bv == -INFINITY) ? -1 : bi;
-    }
-    __syncthreads();
-    chunk = s_chunk;
+    float bv = sv[0];
+    int bi = si[0];
+#pragma unroll
+    for (int x = 1; x < 4; ++x)
+      if (better(sv[x], si[x], bv, bi)) { bv = sv[x]; bi = si[x]; }
+    chunk = (bv == -INFINITY) ? -1 : bi;
     if (chunk < 0) break;
 #pragma unroll
     for (int q = 0; q < 8; ++q)
       if (tid + 256 * q == chunk) mine[q] = -INFINITY;
-    __syncthreads();
   }
-  if (chunk < 0) {                                  // fewer than k+1 chunks hold anything
-    if (tid < a.K) { cv[tid] = -INFINITY; ci[tid] = -1; }
-    return;
-  }
-  // ---- its 128 logits: wavefront w takes vocabulary rows v0 + 32w .. v0 + 32w + 31
-  const int v0 = chunk * 128;
+  if (blockIdx.z == 0 && tid == 0) a.chunk_id[b * KMAX + k] = chunk;
+  if (chunk < 0) return;                            // fewer than k+1 chunks hold anything
+  // ---- its logits: four vocabulary rows at a time, so that their loads are in flight together (every row keeps its own
+  // accumulation order: the logits are those of one row after the other)
   const T* x = reinterpret_cast<const T*>(a.nf) + (size_t)r * a.d;
-  // four vocabulary rows at a time, so that their loads are in flight together (every row keeps its own accumulation
-  // order: the logits are those of one row after the other)
-  for (int i = 0; i < 32; i += 4) {
+  float* logits = a.logits + ((size_t)b * KMAX + k) * 128;
+  for (int i = blockIdx.z * kRefineRows + w * 4; i < (int)(blockIdx.z + 1) * kRefineRows; i += 16) {
+    const int v0 = chunk * 128 + i;
     float l[4];
-    if (v0 + w * 32 + i + 3 < a.V) {
-      dot_rows4<T>(x, reinterpret_cast<const T*>(a.w_vocab) + (size_t)(v0 + w * 32 + i) * a.d, a.d, lane, l);
+    if (v0 + 3 < a.V) {
+      dot_rows4<T>(x, reinterpret_cast<const T*>(a.w_vocab) + (size_t)v0 * a.d, a.d, lane, l);
 #pragma unroll
       for (int u = 0; u < 4; ++u) l[u] *= a.scale;
     } else {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int v = v0 + w * 32 + i + u;
         l[u] = -INFINITY;
-        if (v < a.V) l[u] = dot_row<T>(x, reinterpret_cast<const T*>(a.w_vocab) + (size_t)v * a.d, a.d, lane) * a.scale;
+        if (v0 + u < a.V) l[u] = dot_row<T>(x, reinterpret_cast<const T*>(a.w_vocab) + (size_t)(v0 + u) * a.d, a.d, lane) * a.scale;
       }
     }
-    if (lane == 0) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) s_logit[w * 32 + i + u] = l[u];
-    }
-  }
-  __syncthreads();
-  // ---- the chunk's K best
-  if (w == 0) {
-    float c0 = s_logit[lane], c1 = s_logit[lane + 64];
-    for (int j = 0; j < a.K; ++j) {
-      float v = c0;
-      int i = v0 + lane;
-      if (better(c1, v0 + lane + 64, v, i)) { v = c1; i = v0 + lane + 64; }
-      wave_best(v, i);
-      if (lane == 0) { cv[j] = v; ci[j] = (v == -INFINITY) ? -1 : i; }
-      if (i == v0 + lane) c0 = -INFINITY;
-      if (i == v0 + lane + 64) c1 = -INFINITY;
-    }
+    if (lane == 0) *reinterpret_cast<f32x4*>(logits + i) = f32x4{l[0], l[1], l[2], l[3]};
   }
 }
 
@@ -237,6 +216,8 @@ __global__ __launch_bounds__(256) void topk_full_kernel(HeadTopkArgs a) {
   }
 }
 
+// CHUNKS: the candidates are the logits of the row's K best chunks; otherwise the K best of the whole vocabulary
+template <bool CHUNKS>
 __global__ __launch_bounds__(64) void topk_merge_kernel(HeadTopkArgs a) {
   const int b = blockIdx.x, lane = threadIdx.x;
   const int node = a.result ? a.result->node : a.node;
@@ -256,33 +237,41 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(HeadTopkArgs a) {
   // candidate whose recomputed logit exceeds the head's top logit is held at it, so probabilities never increase
   // along a row.
   if (lane == 0) { ot[0] = top.idx; op[0] = 1.0f / top.s; }
-  // lane = k * K + j of the candidate table
-  float v = -INFINITY;
-  int i = -1;
-  if (lane < a.K * a.K) {
-    const int k = lane / a.K, j = lane % a.K;
-    v = a.cand_val[((size_t)b * KMAX + k) * KMAX + j];
-    i = a.cand_idx[((size_t)b * KMAX + k) * KMAX + j];
-  }
-  if (i < 0 || i == top.idx) { v = -INFINITY; i = -1; }
-  float key = v;
-  const float val = fminf(v, top.m);
-  for (int j = 1; j < a.K; ++j) {
-    float bk = key;
-    int bi = (i < 0) ? 0x7fffffff : i;
-    wave_best(bk, bi);
-    const bool won = (i >= 0) && i == bi && key == bk && bk != -INFINITY;
-    const unsigned long long wm = __ballot(won);
-    float pv = 0.f;
-    int pt = -1;
-    if (wm) {
-      const int src = __ffsll((long long)wm) - 1;
-      const float lv = __shfl(val, src, 64);
-      pt = bi;
-      pv = __expf(lv - top.m) / top.s;
+  // the lane's candidates: elements lane and lane + 64 of every chunk, or element lane of the candidate list
+  constexpr int NC = CHUNKS ? 2 * KMAX : 1;
+  float cv[NC];
+  int ci[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    cv[q] = -INFINITY;
+    ci[q] = -1;
+    if (CHUNKS) {
+      const int k = q >> 1, chunk = k < a.K ? a.chunk_id[b * KMAX + k] : -1, e = lane + 64 * (q & 1);
+      if (chunk >= 0) {
+        cv[q] = a.logits[((size_t)b * KMAX + k) * 128 + e];
+        ci[q] = chunk * 128 + e;
+      }
+    } else if (lane < a.K) {
+      cv[q] = a.cand_val[(size_t)b * KMAX * KMAX + lane];
+      ci[q] = a.cand_idx[(size_t)b * KMAX * KMAX + lane];
     }
-    if (lane == 0) { ot[j] = pt; op[j] = pv; }
-    if (won) key = -INFINITY;
+    if (ci[q] < 0 || ci[q] == top.idx) { cv[q] = -INFINITY; ci[q] = -1; }
+  }
+  for (int j = 1; j < a.K; ++j) {
+    float bk = -INFINITY;
+    int bi = 0x7fffffff;
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      if (ci[q] >= 0 && better(cv[q], ci[q], bk, bi)) { bk = cv[q]; bi = ci[q]; }
+    wave_best(bk, bi);
+    const bool any = bk != -INFINITY;               // -inf: no candidate is left
+    if (lane == 0) {
+      ot[j] = any ? bi : -1;
+      op[j] = any ? __expf(fminf(bk, top.m) - top.m) / top.s : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      if (ci[q] == bi) { cv[q] = -INFINITY; ci[q] = -1; }
   }
 }
 
@@ -292,14 +281,17 @@ hipError_t launch_head_topk(const HeadTopkArgs& a, hipStream_t st) {
   if (a.K < 1 || a.K > KMAX || a.B < 1) return hipErrorInvalidValue;
   if (a.n_part > 0) {
     if (a.n_part > 2048 || a.dtype != SPIFFY_BF16 || a.d % 8 != 0) return hipErrorInvalidValue;
-    topk_refine_kernel<bf16_t><<<dim3(a.B, a.K), 256, 0, st>>>(a);
-  } else if (a.dtype == SPIFFY_F32) {
+    topk_refine_kernel<bf16_t><<<dim3(a.B, a.K, 128 / kRefineRows), 256, 0, st>>>(a);
+    topk_merge_kernel<true><<<a.B, 64, 0, st>>>(a);
+    return hipGetLastError();
+  }
+  if (a.dtype == SPIFFY_F32) {
     topk_full_kernel<float><<<a.B, 256, 0, st>>>(a);
   } else {
     if (a.d % 8 != 0) return hipErrorInvalidValue;
     topk_full_kernel<bf16_t><<<a.B, 256, 0, st>>>(a);
   }
-  topk_merge_kernel<<<a.B, 64, 0, st>>>(a);
+  topk_merge_kernel<false><<<a.B, 64, 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -83,7 +83,9 @@ struct HeadTopkArgs {
   const int32_t* tokens;          // [G*B] block tokens
   const spiffy_accept_result* result;   // node read on the device; NULL: use `node`
   int node, G, B, K;
-  float* cand_val;                // [B][SPIFFY_MAX_TOPK][SPIFFY_MAX_TOPK]
+  float* logits;                  // with summaries: [B][SPIFFY_MAX_TOPK][128], logits of the row's best chunks
+  int32_t* chunk_id;              // [B][SPIFFY_MAX_TOPK]
+  float* cand_val;                // without: [B][SPIFFY_MAX_TOPK][SPIFFY_MAX_TOPK], the first SPIFFY_MAX_TOPK of each in use
   int32_t* cand_idx;
   int32_t* out_tokens;            // [B][K]
   float* out_probs;               // [B][K]
