@@ -35,12 +35,6 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// value of the lane whose id differs in bit 0.  One vector instruction (DPP quad permutation); __shfl_xor(x, 1) becomes a
-// trip through the LDS crossbar with an address of its own (gate/up at 1024 rows 165.6 -> 160.1 us, QKV 89.9 -> 85.4).
-__device__ __forceinline__ float swap_neighbours(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]
-}
-
 // Running summary of a set of logits: top value, its lowest index, runner-up value and
 // sum of exp(l - top).  Merging two summaries is exact for (top, index) and stable for the sum.
 struct Top {

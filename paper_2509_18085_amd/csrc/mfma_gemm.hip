@@ -260,6 +260,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
     if (NF <= NMF - 1) return m < 1 ? 0 : (m - 1 < NF ? m - 1 : NF);
     return m < NMF - 1 ? (m * NF) / (NMF - 1) : NF;
   };
+  // Weights as the A operand (ROW_LANES): a lane owns one row of the result (a token) and runs of four columns, so the
+  // epilogues work inside a lane - no partner values to fetch - and store 16 bytes at a time (gate/up at 1024 rows
+  // 160 -> 157 us, 768 rows of 18944 features 146 -> 139).  The LM head has its vocabulary there anyway; fp32 partials keep 32 columns side by side in the
+  // lanes, whole 128-byte lines a store (1 - 2 us faster at 1024 rows than 16-byte runs of 32 rows).
+  constexpr bool ROW_LANES = EPI != EPI_LMHEAD && EPI != EPI_PARTIAL;
+  auto mfma = [&](int i, int j, int buf) {
+    if (!math) return;
+    acc[i][j] = !ROW_LANES ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[buf][i], fy[buf][j], acc[i][j], 0, 0, 0)
+                      : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[buf][j], fx[buf][i], acc[i][j], 0, 0, 0);
+  };
   // one K-tile; STEADY = every tile this iteration prefetches exists (no bounds checks, no branches)
   auto k_tile = [&](int kt, auto steady_tag) {
     constexpr bool STEADY = decltype(steady_tag)::value;
@@ -272,7 +282,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
 #pragma unroll
       for (int m = 0; m < NMF; ++m) {
         const int i = m / TN, j = m % TN;
-        if (math) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kk & 1][i], fy[kk & 1][j], acc[i][j], 0, 0, 0);
+        mfma(i, j, kk & 1);
 #pragma unroll
         for (int r = frag_lo(m); r < frag_lo(m + 1); ++r) ldfrag((kk + 1) & 1, xs, ys, kk + 1, r);
         const int slot = NMF + kk * NMF + m;      // position among the NSLOT MFMAs that follow barrier kt-1
@@ -292,7 +302,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
 #pragma unroll
     for (int m = 0; m < NMF; ++m) {
       const int i = m / TN, j = m % TN;
-      if (math) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[1][i], fy[1][j], acc[i][j], 0, 0, 0);
+      mfma(i, j, 1);
 #pragma unroll
       for (int r = frag_lo(m); r < frag_lo(m + 1); ++r) ldfrag(0, xs1, ys1, 0, r);
 #pragma unroll
@@ -309,9 +319,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
   for (; kt < KT; ++kt) k_tile(kt, std::false_type{});
   if (!math) return;      // (no barrier follows the K loop)
 
-  // accumulator element (i,j,v) of this lane: row  = i0 + wm*RW + i*32 + 8*(v/4) + 4*hh + v%4
-  //                                           col  = wn*CW + j*32 + l32   (within the tile)
   if (EPI == EPI_LMHEAD) {
+    // accumulator element (i,j,v) of this lane: row = i0 + wm*RW + i*32 + 8*(v/4) + 4*hh + v%4, column wn*CW + j*32 + l32
+    // of the tile
     // Per token column: top value, its lowest vocabulary index, runner-up and sum of exponentials over the
     // lane's 64 vocabulary rows, on the unscaled accumulators (the scale is positive, so the order is the
     // same); the lane's rows are visited in increasing vocabulary index, so "strictly greater" keeps the
@@ -361,6 +371,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
   }
 
   if (EPI == EPI_PARTIAL) {
+    // accumulator elements as for the LM head
     float* P = reinterpret_cast<float*>(a.C) + (size_t)kz * (a.Mz ? a.Mz : a.M) * a.ldc;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -374,95 +385,79 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
     return;
   }
 
+  // accumulator element (i,j,v) of this lane: row i0 + wm*RW + i*32 + l32, column wn*CW + j*32 + 8*(v/4) + 4*hh + v%4 of the
+  // tile: four runs of four columns, the lane 32 further on holds the runs in between
+  const int r_lane = i0 + wm * RW + l32;
+  // Sixteen consecutive columns of the lane's row: run 0 of the lower lane, run 0 of the upper, run 1 of the lower, run 1 of
+  // the upper.  The lanes trade run 1 against run 0 and hold eight columns each: columns 8*hh .. 8*hh+7, one 16-byte store.
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  auto pack2 = [](float x, float y) {
+    bf16x2 t;
+    t[0] = static_cast<bf16_t>(x);
+    t[1] = static_cast<bf16_t>(y);
+    return __builtin_bit_cast(unsigned int, t);
+  };
+  auto pack16 = [&](const float (&x)[8]) {     // x: run 0, run 1
+    const u32x2 s0 = __builtin_amdgcn_permlane32_swap(pack2(x[0], x[1]), pack2(x[4], x[5]), false, false);
+    const u32x2 s1 = __builtin_amdgcn_permlane32_swap(pack2(x[2], x[3]), pack2(x[6], x[7]), false, false);
+    return u32x4{s0[0], s1[0], s0[1], s1[1]};
+  };
+
   bf16_t* C = reinterpret_cast<bf16_t*>(a.C);
   if (EPI == EPI_SWIGLU) {
-    // lanes 0-15 of a half hold gate values, lanes 16-31 the up values of the same features.  For every
-    // pair of rows (v, v+1) the two lanes swap one value (v_permlane16_swap): the gate lane keeps row v and
-    // receives up(v), the up lane keeps row v+1 and receives gate(v+1); each then finishes one row.  Two such
-    // row pairs (v, v+1), (v+2, v+3) are stored together: neighbouring lanes (features f, f+1) trade one result,
-    // the even lane stores both features of the first pair's row, the odd lane those of the second pair's row.
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    const int up = (l32 & 16) ? 1 : 0, odd = l32 & 1;
-    // per-lane part of the address once; the row part below is the same for every lane of the half
-    bf16_t* Cl = C + (size_t)(up + 2 * odd) * a.ldc + tj * (BN / 2) + wn * TN * 16 + (l32 & 15) - odd;
+    // columns 0 .. 15 of a 32-column block are gate values, 16 .. 31 the up values of the same features
+    bf16_t* Cl = C + tj * (BN / 2) + wn * TN * 16 + 8 * hh;
     auto silu_mul = [](float g, float u) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u; };
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+      const int r = r_lane + i * 32;
 #pragma unroll
-      for (int v = 0; v < 16; v += 4) {
-        const int r = i0 + wm * RW + i * 32 + 8 * (v >> 2) + 4 * hh;   // row of accumulator element v in the gate lanes
-        const bool ok = r + up + 2 * odd < i_max;
+      for (int j = 0; j < TN; ++j) {
+        float h[8];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const u32x2 s0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][j][v]), __float_as_uint(acc[i][j][v + 1]),
-                                                            false, false);
-          const u32x2 s1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][j][v + 2]), __float_as_uint(acc[i][j][v + 3]),
-                                                            false, false);
-          const float h0 = silu_mul(__uint_as_float(s0[0]), __uint_as_float(s0[1]));   // row r + up
-          const float h1 = silu_mul(__uint_as_float(s1[0]), __uint_as_float(s1[1]));   // row r + 2 + up
-          const float keep = odd ? h1 : h0;
-          const float got = swap_neighbours(odd ? h0 : h1);
-          bf16x2 out2;
-          out2[0] = static_cast<bf16_t>(odd ? got : keep);
-          out2[1] = static_cast<bf16_t>(odd ? keep : got);
-          if (ok) *reinterpret_cast<bf16x2*>(Cl + (size_t)r * a.ldc + j * 16) = out2;
-        }
+        for (int v = 0; v < 8; ++v) h[v] = silu_mul(acc[i][j][v], acc[i][j][v + 8]);
+        const u32x4 o = pack16(h);
+        if (r < i_max) *reinterpret_cast<u32x4*>(Cl + (size_t)r * a.ldc + j * 16) = o;
       }
+    }
     return;
   }
 
   const bf16_t* R = reinterpret_cast<const bf16_t*>(a.R);
-  const bool has_bias = EPI == EPI_STORE && (a.bias[0] || a.bias[1] || a.bias[2]);
-  // rows (v, v+1) of two neighbouring columns are regrouped so that every lane stores one 4-byte pair: the
-  // even lane takes row v (its own column and the next one), the odd lane row v+1
-  const int odd = l32 & 1;
-  float bv[TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int n = j0 + wn * CW + j * 32 + l32;
-    bv[j] = 0.f;
-    if (has_bias) {
-      const bf16_t* bp = nullptr;
-      if (n < a.Nseg[0]) { if (a.bias[0]) bp = (const bf16_t*)a.bias[0] + n; }
-      else if (n < a.Nseg[0] + a.Nseg[1]) { if (a.bias[1]) bp = (const bf16_t*)a.bias[1] + (n - a.Nseg[0]); }
-      else { if (a.bias[2]) bp = (const bf16_t*)a.bias[2] + (n - a.Nseg[0] - a.Nseg[1]); }
-      if (bp) bv[j] = static_cast<float>(*bp);
-    }
-  }
-  // per-lane part of the address once; the row part below is the same for every lane of the half
-  const size_t lane_off = (size_t)odd * a.ldc + (j0 + wn * CW + l32 - odd);
-  bf16_t* Cl = C + lane_off;
-  const bf16_t* Rl = R + lane_off;
-  auto store_all = [&](auto checked_tag) {
-    constexpr bool CHECKED = decltype(checked_tag)::value;
+  for (int i = 0; i < TM; ++i) {
+    const int r = r_lane + i * 32;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        const int r = i0 + wm * RW + i * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);   // the even lane's row
+      for (int v0 = 0; v0 < 16; v0 += 8) {       // sixteen columns
+        const int n = j0 + wn * CW + j * 32 + 2 * v0;
+        float x[8];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          float a0 = acc[i][j][v] + bv[j], a1 = acc[i][j][v + 1] + bv[j];
-          asm volatile("" : "+v"(a0), "+v"(a1));   // two plain selects below, not a lane-indexed element extract
-          const float keep = odd ? a1 : a0;
-          const float give = odd ? a0 : a1;
-          const float got = swap_neighbours(give);
-          float lo = odd ? got : keep, hi = odd ? keep : got;   // columns n-odd, n-odd+1 of row r+odd
-          if (CHECKED && r + odd >= i_max) continue;
-          const size_t o = (size_t)r * a.ldc + j * 32;
-          if (EPI == EPI_RESID) {
-            const bf16x2 rr = *reinterpret_cast<const bf16x2*>(Rl + o);
-            lo += static_cast<float>(rr[0]);
-            hi += static_cast<float>(rr[1]);
+        for (int v = 0; v < 8; ++v) x[v] = acc[i][j][v0 + v];
+        if (EPI == EPI_STORE) {
+          const int s0 = n < a.Nseg[0] ? 0 : (n < a.Nseg[0] + a.Nseg[1] ? a.Nseg[0] : a.Nseg[0] + a.Nseg[1]);
+          const void* bias = n < a.Nseg[0] ? a.bias[0] : (n < a.Nseg[0] + a.Nseg[1] ? a.bias[1] : a.bias[2]);
+          if (bias) {
+            const bf16_t* bp = (const bf16_t*)bias + (n - s0) + 4 * hh;
+#pragma unroll
+            for (int v = 0; v < 8; ++v) x[v] += static_cast<float>(bp[2 * (v & 4) + (v & 3)]);
           }
-          bf16x2 out2;
-          out2[0] = static_cast<bf16_t>(lo);
-          out2[1] = static_cast<bf16_t>(hi);
-          *reinterpret_cast<bf16x2*>(Cl + o) = out2;
         }
+        if (EPI == EPI_RESID && r < i_max) {
+          const bf16_t* rp = R + (size_t)r * a.ldc + n + 4 * hh;
+#pragma unroll
+          for (int v = 0; v < 8; v += 4) {
+            const bf16x4 rr = *reinterpret_cast<const bf16x4*>(rp + 2 * v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[v + e] += static_cast<float>(rr[e]);
+          }
+        }
+        const u32x4 o = pack16(x);
+        if (r < i_max) *reinterpret_cast<u32x4*>(C + (size_t)r * a.ldc + n + 8 * hh) = o;
       }
-  };
-  if (i0 + BM <= i_max) store_all(std::false_type{}); else store_all(std::true_type{});
+  }
 }
 
 template <int EPI, int BN, int SD, int BMT, int SA>
