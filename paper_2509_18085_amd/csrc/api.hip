@@ -81,7 +81,9 @@ struct Carve {
 };
 
 struct LayerWs {
-  void *n, *qkv, *attn, *h, *act, *attn_partial, *attn_partial_seq, *splitk;
+  void *n, *qkv, *attn, *h, *act;
+  void *rope;                    // rotary table: B rows, then S_seq rows
+  void *attn_partial, *attn_partial_seq, *splitk;
   void *gat_attn, *gat_x;        // last layer, masked rows only: gathered attention rows and residual rows
   int32_t *rows, *count;         // ... and their row list
   size_t bytes;
@@ -98,11 +100,9 @@ LayerWs carve_layer(const spiffy_model_cfg* c, int G, int B, int P, void* base, 
   w.attn = cv.take(M * (size_t)c->n_q_heads * c->head_dim * es);
   w.h = cv.take(M * c->d * es);
   w.act = cv.take(M * c->ffn * es);
-  w.attn_partial = cv.take(layer_mfma(c) ? mfma_attn_partial_bytes(G, B, c->n_q_heads, c->head_dim, P + S_seq)
-                                         : tile_attn_scratch_bytes(B, c->head_dim));
-  w.attn_partial_seq = cv.take(!S_seq ? 0
-                               : layer_mfma(c) ? mfma_attn_partial_bytes(1, S_seq, c->n_q_heads, c->head_dim, P + B + S_seq)
-                                               : tile_attn_scratch_bytes(S_seq, c->head_dim));
+  w.rope = cv.take(tile_attn_scratch_bytes(B + S_seq, c->head_dim));     // of that size on either path
+  w.attn_partial = cv.take(layer_mfma(c) ? mfma_attn_partial_bytes(G, B, c->n_q_heads, c->head_dim, P + S_seq) : 0);
+  w.attn_partial_seq = cv.take(layer_mfma(c) && S_seq ? mfma_attn_partial_bytes(1, S_seq, c->n_q_heads, c->head_dim, P + B + S_seq) : 0);
   w.splitk = cv.take(layer_mfma(c) ? sizeof(float) * 4 * M * c->d : 0);   // up to 4 K slices of [M,d] fp32
   w.gat_attn = cv.take(M * (size_t)c->n_q_heads * c->head_dim * es);
   w.gat_x = cv.take(M * c->d * es);
@@ -210,7 +210,6 @@ struct LayerChain {
   bool normed_out = false;   // set when ws.n holds the next layer's normalised input on return
   bool append_kv = false;    // write the (rotated) K and V rows of state 0 into the cache at rows P .. P+B-1
   int seq_S = 0;             // full-sequence step: this many true suffix rows follow the G*B block rows
-  bool rope_ready_seq = false;
   // commit-and-verify step (seq_S == B): the trailing B rows are the finished block BEFORE the one being decoded.
   // prefix->P counts the rows in front of that finished block; its keys / values are written to cache rows
   // P .. P+B-1 and the G states (positions pos0 = that block's + B) attend to P + B cached rows.
@@ -245,6 +244,7 @@ hipError_t launch_gemm_mfma_rows(int epi, GemmArgs g, int rows_a, int rows_b, in
   b.A = reinterpret_cast<const char*>(g.A) + (size_t)rows_a * g.lda * es;
   b.C = reinterpret_cast<char*>(g.C) + (size_t)rows_a * g.ldc * ces;
   if (g.R) b.R = reinterpret_cast<const char*>(g.R) + (size_t)rows_a * g.ldc * es;
+  b.qkv.row0 += rows_a;
   return launch_gemm_mfma(epi, b, st);
 }
 
@@ -277,11 +277,8 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   g.bias[0] = w->bq; g.bias[1] = w->bk; g.bias[2] = w->bv;
   g.Nseg[0] = qd; g.Nseg[1] = kvd; g.Nseg[2] = kvd;
   g.N = qd + 2 * kvd; g.C = ws.qkv; g.ldc = g.N; g.scale = 1.f;
-  const bool mf_qkv = mf && mfma_gemm_supported(EPI_STORE, g);
-  if ((rc = dev(mf_qkv ? mfma_rows(EPI_STORE, g) : launch_gemm_tile(dt, EPI_STORE, g, st)))) return rc;
-
   AttnArgs a;
-  a.qkv = ws.qkv; a.prefix_k = prefix->k; a.prefix_v = prefix->v; a.out = ws.attn; a.partial = ws.attn_partial;
+  a.qkv = ws.qkv; a.prefix_k = prefix->k; a.prefix_v = prefix->v; a.out = ws.attn;
   a.G = G; a.B = B; a.Hq = cfg->n_q_heads; a.Hkv = cfg->n_kv_heads; a.hd = cfg->head_dim; a.P = prefix->P;
   a.ldp = prefix->capacity;
   a.S = S_seq ? S_seq : prefix->S;
@@ -292,47 +289,39 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   a.own = 1;
   a.pos0 = pos0; a.rope_base = cfg->rope_base; a.rope_ready = chain && chain->rope_ready;
   const int ldp = prefix->capacity ? prefix->capacity : prefix->P;
-  // The appends rotate keys with the tables the attention kernels use (built here, once per step, when the MFMA
-  // attention will run; otherwise the append computes the same values itself).
-  const bool mfa = mf && mfma_attn_supported(a);
   const int tail_pos0 = prev ? pos0 - B : pos0 + B;
-  bool tail_rope_ready = chain && chain->rope_ready_seq;
-  const void *tab = nullptr, *tab_tail = nullptr;
-  if (mfa && chain && (chain->append_kv || S_seq)) {
-    if (!a.rope_ready) {
-      launch_rope_table(ws.attn_partial, B, pos0, cfg->rope_base, st);
-      a.rope_ready = 1;
-    }
-    tab = ws.attn_partial;
-    if (S_seq) {
-      if (!tail_rope_ready) {
-        launch_rope_table(ws.attn_partial_seq, S_seq, tail_pos0, cfg->rope_base, st);
-        tail_rope_ready = true;
-      }
-      tab_tail = ws.attn_partial_seq;
-    }
-  }
-  if (S_seq && !prev) {
-    // the true block (state 0: qkv rows 0 .. B-1) and the suffix (qkv rows G*B ..) land next to each other in the cache,
-    // at consecutive positions: one launch over the two runs of rows
-    if ((rc = dev(launch_kv_append(dt, ws.qkv, a.Hq, a.Hkv, a.hd, B + S_seq, pos0, cfg->rope_base,
-                                   const_cast<void*>(prefix->k), const_cast<void*>(prefix->v), prefix->P, ldp, st, B,
-                                   (G - 1) * B, tab, tab_tail))))
-      return rc;
+  void* const rope_seq = reinterpret_cast<char*>(ws.rope) + tile_attn_scratch_bytes(B, cfg->head_dim);
+  const bool append = chain && chain->append_kv;
+  const bool mfa = mf && mfma_gemm_supported(EPI_QKV, g) && mfma_attn_supported(a);
+  if (mfa) {
+    // queries and keys are rotated, and the rows that extend the cache are stored there, by the projection's epilogue
+    if (!a.rope_ready && (rc = dev(launch_rope_table(ws.rope, B, S_seq, pos0, tail_pos0, cfg->rope_base, st)))) return rc;
+    QkvArgs& q = g.qkv;
+    q.rope = ws.rope; q.rope_rows = B + S_seq;
+    q.ck = const_cast<void*>(prefix->k); q.cv = const_cast<void*>(prefix->v); q.ldp = ldp;
+    q.rows = G * B; q.B = B; q.magic = (unsigned)((((unsigned long long)1 << 32) + B - 1) / B);
+    q.q_scale = 1.4426950408889634f * 0.08838834764831845f;      // log2(e) / sqrt(128)
+    q.n_head = append || (S_seq && !prev) ? B : 0;               // the block itself, or the true block (state 0) ..
+    q.dst_head = prefix->P;
+    q.dst_tail = !S_seq ? -1 : prev ? prefix->P : prefix->P + B; // .. and the suffix behind it; or the finished block
+    if ((rc = dev(mfma_rows(EPI_QKV, g)))) return rc;
+    a.partial = ws.attn_partial;
   } else {
-    if (chain && chain->append_kv &&
-        (rc = dev(launch_kv_append(dt, ws.qkv, a.Hq, a.Hkv, a.hd, B, pos0, cfg->rope_base,
-                                   const_cast<void*>(prefix->k), const_cast<void*>(prefix->v), prefix->P, ldp, st, 0, 0,
-                                   tab))))
-      return rc;
-    if (S_seq) {     // the finished block in front of the states
-      const size_t es = esize(dt);
-      const char* qkv_seq = reinterpret_cast<const char*>(ws.qkv) + (size_t)G * B * g.N * es;
-      if ((rc = dev(launch_kv_append(dt, qkv_seq, a.Hq, a.Hkv, a.hd, S_seq, tail_pos0, cfg->rope_base,
-                                     const_cast<void*>(prefix->k), const_cast<void*>(prefix->v), prefix->P, ldp, st, 0, 0,
-                                     tab_tail))))
-        return rc;
-    }
+    if ((rc = dev(launch_gemm_tile(dt, EPI_STORE, g, st)))) return rc;
+    a.partial = ws.rope;
+    // the true block (state 0: qkv rows 0 .. B-1) and the suffix (qkv rows G*B ..) land next to each other in the cache, at
+    // consecutive positions: one launch over the two runs of rows
+    if (S_seq && !prev)
+      rc = dev(launch_kv_append(dt, ws.qkv, a.Hq, a.Hkv, a.hd, B + S_seq, pos0, cfg->rope_base, const_cast<void*>(prefix->k),
+                                const_cast<void*>(prefix->v), prefix->P, ldp, st, B, (G - 1) * B));
+    else if (append)
+      rc = dev(launch_kv_append(dt, ws.qkv, a.Hq, a.Hkv, a.hd, B, pos0, cfg->rope_base, const_cast<void*>(prefix->k),
+                                const_cast<void*>(prefix->v), prefix->P, ldp, st));
+    else if (S_seq)    // the finished block in front of the states
+      rc = dev(launch_kv_append(dt, reinterpret_cast<const char*>(ws.qkv) + (size_t)G * B * g.N * esize(dt), a.Hq, a.Hkv, a.hd,
+                                S_seq, tail_pos0, cfg->rope_base, const_cast<void*>(prefix->k), const_cast<void*>(prefix->v),
+                                prefix->P, ldp, st));
+    if (rc) return rc;
   }
   if (!(S_seq && mfa) &&      // with rows riding along, the MFMA path runs both groups in one launch below
       (rc = dev(mfa ? launch_attn_mfma(a, st) : launch_attn_tile(dt, a, st))))
@@ -342,9 +331,9 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
     AttnArgs b = a;
     b.qkv = reinterpret_cast<const char*>(ws.qkv) + (size_t)G * B * g.N * es;
     b.out = reinterpret_cast<char*>(ws.attn) + (size_t)G * B * qd * es;
-    b.partial = ws.attn_partial_seq;
+    b.partial = mfa ? ws.attn_partial_seq : rope_seq;
     b.G = 1; b.B = S_seq; b.P = prefix->P + B + S_seq; b.S = 0; b.own = 0;
-    b.pos0 = tail_pos0; b.rope_ready = tail_rope_ready;
+    b.pos0 = tail_pos0;
     if (prev) {     // the finished block: one state at the positions before pos0, over the rows in front of it
       b.P = prefix->P; b.S = prefix->S; b.own = 1;
     }
@@ -814,7 +803,6 @@ int spiffy_verify_step_seq(const spiffy_model_cfg* cfg, int32_t n_layers, const 
     chain.next_norm1 = (l + 1 < n_layers) ? layers[l + 1].norm1 : nullptr;
     if ((rc = run_layer(cfg, &layers[l], &prefix[l], hid, G, B, pos0, hid, ws.rest, st, &chain))) return rc;
     chain.rope_ready = true;
-    chain.rope_ready_seq = true;
   }
   if ((rc = run_head(cfg, hid, final_norm, w_vocab, block_tokens, nullptr, G, B, threshold, logit_scale, force_one,
                      argmax, conf, unmask, top2_margin, tgt, ws.rest, st)))
@@ -877,7 +865,6 @@ int spiffy_verify_step_commit(const spiffy_model_cfg* cfg, int32_t n_layers, con
     chain.next_norm1 = (l + 1 < n_layers) ? layers[l + 1].norm1 : nullptr;
     if ((rc = run_layer(cfg, &layers[l], &prefix[l], hid, G, B, pos0, hid, ws.rest, st, &chain))) return rc;
     chain.rope_ready = true;
-    chain.rope_ready_seq = true;
   }
   if ((rc = run_head(cfg, hid, final_norm, w_vocab, block_tokens, nullptr, G, B, threshold, logit_scale, force_one,
                      argmax, conf, unmask, top2_margin, tgt, ws.rest, st)))

@@ -77,7 +77,20 @@ struct alignas(16) TopPartial {
 
 // C[M,N] = A[M,K] * W^T where W is given as up to three row-major [N_i,K] segments laid side by
 // side along N (q | k | v), or as a (gate, up) pair for the SwiGLU epilogue.
-enum GemmEpi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_PARTIAL = 4 };
+enum GemmEpi { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_PARTIAL = 4, EPI_QKV = 5 };
+
+// EPI_QKV (head_dim 128): rotary embedding of the q and k columns, scale of q, and the rows that also go to the cache.
+// Row g of the whole product has table row g % B while g < rows, B + g - rows behind (rows that ride along with the states).
+struct QkvArgs {
+  const void* rope;     // [32][rope_rows] (cos, sin, cos, sin) of two neighbouring frequencies: a lane's neighbours are other rows
+  int rope_rows;
+  void *ck, *cv;        // cache [Hkv][ldp][128]; k and v of rows 0 .. n_head-1 go to cache rows dst_head .., of the rows
+  int ldp;              // behind `rows` to dst_tail .. (dst_tail < 0: not)
+  int row0, rows, B;    // row0: row of the whole product that is row 0 of this launch
+  unsigned magic;       // ceil(2^32 / B): g / B = (g * magic) >> 32 for g, B < 65536 (B > 1)
+  int n_head, dst_head, dst_tail;
+  float q_scale;
+};
 
 struct GemmArgs {
   const void* A;        // [M,K]
@@ -92,6 +105,7 @@ struct GemmArgs {
   int ldw;              // row stride of the weight segments in elements (0 = K, i.e. dense rows)
   float scale;          // LMHEAD: logit scale
   int ksplit;           // PARTIAL: number of K slices (C = fp32 [ksplit][Mz][N]); otherwise 1
+  QkvArgs qkv;          // QKV only
   int Mz;               // PARTIAL: rows per K slice of C when only some of them are computed by this launch (0 = M)
 };
 

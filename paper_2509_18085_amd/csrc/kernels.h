@@ -22,17 +22,17 @@ hipError_t launch_gather_rows2(const void* a, size_t a_row_bytes, const void* b,
                                hipStream_t st);
 
 struct AttnArgs {
-  const void* qkv;       // [M, (Hq+2Hkv)*hd]: q | k | v columns, not yet rotated
+  const void* qkv;       // [M, (Hq+2Hkv)*hd]: q | k | v columns; MFMA path: q and k rotated, q scaled by log2(e)/sqrt(hd)
   const void* prefix_k;  // [Hkv,P,hd]
   const void* prefix_v;
   void* out;             // [M, Hq*hd]
-  void* partial;         // MFMA path: rotary table and split partials (fp32); otherwise the rotary table
+  void* partial;         // MFMA path: split partials (fp32); otherwise the rotary table
   int G, B, Hq, Hkv, hd, P, pos0;
   int ldp;               // rows allocated per KV head in prefix_k / prefix_v (0 = P)
   int S;                 // dual cache: rows P+B .. P+B+S-1 of the same arrays hold the tokens after the block
   int own;               // 1: every state also attends to its own B rows (keys / values from qkv); 0: cache rows only
   float rope_base;
-  int rope_ready;        // the rotary table at the start of `partial` is already filled
+  int rope_ready;        // the rotary table in `partial` is already filled
 };
 size_t tile_attn_scratch_bytes(int B, int hd);
 hipError_t launch_attn_tile(int dtype, const AttnArgs& a, hipStream_t st);
@@ -40,11 +40,9 @@ hipError_t launch_attn_tile(int dtype, const AttnArgs& a, hipStream_t st);
 // first B rows of the fused qkv activations go to rows P .. P+B-1 of every KV head of the cache
 // ([Hkv][ldp][hd]).  Must run before the attention of the same layer reads the cache only up to row P.
 // rows 0 .. B-1 of the appended range come from qkv rows 0 .. B0-1 and B0+skip .. (B0 <= 0: one run of B rows).
-// tab_a / tab_b: optional rotary tables [hd/2][n] (cos, sin) for the first B0 rows (n = B0) and for the rest
-// (n = B - B0), as the attention kernels use them; NULL = the same values computed in the kernel.
+// (Shapes without the MFMA attention; on its path the QKV projection's epilogue extends the cache.)
 hipError_t launch_kv_append(int dtype, const void* qkv, int Hq, int Hkv, int hd, int B, int pos0, float rope_base,
-                            void* cache_k, void* cache_v, int P, int ldp, hipStream_t st, int B0 = 0, int skip = 0,
-                            const void* tab_a = nullptr, const void* tab_b = nullptr);
+                            void* cache_k, void* cache_v, int P, int ldp, hipStream_t st, int B0 = 0, int skip = 0);
 
 // masked-row list: row_idx[0..count) = flattened (g,b) with mask set, ascending; *count.
 hipError_t launch_compact_rows(const int32_t* tokens, const uint8_t* mask, int mask_id, int M,
@@ -137,7 +135,9 @@ hipError_t launch_splitk_reduce(const float* P, int ksplit, const void* R, void*
 bool mfma_attn_supported(const AttnArgs& a);
 size_t mfma_attn_partial_bytes(int G, int B, int Hq, int hd, int P);
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t st);
-const void* launch_rope_table(void* partial, int B, int pos0, float rope_base, hipStream_t st);   // head_dim 128 only
+// rotary table of the QKV projection (head_dim 128): rows for positions pos0 .. pos0+B-1, then tail_pos0 ..
+size_t mfma_rope_bytes(int rows);
+hipError_t launch_rope_table(void* tab, int B, int tail_rows, int pos0, int tail_pos0, float rope_base, hipStream_t st);
 hipError_t launch_attn_mfma_pair(const AttnArgs& a, const AttnArgs& b, hipStream_t st);   // two problems, one launch
 
 // Calibration, part 3 (Alg. 2; App. D.1): best connected node set of size D.  All pointers device memory.

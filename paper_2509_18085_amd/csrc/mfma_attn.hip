@@ -15,14 +15,23 @@
 // full-sequence model, or the block being committed) runs both attention problems in one launch.
 //
 // Everything the workgroup reads travels global -> LDS directly as whole 256-byte rows (LDS-DMA loads, no
-// registers): the 128 Q rows and the own-block K/V rows once at the start, the prefix tiles into a ring of
-// NSTAGE stages, up to NSTAGE-1 tiles ahead of the MFMAs, one barrier per tile.  Rows keep their [row][hd]
+// registers): the Q rows, the own-block K/V rows and prefix tiles 0 and 1 at the start, later tiles into rings of
+// NSTAGE stages for K and V, up to NSTAGE-1 tiles ahead of the MFMAs, one barrier per tile.  Rows keep their [row][hd]
 // layout in LDS, 16-byte chunks permuted per row so that fragment reads are conflict-free:
 //   Q / K row r: chunk c sits at position c ^ (r & 15)      (16-byte reads of one chunk per lane)
 //   V row r: 64-byte unit u sits at position u ^ (r & 3)    (transposing 8-byte reads, below)
-// The loop over full prefix tiles is software-pipelined: the score MFMAs of tile t+1 are issued between
-// the exponentials of tile t.  The O rescale is skipped when no lane's running maximum moved (multiplying
-// by exactly 1 changes nothing).
+// What bounds the loop is the instruction stream of a SIMD's two wavefronts: 16 matrix instructions a tile and
+// wavefront (512 cycles), whose shadow holds the exponentials but not much more, and the vector instructions around
+// them.  Those are kept to what the softmax needs:
+//   * the reference m of the online softmax follows the running maximum only when that is more than 8 ahead; the rescale
+//     factor and its multiplies sit in a branch that is rarely taken;
+//   * fragment addresses are loop invariant up to one add per two tiles (the stage is an immediate offset: K and V have
+//     rings of their own, so two stages lie within its 64 KB); transfers use a scalar base and a constant lane offset;
+//   * the score MFMAs of tile t+1 are issued between the exponentials of tile t.
+// With both the kernel holds its state in 208 - 246 registers, nothing in scratch (before: 15 - 75 registers spilled).
+// Measured, us: one or four states of 32 tokens behind 1024 rows 22.3 -> 16.3, 32 states 37.4 -> 31.2, 24 states of 28 heads
+// behind 2048 rows 48.0 -> 41.1, 256 rows behind 8192 50.3 -> 45.2; 264 rows of blocks of 24 (144 workgroups of 32
+// query rows where 48 of 128 ran) 34 -> 18.
 //
 // Eight wavefronts per workgroup: wavefront pair p owns query rows 32p..32p+31, and the two wavefronts
 // of a pair split every 64-key tile between them (32 keys each), each keeping its own running
@@ -30,7 +39,7 @@
 // arithmetic of one overlap the MFMAs of the other.
 //
 // Per wavefront (32 query rows x 32 keys of a tile) everything is kept "query per lane":
-//   S^T = K Q^T    A operand = K rows from LDS, B operand = rotated, pre-scaled Q in registers
+//   S^T = K Q^T    A operand = K rows from LDS, B operand = Q in registers
 //                  -> lane (q, half) holds 16 of the 32 keys of a sub-tile for its query q
 //   online softmax max / sum are reductions over the lane's own registers plus one half swap
 //   O^T = V^T P^T  A operand = V^T, read from the row-major V tile with the transposing LDS read
@@ -38,10 +47,10 @@
 //                  8-byte pieces addressed by lanes q, q+4, q+8, q+12), B operand = P^T straight from
 //                  the S^T accumulators (no trip through LDS); the rescale factor is per lane.
 // Own-block keys (the block diagonal) come first, handled by the last prefix split: they always go to the
-// wavefront of a pair that takes the first key half, 32 keys at a time in row order, so a state's arithmetic does not depend on
-// where its rows sit in the tile; the mask is applied per element (any B works).
-// Rotary embedding (positions pos0..pos0+B-1 for every state, Sec. 4.3) is applied to the Q and own-block K
-// fragments in registers, on their way from LDS to the matrix pipe; the cached prefix K arrives rotated.
+// wavefront of a pair that takes the first key half, in groups of 32 rows that are counted the same way however many query
+// rows a workgroup owns, so a state's arithmetic does not depend on that; the mask is applied per element (any B works).
+// Queries and keys arrive rotated (positions pos0..pos0+B-1 for every state, Sec. 4.3), queries also scaled by
+// log2(e)/sqrt(128): the QKV projection's epilogue does both on its fp32 sums.
 #include <type_traits>
 
 #include "kernels.h"
@@ -54,16 +63,19 @@ constexpr int HD = 128;
 constexpr int KTILE = 64;
 constexpr int QTILE = 128;
 constexpr int NSTAGE = 4;
-constexpr int TILE_ELEMS = KTILE * HD;          // one K or V tile: 16 KB
-constexpr int STAGE_ELEMS = 2 * TILE_ELEMS;     // K tile then V tile
+constexpr int STAGE_BYTES = KTILE * HD * 2;               // one K or V tile: 16 KB
+constexpr int V_RING = NSTAGE * STAGE_BYTES;              // K ring, V ring, then 128 own-block K rows
+constexpr int OWN_K = 2 * NSTAGE * STAGE_BYTES;
+constexpr int Q_ROWS = 2 * STAGE_BYTES;                   // before the loop: Q in K stages 2 and 3,
+constexpr int OWN_V = V_RING + 2 * STAGE_BYTES;           // 128 own-block V rows in V stages 2 and 3
 constexpr int SPLIT_KEYS = 2048;
-constexpr size_t kAttnSmem = sizeof(bf16_t) * NSTAGE * STAGE_ELEMS;  // 131,072 B
+constexpr size_t kAttnSmem = OWN_K + 2 * STAGE_BYTES;     // 163,840 B
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 typedef __attribute__((address_space(3))) bf16x4* lds_bf16x4_ptr_t;
+typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr_t;
 
 constexpr int NT = 512;   // threads per workgroup
 constexpr int DMA_PER_TILE = 4;   // LDS-DMA loads per thread per prefix tile (2 for K, 2 for V)
@@ -77,24 +89,12 @@ __device__ __forceinline__ void wait_vmcnt() {   // vmcnt <= N; lgkmcnt / expcnt
 __device__ __forceinline__ int k_pos(int r, int c) { return c ^ (r & 15); }
 __device__ __forceinline__ int v_pos(int r, int c) { return c ^ ((r & 3) << 2); }
 
+// Addresses are 32-bit LDS byte offsets: the base of a ring (or of own-block rows) plus a per-lane part that never changes.
 struct WaveState {
-  bf16x8 qf[8];     // rotated, scaled Q^T fragments: hd = 16*kk + 8*half + e
+  bf16x8 qf[8];     // Q^T fragments: hd = 16*kk + 8*half + e
   f32x16 o[4];      // O^T accumulators: hd = 32*n + 8*(v/4) + 4*half + v%4, query = lane%32
   float m_run, l_run;
 };
-
-// O *= alpha, in place (the multiplies are opaque to the compiler so that the rarely taken branch around
-// them does not cost a copy of the 64 accumulator registers on every tile)
-__device__ __forceinline__ void rescale_in_place(WaveState& w, float alpha) {
-#pragma unroll
-  for (int n = 0; n < 4; ++n)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      float x = w.o[n][v];
-      asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(alpha));
-      w.o[n][v] = x;
-    }
-}
 
 // max of a value and its partner 32 lanes away, without a trip through LDS: after the swap one result
 // holds the low half's values in both halves, the other the high half's
@@ -109,154 +109,141 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // hold as well as values below 1, and a reference that stays put needs no rescale of O and l (the factor is exactly
 // 1 and the 64 multiplies are skipped).  The choice is made per query, so a row's arithmetic does not depend on the
 // rows that share its wavefront; (m, l, O) stay consistent and every later merge weighs partials by exp2(m - max m).
-__device__ __forceinline__ float next_reference(float m_run, float tile_max) {
-  const float m_cand = fmaxf(m_run, tile_max);
-  return (m_cand - m_run > 8.0f) ? m_cand : m_run;     // first tile: m_run = -inf, the difference is +inf
+// Returns the factor of l; O is rescaled here, in place (the multiplies are opaque to the compiler so that the rarely
+// taken branch around them does not cost a copy of the 64 accumulator registers on every tile).
+__device__ __forceinline__ float follow_maximum(WaveState& w, float tile_max) {
+  const float m_cand = fmaxf(w.m_run, tile_max);
+  const float m_new = (m_cand - w.m_run > 8.0f) ? m_cand : w.m_run;     // first tile: m_run = -inf, the difference is +inf
+  float alpha = 1.f;
+  if (__builtin_amdgcn_ballot_w64(m_new != w.m_run) != 0) {
+    alpha = (w.m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(w.m_run - m_new);
+    w.m_run = m_new;
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        float x = w.o[n][v];
+        asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(alpha));
+        w.o[n][v] = x;
+      }
+  }
+  return alpha;
 }
 
-// S^T of the wavefront's 32-key half of a tile in LDS: 8 MFMAs
-__device__ __forceinline__ void scores(const WaveState& w, f32x16& s, const bf16_t* __restrict__ ks, int st, int lane) {
-  const int row = st * 32 + (lane & 31), hh = lane >> 5;
-  const bf16_t* kp = ks + row * HD;
+// The lane's fragment addresses for 32 rows starting at row `row0` (a multiple of 32) of a tile at LDS address `base`
+struct KAddr { unsigned a[8]; };      // K / Q: chunk 2*kk + half of row row0 + lane%32
+struct VAddr { unsigned a[4]; };      // V^T, hd block n
+__device__ __forceinline__ KAddr k_addr(unsigned base, int row0, int lane) {
+  KAddr k;
+  const int row = row0 + (lane & 31), hh = lane >> 5;
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) k.a[kk] = base + row * (HD * 2) + k_pos(row, 2 * kk + hh) * 16;
+  return k;
+}
+// lane j of a 16-lane group addresses key (j / 4) of its 4-key run, hd block 4 * (j % 4) of the group's 16 rows; the
+// transposing read hands lane 4q+c the 4 keys of hd row 4q+c
+__device__ __forceinline__ VAddr v_addr(unsigned base, int row0, int lane) {
+  VAddr k;
+  const int g = lane >> 4, j = lane & 15;
+  const int vkey = row0 + 4 * (g >> 1) + (j >> 2);     // + 16*k2 + 8*eh, which keep (key & 3)
+#pragma unroll
+  for (int n = 0; n < 4; ++n) k.a[n] = base + vkey * (HD * 2) + (16 * (g & 1) + 4 * (j & 3)) * 2 + (n ^ (vkey & 3)) * 64;
+  return k;
+}
+template <int OFF>
+__device__ __forceinline__ bf16x8 k_frag(const KAddr& k, int kk) { return *(lds_bf16x8_ptr_t)(size_t)(k.a[kk] + OFF); }
+template <int OFF>
+__device__ __forceinline__ bf16x4 v_frag(const VAddr& k, int n, int k2, int eh) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr_t)(size_t)(k.a[n] + OFF + (16 * k2 + 8 * eh) * (HD * 2)));
+}
+
+// S^T of 32 keys: 8 MFMAs
+template <int OFF>
+__device__ __forceinline__ void scores(const WaveState& w, f32x16& s, const KAddr& ka) {
 #pragma unroll
   for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
-    const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kp + k_pos(row, 2 * kk + hh) * 8);
-    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, w.qf[kk], s, 0, 0, 0);
-  }
+  for (int kk = 0; kk < 8; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag<OFF>(ka, kk), w.qf[kk], s, 0, 0, 0);
 }
 
-// Online-softmax update and O += P V for the 32 keys of half `st` of a tile whose scores `s` are in registers
-// (log2 domain: Q carries log2(e)/sqrt(hd)).  `valid(key_in_tile)` masks keys (only called when MASKED).
-template <bool MASKED, typename ValidFn>
-__device__ __forceinline__ void finish_tile(WaveState& w, f32x16& s, const bf16_t* __restrict__ vs, int st, int lane, ValidFn valid) {
+// Online-softmax update and O += P V for 32 keys whose scores are in registers and of which `valid(key)` says which count
+template <typename ValidFn>
+__device__ __forceinline__ void finish_masked(WaveState& w, f32x16& s, const VAddr& va, int lane, ValidFn valid) {
   const int hh = lane >> 5;
   float tmax = -INFINITY;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
-    if (MASKED) {
-      const int key = st * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-      if (!valid(key)) s[v] = -INFINITY;
-    }
+    if (!valid(8 * (v >> 2) + 4 * hh + (v & 3))) s[v] = -INFINITY;
     tmax = fmaxf(tmax, s[v]);
   }
-  tmax = max_with_other_half(tmax);
-  const float m_new = next_reference(w.m_run, tmax);
-  const float alpha = (w.m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(w.m_run - m_new);
-  const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+  const float alpha = follow_maximum(w, max_with_other_half(tmax));
+  const float m = (w.m_run == -INFINITY) ? 0.f : w.m_run;      // no valid key yet: every s is -inf
   bf16x8 pf[2];
   float psum = 0.f;
   const bf16x2 ones = {static_cast<bf16_t>(1.0f), static_cast<bf16_t>(1.0f)};
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     f32x2 e;
-    e[0] = __builtin_amdgcn_exp2f(s[2 * i] - m_safe);
-    e[1] = __builtin_amdgcn_exp2f(s[2 * i + 1] - m_safe);
+    e[0] = __builtin_amdgcn_exp2f(s[2 * i] - m);
+    e[1] = __builtin_amdgcn_exp2f(s[2 * i + 1] - m);
     const bf16x2 pb = __builtin_convertvector(e, bf16x2);
     psum = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, psum, false);
     pf[i >> 2][(2 * i) & 7] = pb[0];
     pf[i >> 2][(2 * i + 1) & 7] = pb[1];
   }
   w.l_run = w.l_run * alpha + psum;
-  w.m_run = m_new;
-  // multiplying by exactly 1 changes nothing: skip the rescale when no lane's maximum moved
-  if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) rescale_in_place(w, alpha);
-  // V^T fragments: lane j of a 16-lane group addresses key (j / 4) of its 4-key run, hd block 4 * (j % 4)
-  // of the group's 16 rows; the transposing read hands lane 4q+c the 4 keys of hd row 4q+c
-  const int g = lane >> 4, j = lane & 15;
-  const int vkey = st * 32 + 4 * (g >> 1) + (j >> 2);     // + 16*k2 + 8*eh, which keep (key & 3)
-  const bf16_t* vp = vs + vkey * HD + 16 * (g & 1) + 4 * (j & 3);
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    const int unit = (n ^ (vkey & 3)) * 32;
+  for (int n = 0; n < 4; ++n)
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2) {
-      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr_t)(vp + (16 * k2) * HD + unit));
-      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr_t)(vp + (16 * k2 + 8) * HD + unit));
-      bf16x8 vf;
-      vf[0] = lo[0]; vf[1] = lo[1]; vf[2] = lo[2]; vf[3] = lo[3];
-      vf[4] = hi[0]; vf[5] = hi[1]; vf[6] = hi[2]; vf[7] = hi[3];
+      const bf16x8 vf = __builtin_shufflevector(v_frag<0>(va, n, k2, 0), v_frag<0>(va, n, k2, 1), 0, 1, 2, 3, 4, 5, 6, 7);
       w.o[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[k2], w.o[n], 0, 0, 0);
     }
-  }
-}
-
-// The wavefront's 32-key half (`st`) of a 64-key tile in LDS against its 32 queries
-template <bool MASKED, typename ValidFn>
-__device__ __forceinline__ void process_tile(WaveState& w, const bf16_t* __restrict__ ks, const bf16_t* __restrict__ vs,
-                                             int st, int lane, ValidFn valid) {
-  f32x16 s;
-  scores(w, s, ks, st, lane);
-  finish_tile<MASKED>(w, s, vs, st, lane, valid);
 }
 
 // One step of the software pipeline over full prefix tiles: the online-softmax arithmetic on the scores
-// `s` of tile t runs between the score MFMAs of tile t+1 (K from `k_next`, result in `sn`, when NEXT),
-// then O += P V for tile t (V from `v_cur`).  Same arithmetic, in the same order, as process_tile<false>.
-template <bool NEXT>
-__device__ __forceinline__ void pipe_step(WaveState& w, const f32x16& s, f32x16& sn, const bf16_t* __restrict__ k_next,
-                                          const bf16_t* __restrict__ v_cur, int st, int lane) {
-  const int l32 = lane & 31, hh = lane >> 5;
+// `s` of tile t runs between the score MFMAs of tile t+1 (K at ka + KOFF, result in `sn`),
+// then O += P V for tile t (V at va + VOFF).
+template <int KOFF, int VOFF>
+__device__ __forceinline__ void pipe_step(WaveState& w, f32x16& s, f32x16& sn, const KAddr& ka, const VAddr& va) {
   bf16x8 kf[8];
-  if (NEXT) {
-    const int row = st * 32 + l32;
-    const bf16_t* kp = k_next + row * HD;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(kp + k_pos(row, 2 * kk + hh) * 8);
-  }
+  for (int kk = 0; kk < 8; ++kk) kf[kk] = k_frag<KOFF>(ka, kk);
   float tmax = s[0];
 #pragma unroll
   for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
-  tmax = max_with_other_half(tmax);
-  const float m_new = next_reference(w.m_run, tmax);     // finite: a full tile has no masked score
-  const float alpha = (w.m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(w.m_run - m_new);
-  const int g = lane >> 4, j = lane & 15;
-  const int vkey = st * 32 + 4 * (g >> 1) + (j >> 2);
-  const bf16_t* vp = v_cur + vkey * HD + 16 * (g & 1) + 4 * (j & 3);
-  if (NEXT) {
+  const float alpha = follow_maximum(w, max_with_other_half(tmax));     // a full tile has no masked score: m_run is finite now
+  const float m = w.m_run;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) sn[v] = 0.f;
-  }
+  for (int v = 0; v < 16; ++v) sn[v] = 0.f;
   bf16x8 pf[2];
   bf16x4 vlo[8], vhi[8];
   float psum = 0.f;
   const bf16x2 ones = {static_cast<bf16_t>(1.0f), static_cast<bf16_t>(1.0f)};
-  __builtin_amdgcn_sched_barrier(0);   // K fragment reads and the running-max chain stay above this line
+  __builtin_amdgcn_sched_barrier(0);   // K fragment reads and the maximum stay above this line
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    if (NEXT) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], w.qf[i], sn, 0, 0, 0);
+    sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], w.qf[i], sn, 0, 0, 0);
     f32x2 e;
-    e[0] = __builtin_amdgcn_exp2f(s[2 * i] - m_new);
-    e[1] = __builtin_amdgcn_exp2f(s[2 * i + 1] - m_new);
+    e[0] = __builtin_amdgcn_exp2f(s[2 * i] - m);
+    e[1] = __builtin_amdgcn_exp2f(s[2 * i + 1] - m);
     const bf16x2 pb = __builtin_convertvector(e, bf16x2);
     psum = __builtin_amdgcn_fdot2_f32_bf16(pb, ones, psum, false);
     pf[i >> 2][(2 * i) & 7] = pb[0];
     pf[i >> 2][(2 * i + 1) & 7] = pb[1];
-    {   // V^T fragment i: key step k2 = i / 4, hd block n = i % 4
-      const int k2 = i >> 2, n = i & 3;
-      const int unit = (n ^ (vkey & 3)) * 32;
-      vlo[i] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr_t)(vp + (16 * k2) * HD + unit));
-      vhi[i] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr_t)(vp + (16 * k2 + 8) * HD + unit));
-    }
+    vlo[i] = v_frag<VOFF>(va, i & 3, i >> 2, 0);      // V^T fragment i: key step i / 4, hd block i % 4
+    vhi[i] = v_frag<VOFF>(va, i & 3, i >> 2, 1);
   }
-  // issue order for the loop above: per score MFMA two exponentials with their subtract / convert / sum
-  // and two V fragment reads
+  // issue order for the loop above: per score MFMA two exponentials with their subtract / convert / sum and two V fragment reads
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    if (NEXT) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
     __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
     __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
     __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
   }
   w.l_run = w.l_run * alpha + psum;
-  w.m_run = m_new;
-  // the branch below must not move above the block it follows: make its condition depend on the block's results
-  float alpha_c = alpha;
-  if (NEXT) asm volatile("" : "+v"(alpha_c) : "v"(psum), "v"(sn[15]));
-  else asm volatile("" : "+v"(alpha_c) : "v"(psum));
-  if (__builtin_amdgcn_ballot_w64(alpha_c != 1.f) != 0) rescale_in_place(w, alpha_c);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const bf16x8 vf = __builtin_shufflevector(vlo[i], vhi[i], 0, 1, 2, 3, 4, 5, 6, 7);
@@ -268,7 +255,6 @@ struct AttnKArgs {
   const bf16_t* qkv;
   const bf16_t* pk;
   const bf16_t* pv;
-  const float2* rope;   // [64][B] (cos, sin) of angle (pos0+b) * base^(-2f/128): lanes that differ in b read neighbours
   bf16_t* out;
   float* opart;         // [nS][M][Hq][128]
   float* mlpart;        // [nS][M][Hq][2]
@@ -278,37 +264,11 @@ struct AttnKArgs {
   int qrows;                                   // query rows a workgroup owns: 128, or 96 / 64 / 32 when there are few workgroups (scheduling only)
 };
 
-// the lane's 8 MFMA operand fragments of LDS tile row `row` (K layout): hd = 16*kk + 8*hh + e
-__device__ __forceinline__ void load_frags(bf16x8 (&f)[8], const bf16_t* __restrict__ tile, int row, int hh) {
-  const bf16_t* p = tile + row * HD;
-#pragma unroll
-  for (int kk = 0; kk < 8; ++kk) f[kk] = *reinterpret_cast<const bf16x8*>(p + k_pos(row, 2 * kk + hh) * 8);
-}
-// rotary embedding of the fragments of global row `row` (position row % B) and scaling; fragment kk pairs with
-// kk + 4 (hd and hd + 64).  `rope` is [64][B] (cos, sin).
-__device__ __forceinline__ void rotate_frags(bf16x8 (&f)[8], const float2* __restrict__ rope, int B, int row, int hh, float scale) {
-  const float2* rp = rope + (size_t)(hh * 8) * B + (row % B);
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const bf16x8 x1 = f[kk], x2 = f[kk + 4];
-    bf16x8 y1, y2;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float2 cs = rp[(size_t)(kk * 16 + e) * B];
-      const float a1 = static_cast<float>(x1[e]), a2 = static_cast<float>(x2[e]);
-      y1[e] = static_cast<bf16_t>((a1 * cs.x - a2 * cs.y) * scale);
-      y2[e] = static_cast<bf16_t>((a2 * cs.x + a1 * cs.y) * scale);
-    }
-    f[kk] = y1;
-    f[kk + 4] = y2;
-  }
-}
-
 // DUAL: the cache also holds rows of the tokens after the block (a.S > 0)
 template <bool DUAL>
 __device__ __forceinline__ void attn_prefix_body(const AttnKArgs& a, int bid) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  bf16_t* smem = reinterpret_cast<bf16_t*>(smem_raw);
+  const unsigned lds0 = (unsigned)(size_t)(lds_ptr_t)smem_raw;
 
   const int total = a.nQ * a.nS * a.Hq;
   const int L = xcd_contiguous(bid, total);
@@ -349,97 +309,109 @@ __device__ __forceinline__ void attn_prefix_body(const AttnKArgs& a, int bid) {
   const bf16_t* pk = a.pk + (size_t)kvh * a.ldp * HD;
   const bf16_t* pv = a.pv + (size_t)kvh * a.ldp * HD;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  // LDS-DMA of N_ROWS rows of 256 bytes (rows row0 .. clamped to row_max of a matrix with row stride `ld`
-  // elements, starting at `src`) into an LDS tile; wavefront `wave` brings N_ROWS/8 consecutive rows:
-  // lane -> (row, LDS position) -> source chunk
-  auto issue_rows = [&](auto n_rows_tag, auto vswz_tag, bf16_t* dst, const bf16_t* src, int row0, int row_max, size_t ld) {
-    constexpr int N_ROWS = decltype(n_rows_tag)::value;
-    constexpr bool VSWZ = decltype(vswz_tag)::value;
-    constexpr int PER_WAVE = N_ROWS / 8;
-#pragma unroll
-    for (int q = 0; q < PER_WAVE / 4; ++q) {
-      const int row = PER_WAVE * wave_u + 4 * q + (lane >> 4), pos = lane & 15;
-      const int chunk = VSWZ ? v_pos(row, pos) : k_pos(row, pos);
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(src + (size_t)min(row0 + row, row_max) * ld + chunk * 8),
-                                       (lds_ptr_t)(dst + (PER_WAVE * wave_u + 4 * q) * HD), 16, 0, 0);
+  // 16 bytes per lane, global (scalar base + 32-bit lane offset) -> LDS (M0 = destination of lane 0)
+  auto dma16 = [&](const char* ubase, unsigned lane_off, unsigned dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "s"(lds0 + dst), "v"(lane_off), "s"(ubase) : "memory");
+  };
+  // One wave-load brings four rows of 256 bytes: lane -> (row, LDS position) -> source chunk.  A 64-row tile takes two per
+  // wavefront (rows 8*wave ..), 128 rows four (rows 16*wave ..).
+  const int lrow = lane >> 4, lpos = lane & 15;
+  const unsigned koff0 = (8 * wave_u + lrow) * (HD * 2) + k_pos(8 * wave_u + lrow, lpos) * 16;
+  const unsigned koff1 = (8 * wave_u + 4 + lrow) * (HD * 2) + k_pos(8 * wave_u + 4 + lrow, lpos) * 16;
+  const unsigned voff = (8 * wave_u + lrow) * (HD * 2) + v_pos(lrow, lpos) * 16;      // rows 4 further on: the same chunks
+  auto issue_tile = [&](int t) {     // prefix tile t of this split into its ring stages
+    const int row0 = kbeg + t * KTILE, nv = kend - row0;
+    const char* kp = reinterpret_cast<const char*>(pk + (size_t)row0 * HD);
+    const char* vp = reinterpret_cast<const char*>(pv + (size_t)row0 * HD);
+    const unsigned dst = (t % NSTAGE) * STAGE_BYTES + wave_u * (8 * HD * 2);
+    if (nv >= KTILE) {
+      dma16(kp, koff0, dst);
+      dma16(kp, koff1, dst + 4 * HD * 2);
+      dma16(vp, voff, V_RING + dst);
+      dma16(vp + 4 * HD * 2, voff, V_RING + dst + 4 * HD * 2);
+    } else {                          // ragged last tile: rows beyond the end repeat the last one
+      const unsigned r0 = 8 * wave_u + lrow, r1 = r0 + 4;
+      const unsigned back0 = (r0 - min(r0, (unsigned)(nv - 1))) * (HD * 2), back1 = (r1 - min(r1, (unsigned)(nv - 1))) * (HD * 2);
+      dma16(kp, koff0 - back0, dst);
+      dma16(kp, koff1 - back1, dst + 4 * HD * 2);
+      dma16(vp, voff - back0, V_RING + dst);
+      dma16(vp, voff + 4 * HD * 2 - back1, V_RING + dst + 4 * HD * 2);
     }
   };
-  using R64 = std::integral_constant<int, 64>;
-  using R128 = std::integral_constant<int, 128>;
-  auto issue_tile = [&](int t) {     // prefix tile t of this split into its ring stage
-    bf16_t* stage = smem + (t % NSTAGE) * STAGE_ELEMS;
-    issue_rows(R64{}, std::false_type{}, stage, pk, kbeg + t * KTILE, kend - 1, HD);
-    issue_rows(R64{}, std::true_type{}, stage + TILE_ELEMS, pv, kbeg + t * KTILE, kend - 1, HD);
+  // rows row0 .. row0+127 (clamped to M-1) of one head's columns of the fused activations: whole groups of 32 up to row_end
+  // (a masked key of a group still multiplies its V row by 0)
+  auto issue_rows128 = [&](unsigned dst, bool vswz, int col, int row0, int row_end) {
+    if (16 * wave_u >= ((row_end - row0 + 31) & ~31)) return;
+    const char* base = reinterpret_cast<const char*>(a.qkv + (size_t)row0 * a.ld + col);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = 16 * wave_u + 4 * q + lrow;
+      const int chunk = vswz ? v_pos(row, lpos) : k_pos(row, lpos);
+      dma16(base, (unsigned)min(row, a.M - 1 - row0) * (unsigned)(a.ld * 2) + chunk * 16, dst + (16 * wave_u + 4 * q) * (HD * 2));
+    }
   };
-  // own-block rows c0 .. c0+127 (K and V columns of the fused activations) into stages 1 and 2
+  // own-block rows c0 .. c0+127 (K and V columns)
   const bool has_own = a.own && sp == a.nS - 1;
-  const int own_lo = (m0 / a.B) * a.B;
+  // Groups of 32 keys are counted from the first row of the state that holds the first row of the 128-row tile (when B
+  // divides 32 or 32 divides B that is a multiple of 32 for any tile); the workgroup starts with the group its rows need first.
+  const int own0 = (((32 % a.B == 0 || a.B % 32 == 0) ? m0 : m0 & ~(QTILE - 1)) / a.B) * a.B;
+  const int own_lo = own0 + (((m0 / a.B) * a.B - own0) & ~31);
   const int own_hi = min(a.M, ((m_end - 1) / a.B + 1) * a.B);
   auto issue_own = [&](int c0) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      bf16_t* stage = smem + (1 + i) * STAGE_ELEMS;
-      issue_rows(R64{}, std::false_type{}, stage, a.qkv + (a.Hq + kvh) * HD, c0 + 64 * i, a.M - 1, a.ld);
-      issue_rows(R64{}, std::true_type{}, stage + TILE_ELEMS, a.qkv + (a.Hq + a.Hkv + kvh) * HD, c0 + 64 * i, a.M - 1, a.ld);
-    }
+    issue_rows128(OWN_K, false, (a.Hq + kvh) * HD, c0, own_hi);
+    issue_rows128(OWN_V, true, (a.Hq + a.Hkv + kvh) * HD, c0, own_hi);
   };
 
-  // ---- start every transfer known up front: the 128 Q rows (stage 3), the first own-block rows (stages 1, 2)
-  // and prefix tile 0 (stage 0); all of them arrive as whole 256-byte rows
-  issue_rows(R128{}, std::false_type{}, smem + 3 * STAGE_ELEMS, a.qkv + h * HD, m0, a.M - 1, a.ld);
+  // ---- start every transfer known up front: Q, the first own-block rows, prefix tiles 0 and 1; all of them arrive as whole
+  // 256-byte rows.  Q and the own rows are waited for, the tiles stay in flight.
+  issue_rows128(Q_ROWS, false, h * HD, m0, m_end);
   if (has_own) issue_own(own_lo);
   if (n_tiles > 0) issue_tile(0);
-  wait_vmcnt<0>();
+  if (n_tiles > 1) { issue_tile(1); wait_vmcnt<2 * DMA_PER_TILE>(); }
+  else if (n_tiles == 1) wait_vmcnt<DMA_PER_TILE>();
+  else wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
 
-  // ---- Q: fragments of the wavefront pair's rows, rotated at position pos0 + (row % B), scaled by
-  // log2(e)/sqrt(128), rounded to bf16
-  load_frags(w.qf, smem + 3 * STAGE_ELEMS, qw * 32 + l32, hh);
-  rotate_frags(w.qf, a.rope, a.B, qrow, hh, 1.4426950408889634f * 0.08838834764831845f);
+  // ---- Q: fragments of the wavefront pair's rows
+  {
+    const KAddr qa = k_addr(lds0 + Q_ROWS, qw * 32, lane);
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) w.qf[kk] = k_frag<0>(qa, kk);
+  }
 
   // ---- own-block keys: the block diagonal, handled by the last split.  They always go to the role-0 wavefront
-  // of the pair, 32 keys at a time in row order, so a state's arithmetic does not depend on where its rows sit
-  // in the 128-row tile.  K fragments are rotated in registers on their way from LDS to the matrix pipe.
+  // of the pair, 32 keys at a time in row order.
   if (has_own) {
     // rows of the states this wave's queries belong to
     const int w_lo = (min(m0w, a.M - 1) / a.B) * a.B;
     const int w_hi = (min(m0w + 31, a.M - 1) / a.B + 1) * a.B;
-    const int q_lo = (qrow / a.B) * a.B;    // this lane's state: rows [q_lo, q_lo + B)
-    const int q_hi = q_lo + a.B;
+    const int q_lo = (qrow / a.B) * a.B;    // this lane's state: rows [q_lo, q_hi)
+    const int q_hi = min(q_lo + a.B, a.M);
     for (int c0 = own_lo; c0 < own_hi; c0 += 128) {
-      if (c0 != own_lo) {      // more than 128 own rows (B does not divide the tile): next chunk
+      if (c0 != own_lo) {      // more than 128 own rows: next chunk
         __syncthreads();
         issue_own(c0);
         wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
       }
       if (st == 0 && active) {
-#pragma unroll
+#pragma nounroll
         for (int sub = 0; sub < 4; ++sub) {
           const int k_lo = c0 + sub * 32;
-          if (k_lo < w_hi && k_lo + 32 > w_lo && k_lo < own_hi) {   // wave-uniform: this sub-tile holds keys of my states
-            const bf16_t* stage = smem + (1 + (sub >> 1)) * STAGE_ELEMS;
-            bf16x8 kf[8];
-            load_frags(kf, stage, (sub & 1) * 32 + l32, hh);
-            rotate_frags(kf, a.rope, a.B, min(k_lo + l32, a.M - 1), hh, 1.0f);
+          if (k_lo < w_hi && k_lo + 32 > w_lo && k_lo < own_hi) {   // wave-uniform: this group holds keys of my states
             f32x16 sc;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sc[v] = 0.f;
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], sc, 0, 0, 0);
-            const int t0 = c0 + (sub >> 1) * 64;     // first row of the 64-row tile
-            finish_tile<true>(w, sc, stage + TILE_ELEMS, sub & 1, lane, [t0, q_lo, q_hi, own_hi](int key) {
-              const int row = t0 + key;
-              return row >= q_lo && row < q_hi && row < own_hi;
-            });
+            scores<0>(w, sc, k_addr(lds0 + OWN_K, sub * 32, lane));
+            finish_masked(w, sc, v_addr(lds0 + OWN_V, sub * 32, lane), lane,
+                          [k_lo, q_lo, q_hi](int key) { return k_lo + key >= q_lo && k_lo + key < q_hi; });
           }
         }
       }
     }
   }
-  __syncthreads();   // Q and own-block stages are free again
+  __syncthreads();   // Q and own-block rows are consumed: stages 2 and 3 are free
 
-  // ---- cached keys of this split: LDS-DMA ring, up to NSTAGE-1 tiles ahead --------------------------
+  // ---- cached keys of this split: LDS-DMA rings, up to NSTAGE-1 tiles ahead --------------------------
 #pragma nounroll
   for (int part = 0; part < (DUAL ? 2 : 1); ++part) {
   if (part == 1) {
@@ -447,56 +419,56 @@ __device__ __forceinline__ void attn_prefix_body(const AttnKArgs& a, int bid) {
     kend = max(v1, a.P) + a.B;
     n_tiles = kend > kbeg ? (kend - kbeg + KTILE - 1) / KTILE : 0;
     if (n_tiles > 0) issue_tile(0);      // the ring is drained: every stage is free
+    if (n_tiles > 1) issue_tile(1);
   }
   if (n_tiles == 0) continue;
-  if (1 < n_tiles) issue_tile(1);
   if (2 < n_tiles) issue_tile(2);
   // full tiles run through the software pipeline (scores of tile t+1 under the softmax of tile t); a ragged
-  // last tile takes the masked path afterwards
-  const bool ragged = n_tiles > 0 && ((kend - kbeg) % KTILE) != 0;
+  // last tile, whose scores come out of it too, takes the masked path afterwards
+  const bool ragged = ((kend - kbeg) % KTILE) != 0;
   const int n_pipe = ragged ? n_tiles - 1 : n_tiles;
-  if (n_pipe > 0) {
-    // tile 0 has landed; tiles 1 .. min(2, n_tiles-1) may still be in flight
-    if (n_tiles >= 3) wait_vmcnt<2 * DMA_PER_TILE>(); else if (n_tiles == 2) wait_vmcnt<DMA_PER_TILE>(); else wait_vmcnt<0>();
+  KAddr ka = k_addr(lds0, st * 32, lane);
+  VAddr va = v_addr(lds0 + V_RING, st * 32, lane);
+  // tile 0 has landed; tiles 1 .. min(2, n_tiles-1) may still be in flight
+  if (n_tiles >= 3) wait_vmcnt<2 * DMA_PER_TILE>(); else if (n_tiles == 2) wait_vmcnt<DMA_PER_TILE>(); else wait_vmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+  f32x16 sa, sb;
+  if (active) scores<0>(w, sa, ka);
+  // step t: tile t+1 has landed (tile t+2 may be in flight) and every wavefront is done with step t-1,
+  // i.e. with K of tile t and V of tile t-1, whose stage the next prefetch overwrites
+  auto sync_and_prefetch = [&](int t) {
+    if (t + 2 < n_tiles) wait_vmcnt<DMA_PER_TILE>(); else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
-    f32x16 sa, sb;
-    if (active) scores(w, sa, smem, st, lane);
-    // step t: tile t+1 has landed (tile t+2 may be in flight) and every wavefront is done with step t-1,
-    // i.e. with K of tile t and V of tile t-1, whose stage the next prefetch overwrites
-    auto sync_and_prefetch = [&](int t) {
-      if (t + 2 < n_tiles) wait_vmcnt<DMA_PER_TILE>(); else wait_vmcnt<0>();
-      __builtin_amdgcn_s_barrier();
-      if (t + NSTAGE - 1 < n_tiles) issue_tile(t + NSTAGE - 1);
-    };
-    auto k_of = [&](int t) { return smem + (t % NSTAGE) * STAGE_ELEMS; };
-    auto v_of = [&](int t) { return smem + (t % NSTAGE) * STAGE_ELEMS + TILE_ELEMS; };
-    int t = 0;
-    for (; t + 2 < n_pipe; t += 2) {     // two steps per trip: the score registers swap roles
-      sync_and_prefetch(t);
-      if (active) pipe_step<true>(w, sa, sb, k_of(t + 1), v_of(t), st, lane);
-      sync_and_prefetch(t + 1);
-      if (active) pipe_step<true>(w, sb, sa, k_of(t + 2), v_of(t + 1), st, lane);
-    }
-    if (t + 1 < n_pipe) {
-      sync_and_prefetch(t);
-      if (active) pipe_step<true>(w, sa, sb, k_of(t + 1), v_of(t), st, lane);
-      sync_and_prefetch(t + 1);
-      if (active) pipe_step<false>(w, sb, sa, nullptr, v_of(t + 1), st, lane);
-    } else {
-      sync_and_prefetch(t);
-      if (active) pipe_step<false>(w, sa, sb, nullptr, v_of(t), st, lane);
-    }
+    if (t + NSTAGE - 1 < n_tiles) issue_tile(t + NSTAGE - 1);
+  };
+  // Two steps per trip: the score registers swap roles and the addresses move on by two stages, alternately up and down
+  // (K of tile t+1 sits one stage ahead of V of tile t, so its addresses move between the steps).  The step of the last
+  // tile also takes scores of whatever the next stage holds; nothing reads them.
+  unsigned hop = 2 * STAGE_BYTES;
+  int t = 0;
+  for (; t + 1 < n_pipe; t += 2) {
+    sync_and_prefetch(t);
+    if (active) pipe_step<STAGE_BYTES, 0>(w, sa, sb, ka, va);
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) ka.a[kk] += hop;
+    sync_and_prefetch(t + 1);
+    if (active) pipe_step<0, STAGE_BYTES>(w, sb, sa, ka, va);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) va.a[n] += hop;
+    hop = 0u - hop;
   }
-  if (ragged) {
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    const bf16_t* ks = smem + ((n_tiles - 1) % NSTAGE) * STAGE_ELEMS;
-    const int nvalid = kend - (kbeg + (n_tiles - 1) * KTILE);
-    if (active) process_tile<true>(w, ks, ks + TILE_ELEMS, st, lane, [nvalid](int key) { return key < nvalid; });
+  if (t < n_pipe) {
+    sync_and_prefetch(t);
+    if (active) pipe_step<STAGE_BYTES, 0>(w, sa, sb, ka, va);
+    sa = sb;
+  }
+  if (ragged && active) {
+    const int nvalid = kend - (kbeg + n_pipe * KTILE) - st * 32;
+    finish_masked(w, sa, v_addr(lds0 + V_RING + (n_pipe % NSTAGE) * STAGE_BYTES, st * 32, lane), lane,
+                  [nvalid](int key) { return key < nvalid; });
   }
   __syncthreads();   // all tiles consumed, no DMA in flight: the ring can be reused
   }
-
   // ---- merge the two key halves of each wavefront pair through LDS ------------------------------
   {
     float* xb = reinterpret_cast<float*>(smem_raw) + (size_t)qw * 66 * 64;   // [66][64 lanes] per pair
@@ -597,12 +569,14 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
   *reinterpret_cast<bf16x4*>(out + rowh * HD + t) = r;
 }
 
-__global__ void rope_table_kernel(float2* __restrict__ tab, int B, int half, int hd, int pos0, float base) {
+// tab[f / 2][row][f % 2] = (cos, sin) of position * base^(-2f/128): rows 0 .. B-1 at positions pos0 .., rows B .. at tail_pos0 ..
+__global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ tab, int rows, int B, int pos0, int tail_pos0, float base) {
+  constexpr int HALF = HD / 2;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * half) return;
-  const int f = i / B, b = i % B;      // tab[f][b]
-  const double inv_freq = pow((double)base, -2.0 * (double)f / (double)hd);
-  const double ang = (double)(pos0 + b) * inv_freq;
+  if (i >= rows * HALF) return;
+  const int f = 2 * (i / (2 * rows)) + i % 2, b = (i / 2) % rows;
+  const double inv_freq = pow((double)base, -2.0 * (double)f / (double)HD);
+  const double ang = (double)(b < B ? pos0 + b : tail_pos0 + b - B) * inv_freq;
   tab[i] = make_float2((float)cos(ang), (float)sin(ang));
 }
 
@@ -614,10 +588,10 @@ bool mfma_attn_supported(const AttnArgs& a) {
   return a.hd == HD && a.Hq % a.Hkv == 0 && a.B >= 1 && a.G >= 1;
 }
 
-// rope table + split partials; P = cached keys, prefix and suffix together
+// split partials; P = cached keys, prefix and suffix together
 size_t mfma_attn_partial_bytes(int G, int B, int Hq, int hd, int P) {
   const size_t M = (size_t)G * B;
-  size_t bytes = align_up(sizeof(float2) * (size_t)B * (hd / 2), 256);
+  size_t bytes = 0;
   const int nS = n_splits(P);
   if (nS > 1) {
     bytes += align_up(sizeof(float) * nS * M * Hq * hd, 256);
@@ -626,36 +600,29 @@ size_t mfma_attn_partial_bytes(int G, int B, int Hq, int hd, int P) {
   return bytes;
 }
 
-// The rotary table of an attention problem with B rows per state at positions pos0 ..: [hd/2][B] (cos, sin), at the start
-// of that problem's scratch.  Callers that need it before the attention launch (the cache append) build it here and
-// pass rope_ready = 1 to the attention launch.
-const void* launch_rope_table(void* partial, int B, int pos0, float rope_base, hipStream_t st) {
-  const int nrope = B * (HD / 2);
-  rope_table_kernel<<<cdiv(nrope, 256), 256, 0, st>>>(reinterpret_cast<float2*>(partial), B, HD / 2, HD, pos0, rope_base);
-  return partial;
+size_t mfma_rope_bytes(int rows) { return sizeof(float2) * (size_t)rows * (HD / 2); }
+
+hipError_t launch_rope_table(void* tab, int B, int tail_rows, int pos0, int tail_pos0, float rope_base, hipStream_t st) {
+  const int rows = B + tail_rows;
+  rope_table_kernel<<<cdiv(rows * (HD / 2), 256), 256, 0, st>>>(reinterpret_cast<float2*>(tab), rows, B, pos0, tail_pos0, rope_base);
+  return hipGetLastError();
 }
 
 namespace {
 
-// kernel arguments of one attention problem; launches the rotary table kernel when the table is not in place yet
-AttnKArgs prepare_attn(const AttnArgs& a, hipStream_t st) {
+// kernel arguments of one attention problem
+AttnKArgs prepare_attn(const AttnArgs& a) {
   const int M = a.G * a.B;
   const int nS = n_splits(a.P + a.S);
   unsigned char* ws = reinterpret_cast<unsigned char*>(a.partial);
-  float2* rope = reinterpret_cast<float2*>(ws);
-  ws += align_up(sizeof(float2) * (size_t)a.B * (HD / 2), 256);
   float* opart = reinterpret_cast<float*>(ws);
   ws += align_up(sizeof(float) * (size_t)nS * M * a.Hq * HD, 256);
   float* mlpart = reinterpret_cast<float*>(ws);
-
-  const int nrope = a.B * (HD / 2);
-  if (!a.rope_ready) rope_table_kernel<<<cdiv(nrope, 256), 256, 0, st>>>(rope, a.B, HD / 2, HD, a.pos0, a.rope_base);
 
   AttnKArgs k;
   k.qkv = (const bf16_t*)a.qkv;
   k.pk = (const bf16_t*)a.prefix_k;
   k.pv = (const bf16_t*)a.prefix_v;
-  k.rope = rope;
   k.out = (bf16_t*)a.out;
   k.opart = opart;
   k.mlpart = mlpart;
@@ -663,18 +630,17 @@ AttnKArgs prepare_attn(const AttnArgs& a, hipStream_t st) {
   k.own = a.own;
   k.ld = (a.Hq + 2 * a.Hkv) * HD;
   // With few workgroups (one to eight states) a workgroup takes 64 or 32 query rows instead of 128, so that more CUs
-  // stream the keys; the wavefront pairs without rows only move data.  A row's arithmetic is the same (own-block keys
-  // are visited in 32-row groups counted from a multiple of 32 either way) as long as B divides 32 or 32 divides B,
-  // and always when there are no own-block keys.
+  // stream the keys; the wavefront pairs without rows only move data.  A row's arithmetic is the same: the groups of own-block
+  // keys are those of the 128-row tile.
   k.qrows = QTILE;
-  if (!a.own || 32 % a.B == 0 || a.B % 32 == 0) {
-    const int wgs = cdiv(M, QTILE) * nS * a.Hq;
-    if (wgs <= 64) k.qrows = 32;
-    else if (wgs <= 128) k.qrows = 64;
-    // between half and the whole chip (28 heads x 6 tiles of 128 rows = 168 workgroups): 96 rows, three of the four
-    // wavefront pairs at work, if that brings more workgroups and still one round of them (28 x 8 = 224)
-    else if (wgs < 256 && cdiv(M, 96) > cdiv(M, QTILE) && cdiv(M, 96) * nS * a.Hq <= 256) k.qrows = 96;
-  }
+  const int wgs = cdiv(M, QTILE) * nS * a.Hq;
+  if (wgs <= 64) k.qrows = 32;
+  else if (wgs <= 128) k.qrows = 64;
+  // between half and the whole chip (28 heads x 6 tiles of 128 rows = 168 workgroups): 96 rows, three of the four
+  // wavefront pairs at work, if that brings more workgroups and still one round of them (28 x 8 = 224)
+  // (96 rows do not lie inside one tile of 128: for blocks whose groups of own keys start anywhere 128 rows stay)
+  else if (wgs < 256 && cdiv(M, 96) > cdiv(M, QTILE) && cdiv(M, 96) * nS * a.Hq <= 256 &&
+           (!a.own || 32 % a.B == 0 || a.B % 32 == 0)) k.qrows = 96;
   k.nQ = cdiv(M, k.qrows);
   k.nS = nS;
   k.split = (int)align_up(cdiv(a.P + a.S, nS), KTILE);      // at most SPLIT_KEYS; a function of P + S only
@@ -695,7 +661,7 @@ hipError_t attn_lds_limits() {
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   const hipError_t e = attn_lds_limits();
   if (e != hipSuccess) return e;
-  const AttnKArgs k = prepare_attn(a, st);
+  const AttnKArgs k = prepare_attn(a);
   const int grid = k.nQ * k.nS * a.Hq;
   if (a.S > 0) attn_prefix_mfma_kernel<true><<<grid, NT, kAttnSmem, st>>>(k);
   else attn_prefix_mfma_kernel<false><<<grid, NT, kAttnSmem, st>>>(k);
@@ -707,7 +673,7 @@ hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
 hipError_t launch_attn_mfma_pair(const AttnArgs& a, const AttnArgs& b, hipStream_t st) {
   const hipError_t e = attn_lds_limits();
   if (e != hipSuccess) return e;
-  const AttnKArgs ka = prepare_attn(a, st), kb = prepare_attn(b, st);
+  const AttnKArgs ka = prepare_attn(a), kb = prepare_attn(b);
   const int n_a = ka.nQ * ka.nS * a.Hq, n_b = kb.nQ * kb.nS * b.Hq;
   attn_prefix_mfma_pair_kernel<<<n_a + n_b, NT, kAttnSmem, st>>>(ka, kb, n_a);
   if (ka.nS > 1) attn_combine_kernel<<<cdiv(ka.M * a.Hq, 8), 256, 0, st>>>(ka.opart, ka.mlpart, ka.out, ka.M, a.Hq, ka.nS);

@@ -23,6 +23,9 @@
 //
 // Epilogues:
 //   EPI_STORE    C = X W^T (+bias), W given as up to three row segments (q | k | v)
+//   EPI_QKV      the same for head_dim 128 with the rotary embedding on the q and k columns, on the fp32 sums: a
+//                32-column MFMA tile holds 16 columns c and the 16 columns c + 64 of a head, partner values meet
+//                through a lane swap; k and v rows that extend the cache are stored there too
 //   EPI_RESID    C = R + X W^T
 //   EPI_SWIGLU   C = silu(X Wg^T) * (X Wu^T); gate and up rows are interleaved 16/16 inside every
 //                32-column MFMA tile, partner values meet through one lane shuffle
@@ -172,6 +175,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
           else if (n0 < a.Nseg[0] + a.Nseg[1]) { base = (const bf16_t*)a.W[1]; seg0 = a.Nseg[0]; }
           else { base = (const bf16_t*)a.W[2]; seg0 = a.Nseg[0] + a.Nseg[1]; }
           r = j0 + row - seg0;
+          // rows of every 32-row MFMA tile: 16 columns of a head, then the 16 columns 64 further on that rotate with them
+          if (EPI == EPI_QKV) r = (r & ~127) + 16 * ((r >> 5) & 3) + 64 * ((r >> 4) & 1) + (r & 15);
         }
         yoff[q] = (unsigned)r * (unsigned)(ldw * 2) + chunk * 16;
       }
@@ -262,8 +267,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
   };
   // Weights as the A operand (ROW_LANES): a lane owns one row of the result (a token) and runs of four columns, so the
   // epilogues work inside a lane - no partner values to fetch - and store 16 bytes at a time (gate/up at 1024 rows
-  // 160 -> 157 us, 768 rows of 18944 features 146 -> 139).  The LM head has its vocabulary there anyway; fp32 partials keep 32 columns side by side in the
-  // lanes, whole 128-byte lines a store (1 - 2 us faster at 1024 rows than 16-byte runs of 32 rows).
+  // 160 -> 157 us, 768 rows of 18944 features 146 -> 139).  The LM head has its vocabulary there anyway; fp32 partials keep
+  // 32 columns side by side in the lanes, whole 128-byte lines a store (1 - 2 us faster at 1024 rows than 16-byte runs of
+  // 32 rows).
   constexpr bool ROW_LANES = EPI != EPI_LMHEAD && EPI != EPI_PARTIAL;
   auto mfma = [&](int i, int j, int buf) {
     if (!math) return;
@@ -419,6 +425,83 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
         for (int v = 0; v < 8; ++v) h[v] = silu_mul(acc[i][j][v], acc[i][j][v + 8]);
         const u32x4 o = pack16(h);
         if (r < i_max) *reinterpret_cast<u32x4*>(Cl + (size_t)r * a.ldc + j * 16) = o;
+      }
+    }
+    return;
+  }
+
+  if (EPI == EPI_QKV) {
+    // columns 0 .. 15 of a 32-column block are columns c of a head, 16 .. 31 the columns c + 64 that rotate with them.
+    // No more than the plain store took (1024 rows: 85 us, 256 rows: 41) and off the attention kernel, which rotated queries
+    // and own keys in front of its first product, one wavefront at a time (3 us), and a launch of its own for the cache (5).
+    const QkvArgs& q = a.qkv;
+    auto seg_of = [&](int n0) { return n0 < a.Nseg[0] ? 0 : (n0 < a.Nseg[0] + a.Nseg[1] ? 1 : 2); };
+    auto col_of = [&](int n0) { const int s = seg_of(n0); return n0 - (s == 0 ? 0 : (s == 1 ? a.Nseg[0] : a.Nseg[0] + a.Nseg[1])); };
+    // The angles of the next 32 rows are loaded in front of the stores of these: vector stores and loads retire in order, and
+    // a load behind a store waits for it.
+    f32x4 ang[2][TN][4];                           // (cos, sin) of frequencies 0, 1 | 2, 3 of run 0, then of run 1
+    auto load_angles = [&](int i) {
+      const int g = min(r_lane + i * 32, i_max - 1) + q.row0;
+      const int trow = g >= q.rows ? g - q.rows + q.B : q.B > 1 ? g - (int)__umulhi((unsigned)g, q.magic) * q.B : 0;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int fr = 16 * ((col_of(j0 + wn * CW + j * 32) >> 5) & 3);
+        const f32x4* t = reinterpret_cast<const f32x4*>(q.rope) + (size_t)(fr / 2 + 2 * hh) * q.rope_rows + trow;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ang[i & 1][j][u] = t[(size_t)(4 * (u >> 1) + (u & 1)) * q.rope_rows];
+      }
+    };
+    load_angles(0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (i + 1 < TM) load_angles(i + 1);
+      const int r = r_lane + i * 32, g = r + q.row0;
+      // row of the cache this row extends it by, or -1
+      const int dst = r >= i_max ? -1 : g < q.n_head ? q.dst_head + g : g >= q.rows && q.dst_tail >= 0 ? q.dst_tail + g - q.rows : -1;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int n0 = j0 + wn * CW + j * 32;      // uniform; a 32-column block is part of one head of q, k or v
+        const int seg = seg_of(n0), c0 = col_of(n0);
+        const int hcol = c0 & ~127, fr = 16 * ((c0 >> 5) & 3);       // head's first column, first frequency
+        float x1[8], x2[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) { x1[v] = acc[i][j][v]; x2[v] = acc[i][j][v + 8]; }
+        const void* bias = seg == 0 ? a.bias[0] : (seg == 1 ? a.bias[1] : a.bias[2]);
+        if (bias) {
+          const bf16_t* bp = (const bf16_t*)bias + hcol + fr + 4 * hh;
+#pragma unroll
+          for (int v = 0; v < 8; v += 4) {
+            const bf16x4 b1 = *reinterpret_cast<const bf16x4*>(bp + 2 * v), b2 = *reinterpret_cast<const bf16x4*>(bp + 64 + 2 * v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { x1[v + e] += static_cast<float>(b1[e]); x2[v + e] += static_cast<float>(b2[e]); }
+          }
+        }
+        if (seg < 2) {
+          const float scale = seg == 0 ? q.q_scale : 1.f;
+#pragma unroll
+          for (int v = 0; v < 8; v += 4) {
+            const f32x4 ta = ang[i & 1][j][v >> 1], tb = ang[i & 1][j][(v >> 1) + 1];
+            const float c[4] = {ta[0], ta[2], tb[0], tb[2]}, s[4] = {ta[1], ta[3], tb[1], tb[3]};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              // rotated as the rounded values that a reader of the unrotated columns would rotate
+              const float u1 = static_cast<float>(static_cast<bf16_t>(x1[v + e])), u2 = static_cast<float>(static_cast<bf16_t>(x2[v + e]));
+              x1[v + e] = (u1 * c[e] - u2 * s[e]) * scale;
+              x2[v + e] = (u2 * c[e] + u1 * s[e]) * scale;
+            }
+          }
+        }
+        const u32x4 o1 = pack16(x1), o2 = pack16(x2);
+        if (r < i_max) {
+          bf16_t* p = C + (size_t)r * a.ldc + (n0 - c0) + hcol + fr + 8 * hh;
+          *reinterpret_cast<u32x4*>(p) = o1;
+          *reinterpret_cast<u32x4*>(p + 64) = o2;
+        }
+        if (seg > 0 && dst >= 0) {
+          bf16_t* p = reinterpret_cast<bf16_t*>(seg == 1 ? q.ck : q.cv) + ((size_t)(hcol >> 7) * q.ldp + dst) * 128 + fr + 8 * hh;
+          *reinterpret_cast<u32x4*>(p) = o1;
+          *reinterpret_cast<u32x4*>(p + 64) = o2;
+        }
       }
     }
     return;
@@ -635,7 +718,7 @@ static hipError_t launch_shape(const GemmArgs& a, TileShape t, int unit, hipStre
   if constexpr (EPI == EPI_SWIGLU) {
     if (t.bn == 96) return t.bm == 128 ? launch_t<EPI, 96, 5, 128>(a, mt, nt, st) : launch_t<EPI, 96, 7, 64>(a, mt, nt, st);
   }
-  if constexpr (EPI == EPI_STORE) {
+  if constexpr (EPI == EPI_STORE || EPI == EPI_QKV) {
     if (t.bn == 96) return t.bm == 128 ? launch_t<EPI, 96, 4, 128>(a, mt, nt, st) : launch_t<EPI, 96, 6, 64>(a, mt, nt, st);
   }
   if (t.bm == 128) {
@@ -661,6 +744,7 @@ GemmPlan plan_gemm_mfma(int epi, int M, int N, int ksplit) {
   };
   switch (epi) {
     case EPI_STORE:
+    case EPI_QKV:
       one(choose_tile(M, N, 1, 1, true, false, false, true), 1);
       break;
     case EPI_RESID: {
@@ -725,6 +809,8 @@ hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
   switch (epi) {
     case EPI_STORE:
       return launch_shape<EPI_STORE>(a, TileShape{p.part[0].bm, p.part[0].bn}, 1, st);
+    case EPI_QKV:
+      return launch_shape<EPI_QKV>(a, TileShape{p.part[0].bm, p.part[0].bn}, 1, st);
     case EPI_RESID:
       if (p.part[0].bn == 64) return launch_t<EPI_RESID, 64, 4>(a, cdiv(a.M, BM), a.N / 64, st);
       return launch_t<EPI_RESID, 128, 4>(a, cdiv(a.M, BM), a.N / 128, st);

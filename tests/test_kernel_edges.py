@@ -25,3 +25,54 @@ def test_topk_slices_of_the_last_chunk(sp, V, K, B):
     st = synth.random_states(cfg.G, cfg.B, cfg.V, 0.2, 0.9, 3)
     st[1, :] = cfg.mask_id
     check_head_topk(sp, cfg, st, synth.hidden_states(cfg), synth.head_weights(cfg), 6.0, K, (0, 1))
+
+
+@pytest.mark.parametrize("B,G,P,hq,hkv", [(24, 44, 130, 16, 8), (7, 150, 64, 16, 16), (40, 27, 0, 28, 4), (1, 1030, 65, 16, 2)])
+def test_attention_rows_of_any_block_do_not_depend_on_the_query_tile(sp, B, G, P, hq, hkv):
+    """Blocks that neither divide 32 nor are multiples of it: the groups of own-block keys start anywhere, and 128-, 64- and
+    32-row query tiles (all the states, a third of them, the first ones) visit them the same way.  The rotary embedding and
+    the biases come from the projection's epilogue: ragged row tiles, odd table lengths, one token a block."""
+    from test_gpu_parity import run_layer, rel_err, tol, oracle_kw, O
+    cfg = synth.CONFIGS["c4"].scaled(L=1, F=512, V=1280, d=256, Hq=hq, Hkv=hkv, P=P, B=B, G=G)
+    w = synth.layer_weights(cfg, 0, bias=True)
+    pk, pv = synth.prefix_kv(cfg, 0)
+    x = synth.hidden_states(cfg)
+    full = run_layer(sp, cfg, w, pk, pv, x)
+    for n in (1, max(1, G // 9), G // 3):
+        assert torch.equal(run_layer(sp, cfg, w, pk, pv, x[:n].contiguous()), full[:n]), n
+    for g in (0, G - 1):
+        ref = O().verify_layer(np_weights(w), to_np(pk), to_np(pv), to_np(x[g:g + 1]), **oracle_kw(cfg))
+        e_max, _ = rel_err(to_np(full[g:g + 1]), ref)
+        assert e_max < tol(cfg), (g, e_max)
+
+
+@pytest.mark.parametrize("B,S,P", [(7, 45, 131), (32, 300, 64), (1, 3, 0)])
+def test_projection_extends_the_cache(sp, B, S, P):
+    """The projection's epilogue stores the true block and the suffix behind it: rows of the full-sequence step equal those that
+    committing the same tokens as one block leaves, and rows in front of and behind them stay."""
+    cfg = synth.CONFIGS["c4"].scaled(L=1, F=512, V=1280, d=256, P=P, B=B, G=3)
+    scfg = sp.cfg_from_synth(cfg)
+    w = {k: v.to(DEV) for k, v in synth.layer_weights(cfg, 0, bias=True).items()}
+    lw = [sp.layer_weights(w)]
+    hw = synth.head_weights(cfg)
+    emb = synth.embed_weights(cfg).to(DEV)
+    g = torch.Generator().manual_seed(5)
+    rows = P + B + S + 4
+    k0 = torch.randn((cfg.Hkv, rows, cfg.hd), generator=g).to(torch.bfloat16)
+    v0 = torch.randn((cfg.Hkv, rows, cfg.hd), generator=g).to(torch.bfloat16)
+    st = torch.from_numpy(synth.random_states(cfg.G, B, cfg.V, 0.2, 0.9, 7)).to(DEV)
+    suffix = torch.randint(0, cfg.V - 1, (S,), generator=g, dtype=torch.int32).to(DEV)
+    ka, va = k0.to(DEV), v0.to(DEV)
+    plan = sp.SeqStepPlan(scfg, lw, [sp.prefix_kv(ka, va, P, 0)], emb, hw["final_norm"].to(DEV), hw["w_vocab"].to(DEV), cfg.G, B,
+                          S, P, 0.9, logit_scale=1.0, device=DEV)
+    plan.run(st, suffix, None)
+    kb, vb = k0.to(DEV), v0.to(DEV)
+    for tok, p in ((st[0], P), (suffix, P + B)):         # the layer's keys do not depend on the attention: one layer
+        n = tok.numel()
+        sp.StepPlan(scfg, lw, [sp.prefix_kv(kb, vb, p, 0)], emb, hw["final_norm"].to(DEV), hw["w_vocab"].to(DEV), 1, n, p, 0.9,
+                    logit_scale=1.0, device=DEV).commit_block(tok.contiguous())
+    torch.cuda.synchronize()
+    assert torch.equal(ka, kb) and torch.equal(va, vb)
+    for a, b in ((ka, k0), (va, v0)):
+        assert torch.equal(a[:, :P].cpu(), b[:, :P]) and torch.equal(a[:, P + B + S:].cpu(), b[:, P + B + S:])
+        assert not torch.equal(a[:, P:P + B + S].cpu(), b[:, P:P + B + S])
