@@ -194,8 +194,9 @@ int spiffy_gemm(int32_t dtype, int32_t epilogue, const void *A, const void *W0, 
                 const void *R, void *C, int32_t M, int32_t N, int32_t K, void *workspace,
                 size_t workspace_bytes, void *stream);
 
-/* How spiffy_gemm / verify_layer would launch a bf16 projection of M rows, N output columns (SPIFFY_GEMM_SWIGLU: N
+/* How spiffy_gemm would launch a bf16 projection of M rows, N output columns (SPIFFY_GEMM_SWIGLU: N
  * features) and inner size K on the MFMA kernel: host arithmetic only, nothing is launched and no device is touched.
+ * (tiles of 256, 128, 64 and 32 rows; verify_layer starts from this plan and also has heights in between)
  * The choice is scheduling: the order of the K sum of an output element does not depend on it (Sec. 4.3: states of one
  * step are independent rows), only k_slices does, and k_slices depends on (N, K) alone.  with_workspace: as for
  * spiffy_gemm, SPIFFY_GEMM_RESID slices K only when scratch is given.  Returns SPIFFY_ESHAPE for shapes the MFMA

@@ -229,9 +229,14 @@ struct LayerChain {
 hipError_t launch_gemm_mfma_rows(int epi, GemmArgs g, int rows_a, int rows_b, int dtype, hipStream_t st) {
   const size_t es = esize(dtype), ces = epi == EPI_PARTIAL ? sizeof(float) : es;
   g.Mz = rows_a + rows_b;
-  // one launch when there are few rows in all (weight streaming sets the time: stream them once, not twice) or
-  // when the second range adds no 256-row tile
-  if (rows_a + rows_b <= 512 || cdiv(rows_a + rows_b, 256) == cdiv(rows_a, 256)) {
+  // one launch when there are few rows in all (weight streaming sets the time: stream them once, not twice) or when the
+  // measured costs of the tile shapes say that it is no longer than two
+  float one = 0.f, a_us = 0.f, b_us = 0.f;
+  const int ks = g.ksplit < 1 ? 1 : g.ksplit;
+  plan_gemm_layer(epi, rows_a + rows_b, g.N, g.K, ks, &one);
+  plan_gemm_layer(epi, rows_a, g.N, g.K, ks, &a_us);
+  plan_gemm_layer(epi, rows_b, g.N, g.K, ks, &b_us);
+  if (rows_a + rows_b <= 512 || one <= a_us + b_us) {
     g.M = rows_a + rows_b;
     return launch_gemm_mfma(epi, g, st);
   }
@@ -262,7 +267,8 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   const bool mf = layer_mfma(cfg);
   const LayerWs ws = carve_layer(cfg, G, B, prefix->P + prefix->S, workspace, S_seq);
   int rc;
-  auto mfma_rows = [&](int epi, const GemmArgs& ga) {
+  auto mfma_rows = [&](int epi, GemmArgs ga) {
+    ga.layer = 1;
     return S_seq ? launch_gemm_mfma_rows(epi, ga, G * B, S_seq, dt, st) : launch_gemm_mfma(epi, ga, st);
   };
   if (chain) chain->normed_out = false;

@@ -124,6 +124,13 @@ struct GemmPlan {
   struct { int bm, bn, col0, ncols, workgroups; } part[2];
 };
 GemmPlan plan_gemm_mfma(int epi, int M, int N, int ksplit);
+// the same for the projections of a layer (GemmArgs::layer): more tile heights, chosen by measured costs
+GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_us = nullptr);
+struct TileShape { int bm, bn; };
+hipError_t launch_gemm_store(const GemmArgs& a, TileShape t, hipStream_t st);
+hipError_t launch_gemm_qkv(const GemmArgs& a, TileShape t, hipStream_t st);
+hipError_t launch_gemm_swiglu(const GemmArgs& a, TileShape t, hipStream_t st);
+hipError_t launch_gemm_partial(const GemmArgs& a, TileShape t, hipStream_t st);
 int mfma_lmhead_partials_per_row(int V);
 int mfma_ksplit(int N, int K);          // K slices used for a [M,K]x[N,K] projection with residual (depends on N, K only)
 // out = R + sum of the K-slice partials P[ksplit][M][N] (fixed order); if normed != NULL also RMSNorm(out)*gain.

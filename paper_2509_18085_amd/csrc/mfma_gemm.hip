@@ -1,564 +1,11 @@
-// bf16 MFMA GEMM for gfx950:  D[i,j] = sum_k X[i,k] * Y[j,k]  (both operands K-contiguous), fp32
-// accumulation with v_mfma_f32_32x32x16_bf16.
-//
-// Shape of the kernel (what measurements on MI355X pushed it to):
-//   * one workgroup per CU: 256 x BN output tile (BN = 192 or 128), 4 wavefronts in a 2x2 grid, each
-//     wavefront owns 128 x BN/2 (accumulators in AGPRs).  The L2 delivers about 32 B/clk to a CU, so
-//     a tile needs >= 64..128 flop per loaded byte; 128x128 tiles are bound by that, 256x192 is not.
-//     With few rows (one to eight states) the projections only stream weights: the same kernel with
-//     128- or 64-row tiles does half or a quarter of the matrix work per tile and covers more CUs; the
-//     narrow split-K projections of one or two states take 32-column tiles with one wavefront along a
-//     32-wide side (64 x 32: two wavefronts, 32 x 32: one), so 256 workgroups stream instead of 128;
-//     the gate/up projection of up to 128 rows takes 96-column tiles (256 workgroups instead of 192):
-//     a 1 x 4 wavefront grid, three wavefronts own a 32-column block each, the fourth only loads.
-//   * K advances in steps of 64 so every row segment is one full 128-byte line; operands go
-//     global -> LDS directly (LDS-DMA loads, no register staging), rows XOR-swizzled so the
-//     16-byte fragment reads are conflict-free.
-//   * separate LDS rings for the two operands: the activation operand (mostly L2 hits) gets 2 stages,
-//     the weight operand (streamed from HBM) SD = 3-4 stages, 128-144 KB in all.
-//   * one barrier per K-tile; the loads of later tiles and the LDS fragment reads of the next
-//     16-wide K step are threaded between the MFMAs of the current step, fragments double-buffered
-//     in registers, partial s_waitcnt vmcnt so younger loads stay in flight across the barrier.
-//   * workgroup ids are remapped so that the workgroups sharing a weight tile sit on one XCD.
-//
-// Epilogues:
-//   EPI_STORE    C = X W^T (+bias), W given as up to three row segments (q | k | v)
-//   EPI_QKV      the same for head_dim 128 with the rotary embedding on the q and k columns, on the fp32 sums: a
-//                32-column MFMA tile holds 16 columns c and the 16 columns c + 64 of a head, partner values meet
-//                through a lane swap; k and v rows that extend the cache are stored there too
-//   EPI_RESID    C = R + X W^T
-//   EPI_SWIGLU   C = silu(X Wg^T) * (X Wu^T); gate and up rows are interleaved 16/16 inside every
-//                32-column MFMA tile, partner values meet through one lane shuffle
-//   EPI_PARTIAL  fp32 partial sums of one K slice (split-K for narrow N; reduced by a second kernel
-//                in a fixed order, the slice count depends on (N, K) only)
-//   EPI_LMHEAD   rows i = vocabulary entries, columns j = tokens: each lane owns token columns and
-//                reduces its logits to (top, lowest index, runner-up, sum exp) in registers; logits
-//                are never stored (Alg. 1 steps 1-2 fused into the GEMM)
-//
-// The accumulation order along K of every output element is fixed by (N, K) alone, so a row's result
-// does not depend on how many other states are verified with it.
-#include <type_traits>
-
-#include "kernels.h"
+// Host side of the bf16 MFMA GEMM: which tile shapes a projection is launched with, the LM head's and the residual
+// epilogue's instantiations, and the reduction of the K slices.  The kernel is in mfma_gemm_kernel.h; the instantiations of
+// the other epilogues are in mfma_gemm_{store,qkv,swiglu,partial}.hip (one compilation each).
+#include "mfma_gemm_kernel.h"
 
 namespace spiffy {
 
 namespace {
-
-constexpr int BM = 256, BKK = 64;
-
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* glb_ptr_t;
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {   // vmcnt <= N; lgkmcnt / expcnt untouched
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | (7 << 4) | (0xF << 8) | ((N >> 4) << 14));
-}
-__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
-
-// 64-row tiles, and 128-row tiles up to 128 columns wide, are weight-streaming shapes: both operand rings SD deep
-constexpr bool uniform_rings(int epi, int bn, int bmt) { return epi != EPI_LMHEAD && (bmt <= 64 || (bmt == 128 && bn <= 128)); }
-// stages of the shallow operand's ring = how many K-tiles ahead it is loaded; SA = 0 picks the default of the shape
-constexpr int shallow_stages(int epi, int bn, int bmt, int sd, int sa) { return sa ? sa : (uniform_rings(epi, bn, bmt) ? sd : 2); }
-// wavefronts of a workgroup: a 2 x 2 grid over the tile; a 32-row or 32-column tile has one wavefront along that side.
-// A 96-column tile (three 32-column blocks: what gives 256 workgroups when 128 columns give 192) has a 1 x 4 grid whose
-// first three wavefronts own one block each; the fourth only takes its share of the loads.
-constexpr int waves_m(int bmt, int bn) { return bn == 96 ? 1 : (bmt >= 64 ? 2 : 1); }
-constexpr int waves_n(int bn) { return bn == 96 ? 4 : (bn >= 64 ? 2 : 1); }
-constexpr int wave_cols(int bn) { return bn == 96 ? 32 : bn / waves_n(bn); }
-
-template <int EPI, int BN, int SD, int BMT = 256, int SA = 0>
-__global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int tiles_i, int tiles_j) {
-  constexpr int BM = BMT;                         // rows of the output tile: 256, or 128 / 64 / 32 when there are few rows
-  constexpr int WM = waves_m(BMT, BN), WN = waves_n(BN), NW = WM * WN;
-  constexpr int RW = BM / WM, CW = wave_cols(BN);  // rows and columns of the tile that one wavefront owns
-  constexpr int NW_MATH = WM * (BN / CW);          // wavefronts that own a part of the tile (all but one of a 96-column tile's)
-  static_assert(EPI != EPI_LMHEAD || NW == 4, "the LM-head epilogue assumes the 2 x 2 wavefront grid");
-  // which operand is the weight matrix (deep ring): Y for the projections, X for the LM head
-  constexpr bool XDEEP = (EPI == EPI_LMHEAD);
-  // The deep operand (weights) rides a ring of SD stages and is loaded SD tiles ahead; the shallow one (activations)
-  // a ring of SH stages, SH tiles ahead.  The load counter retires in order, so waiting for the shallow operand of
-  // the next tile also waits for every older load: across a barrier stay in flight the deep loads issued with that
-  // shallow tile and the SH-2 whole groups after it (SH = 2: only the newest weight tile, whatever SD; SH = SD, the
-  // weight-streaming shapes with few rows: SD-2 whole tiles).
-  constexpr int SH = shallow_stages(EPI, BN, BMT, SD, SA);
-  static_assert(SH >= 2 && SH <= SD, "the shallow ring is at most as deep as the deep one");
-  constexpr int SX = XDEEP ? SD : SH, SY = XDEEP ? SH : SD;
-  constexpr int TM = RW / 32, TN = CW / 32;
-  constexpr int LX = BM / (8 * NW), LY = BN / (8 * NW);   // 1-KB wave-loads (8 rows x 128 B) per wavefront per K-tile
-  constexpr int NL = LX + LY;
-  constexpr int XSTAGE = BM * BKK, YSTAGE = BN * BKK;
-  constexpr int NMF = TM * TN, NF = TM + TN;
-  constexpr int NSLOT = 4 * NMF;                  // MFMAs between two barriers
-  extern __shared__ __align__(1024) unsigned char smem_raw[];
-  bf16_t* Xs = reinterpret_cast<bf16_t*>(smem_raw);
-  bf16_t* Ys = Xs + SX * XSTAGE;
-
-  // the wavefront id is uniform: keep it (and all LDS destination arithmetic) in scalar registers
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int wm = wave / WN, wn = wave % WN;
-  const int l32 = lane & 31, hh = lane >> 5;
-  const bool math = NW_MATH == NW || wave < NW_MATH;    // wavefront-uniform
-
-  int i_max, j_max, kz, ti, tj;
-  if (EPI == EPI_LMHEAD) {
-    // The grid covers the row capacity; the number of rows in use is only known on the device.  The first
-    // (vocabulary tiles x token tiles in use) workgroup ids take the real tiles, token tiles running fastest
-    // so that the workgroups sharing a vocabulary tile sit next to each other on one XCD; the rest leave.
-    i_max = a.N;
-    j_max = a.M_dev ? min(*a.M_dev, a.M) : a.M;
-    const int used_j = (j_max + BN - 1) / BN;
-    const int used = tiles_i * used_j;
-    if ((int)blockIdx.x >= used) return;
-    const int L = xcd_contiguous(blockIdx.x, used);
-    kz = 0;
-    ti = L / used_j;
-    tj = L % used_j;
-  } else {
-    // XCD-aware order: workgroup ids go round-robin over the 8 XCDs; give each XCD a contiguous range
-    // of logical tiles, running fastest over the activation tiles, so the workgroups that stream the
-    // same weight tile share one L2 and run at the same time.
-    const int per_z = tiles_i * tiles_j;
-    kz = blockIdx.x / per_z;
-    const int L = xcd_contiguous(blockIdx.x % per_z, per_z);
-    ti = L % tiles_i;
-    tj = L / tiles_i;
-    i_max = a.M_dev ? min(*a.M_dev, a.M) : a.M;
-    j_max = a.N;
-    if (ti * BM >= i_max) return;
-  }
-  const int i0 = ti * BM, j0 = tj * BN;
-
-  const int ldw = a.ldw ? a.ldw : a.K;
-  // K range of this slice
-  const int KT_all = a.K / BKK;
-  const int kt0 = (int)(((long long)KT_all * kz) / a.ksplit);
-  const int KT = (int)(((long long)KT_all * (kz + 1)) / a.ksplit) - kt0;
-
-  // ---- global sources.  A wave-load covers 8 rows; lane -> (row, swizzled 16-byte chunk).  Addresses are a
-  // wavefront-uniform base (scalar registers) plus a 32-bit per-lane byte offset that never changes: the
-  // loads take the scalar-base form and the K loop needs no vector arithmetic for them.
-  const char* xbase;
-  const char* ybase[LY];
-  unsigned xoff[LX], yoff[LY];
-  {
-    const bf16_t* X = (EPI == EPI_LMHEAD) ? (const bf16_t*)a.W[0] : (const bf16_t*)a.A;
-    const int ldx = (EPI == EPI_LMHEAD) ? ldw : a.lda;
-    xbase = reinterpret_cast<const char*>(X + (size_t)kt0 * BKK);
-#pragma unroll
-    for (int q = 0; q < LX; ++q) {
-      const int row = 8 * (wave * LX + q) + (lane >> 3);
-      const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-      const int gi = min(i0 + row, i_max - 1);
-      xoff[q] = (unsigned)gi * (unsigned)(ldx * 2) + chunk * 16;
-    }
-#pragma unroll
-    for (int q = 0; q < LY; ++q) {
-      const int row0 = 8 * (wave * LY + q);            // first row of the wave-load: uniform
-      const int row = row0 + (lane >> 3);
-      const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-      const bf16_t* base;
-      int r;                                            // row inside the matrix `base` points to
-      if (EPI == EPI_LMHEAD) {
-        base = (const bf16_t*)a.A;
-        r = min(j0 + row, j_max - 1);
-        yoff[q] = (unsigned)r * (unsigned)(a.lda * 2) + chunk * 16;
-      } else {
-        if (EPI == EPI_SWIGLU) {
-          // rows of every 32-row MFMA tile: 16 gate rows then the 16 up rows of the same features
-          base = (row0 & 16) ? (const bf16_t*)a.W[1] : (const bf16_t*)a.W[0];
-          r = tj * (BN / 2) + (row >> 5) * 16 + (row & 15);
-        } else {
-          const int n0 = j0 + row0;   // column of the fused [seg0 | seg1 | seg2] output; 8-row groups never straddle
-          int seg0;
-          if (n0 < a.Nseg[0]) { base = (const bf16_t*)a.W[0]; seg0 = 0; }
-          else if (n0 < a.Nseg[0] + a.Nseg[1]) { base = (const bf16_t*)a.W[1]; seg0 = a.Nseg[0]; }
-          else { base = (const bf16_t*)a.W[2]; seg0 = a.Nseg[0] + a.Nseg[1]; }
-          r = j0 + row - seg0;
-          // rows of every 32-row MFMA tile: 16 columns of a head, then the 16 columns 64 further on that rotate with them
-          if (EPI == EPI_QKV) r = (r & ~127) + 16 * ((r >> 5) & 3) + 64 * ((r >> 4) & 1) + (r & 15);
-        }
-        yoff[q] = (unsigned)r * (unsigned)(ldw * 2) + chunk * 16;
-      }
-      ybase[q] = reinterpret_cast<const char*>(base + (size_t)kt0 * BKK);
-    }
-  }
-  // 16 bytes per lane, global (scalar base + 32-bit lane offset) -> LDS (M0 = destination of lane 0).  Written
-  // out because the compiler only emits the 64-bit-lane-address form, which costs a 64-bit vector add per load.
-  auto dma16 = [](const char* ubase, unsigned lane_off, const bf16_t* lds_dst) {
-    const unsigned m0v = (unsigned)(size_t)(lds_ptr_t)lds_dst;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(m0v), "v"(lane_off), "s"(ubase) : "memory");
-  };
-  auto load_x = [&](int q, int t) {
-    dma16(xbase + (size_t)t * (BKK * 2), xoff[q], Xs + (t % SX) * XSTAGE + (wave * LX + q) * 512);
-  };
-  auto load_y = [&](int q, int t) {
-    dma16(ybase[q] + (size_t)t * (BKK * 2), yoff[q], Ys + (t % SY) * YSTAGE + (wave * LY + q) * 512);
-  };
-  constexpr int LS = XDEEP ? LY : LX, LD = XDEEP ? LX : LY;   // wave-loads of the shallow / deep operand
-  auto load_sh = [&](int q, int t) { if (XDEEP) load_y(q, t); else load_x(q, t); };
-  auto load_dp = [&](int q, int t) { if (XDEEP) load_x(q, t); else load_y(q, t); };
-  // load `idx` of group g (the loads issued after barrier g): shallow operand of tile g+SH first, then
-  // the deep operand of tile g+SD
-  constexpr int SH_AHEAD = SH;
-  auto group_load = [&](int idx, int g, bool checked = true) {
-    if (idx < LS) { if (!checked || g + SH_AHEAD < KT) load_sh(idx, g + SH_AHEAD); }
-    else { if (!checked || g + SD < KT) load_dp(idx - LS, g + SD); }
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  // short K: not enough tiles for the steady-state wait counts, wait for everything each time
-  const bool short_k = KT <= SD;
-  // prologue, in the order the partial waits rely on: D0 S0 | D1 [S1] .. D(SD-2) [S(SD-2)] (shallow tiles up to SH-2)
-  // | first quarter of group -1 (what a "K step 3 of tile -1" would have issued); the loop issues the rest
-  static_assert(SD >= 3, "the steady-state wait keeps one deep-operand tile in flight across the barrier");
-#pragma unroll
-  for (int q = 0; q < LD; ++q) load_dp(q, 0);
-#pragma unroll
-  for (int q = 0; q < LS; ++q) load_sh(q, 0);
-#pragma unroll
-  for (int t = 1; t < SD - 1; ++t)
-    if (t < KT) {
-#pragma unroll
-      for (int q = 0; q < LD; ++q) load_dp(q, t);
-      if (t < SH - 1) {
-#pragma unroll
-        for (int q = 0; q < LS; ++q) load_sh(q, t);
-      }
-    }
-#pragma unroll
-  for (int idx = 0; idx < NL / 4; ++idx) group_load(idx, -1);
-
-  const int sw_r = (l32 >> 1) & 7;
-  const int xrow = (wm * RW + l32) * BKK;
-  const int yrow = (wn * CW + l32) * BKK;
-  bf16x8 fx[2][TM], fy[2][TN];
-  auto ldfrag = [&](int buf, const bf16_t* xs, const bf16_t* ys, int kk, int r) {
-    if (!math) return;
-    const int slot = ((kk * 2 + hh) ^ sw_r) * 8;
-    if (r < TM) fx[buf][r] = *reinterpret_cast<const bf16x8*>(xs + xrow + r * 32 * BKK + slot);
-    else fy[buf][r - TM] = *reinterpret_cast<const bf16x8*>(ys + yrow + (r - TM) * 32 * BKK + slot);
-  };
-  // loads younger than tile 0's: the deep halves of tiles 1 .. SD-2, the shallow halves of tiles 1 .. SH-2, and the
-  // start of group -1.  Steady state: younger than the shallow operand of the next tile are the deep loads of its
-  // own group and the SH-2 groups after it (every group when both rings have the same depth).
-  constexpr int W_FIRST = (SD - 2) * LD + (SH - 2) * LS + NL / 4;
-  constexpr int W_STEADY = SH == SD ? (SD - 2) * NL : LD + (SH - 2) * NL;
-  static_assert(W_FIRST <= 63 && W_STEADY <= 63, "vmcnt is a 6-bit counter");
-  if (short_k) wait_vmcnt<0>(); else wait_vmcnt<W_FIRST>();   // tile 0 is in LDS
-  __builtin_amdgcn_s_barrier();
-#pragma unroll
-  for (int r = 0; r < NF; ++r) ldfrag(0, Xs, Ys, 0, r);
-
-  // fragment reads of the next K step issued after MFMA m of the current one: [frag_lo(m), frag_lo(m+1)).
-  // One per MFMA from the second on when there are enough MFMAs, else spread over all but the last.
-  auto frag_lo = [](int m) {
-    if (NMF == 1) return m < 1 ? 0 : NF;
-    if (NF <= NMF - 1) return m < 1 ? 0 : (m - 1 < NF ? m - 1 : NF);
-    return m < NMF - 1 ? (m * NF) / (NMF - 1) : NF;
-  };
-  // Weights as the A operand (ROW_LANES): a lane owns one row of the result (a token) and runs of four columns, so the
-  // epilogues work inside a lane - no partner values to fetch - and store 16 bytes at a time (gate/up at 1024 rows
-  // 160 -> 157 us, 768 rows of 18944 features 146 -> 139).  The LM head has its vocabulary there anyway; fp32 partials keep
-  // 32 columns side by side in the lanes, whole 128-byte lines a store (1 - 2 us faster at 1024 rows than 16-byte runs of
-  // 32 rows).
-  constexpr bool ROW_LANES = EPI != EPI_LMHEAD && EPI != EPI_PARTIAL;
-  auto mfma = [&](int i, int j, int buf) {
-    if (!math) return;
-    acc[i][j] = !ROW_LANES ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[buf][i], fy[buf][j], acc[i][j], 0, 0, 0)
-                      : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[buf][j], fx[buf][i], acc[i][j], 0, 0, 0);
-  };
-  // one K-tile; STEADY = every tile this iteration prefetches exists (no bounds checks, no branches)
-  auto k_tile = [&](int kt, auto steady_tag) {
-    constexpr bool STEADY = decltype(steady_tag)::value;
-    const bf16_t* xs = Xs + (kt % SX) * XSTAGE;
-    const bf16_t* ys = Ys + (kt % SY) * YSTAGE;
-    // K steps 0..2 of the tile: MFMAs on fragment buffer kk&1, fragments of step kk+1 into the other
-    // buffer, remaining loads of group kt-1
-#pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {
-#pragma unroll
-      for (int m = 0; m < NMF; ++m) {
-        const int i = m / TN, j = m % TN;
-        mfma(i, j, kk & 1);
-#pragma unroll
-        for (int r = frag_lo(m); r < frag_lo(m + 1); ++r) ldfrag((kk + 1) & 1, xs, ys, kk + 1, r);
-        const int slot = NMF + kk * NMF + m;      // position among the NSLOT MFMAs that follow barrier kt-1
-#pragma unroll
-        for (int idx = (slot * NL) / NSLOT; idx < ((slot + 1) * NL) / NSLOT; ++idx) group_load(idx, kt - 1, !STEADY);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    // barrier kt: tile kt+1 is in LDS for every wavefront (only the deep-operand loads of group kt-1
-    // may still fly), and no wavefront reads the stages of tile kt after this point
-    if (STEADY || (!short_k && kt + SD - 1 < KT)) wait_vmcnt<W_STEADY>(); else wait_vmcnt<0>();
-    wait_lgkm0();
-    __builtin_amdgcn_s_barrier();
-    const bf16_t* xs1 = Xs + ((kt + 1) % SX) * XSTAGE;
-    const bf16_t* ys1 = Ys + ((kt + 1) % SY) * YSTAGE;
-    // K step 3: MFMAs on buffer 1, fragments (kt+1, step 0) into buffer 0, first loads of group kt
-#pragma unroll
-    for (int m = 0; m < NMF; ++m) {
-      const int i = m / TN, j = m % TN;
-      mfma(i, j, 1);
-#pragma unroll
-      for (int r = frag_lo(m); r < frag_lo(m + 1); ++r) ldfrag(0, xs1, ys1, 0, r);
-#pragma unroll
-      for (int idx = (m * NL) / NSLOT; idx < ((m + 1) * NL) / NSLOT; ++idx) group_load(idx, kt, !STEADY);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  // steady state: kt >= 1 (group kt-1 exists as a whole) and kt + SD < KT (everything prefetched exists)
-  int kt = 0;
-  if (!short_k) {
-    k_tile(0, std::false_type{});
-    for (kt = 1; kt + SD < KT; ++kt) k_tile(kt, std::true_type{});
-  }
-  for (; kt < KT; ++kt) k_tile(kt, std::false_type{});
-  if (!math) return;      // (no barrier follows the K loop)
-
-  if (EPI == EPI_LMHEAD) {
-    // accumulator element (i,j,v) of this lane: row = i0 + wm*RW + i*32 + 8*(v/4) + 4*hh + v%4, column wn*CW + j*32 + l32
-    // of the tile
-    // Per token column: top value, its lowest vocabulary index, runner-up and sum of exponentials over the
-    // lane's 64 vocabulary rows, on the unscaled accumulators (the scale is positive, so the order is the
-    // same); the lane's rows are visited in increasing vocabulary index, so "strictly greater" keeps the
-    // lowest index among equals.  One median-of-three per value maintains the runner-up.
-    TopPartial* part = reinterpret_cast<TopPartial*>(a.C);
-    const float c = a.scale * 1.4426950408889634f;
-    auto reduce_columns = [&](auto checked_tag) {
-      constexpr bool CHECKED = decltype(checked_tag)::value;   // the last vocabulary tile: rows beyond V count as -inf
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        float m = -INFINITY, m2 = -INFINITY;
-        int code = 0;      // 16 * i + v of the top value
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            float l = acc[i][j][v];
-            if (CHECKED) {
-              const int idx = i0 + wm * RW + i * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-              if (idx >= i_max) l = -INFINITY;
-              acc[i][j][v] = l;
-            }
-            m2 = __builtin_amdgcn_fmed3f(m, m2, l);
-            code = l > m ? 16 * i + v : code;
-            m = __builtin_amdgcn_fmed3f(m, l, INFINITY);   // max(m, l) as one instruction
-          }
-        // in the last tile a lane may have no row below V: it keeps m = -inf and contributes nothing
-        const float mc = (m == -INFINITY) ? 0.f : m * c;
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][v], c, -mc));
-        Top t;
-        t.m = m * a.scale;
-        t.m2 = m2 * a.scale;
-        t.s = sum;
-        t.idx = (m == -INFINITY) ? 0x7fffffff
-                                 : i0 + wm * RW + (code >> 4) * 32 + 8 * ((code & 15) >> 2) + 4 * hh + (code & 3);
-        t = top_merge(t, top_shfl_xor(t, 32));
-        const int tokr = j0 + wn * CW + j * 32 + l32;
-        if (hh == 0 && tokr < j_max) part[(size_t)(ti * 2 + wm) * a.ldc + tokr] = TopPartial{t.m, t.m2, t.s, t.idx};
-      }
-    };
-    if (i0 + BM <= i_max) reduce_columns(std::false_type{}); else reduce_columns(std::true_type{});
-    return;
-  }
-
-  if (EPI == EPI_PARTIAL) {
-    // accumulator elements as for the LM head
-    float* P = reinterpret_cast<float*>(a.C) + (size_t)kz * (a.Mz ? a.Mz : a.M) * a.ldc;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = i0 + wm * RW + i * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-        if (r >= i_max) continue;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) P[(size_t)r * a.ldc + j0 + wn * CW + j * 32 + l32] = acc[i][j][v];
-      }
-    return;
-  }
-
-  // accumulator element (i,j,v) of this lane: row i0 + wm*RW + i*32 + l32, column wn*CW + j*32 + 8*(v/4) + 4*hh + v%4 of the
-  // tile: four runs of four columns, the lane 32 further on holds the runs in between
-  const int r_lane = i0 + wm * RW + l32;
-  // Sixteen consecutive columns of the lane's row: run 0 of the lower lane, run 0 of the upper, run 1 of the lower, run 1 of
-  // the upper.  The lanes trade run 1 against run 0 and hold eight columns each: columns 8*hh .. 8*hh+7, one 16-byte store.
-  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  auto pack2 = [](float x, float y) {
-    bf16x2 t;
-    t[0] = static_cast<bf16_t>(x);
-    t[1] = static_cast<bf16_t>(y);
-    return __builtin_bit_cast(unsigned int, t);
-  };
-  auto pack16 = [&](const float (&x)[8]) {     // x: run 0, run 1
-    const u32x2 s0 = __builtin_amdgcn_permlane32_swap(pack2(x[0], x[1]), pack2(x[4], x[5]), false, false);
-    const u32x2 s1 = __builtin_amdgcn_permlane32_swap(pack2(x[2], x[3]), pack2(x[6], x[7]), false, false);
-    return u32x4{s0[0], s1[0], s0[1], s1[1]};
-  };
-
-  bf16_t* C = reinterpret_cast<bf16_t*>(a.C);
-  if (EPI == EPI_SWIGLU) {
-    // columns 0 .. 15 of a 32-column block are gate values, 16 .. 31 the up values of the same features
-    bf16_t* Cl = C + tj * (BN / 2) + wn * TN * 16 + 8 * hh;
-    auto silu_mul = [](float g, float u) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u; };
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int r = r_lane + i * 32;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        float h[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) h[v] = silu_mul(acc[i][j][v], acc[i][j][v + 8]);
-        const u32x4 o = pack16(h);
-        if (r < i_max) *reinterpret_cast<u32x4*>(Cl + (size_t)r * a.ldc + j * 16) = o;
-      }
-    }
-    return;
-  }
-
-  if (EPI == EPI_QKV) {
-    // columns 0 .. 15 of a 32-column block are columns c of a head, 16 .. 31 the columns c + 64 that rotate with them.
-    // No more than the plain store took (1024 rows: 85 us, 256 rows: 41) and off the attention kernel, which rotated queries
-    // and own keys in front of its first product, one wavefront at a time (3 us), and a launch of its own for the cache (5).
-    const QkvArgs& q = a.qkv;
-    auto seg_of = [&](int n0) { return n0 < a.Nseg[0] ? 0 : (n0 < a.Nseg[0] + a.Nseg[1] ? 1 : 2); };
-    auto col_of = [&](int n0) { const int s = seg_of(n0); return n0 - (s == 0 ? 0 : (s == 1 ? a.Nseg[0] : a.Nseg[0] + a.Nseg[1])); };
-    // The angles of the next 32 rows are loaded in front of the stores of these: vector stores and loads retire in order, and
-    // a load behind a store waits for it.
-    f32x4 ang[2][TN][4];                           // (cos, sin) of frequencies 0, 1 | 2, 3 of run 0, then of run 1
-    auto load_angles = [&](int i) {
-      const int g = min(r_lane + i * 32, i_max - 1) + q.row0;
-      const int trow = g >= q.rows ? g - q.rows + q.B : q.B > 1 ? g - (int)__umulhi((unsigned)g, q.magic) * q.B : 0;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int fr = 16 * ((col_of(j0 + wn * CW + j * 32) >> 5) & 3);
-        const f32x4* t = reinterpret_cast<const f32x4*>(q.rope) + (size_t)(fr / 2 + 2 * hh) * q.rope_rows + trow;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) ang[i & 1][j][u] = t[(size_t)(4 * (u >> 1) + (u & 1)) * q.rope_rows];
-      }
-    };
-    load_angles(0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      if (i + 1 < TM) load_angles(i + 1);
-      const int r = r_lane + i * 32, g = r + q.row0;
-      // row of the cache this row extends it by, or -1
-      const int dst = r >= i_max ? -1 : g < q.n_head ? q.dst_head + g : g >= q.rows && q.dst_tail >= 0 ? q.dst_tail + g - q.rows : -1;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n0 = j0 + wn * CW + j * 32;      // uniform; a 32-column block is part of one head of q, k or v
-        const int seg = seg_of(n0), c0 = col_of(n0);
-        const int hcol = c0 & ~127, fr = 16 * ((c0 >> 5) & 3);       // head's first column, first frequency
-        float x1[8], x2[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) { x1[v] = acc[i][j][v]; x2[v] = acc[i][j][v + 8]; }
-        const void* bias = seg == 0 ? a.bias[0] : (seg == 1 ? a.bias[1] : a.bias[2]);
-        if (bias) {
-          const bf16_t* bp = (const bf16_t*)bias + hcol + fr + 4 * hh;
-#pragma unroll
-          for (int v = 0; v < 8; v += 4) {
-            const bf16x4 b1 = *reinterpret_cast<const bf16x4*>(bp + 2 * v), b2 = *reinterpret_cast<const bf16x4*>(bp + 64 + 2 * v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { x1[v + e] += static_cast<float>(b1[e]); x2[v + e] += static_cast<float>(b2[e]); }
-          }
-        }
-        if (seg < 2) {
-          const float scale = seg == 0 ? q.q_scale : 1.f;
-#pragma unroll
-          for (int v = 0; v < 8; v += 4) {
-            const f32x4 ta = ang[i & 1][j][v >> 1], tb = ang[i & 1][j][(v >> 1) + 1];
-            const float c[4] = {ta[0], ta[2], tb[0], tb[2]}, s[4] = {ta[1], ta[3], tb[1], tb[3]};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              // rotated as the rounded values that a reader of the unrotated columns would rotate
-              const float u1 = static_cast<float>(static_cast<bf16_t>(x1[v + e])), u2 = static_cast<float>(static_cast<bf16_t>(x2[v + e]));
-              x1[v + e] = (u1 * c[e] - u2 * s[e]) * scale;
-              x2[v + e] = (u2 * c[e] + u1 * s[e]) * scale;
-            }
-          }
-        }
-        const u32x4 o1 = pack16(x1), o2 = pack16(x2);
-        if (r < i_max) {
-          bf16_t* p = C + (size_t)r * a.ldc + (n0 - c0) + hcol + fr + 8 * hh;
-          *reinterpret_cast<u32x4*>(p) = o1;
-          *reinterpret_cast<u32x4*>(p + 64) = o2;
-        }
-        if (seg > 0 && dst >= 0) {
-          bf16_t* p = reinterpret_cast<bf16_t*>(seg == 1 ? q.ck : q.cv) + ((size_t)(hcol >> 7) * q.ldp + dst) * 128 + fr + 8 * hh;
-          *reinterpret_cast<u32x4*>(p) = o1;
-          *reinterpret_cast<u32x4*>(p + 64) = o2;
-        }
-      }
-    }
-    return;
-  }
-
-  const bf16_t* R = reinterpret_cast<const bf16_t*>(a.R);
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int r = r_lane + i * 32;
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v0 = 0; v0 < 16; v0 += 8) {       // sixteen columns
-        const int n = j0 + wn * CW + j * 32 + 2 * v0;
-        float x[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) x[v] = acc[i][j][v0 + v];
-        if (EPI == EPI_STORE) {
-          const int s0 = n < a.Nseg[0] ? 0 : (n < a.Nseg[0] + a.Nseg[1] ? a.Nseg[0] : a.Nseg[0] + a.Nseg[1]);
-          const void* bias = n < a.Nseg[0] ? a.bias[0] : (n < a.Nseg[0] + a.Nseg[1] ? a.bias[1] : a.bias[2]);
-          if (bias) {
-            const bf16_t* bp = (const bf16_t*)bias + (n - s0) + 4 * hh;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) x[v] += static_cast<float>(bp[2 * (v & 4) + (v & 3)]);
-          }
-        }
-        if (EPI == EPI_RESID && r < i_max) {
-          const bf16_t* rp = R + (size_t)r * a.ldc + n + 4 * hh;
-#pragma unroll
-          for (int v = 0; v < 8; v += 4) {
-            const bf16x4 rr = *reinterpret_cast<const bf16x4*>(rp + 2 * v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[v + e] += static_cast<float>(rr[e]);
-          }
-        }
-        const u32x4 o = pack16(x);
-        if (r < i_max) *reinterpret_cast<u32x4*>(C + (size_t)r * a.ldc + n + 8 * hh) = o;
-      }
-  }
-}
-
-template <int EPI, int BN, int SD, int BMT, int SA>
-constexpr size_t smem_bytes() {
-  constexpr int SH = shallow_stages(EPI, BN, BMT, SD, SA);
-  return sizeof(bf16_t) * (size_t)(EPI == EPI_LMHEAD ? SD * BMT + SH * BN : SH * BMT + SD * BN) * BKK;
-}
-
-template <int EPI, int BN, int SD, int BMT = 256, int SA = 0>
-hipError_t launch_t(const GemmArgs& a, int tiles_i, int tiles_j, hipStream_t st) {
-  static_assert(smem_bytes<EPI, BN, SD, BMT, SA>() <= 160 * 1024, "a workgroup has 160 KB of LDS");
-  static std::atomic<unsigned long long> lds_ok{0};
-  const hipError_t e = allow_dynamic_lds((const void*)gemm_bf16_mfma_kernel<EPI, BN, SD, BMT, SA>,
-                                         (int)smem_bytes<EPI, BN, SD, BMT, SA>(), lds_ok);
-  if (e != hipSuccess) return e;
-  gemm_bf16_mfma_kernel<EPI, BN, SD, BMT, SA><<<tiles_i * tiles_j * a.ksplit, 64 * waves_m(BMT, BN) * waves_n(BN), smem_bytes<EPI, BN, SD, BMT, SA>(), st>>>(a, tiles_i, tiles_j);
-  return hipGetLastError();
-}
 
 // out[m,:] = R[m,:] + sum_z P[z][m,:]  (fixed order), optionally followed by RMSNorm of that row.
 // One workgroup per row, of 256 or 1024 threads: with few rows the launch is latency-bound and 1024 threads have every
@@ -667,7 +114,6 @@ int mfma_lmhead_partials_per_row(int V) { return cdiv(V, BM) * 2; }
 // narrow tiles) and the time to bring its operands in (about 40 bytes per clock per CU).  With few rows
 // (one or a few states) the projections are weight-streaming problems: 64- and 128-row tiles spend a quarter
 // or half of the matrix work of a 256-row tile on them and cover more CUs.
-struct TileShape { int bm, bn; };
 static const int kTileWidths[5] = {192, 128, 96, 64, 32};
 // estimated time of one K-tile of one workgroup of shape bm x kTileWidths[wi]
 static float tile_cost(int bm, int wi) {
@@ -701,36 +147,6 @@ static TileShape choose_tile(int M, int n_cols, int unit, int ksplit, bool allow
     }
   if (cost_out) *cost_out = best_cost;
   return best;
-}
-
-template <int EPI>
-static hipError_t launch_shape(const GemmArgs& a, TileShape t, int unit, hipStream_t st) {
-  const int mt = cdiv(a.M, t.bm), nt = a.N / (t.bn / unit);
-  constexpr bool W192 = EPI != EPI_PARTIAL;       // the split-K projections never take the 192-wide tile
-  if (t.bm == 256) {
-    if constexpr (W192) if (t.bn == 192) return launch_t<EPI, 192, 3>(a, mt, nt, st);
-    // 256 x 128: room for a third activation stage beside four weight stages (160 KB); in interleaved A/B runs 2-5%
-    // faster than two stages on every projection that takes this tile (down projection 95.9 -> 91.4 us at 1024 rows)
-    if (t.bn == 128) return launch_t<EPI, 128, 4, 256, 3>(a, mt, nt, st);
-    return launch_t<EPI, 64, 4>(a, mt, nt, st);
-  }
-  // few rows: the weight ring is as deep as the LDS allows (bytes in flight are what sets the streaming rate)
-  if constexpr (EPI == EPI_SWIGLU) {
-    if (t.bn == 96) return t.bm == 128 ? launch_t<EPI, 96, 5, 128>(a, mt, nt, st) : launch_t<EPI, 96, 7, 64>(a, mt, nt, st);
-  }
-  if constexpr (EPI == EPI_STORE || EPI == EPI_QKV) {
-    if (t.bn == 96) return t.bm == 128 ? launch_t<EPI, 96, 4, 128>(a, mt, nt, st) : launch_t<EPI, 96, 6, 64>(a, mt, nt, st);
-  }
-  if (t.bm == 128) {
-    if constexpr (W192) if (t.bn == 192) return launch_t<EPI, 192, 4, 128>(a, mt, nt, st);
-    return launch_t<EPI, 128, 4, 128>(a, mt, nt, st);
-  }
-  if constexpr (EPI == EPI_PARTIAL) {
-    if (t.bm == 32) return launch_t<EPI, 32, 9, 32>(a, mt, nt, st);
-    if (t.bn == 32) return launch_t<EPI, 32, 10, 64>(a, mt, nt, st);
-  }
-  if (t.bn == 64) return launch_t<EPI, 64, 8, 64>(a, mt, nt, st);
-  return launch_t<EPI, 128, 6, 64>(a, mt, nt, st);
 }
 
 // The launches of one projection: one, or two column ranges (the two-part schedule of the gate/up projection).
@@ -801,21 +217,114 @@ GemmPlan plan_gemm_mfma(int epi, int M, int N, int ksplit) {
   return p;
 }
 
+// Tile shapes of a layer's projections.  Every shape's time is taken as
+//   3.5 us + 1 us per further round + K-tiles x (c0 r + c1 w + c2 w / mt + c3 r fill)
+// r = rounds over the 256 compute units, w = rounds in workgroups (the last one not rounded up), mt = row tiles (workgroups
+// that share a weight tile), fill = rows per tile row.  The coefficients (us per K-tile of 64) are a non-negative least
+// squares fit to 5,500 measured launches: rows 16 .. 1088, the projections of three models (K slices of 11 .. 99 tiles,
+// 2048 .. 37888 columns), 7 - 11% rms of a launch for the small shapes, 2 - 5% for the large ones.  Picking by them
+// costs 1.7% over the best shape of each launch, the rule of plan_gemm_mfma 5.4%; its shape stays where the fit
+// does not promise 3%.  Measured, us, its shape -> this one: gate/up at 352 rows 78 -> 68 (256 x 192 -> 192 x 192), 768 rows
+// 142 -> 128; down at 192 rows 49.8 -> 40.9 (64 x 128 -> 128 x 64); QKV of 4608 columns at 320 rows 27.9 -> 22.4.
+struct ShapeCost { int bm, bn; float c[4]; };
+static const ShapeCost kShapeCost[] = {
+    {256, 256, {0.943f, 0.329f, 0.143f, 0.076f}}, {256, 192, {0.743f, 0.232f, 0.118f, 0.083f}},
+    {256, 128, {0.497f, 0.057f, 0.198f, 0.179f}}, {256, 64, {0.478f, 0.110f, 0.062f, 0.076f}},
+    {384, 128, {0.816f, 0.198f, 0.071f, 0.069f}}, {320, 192, {0.868f, 0.379f, 0.064f, 0.081f}},
+    {320, 128, {0.706f, 0.151f, 0.132f, 0.059f}}, {192, 192, {0.520f, 0.154f, 0.225f, 0.164f}},
+    {192, 128, {0.296f, 0.000f, 0.343f, 0.279f}}, {128, 192, {0.475f, 0.000f, 0.350f, 0.164f}},
+    {128, 128, {0.206f, 0.000f, 0.382f, 0.245f}}, {128, 96, {0.477f, 0.091f, 0.026f, 0.013f}},
+    {128, 64, {0.189f, 0.000f, 0.134f, 0.168f}},  {64, 128, {0.260f, 0.000f, 0.295f, 0.109f}},
+    {64, 96, {0.290f, 0.024f, 0.156f, 0.047f}},   {64, 64, {0.128f, 0.000f, 0.139f, 0.125f}},
+    {64, 32, {0.204f, 0.017f, 0.020f, 0.024f}},   {32, 32, {0.054f, 0.016f, 0.097f, 0.046f}}};
+
+static float shape_cost(const ShapeCost& s, int M, int n_cols, int unit, int k_tiles, int ksplit) {
+  const int mt = cdiv(M, s.bm), tiles = mt * (n_cols / (s.bn / unit)) * ksplit, r = cdiv(tiles, 256);
+  const float w = (float)tiles / 256.f, fill = (float)M / (float)(mt * s.bm), kt = (float)k_tiles / (float)ksplit;
+  return 3.5f + (float)(r - 1) + kt * (s.c[0] * (float)r + s.c[1] * w + s.c[2] * w / (float)mt + s.c[3] * (float)r * fill);
+}
+static bool layer_shape(int epi, int bm, int bn, int ksplit) {      // the shapes launch_shape has for an epilogue
+  if (bn == 32) return epi == EPI_PARTIAL;
+  if (epi == EPI_PARTIAL)      // (192 rows with four slices: 16 columns x 4 x 4 workgroups; 26.7 us, 256 x 128 24.8)
+    return bn != 192 && bn != 96 && bn != 256 && bm != 384 && !(bm == 192 && ksplit == 4);
+  return epi == EPI_SWIGLU || (bm != 384 && !(bm == 320 && bn == 192));
+}
+
+GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_us) {
+  GemmPlan p = plan_gemm_mfma(epi, M, N, ksplit);
+  if (ksplit < 1) ksplit = 1;
+  const int unit = epi == EPI_SWIGLU ? 2 : 1, kt = K / BKK;
+  auto cost_of = [&](int bm, int bn, int n) {
+    for (const ShapeCost& s : kShapeCost)
+      if (s.bm == bm && s.bn == bn) return shape_cost(s, M, n, unit, kt, ksplit);
+    return 1e30f;
+  };
+  auto best_shape = [&](int n, TileShape& t) {
+    float best = 1e30f;
+    for (const ShapeCost& s : kShapeCost) {
+      if (n % (s.bn / unit) != 0 || !layer_shape(epi, s.bm, s.bn, ksplit)) continue;
+      const float c = shape_cost(s, M, n, unit, kt, ksplit);
+      if (c < best) { best = c; t = {s.bm, s.bn}; }
+    }
+    return best;
+  };
+  float now = 0.f;
+  for (int i = 0; i < p.n_parts; ++i) now += cost_of(p.part[i].bm, p.part[i].bn, p.part[i].ncols);
+  if (cost_us) *cost_us = now;
+  if (epi != EPI_QKV && epi != EPI_PARTIAL && epi != EPI_SWIGLU) return p;
+  float best = 0.97f * now;
+  TileShape t = {0, 0};
+  const float whole = best_shape(N, t);
+  if (whole < best) {
+    best = whole;
+    p.n_parts = 1;
+    p.part[0] = {t.bm, t.bn, 0, N, cdiv(M, t.bm) * (N / (t.bn / unit)) * ksplit};
+  }
+  // gate/up in two column ranges: whole rounds of one shape, then the rest (plan_gemm_mfma says why)
+  if (epi == EPI_SWIGLU) {
+    best = best < 0.97f * whole ? best : 0.97f * whole;
+    for (const ShapeCost& s : kShapeCost) {
+      if (!layer_shape(epi, s.bm, s.bn, ksplit)) continue;
+      const int per = s.bn / 2, mt = cdiv(M, s.bm);
+      for (int r = 1; r <= (int)((long long)mt * (N / per) / 256); ++r) {
+        const int main_tiles = 256 * r / mt, rest = N - per * main_tiles;
+        if (rest <= 0 || rest % 32 != 0) continue;
+        const float c_main = shape_cost(s, M, per * main_tiles, 2, kt, 1);
+        if (c_main >= best) break;
+        TileShape tr = {0, 0};
+        const float c = c_main + best_shape(rest, tr);
+        if (tr.bn == 0 || c >= best) continue;
+        best = c;
+        p.n_parts = 2;
+        p.part[0] = {s.bm, s.bn, 0, per * main_tiles, mt * main_tiles};
+        p.part[1] = {tr.bm, tr.bn, per * main_tiles, rest, cdiv(M, tr.bm) * (rest / (tr.bn / 2))};
+      }
+    }
+  }
+  if (cost_us) {
+    *cost_us = 0.f;
+    for (int i = 0; i < p.n_parts; ++i) *cost_us += cost_of(p.part[i].bm, p.part[i].bn, p.part[i].ncols);
+  }
+  return p;
+}
+
 hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
   GemmArgs a = a0;
   if (a.ksplit < 1) a.ksplit = 1;
-  const GemmPlan p = plan_gemm_mfma(epi, a.M, a.N, a.ksplit);
+  const bool layer = a.layer && (epi == EPI_QKV || epi == EPI_PARTIAL || epi == EPI_SWIGLU);
+  const GemmPlan p = layer ? plan_gemm_layer(epi, a.M, a.N, a.K, a.ksplit) : plan_gemm_mfma(epi, a.M, a.N, a.ksplit);
   if (p.n_parts < 1) return hipErrorInvalidValue;
+  const TileShape t = {p.part[0].bm, p.part[0].bn};
   switch (epi) {
     case EPI_STORE:
-      return launch_shape<EPI_STORE>(a, TileShape{p.part[0].bm, p.part[0].bn}, 1, st);
+      return launch_gemm_store(a, t, st);
     case EPI_QKV:
-      return launch_shape<EPI_QKV>(a, TileShape{p.part[0].bm, p.part[0].bn}, 1, st);
+      return launch_gemm_qkv(a, t, st);
     case EPI_RESID:
-      if (p.part[0].bn == 64) return launch_t<EPI_RESID, 64, 4>(a, cdiv(a.M, BM), a.N / 64, st);
+      if (t.bn == 64) return launch_t<EPI_RESID, 64, 4>(a, cdiv(a.M, BM), a.N / 64, st);
       return launch_t<EPI_RESID, 128, 4>(a, cdiv(a.M, BM), a.N / 128, st);
     case EPI_PARTIAL:
-      return launch_shape<EPI_PARTIAL>(a, TileShape{p.part[0].bm, p.part[0].bn}, 1, st);
+      return launch_gemm_partial(a, t, st);
     case EPI_SWIGLU: {
       const size_t ldw = a.ldw ? a.ldw : a.K;
       for (int i = 0; i < p.n_parts; ++i) {
@@ -824,7 +333,7 @@ hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
         g.W[0] = (const bf16_t*)a.W[0] + (size_t)p.part[i].col0 * ldw;
         g.W[1] = (const bf16_t*)a.W[1] + (size_t)p.part[i].col0 * ldw;
         g.C = (bf16_t*)a.C + p.part[i].col0;
-        const hipError_t e = launch_shape<EPI_SWIGLU>(g, TileShape{p.part[i].bm, p.part[i].bn}, 2, st);
+        const hipError_t e = launch_gemm_swiglu(g, TileShape{p.part[i].bm, p.part[i].bn}, st);
         if (e != hipSuccess) return e;
       }
       return hipSuccess;

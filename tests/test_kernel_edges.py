@@ -76,3 +76,32 @@ def test_projection_extends_the_cache(sp, B, S, P):
     for a, b in ((ka, k0), (va, v0)):
         assert torch.equal(a[:, :P].cpu(), b[:, :P]) and torch.equal(a[:, P + B + S:].cpu(), b[:, P + B + S:])
         assert not torch.equal(a[:, P:P + B + S].cpu(), b[:, P:P + B + S])
+
+
+@pytest.mark.parametrize("name,d,hq,hkv,F,states", [("c3", 4096, 32, 32, 12288, (6, 9, 11, 19, 24)),
+                                                    ("c4", 3584, 28, 4, 18944, (7, 8, 11, 14, 24)),
+                                                    ("c4", 2048, 16, 8, 5632, (4, 11, 19, 24, 32))])
+def test_layer_rows_are_bit_identical_across_all_tile_heights(sp, name, d, hq, hkv, F, states):
+    """The row counts (192 .. 1024) run the projections in tiles of 192 x 128, 128 x 64, 320 x 128, 192 x 192, 256 x 256, 320 x 192
+    and 384 x 128 beside the others, gate/up in one and in two column ranges; every state equals what it gives alone, where
+    the layer runs in tiles of 32 and 64 rows.  Two row counts are not multiples of 32."""
+    cfg = synth.CONFIGS[name].scaled(L=1, V=1280, P=64, d=d, Hq=hq, Hkv=hkv, F=F, G=max(states))
+    g = torch.Generator(device=DEV).manual_seed(3)
+    rn = lambda *s: (torch.randn(s, generator=g, device=DEV) * 0.02).to(torch.bfloat16)
+    w = dict(wq=rn(hq * 128, d), wk=rn(hkv * 128, d), wv=rn(hkv * 128, d), wo=rn(d, hq * 128), w_gate=rn(F, d), w_up=rn(F, d),
+             w_down=rn(d, F), norm1=1 + rn(d), norm2=1 + rn(d))
+    pk, pv = rn(hkv, 64, 128) * 50, rn(hkv, 64, 128) * 50
+    scfg, lw, pf = sp.cfg_from_synth(cfg), sp.layer_weights(w), sp.prefix_kv(pk, pv)
+
+    def run(x):
+        ws = sp.alloc_workspace(scfg, x.shape[0], x.shape[1], 64, DEV)
+        return sp.verify_layer(scfg, lw, pf, x, 64, ws).clone()
+
+    x = rn(max(states), 32, d) * 50
+    alone = torch.cat([run(x[i:i + 1].contiguous()) for i in range(max(states))])
+    for n in states:
+        assert torch.equal(run(x[:n].contiguous()), alone[:n]), n
+    x = rn(17, 21, d) * 50                               # 357 rows; 16 states are 336 (a state's place decides how its keys
+    full = run(x)                                        # fall into groups of 32, so states keep their places here)
+    for n in (1, 3, 16):
+        assert torch.equal(run(x[:n].contiguous()), full[:n]), n
