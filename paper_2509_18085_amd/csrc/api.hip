@@ -100,14 +100,14 @@ LayerWs carve_layer(const spiffy_model_cfg* c, int G, int B, int P, void* base, 
   w.attn = cv.take(M * (size_t)c->n_q_heads * c->head_dim * es);
   w.h = cv.take(M * c->d * es);
   w.act = cv.take(M * c->ffn * es);
-  w.rope = cv.take(tile_attn_scratch_bytes(B + S_seq, c->head_dim));     // of that size on either path
+  w.rope = cv.take(sizeof(float2) * (size_t)(B + S_seq) * (c->head_dim / 2));
+  w.rows = (int32_t*)cv.take(sizeof(int32_t) * M);       // in front of everything whose size depends on P: the step's first
+  w.count = (int32_t*)cv.take(sizeof(int32_t) * 4);      // kernel fills the table and the list for all layers
   w.attn_partial = cv.take(layer_mfma(c) ? mfma_attn_partial_bytes(G, B, c->n_q_heads, c->head_dim, P + S_seq) : 0);
   w.attn_partial_seq = cv.take(layer_mfma(c) && S_seq ? mfma_attn_partial_bytes(1, S_seq, c->n_q_heads, c->head_dim, P + B + S_seq) : 0);
   w.splitk = cv.take(layer_mfma(c) ? sizeof(float) * 4 * M * c->d : 0);   // up to 4 K slices of [M,d] fp32
   w.gat_attn = cv.take(M * (size_t)c->n_q_heads * c->head_dim * es);
   w.gat_x = cv.take(M * c->d * es);
-  w.rows = (int32_t*)cv.take(sizeof(int32_t) * M);
-  w.count = (int32_t*)cv.take(sizeof(int32_t) * 4);
   w.bytes = cv.off;
   return w;
 }
@@ -221,7 +221,31 @@ struct LayerChain {
   bool masked_rows_only = false;
   const int32_t* tokens = nullptr;    // [G,B] block tokens and optional explicit mask, for the row list
   const uint8_t* mask = nullptr;
+  bool rows_ready = false;            // the row list is already in the layer scratch
+  // The head follows on these rows: their final RMSNorm, row list and count go to its scratch when the last kernel of the
+  // layer can do that (head_ready is set then).
+  const void* final_norm = nullptr;
+  void* head_nf = nullptr;
+  HeadRows head = {nullptr, nullptr};
+  bool head_ready = false;
 };
+
+// the arguments of the QKV projection that decide which path it and the attention take
+GemmArgs qkv_args(const spiffy_model_cfg* cfg, int M) {
+  GemmArgs g;
+  std::memset(&g, 0, sizeof(g));
+  const int qd = cfg->n_q_heads * cfg->head_dim, kvd = cfg->n_kv_heads * cfg->head_dim;
+  g.lda = cfg->d; g.M = M; g.K = cfg->d;
+  g.Nseg[0] = qd; g.Nseg[1] = kvd; g.Nseg[2] = kvd;
+  g.N = qd + 2 * kvd; g.ldc = g.N; g.scale = 1.f;
+  return g;
+}
+bool attn_on_mfma(const spiffy_model_cfg* cfg, int M) { return layer_mfma(cfg) && mfma_gemm_supported(EPI_QKV, qkv_args(cfg, M)); }
+
+// rotary table of a layer's block rows (positions pos0 ..) and of the rows behind them
+RopeArgs rope_args(const spiffy_model_cfg* cfg, void* tab, int M, int B, int S_seq, int pos0, int tail_pos0) {
+  return RopeArgs{(float2*)tab, B + S_seq, B, cfg->head_dim / 2, pos0, tail_pos0, attn_on_mfma(cfg, M) ? 1 : 0, cfg->rope_base};
+}
 
 // The same product as two launches over the row ranges [0, rows_a) and [rows_a, rows_a + rows_b): each range gets the
 // tile shape that suits its height (a ragged total would otherwise pay a whole extra round of the tall tiles).
@@ -276,13 +300,11 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
       (rc = dev(launch_rmsnorm(dt, hidden_in, w->norm1, cfg->rms_eps, M, d, nullptr, nullptr, ws.n, st))))
     return rc;
 
-  GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.A = ws.n; g.lda = d; g.M = M; g.K = d;
+  GemmArgs g = qkv_args(cfg, M);
+  g.A = ws.n;
   g.W[0] = w->wq; g.W[1] = w->wk; g.W[2] = w->wv;
   g.bias[0] = w->bq; g.bias[1] = w->bk; g.bias[2] = w->bv;
-  g.Nseg[0] = qd; g.Nseg[1] = kvd; g.Nseg[2] = kvd;
-  g.N = qd + 2 * kvd; g.C = ws.qkv; g.ldc = g.N; g.scale = 1.f;
+  g.C = ws.qkv;
   AttnArgs a;
   a.qkv = ws.qkv; a.prefix_k = prefix->k; a.prefix_v = prefix->v; a.out = ws.attn;
   a.G = G; a.B = B; a.Hq = cfg->n_q_heads; a.Hkv = cfg->n_kv_heads; a.hd = cfg->head_dim; a.P = prefix->P;
@@ -293,15 +315,17 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
     a.S = prefix->S > B ? prefix->S - B : 0;
   }
   a.own = 1;
-  a.pos0 = pos0; a.rope_base = cfg->rope_base; a.rope_ready = chain && chain->rope_ready;
+  a.pos0 = pos0; a.rope_base = cfg->rope_base;
   const int ldp = prefix->capacity ? prefix->capacity : prefix->P;
   const int tail_pos0 = prev ? pos0 - B : pos0 + B;
-  void* const rope_seq = reinterpret_cast<char*>(ws.rope) + tile_attn_scratch_bytes(B, cfg->head_dim);
+  void* const rope_seq = reinterpret_cast<float2*>(ws.rope) + (size_t)B * (cfg->head_dim / 2);
   const bool append = chain && chain->append_kv;
-  const bool mfa = mf && mfma_gemm_supported(EPI_QKV, g) && mfma_attn_supported(a);
+  const bool mfa = attn_on_mfma(cfg, M);
+  if (!(chain && chain->rope_ready) &&
+      (rc = dev(launch_rope_table(rope_args(cfg, ws.rope, M, B, S_seq, pos0, tail_pos0), st))))
+    return rc;
   if (mfa) {
     // queries and keys are rotated, and the rows that extend the cache are stored there, by the projection's epilogue
-    if (!a.rope_ready && (rc = dev(launch_rope_table(ws.rope, B, S_seq, pos0, tail_pos0, cfg->rope_base, st)))) return rc;
     QkvArgs& q = g.qkv;
     q.rope = ws.rope; q.rope_rows = B + S_seq;
     q.ck = const_cast<void*>(prefix->k); q.cv = const_cast<void*>(prefix->v); q.ldp = ldp;
@@ -355,28 +379,37 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   const int32_t* n_rows = cm ? ws.count : nullptr;
   const void* attn_rows = ws.attn;
   const void* resid = hidden_in;
+  std::memset(&g, 0, sizeof(g));
+  g.lda = qd; g.M = M; g.M_dev = n_rows; g.K = qd; g.W[0] = w->wo; g.Nseg[0] = d; g.N = d;
+  g.C = ws.h; g.ldc = d; g.scale = 1.f;
+  const bool o_mfma = mf && mfma_gemm_supported(EPI_RESID, g);
+  const int o_slices = o_mfma ? mfma_ksplit(d, qd) : 1;
+  const int32_t* src_rows = nullptr;       // the output projection and its reduction read the rows where they are ..
   if (cm) {
     const size_t es = esize(dt);
-    if ((rc = dev(launch_compact_rows(chain->tokens, chain->mask, cfg->mask_id, M, ws.rows, ws.count, st)))) return rc;
-    if ((rc = dev(launch_gather_rows2(ws.attn, (size_t)qd * es, hidden_in, (size_t)d * es, ws.rows, ws.count, M, ws.gat_attn,
-                                      ws.gat_x, st))))
+    if (!chain->rows_ready &&
+        (rc = dev(launch_compact_rows(chain->tokens, chain->mask, cfg->mask_id, M, ws.rows, ws.count, st))))
       return rc;
-    attn_rows = ws.gat_attn;
-    resid = ws.gat_x;
+    if (o_slices > 1) {
+      src_rows = ws.rows;
+    } else {                               // .. or they are gathered first
+      if ((rc = dev(launch_gather_rows2(ws.attn, (size_t)qd * es, hidden_in, (size_t)d * es, ws.rows, ws.count, M, ws.gat_attn,
+                                        ws.gat_x, st))))
+        return rc;
+      attn_rows = ws.gat_attn;
+      resid = ws.gat_x;
+    }
   }
 
   // output projection + residual (+ RMSNorm-2 fused into the split-K reduction when K is sliced)
-  std::memset(&g, 0, sizeof(g));
-  g.A = attn_rows; g.lda = qd; g.M = M; g.M_dev = n_rows; g.K = qd; g.W[0] = w->wo; g.Nseg[0] = d; g.N = d;
-  g.C = ws.h; g.ldc = d; g.R = resid; g.scale = 1.f;
+  g.A = attn_rows; g.R = resid;
   bool normed = false;
-  if (mf && mfma_gemm_supported(EPI_RESID, g)) {
-    const int ks = mfma_ksplit(d, qd);
-    if (ks > 1) {
-      g.C = ws.splitk; g.ksplit = ks;
+  if (o_mfma) {
+    if (o_slices > 1) {
+      g.C = ws.splitk; g.ksplit = o_slices; g.a_rows = src_rows;
       if ((rc = dev(mfma_rows(EPI_PARTIAL, g)))) return rc;
-      if ((rc = dev(launch_splitk_reduce((const float*)ws.splitk, ks, resid, ws.h, w->norm2, cfg->rms_eps, ws.n, M,
-                                         d, st, n_rows))))
+      if ((rc = dev(launch_splitk_reduce((const float*)ws.splitk, o_slices, resid, ws.h, w->norm2, cfg->rms_eps, ws.n, M,
+                                         d, st, n_rows, nullptr, src_rows))))
         return rc;
       normed = true;
     } else if ((rc = dev(mfma_rows(EPI_RESID, g)))) return rc;
@@ -402,6 +435,11 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
     if (ks > 1) {
       g.C = ws.splitk; g.ksplit = ks;
       if ((rc = dev(mfma_rows(EPI_PARTIAL, g)))) return rc;
+      if (cm && chain->head_nf) {
+        chain->head_ready = true;
+        return dev(launch_splitk_reduce((const float*)ws.splitk, ks, ws.h, hidden_out, chain->final_norm, cfg->rms_eps,
+                                        chain->head_nf, M, d, st, n_rows, ws.rows, nullptr, &chain->head));
+      }
       const void* ng = chain ? chain->next_norm1 : nullptr;
       if (chain && ng) chain->normed_out = true;
       return dev(launch_splitk_reduce((const float*)ws.splitk, ks, ws.h, hidden_out, ng, cfg->rms_eps,
@@ -413,14 +451,35 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   return SPIFFY_OK;
 }
 
+// First kernel of a step: hidden rows of the block tokens (and of the n_tail rows behind them), the first layer's normalised
+// input at the start of the layer scratch, the rotary table of all layers and, when the last layer is to compute the masked
+// rows only, their list.  The table and the list lie in front of everything whose place depends on a layer's cached rows.
+int begin_step(const spiffy_model_cfg* cfg, int n_layers, const spiffy_layer_weights* layers, const void* w_embed,
+               const int32_t* tokens, int G, int B, const int32_t* tail_tokens, int n_tail, int pos0, int tail_pos0, void* hid,
+               bool list, void* scratch, LayerChain& chain, hipStream_t st) {
+  const LayerWs ws = carve_layer(cfg, G, B, 0, scratch, n_tail);
+  EmbedArgs e = {};
+  e.w = w_embed; e.tok = tokens; e.tok2 = tail_tokens; e.M = G * B; e.M2 = n_tail; e.d = cfg->d; e.V = cfg->vocab;
+  e.out = hid; e.n_out = ws.n; e.eps = cfg->rms_eps; e.mask_id = cfg->mask_id;
+  if (n_layers > 0) {
+    e.gain = layers[0].norm1;
+    e.rope = rope_args(cfg, ws.rope, G * B + n_tail, B, n_tail, pos0, tail_pos0);
+    if (list) { e.rows = ws.rows; e.count = ws.count; }
+  }
+  chain.normed_out = chain.rope_ready = true;
+  chain.rows_ready = list;
+  return dev(launch_embed(cfg->dtype, e, st));
+}
+
 int run_head(const spiffy_model_cfg* cfg, const void* hidden, const void* final_norm, const void* w_vocab,
              const int32_t* tokens, const uint8_t* mask, int G, int B, float threshold, float logit_scale,
              int force_one, int32_t* argmax, float* conf, uint8_t* unmask, float* margin, int32_t* target,
-             void* workspace, hipStream_t st) {
+             void* workspace, hipStream_t st, bool rows_ready = false) {
   const int M = G * B, dt = cfg->dtype;
   const HeadWs ws = carve_head(cfg, G, B, workspace);
   int rc;
-  if ((rc = dev(launch_masked_rmsnorm(dt, hidden, final_norm, cfg->rms_eps, M, cfg->d, tokens, mask, cfg->mask_id,
+  if (!rows_ready &&
+      (rc = dev(launch_masked_rmsnorm(dt, hidden, final_norm, cfg->rms_eps, M, cfg->d, tokens, mask, cfg->mask_id,
                                       ws.row_idx, ws.count, ws.nf, st))))
     return rc;
   int n_part = ws.n_part;
@@ -514,8 +573,9 @@ int spiffy_embed(const spiffy_model_cfg* cfg, const void* w_embed, const int32_t
   if ((rc = check_cfg(cfg)) || (rc = check_gb(G, B))) return rc;
   if (!w_embed || !block_tokens || !hidden_out) return SPIFFY_EINVAL;
   if (!aligned16(w_embed) || !aligned16(hidden_out)) return SPIFFY_EALIGN;
-  return dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hidden_out,
-                          nullptr, 0.f, nullptr, (hipStream_t)stream));
+  EmbedArgs e = {};
+  e.w = w_embed; e.tok = block_tokens; e.M = G * B; e.d = cfg->d; e.V = cfg->vocab; e.out = hidden_out;
+  return dev(launch_embed(cfg->dtype, e, (hipStream_t)stream));
 }
 
 int spiffy_verify_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const spiffy_prefix_kv* prefix,
@@ -727,13 +787,16 @@ int spiffy_verify_step(const spiffy_model_cfg* cfg, int32_t n_layers, const spif
   hipStream_t st = (hipStream_t)stream;
   void* hid = hidden_out ? hidden_out : ws.hidden;
   int32_t* tgt = target_states ? target_states : ws.target;
-  // the layer scratch starts with the first layer's normalised input
-  const void* norm1 = n_layers > 0 ? layers[0].norm1 : nullptr;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, norm1, cfg->rms_eps, ws.rest, st))))
-    return rc;
   LayerChain chain;
-  chain.normed_out = true;
   chain.tokens = block_tokens;
+  if ((rc = begin_step(cfg, n_layers, layers, w_embed, block_tokens, G, B, nullptr, 0, pos0, 0, hid, !hidden_out, ws.rest, chain, st)))
+    return rc;
+  if (!hidden_out) {
+    const HeadWs hw = carve_head(cfg, G, B, ws.rest);
+    chain.final_norm = final_norm;
+    chain.head_nf = hw.nf;
+    chain.head = HeadRows{hw.row_idx, hw.count};
+  }
   for (int l = 0; l < n_layers; ++l) {
     chain.normed_in = chain.normed_out;
     chain.next_norm1 = (l + 1 < n_layers) ? layers[l + 1].norm1 : nullptr;
@@ -741,10 +804,9 @@ int spiffy_verify_step(const spiffy_model_cfg* cfg, int32_t n_layers, const spif
     // nothing else
     chain.masked_rows_only = !hidden_out && l + 1 == n_layers;
     if ((rc = run_layer(cfg, &layers[l], &prefix[l], hid, G, B, pos0, hid, ws.rest, st, &chain))) return rc;
-    chain.rope_ready = true;      // same pos0 / B / base for every layer: the table is computed once
   }
   if ((rc = run_head(cfg, hid, final_norm, w_vocab, block_tokens, nullptr, G, B, threshold, logit_scale, force_one,
-                     argmax, conf, unmask, top2_margin, tgt, ws.rest, st)))
+                     argmax, conf, unmask, top2_margin, tgt, ws.rest, st, chain.head_ready)))
     return rc;
   return dev(launch_graph_accept(graph_edges, E, block_tokens, tgt, G, B, root, result, accepted_state, st));
 }
@@ -791,24 +853,14 @@ int spiffy_verify_step_seq(const spiffy_model_cfg* cfg, int32_t n_layers, const 
   hipStream_t st = (hipStream_t)stream;
   void* hid = hidden_out ? hidden_out : ws.hidden;
   int32_t* tgt = target_states ? target_states : ws.target;
-  // the layer scratch starts with the first layer's normalised input
-  const void* norm1 = n_layers > 0 ? layers[0].norm1 : nullptr;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, norm1, cfg->rms_eps, ws.rest, st))))
-    return rc;
-  if (S > 0) {
-    void* hid_seq = reinterpret_cast<char*>(hid) + (size_t)G * B * cfg->d * esize(cfg->dtype);
-    void* n_seq = reinterpret_cast<char*>(ws.rest) + (size_t)G * B * cfg->d * esize(cfg->dtype);
-    if ((rc = dev(launch_embed(cfg->dtype, w_embed, suffix_tokens, S, cfg->d, cfg->vocab, hid_seq, norm1, cfg->rms_eps, n_seq, st))))
-      return rc;
-  }
   LayerChain chain;
-  chain.normed_out = true;
+  if ((rc = begin_step(cfg, n_layers, layers, w_embed, block_tokens, G, B, suffix_tokens, S, pos0, pos0 + B, hid, false, ws.rest, chain, st)))
+    return rc;
   chain.seq_S = S;
   for (int l = 0; l < n_layers; ++l) {
     chain.normed_in = chain.normed_out;
     chain.next_norm1 = (l + 1 < n_layers) ? layers[l + 1].norm1 : nullptr;
     if ((rc = run_layer(cfg, &layers[l], &prefix[l], hid, G, B, pos0, hid, ws.rest, st, &chain))) return rc;
-    chain.rope_ready = true;
   }
   if ((rc = run_head(cfg, hid, final_norm, w_vocab, block_tokens, nullptr, G, B, threshold, logit_scale, force_one,
                      argmax, conf, unmask, top2_margin, tgt, ws.rest, st)))
@@ -854,23 +906,15 @@ int spiffy_verify_step_commit(const spiffy_model_cfg* cfg, int32_t n_layers, con
   hipStream_t st = (hipStream_t)stream;
   void* hid = hidden_out ? hidden_out : ws.hidden;
   int32_t* tgt = target_states ? target_states : ws.target;
-  void* hid_prev = reinterpret_cast<char*>(hid) + (size_t)G * B * cfg->d * esize(cfg->dtype);
-  // the layer scratch starts with the first layer's normalised input
-  const void* norm1 = n_layers > 0 ? layers[0].norm1 : nullptr;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, G * B, cfg->d, cfg->vocab, hid, norm1, cfg->rms_eps, ws.rest, st))))
-    return rc;
-  void* n_prev = reinterpret_cast<char*>(ws.rest) + (size_t)G * B * cfg->d * esize(cfg->dtype);
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, prev_block_tokens, B, cfg->d, cfg->vocab, hid_prev, norm1, cfg->rms_eps, n_prev, st))))
-    return rc;
   LayerChain chain;
-  chain.normed_out = true;
+  if ((rc = begin_step(cfg, n_layers, layers, w_embed, block_tokens, G, B, prev_block_tokens, B, pos0, pos0 - B, hid, false, ws.rest, chain, st)))
+    return rc;
   chain.seq_S = B;
   chain.tail_is_prev_block = true;
   for (int l = 0; l < n_layers; ++l) {
     chain.normed_in = chain.normed_out;
     chain.next_norm1 = (l + 1 < n_layers) ? layers[l + 1].norm1 : nullptr;
     if ((rc = run_layer(cfg, &layers[l], &prefix[l], hid, G, B, pos0, hid, ws.rest, st, &chain))) return rc;
-    chain.rope_ready = true;
   }
   if ((rc = run_head(cfg, hid, final_norm, w_vocab, block_tokens, nullptr, G, B, threshold, logit_scale, force_one,
                      argmax, conf, unmask, top2_margin, tgt, ws.rest, st)))
@@ -898,17 +942,14 @@ int spiffy_commit_block(const spiffy_model_cfg* cfg, int32_t n_layers, const spi
   const StepWs ws = carve_step(cfg, 1, B, P_max, workspace);
   if (workspace_bytes < ws.bytes) return SPIFFY_EWORKSPACE;
   hipStream_t st = (hipStream_t)stream;
-  if ((rc = dev(launch_embed(cfg->dtype, w_embed, block_tokens, B, cfg->d, cfg->vocab, ws.hidden,
-                             n_layers > 0 ? layers[0].norm1 : nullptr, cfg->rms_eps, ws.rest, st))))
-    return rc;
   LayerChain chain;
-  chain.normed_out = true;
+  if ((rc = begin_step(cfg, n_layers, layers, w_embed, block_tokens, 1, B, nullptr, 0, pos0, 0, ws.hidden, false, ws.rest, chain, st)))
+    return rc;
   chain.append_kv = true;
   for (int l = 0; l < n_layers; ++l) {
     chain.normed_in = chain.normed_out;
     chain.next_norm1 = (l + 1 < n_layers) ? layers[l + 1].norm1 : nullptr;
     if ((rc = run_layer(cfg, &layers[l], &prefix[l], ws.hidden, 1, B, pos0, ws.hidden, ws.rest, st, &chain))) return rc;
-    chain.rope_ready = true;
   }
   return SPIFFY_OK;
 }

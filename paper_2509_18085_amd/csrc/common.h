@@ -100,6 +100,7 @@ struct GemmArgs {
   void* C;              // [M,N] (STORE/RESID/SWIGLU); LMHEAD: TopPartial [M, n_tiles_total]
   const void* R;        // residual [M,N] for EPI_RESID
   const int* M_dev;     // optional device row count (rows >= *M_dev are skipped), NULL = use M
+  const int32_t* a_rows; // PARTIAL: optional row list, row r of the product reads row a_rows[r] of A (r < *M_dev)
   int M, N, K;
   int lda, ldc;
   int ldw;              // row stride of the weight segments in elements (0 = K, i.e. dense rows)
@@ -109,6 +110,21 @@ struct GemmArgs {
   QkvArgs qkv;          // QKV only
   int Mz;               // PARTIAL: rows per K slice of C when only some of them are computed by this launch (0 = M)
 };
+
+// Rotary table: `rows` rows of `half` (cos, sin) pairs, rows 0 .. B-1 at positions pos0 .., rows B .. at tail_pos0 ...
+// paired: [half / 2][rows][2] (lanes of the QKV projection's epilogue are rows), otherwise [rows][half].
+struct RopeArgs {
+  float2* tab;
+  int rows, B, half, pos0, tail_pos0, paired;
+  float base;
+};
+// entry i: angle in double, cos and sin rounded to float
+__device__ __forceinline__ void rope_entry(const RopeArgs& a, int i) {
+  const int f = a.paired ? 2 * (i / (2 * a.rows)) + i % 2 : i % a.half, b = a.paired ? (i / 2) % a.rows : i / a.half;
+  const double inv_freq = pow((double)a.base, -(double)f / (double)a.half);
+  const double ang = (double)(b < a.B ? a.pos0 + b : a.tail_pos0 + b - a.B) * inv_freq;
+  a.tab[i] = make_float2((float)cos(ang), (float)sin(ang));
+}
 
 // Workgroup ids are handed to the 8 XCDs round-robin (id % 8).  Map id -> logical index so that every
 // XCD owns one contiguous range of logical indices (XCD x owns ids x, x+8, ...), for any total.

@@ -133,41 +133,10 @@ hipError_t launch_rmsnorm(int dtype, const void* x, const void* gain, float eps,
 }
 
 // ---------------------------------------------------------------------------------------------
-// embedding gather: out[m,:] = w[tok[m],:]; with a gain also n_out[m,:] = RMSNorm of that row, which the first layer
-// starts from (a launch of its own took 2.9 - 4.2 us; the row is still in L1 here)
+// masked-row compaction: row_idx[0..count) ascending, plus count (one workgroup)
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ w, const int32_t* __restrict__ tok,
-                                                    int d, int V, T* __restrict__ out, const T* __restrict__ gain,
-                                                    float eps, T* __restrict__ n_out) {
-  __shared__ float red[4];
-  const int m = blockIdx.x;
-  int t = tok[m];
-  t = t < 0 ? 0 : (t >= V ? V - 1 : t);
-  const uint4* src = reinterpret_cast<const uint4*>(w + (size_t)t * d);
-  uint4* dst = reinterpret_cast<uint4*>(out + (size_t)m * d);
-  const int n16 = d * (int)sizeof(T) / 16;
-  for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = src[i];
-  if (gain) rmsnorm_row<T>(w, gain, eps, d, t, m, n_out, red);
-}
-
-hipError_t launch_embed(int dtype, const void* w, const int32_t* tok, int M, int d, int V, void* out, const void* gain,
-                        float eps, void* n_out, hipStream_t st) {
-  if (dtype == SPIFFY_F32)
-    embed_kernel<float><<<M, 256, 0, st>>>((const float*)w, tok, d, V, (float*)out, (const float*)gain, eps, (float*)n_out);
-  else
-    embed_kernel<bf16_t><<<M, 256, 0, st>>>((const bf16_t*)w, tok, d, V, (bf16_t*)out, (const bf16_t*)gain, eps,
-                                            (bf16_t*)n_out);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------------
-// masked-row compaction: row_idx[0..count) ascending, plus count (single workgroup)
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void compact_rows_kernel(const int32_t* __restrict__ tok,
-                                                           const uint8_t* __restrict__ mask, int mask_id, int M,
-                                                           int32_t* __restrict__ row_idx, int32_t* __restrict__ count) {
-  __shared__ int cnt[256];
+__device__ __forceinline__ void compact_rows(const int32_t* __restrict__ tok, const uint8_t* __restrict__ mask, int mask_id,
+                                             int M, int32_t* __restrict__ row_idx, int32_t* __restrict__ count, int* cnt) {
   const int per = (M + 255) / 256;
   const int i0 = threadIdx.x * per, i1 = min(M, i0 + per);
   int c = 0;
@@ -189,9 +158,67 @@ __global__ __launch_bounds__(256) void compact_rows_kernel(const int32_t* __rest
   if (threadIdx.x == 255) *count = cnt[255];
 }
 
+__global__ __launch_bounds__(256) void compact_rows_kernel(const int32_t* __restrict__ tok,
+                                                           const uint8_t* __restrict__ mask, int mask_id, int M,
+                                                           int32_t* __restrict__ row_idx, int32_t* __restrict__ count) {
+  __shared__ int cnt[256];
+  compact_rows(tok, mask, mask_id, M, row_idx, count, cnt);
+}
+
 hipError_t launch_compact_rows(const int32_t* tok, const uint8_t* mask, int mask_id, int M, int32_t* row_idx,
                                int32_t* count, hipStream_t st) {
   compact_rows_kernel<<<1, 256, 0, st>>>(tok, mask, mask_id, M, row_idx, count);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void rope_table_kernel(RopeArgs a) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < a.rows * a.half) rope_entry(a, i);
+}
+
+hipError_t launch_rope_table(const RopeArgs& a, hipStream_t st) {
+  rope_table_kernel<<<cdiv(a.rows * a.half, 256), 256, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------
+// Start of a step.  Embedding gather: out[m,:] = w[tok[m],:], rows M .. M+M2-1 from tok2; with a gain also n_out[m,:] =
+// RMSNorm of that row, which the first layer starts from (a launch of its own took 2.9 - 4.2 us; the row is still in L1
+// here).  Beside the rows, in workgroups of their own, what later kernels of the step need and nothing before them
+// provides: the rotary table and the list of masked rows, which had launches of 4.7 us each.
+// ---------------------------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a, int rope_blocks, int list_blocks) {
+  __shared__ int cnt[256];
+  int m = blockIdx.x;
+  if (m < rope_blocks) {
+    const int i = m * 256 + threadIdx.x;
+    if (i < a.rope.rows * a.rope.half) rope_entry(a.rope, i);
+    return;
+  }
+  m -= rope_blocks;
+  if (m < list_blocks) {
+    compact_rows(a.tok, nullptr, a.mask_id, a.M, a.rows, a.count, cnt);
+    return;
+  }
+  m -= list_blocks;
+  int t = m < a.M ? a.tok[m] : a.tok2[m - a.M];
+  t = t < 0 ? 0 : (t >= a.V ? a.V - 1 : t);
+  const T* w = reinterpret_cast<const T*>(a.w);
+  const uint4* src = reinterpret_cast<const uint4*>(w + (size_t)t * a.d);
+  uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.out) + (size_t)m * a.d);
+  const int n16 = a.d * (int)sizeof(T) / 16;
+  for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = src[i];
+  if (a.gain)
+    rmsnorm_row<T>(w, reinterpret_cast<const T*>(a.gain), a.eps, a.d, t, m, reinterpret_cast<T*>(a.n_out),
+                   reinterpret_cast<float*>(cnt));
+}
+
+hipError_t launch_embed(int dtype, const EmbedArgs& a, hipStream_t st) {
+  const int rope = a.rope.tab ? cdiv(a.rope.rows * a.rope.half, 256) : 0, list = a.rows ? 1 : 0;
+  const int grid = rope + list + a.M + a.M2;
+  if (dtype == SPIFFY_F32) embed_kernel<float><<<grid, 256, 0, st>>>(a, rope, list);
+  else embed_kernel<bf16_t><<<grid, 256, 0, st>>>(a, rope, list);
   return hipGetLastError();
 }
 
@@ -272,9 +299,17 @@ __global__ __launch_bounds__(256) void lmhead_combine_kernel(const TopPartial* _
   const int r = r0 + lane;
   Top t = top_empty();
   if (r < n) {
-    for (int i = p0 + w; i < p1; i += 4) {
-      const TopPartial p = part[(size_t)i * m_cap + r];
-      t = top_merge(t, Top{p.m, p.m2, p.s, p.idx});
+    // sixteen loads in flight: one at a time the loop was a chain of memory latencies (11.3 us for 32 rows of 988 summaries,
+    // 5.0 like this); the merges keep their order
+    constexpr int NB = 16;
+    for (int i0 = p0 + w; i0 < p1; i0 += 4 * NB) {
+      TopPartial p[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (i0 + 4 * k < p1) p[k] = part[(size_t)(i0 + 4 * k) * m_cap + r];
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (i0 + 4 * k < p1) t = top_merge(t, Top{p[k].m, p[k].m2, p[k].s, p[k].idx});
     }
   }
   sh[w][lane] = TopPartial{t.m, t.m2, t.s, t.idx};

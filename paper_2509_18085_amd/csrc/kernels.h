@@ -6,8 +6,18 @@
 namespace spiffy {
 
 // ---- any shape, T = float or bf16 storage -----------------------------------------------------
-hipError_t launch_embed(int dtype, const void* w_embed, const int32_t* tokens, int M, int d, int V, void* out,
-                        const void* gain, float eps, void* n_out, hipStream_t st);   // gain: n_out = RMSNorm(out) too
+struct EmbedArgs {
+  const void* w;                 // [V][d]
+  const int32_t *tok, *tok2;     // rows 0 .. M-1, rows M .. M+M2-1
+  int M, M2, d, V;
+  void *out, *n_out;             // rows; with a gain also their RMSNorm
+  const void* gain;
+  float eps;
+  RopeArgs rope;                 // tab set: the rotary table of the step
+  int32_t *rows, *count;         // set: list of the rows of tok that hold mask_id, ascending
+  int mask_id;
+};
+hipError_t launch_embed(int dtype, const EmbedArgs& a, hipStream_t st);
 // out[r,:] = rmsnorm(x[src(r),:]) * gain, src(r) = row_idx ? row_idx[r] : r, rows r < *n_rows_dev
 // (or < M when n_rows_dev is NULL).
 hipError_t launch_rmsnorm(int dtype, const void* x, const void* gain, float eps, int M, int d,
@@ -26,15 +36,13 @@ struct AttnArgs {
   const void* prefix_k;  // [Hkv,P,hd]
   const void* prefix_v;
   void* out;             // [M, Hq*hd]
-  void* partial;         // MFMA path: split partials (fp32); otherwise the rotary table
+  void* partial;         // MFMA path: split partials (fp32); otherwise the rotary table of its rows
   int G, B, Hq, Hkv, hd, P, pos0;
   int ldp;               // rows allocated per KV head in prefix_k / prefix_v (0 = P)
   int S;                 // dual cache: rows P+B .. P+B+S-1 of the same arrays hold the tokens after the block
   int own;               // 1: every state also attends to its own B rows (keys / values from qkv); 0: cache rows only
   float rope_base;
-  int rope_ready;        // the rotary table in `partial` is already filled
 };
-size_t tile_attn_scratch_bytes(int B, int hd);
 hipError_t launch_attn_tile(int dtype, const AttnArgs& a, hipStream_t st);
 // Prefix-cache extension (Sec. 3.1): the K rows (rotated at positions pos0 .. pos0+B-1) and V rows of the
 // first B rows of the fused qkv activations go to rows P .. P+B-1 of every KV head of the cache
@@ -134,17 +142,19 @@ hipError_t launch_gemm_partial(const GemmArgs& a, TileShape t, hipStream_t st);
 int mfma_lmhead_partials_per_row(int V);
 int mfma_ksplit(int N, int K);          // K slices used for a [M,K]x[N,K] projection with residual (depends on N, K only)
 // out = R + sum of the K-slice partials P[ksplit][M][N] (fixed order); if normed != NULL also RMSNorm(out)*gain.
-// n_rows_dev (optional): only rows below *n_rows_dev exist; out_rows (optional): row m of the result goes to row
-// out_rows[m] of `out` (the partials, R and normed keep row m).
+// n_rows_dev (optional): only rows below *n_rows_dev exist.
+// r_rows (optional): row m reads row r_rows[m] of R.  out_rows (optional): row m of the result goes to row out_rows[m] of
+// `out` (the partials and normed keep row m).  head (optional, with out_rows): the rows are the head's; `normed` is then the
+// RMSNorm of the rounded rows, as launch_masked_rmsnorm gives it, and the row list and its length are left there too.
+struct HeadRows { int32_t *row_idx, *count; };
 hipError_t launch_splitk_reduce(const float* P, int ksplit, const void* R, void* out, const void* gain, float eps,
                                 void* normed, int M, int N, hipStream_t st, const int32_t* n_rows_dev = nullptr,
-                                const int32_t* out_rows = nullptr);
+                                const int32_t* out_rows = nullptr, const int32_t* r_rows = nullptr,
+                                const HeadRows* head = nullptr);
 bool mfma_attn_supported(const AttnArgs& a);
 size_t mfma_attn_partial_bytes(int G, int B, int Hq, int hd, int P);
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t st);
-// rotary table of the QKV projection (head_dim 128): rows for positions pos0 .. pos0+B-1, then tail_pos0 ..
-size_t mfma_rope_bytes(int rows);
-hipError_t launch_rope_table(void* tab, int B, int tail_rows, int pos0, int tail_pos0, float rope_base, hipStream_t st);
+hipError_t launch_rope_table(const RopeArgs& a, hipStream_t st);
 hipError_t launch_attn_mfma_pair(const AttnArgs& a, const AttnArgs& b, hipStream_t st);   // two problems, one launch
 
 // Calibration, part 3 (Alg. 2; App. D.1): best connected node set of size D.  All pointers device memory.

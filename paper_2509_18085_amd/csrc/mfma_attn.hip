@@ -569,17 +569,6 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
   *reinterpret_cast<bf16x4*>(out + rowh * HD + t) = r;
 }
 
-// tab[f / 2][row][f % 2] = (cos, sin) of position * base^(-2f/128): rows 0 .. B-1 at positions pos0 .., rows B .. at tail_pos0 ..
-__global__ __launch_bounds__(256) void rope_table_kernel(float2* __restrict__ tab, int rows, int B, int pos0, int tail_pos0, float base) {
-  constexpr int HALF = HD / 2;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * HALF) return;
-  const int f = 2 * (i / (2 * rows)) + i % 2, b = (i / 2) % rows;
-  const double inv_freq = pow((double)base, -2.0 * (double)f / (double)HD);
-  const double ang = (double)(b < B ? pos0 + b : tail_pos0 + b - B) * inv_freq;
-  tab[i] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
 inline int n_splits(int P) { return P > 0 ? cdiv(P, SPLIT_KEYS) : 1; }
 
 }  // namespace
@@ -598,14 +587,6 @@ size_t mfma_attn_partial_bytes(int G, int B, int Hq, int hd, int P) {
     bytes += align_up(sizeof(float) * nS * M * Hq * 2, 256);
   }
   return bytes;
-}
-
-size_t mfma_rope_bytes(int rows) { return sizeof(float2) * (size_t)rows * (HD / 2); }
-
-hipError_t launch_rope_table(void* tab, int B, int tail_rows, int pos0, int tail_pos0, float rope_base, hipStream_t st) {
-  const int rows = B + tail_rows;
-  rope_table_kernel<<<cdiv(rows * (HD / 2), 256), 256, 0, st>>>(reinterpret_cast<float2*>(tab), rows, B, pos0, tail_pos0, rope_base);
-  return hipGetLastError();
 }
 
 namespace {

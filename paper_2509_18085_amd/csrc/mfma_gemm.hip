@@ -13,18 +13,28 @@ namespace {
 // 256-thread order: a lane adds the sums of its four elements over the 256-element chunks w, w+4, w+8, .. (w = its
 // wavefront), the 64 lanes of a wavefront are summed, then the four wavefront sums.  With 1024 threads every
 // (chunk, lane) sum goes through LDS and the first four wavefronts add them in that same order.
-template <bool NORM>
+//
+// HEAD: the last layer's masked rows, which the head starts from.  Their RMSNorm is taken from the rounded row in the order of
+// rmsnorm_row (256 threads, eight elements each at a time), the bits that a launch of its own gave (4.7 us).
+enum { RED_PLAIN = 0, RED_NORM = 1, RED_HEAD = 2 };
+template <int MODE>
 __global__ __launch_bounds__(1024) void splitk_reduce_kernel(const float* __restrict__ P, int ksplit,
                                                             const bf16_t* __restrict__ R, bf16_t* __restrict__ out,
                                                             const bf16_t* __restrict__ gain, float eps,
                                                             bf16_t* __restrict__ normed, int M, int N,
                                                             const int32_t* __restrict__ n_rows_dev,
-                                                            const int32_t* __restrict__ out_rows) {
+                                                            const int32_t* __restrict__ out_rows,
+                                                            const int32_t* __restrict__ r_rows,
+                                                            int32_t* __restrict__ head_rows, int32_t* __restrict__ head_count) {
+  constexpr bool NORM = MODE == RED_NORM;
   __shared__ float red[4];
   extern __shared__ float rowbuf[];               // NORM: the row in fp32; 1024 threads: then one sum per (chunk, lane)
   const int m = blockIdx.x;
+  if (MODE == RED_HEAD && m == 0 && threadIdx.x == 0) *head_count = *n_rows_dev;
   if (n_rows_dev && m >= *n_rows_dev) return;
   const size_t mo = out_rows ? (size_t)out_rows[m] : (size_t)m;     // where the row goes (compacted rows scatter back)
+  const size_t mr = r_rows ? (size_t)r_rows[m] : (size_t)m;
+  if (MODE == RED_HEAD && threadIdx.x == 0) head_rows[m] = (int32_t)mo;
   const int stride = 4 * (int)blockDim.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool wide = blockDim.x > 256;
@@ -39,7 +49,7 @@ __global__ __launch_bounds__(1024) void splitk_reduce_kernel(const float* __rest
         const f32x4 p = *reinterpret_cast<const f32x4*>(P + ((size_t)z * M + m) * N + n);
         s[0] += p[0]; s[1] += p[1]; s[2] += p[2]; s[3] += p[3];
       }
-      const bf16x4 r = *reinterpret_cast<const bf16x4*>(R + (size_t)m * N + n);
+      const bf16x4 r = *reinterpret_cast<const bf16x4*>(R + mr * N + n);
       bf16x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -48,10 +58,37 @@ __global__ __launch_bounds__(1024) void splitk_reduce_kernel(const float* __rest
         if (NORM) { rowbuf[n + e] = s[e]; c += s[e] * s[e]; }
       }
       *reinterpret_cast<bf16x4*>(out + mo * N + n) = o;
+      if (MODE == RED_HEAD) *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(rowbuf) + n) = o;
     }
     if (NORM) {
       if (wide) lane_ss[(base >> 8) * 64 + lane] = c; else ss += c;
     }
+  }
+  if (MODE == RED_HEAD) {
+    const bf16x8* row = reinterpret_cast<const bf16x8*>(rowbuf);
+    const bf16x8* g8 = reinterpret_cast<const bf16x8*>(gain);
+    bf16x8* n8 = reinterpret_cast<bf16x8*>(normed + (size_t)m * N);
+    const int nv = N / 8;
+    __syncthreads();
+    if (wave < 4) {
+      for (int i = threadIdx.x; i < nv; i += 256) {
+        const bf16x8 v = row[i];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { const float f = static_cast<float>(v[e]); ss += f * f; }
+      }
+      ss = wave_sum(ss);
+      if (lane == 0) red[wave] = ss;
+    }
+    __syncthreads();
+    const float inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)N + eps);
+    for (int i = threadIdx.x; i < nv; i += (int)blockDim.x) {
+      const bf16x8 v = row[i], g = g8[i];
+      bf16x8 o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = static_cast<bf16_t>(static_cast<float>(v[e]) * inv * static_cast<float>(g[e]));
+      n8[i] = o;
+    }
+    return;
   }
   if (!NORM) return;
   if (wide) {
@@ -347,17 +384,22 @@ hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
 
 hipError_t launch_splitk_reduce(const float* P, int ksplit, const void* R, void* out, const void* gain, float eps,
                                 void* normed, int M, int N, hipStream_t st, const int32_t* n_rows_dev,
-                                const int32_t* out_rows) {
+                                const int32_t* out_rows, const int32_t* r_rows, const HeadRows* head) {
   // 1024 threads per row with few rows, while the row and its (chunk, lane) sums fit the 64 KB a launch gets by default
-  const bool wide_fits = sizeof(float) * ((size_t)N + 64 * ((N + 255) / 256)) <= 64 * 1024;
+  const size_t sums = 64 * (size_t)((N + 255) / 256);
+  const bool wide_fits = sizeof(float) * (N + sums) <= 64 * 1024;
   const int threads = (N >= 4096 && M <= 512 && (!normed || wide_fits)) ? 1024 : 256;
-  if (normed)
-    splitk_reduce_kernel<true><<<M, threads, sizeof(float) * ((size_t)N + (threads > 256 ? 64 * ((N + 255) / 256) : 0)), st>>>(P, ksplit, (const bf16_t*)R, (bf16_t*)out,
-                                                                       (const bf16_t*)gain, eps, (bf16_t*)normed, M, N,
-                                                                       n_rows_dev, out_rows);
+  const bf16_t *r = (const bf16_t*)R, *g = (const bf16_t*)gain;
+  bf16_t *o = (bf16_t*)out, *n = (bf16_t*)normed;
+  if (head)
+    splitk_reduce_kernel<RED_HEAD><<<M, threads, sizeof(bf16_t) * (size_t)N, st>>>(P, ksplit, r, o, g, eps, n, M, N, n_rows_dev,
+                                                                                    out_rows, r_rows, head->row_idx, head->count);
+  else if (normed)
+    splitk_reduce_kernel<RED_NORM><<<M, threads, sizeof(float) * (N + (threads > 256 ? sums : 0)), st>>>(
+        P, ksplit, r, o, g, eps, n, M, N, n_rows_dev, out_rows, r_rows, nullptr, nullptr);
   else
-    splitk_reduce_kernel<false><<<M, threads, 0, st>>>(P, ksplit, (const bf16_t*)R, (bf16_t*)out, nullptr, 0.f, nullptr, M, N,
-                                                   n_rows_dev, out_rows);
+    splitk_reduce_kernel<RED_PLAIN><<<M, threads, 0, st>>>(P, ksplit, r, o, nullptr, 0.f, nullptr, M, N, n_rows_dev, out_rows,
+                                                           r_rows, nullptr, nullptr);
   return hipGetLastError();
 }
 

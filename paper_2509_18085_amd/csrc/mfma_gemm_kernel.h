@@ -150,7 +150,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_mfma_kernel(GemmArgs a, int til
     for (int q = 0; q < LX; ++q) {
       const int row = 8 * (wave * LX + q) + (lane >> 3);
       const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-      const int gi = min(i0 + row, i_max - 1);
+      int gi = min(i0 + row, i_max - 1);
+      if (EPI == EPI_PARTIAL && a.a_rows) gi = a.a_rows[gi];
       xoff[q] = (unsigned)gi * (unsigned)(ldx * 2) + chunk * 16;
     }
 #pragma unroll

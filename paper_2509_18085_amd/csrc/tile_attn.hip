@@ -207,16 +207,6 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
   }
 }
 
-// rotary table [row][half] of (cos, sin): angle in double, rounded to float
-__global__ void tile_rope_kernel(float2* __restrict__ tab, int B, int half, int hd, int pos0, float base) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * half) return;
-  const int f = i % half, b = i / half;
-  const double inv_freq = pow((double)base, -2.0 * (double)f / (double)hd);
-  const double ang = (double)(pos0 + b) * inv_freq;
-  tab[i] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
 template <typename T, int H64>
 hipError_t launch_h(const AttnArgs& a, hipStream_t st) {
   const int grid = a.G * a.Hkv * cdiv(a.B * (a.Hq / a.Hkv), 16);
@@ -245,13 +235,7 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t st) {
 
 }  // namespace
 
-size_t tile_attn_scratch_bytes(int B, int hd) { return sizeof(float2) * (size_t)B * (hd / 2); }
-
 hipError_t launch_attn_tile(int dtype, const AttnArgs& a, hipStream_t st) {
-  if (!a.rope_ready) {
-    const int n = a.B * (a.hd / 2);
-    tile_rope_kernel<<<cdiv(n, 256), 256, 0, st>>>((float2*)a.partial, a.B, a.hd / 2, a.hd, a.pos0, a.rope_base);
-  }
   return dtype == SPIFFY_F32 ? launch_t<float>(a, st) : launch_t<bf16_t>(a, st);
 }
 

@@ -105,3 +105,35 @@ def test_layer_rows_are_bit_identical_across_all_tile_heights(sp, name, d, hq, h
     full = run(x)                                        # fall into groups of 32, so states keep their places here)
     for n in (1, 3, 16):
         assert torch.equal(run(x[:n].contiguous()), full[:n]), n
+
+
+@pytest.mark.parametrize("d,G,B,masked", [(4096, 2, 7, "some"), (4096, 20, 32, "some"), (2048, 3, 33, "none"), (2048, 5, 24, "all"),
+                                          (384, 6, 5, "one")])
+def test_head_rows_from_the_last_reduction(sp, d, G, B, masked):
+    """Without hidden states the last layer's reduction leaves the head's normalised rows and their list (1024 or 256 threads a
+    row; none, one, some or all rows masked; 384 columns: not sliced, a launch of its own).  Layers with different numbers of
+    cached rows share the table and the list that the step's first kernel made.  Every output equals that of the same step
+    with hidden states."""
+    cfg = synth.CONFIGS["c4"].scaled(L=2, F=512, V=1280, d=d, Hq=d // 128, Hkv=d // 128, P=70, B=B, G=G)
+    scfg = sp.cfg_from_synth(cfg)
+    lw = [sp.layer_weights({k: v.to(DEV) for k, v in synth.layer_weights(cfg, l).items()}) for l in range(2)]
+    kv = [tuple(t.to(DEV) for t in synth.prefix_kv(cfg, l)) for l in range(2)]
+    pf = [sp.prefix_kv(kv[0][0], kv[0][1], 70, 0), sp.prefix_kv(kv[1][0], kv[1][1], 3, 0)]
+    hw = {k: v.to(DEV) for k, v in synth.head_weights(cfg).items()}
+    emb = synth.embed_weights(cfg).to(DEV)
+    st = synth.random_states(G, B, cfg.V, 0.2, 0.9, 13)
+    if masked in ("none", "one"):
+        st[st == cfg.mask_id] = 1
+    if masked == "all":
+        st[:] = cfg.mask_id
+    if masked == "one":
+        st[G - 1, B - 1] = cfg.mask_id
+    toks = torch.from_numpy(st).to(DEV)
+    outs = []
+    for keep in (False, True):
+        plan = sp.StepPlan(scfg, lw, pf, emb, hw["final_norm"], hw["w_vocab"], G, B, 70, 0.9, logit_scale=8.0, device=DEV,
+                           keep_hidden=keep)
+        o = plan.run(toks, None)
+        outs.append({k: v.clone() for k, v in o.items() if k != "hidden" and torch.is_tensor(v)})
+    for k in outs[0]:
+        assert torch.equal(outs[0][k], outs[1][k]), k
