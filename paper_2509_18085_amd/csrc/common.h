@@ -24,15 +24,38 @@ template <typename T> __device__ __forceinline__ T from_f32(float x);
 template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float x) { return static_cast<bf16_t>(x); }
 
+// Reductions over the wavefront, distances 32, 16, .. 1 in turn, every lane gets the result.  The partner's value comes from
+// vector instructions (swaps of 32- and 16-lane rows hold both values in one lane, then DPP permutations); __shfl_xor takes
+// each through the LDS crossbar, some 60 cycles a step.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <typename Op>
+__device__ __forceinline__ float reduce_32(float v, Op op) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <typename Op>
+__device__ __forceinline__ float reduce_16(float v, Op op) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  v = reduce_16(reduce_32(v, op), op);
+  v = op(v, dpp_move<0x128>(v));                       // row_ror:8
+  v = op(v, dpp_move<0x1B>(dpp_move<0x141>(v)));       // lane ^ 7, then lane ^ 3
+  v = op(v, dpp_move<0x4E>(v));                        // quad_perm [2,3,0,1]
+  return op(v, dpp_move<0xB1>(v));                     // quad_perm [1,0,3,2]
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 // Running summary of a set of logits: top value, its lowest index, runner-up value and

@@ -147,8 +147,8 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
       s[v] = 16 * c + 4 * grp + v < n_keys ? s[v] * scale : -INFINITY;
       mc = fmaxf(mc, s[v]);
     }
-    mc = fmaxf(mc, __shfl_xor(mc, 16, 64));
-    mc = fmaxf(mc, __shfl_xor(mc, 32, 64));
+    const auto larger = [](float x, float y) { return fmaxf(x, y); };
+    mc = reduce_32(reduce_16(mc, larger), larger);
     const float f = m == -INFINITY ? 0.f : __expf(m - mc);     // nothing accumulated yet: the sums are zero
     float ps = 0.f;
 #pragma unroll
@@ -169,8 +169,8 @@ __global__ __launch_bounds__(64 * NW) void tile_attn_kernel(const T* __restrict_
           o[u][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(static_cast<float>(cur.v[v][u][j]), s[v], o[u][j], 0, 0, 0);
       }
   }
-  sum += __shfl_xor(sum, 16, 64);
-  sum += __shfl_xor(sum, 32, 64);
+  const auto plus = [](float x, float y) { return x + y; };
+  sum = reduce_32(reduce_16(sum, plus), plus);
   // merge through LDS: every wavefront leaves its sums, then all threads add the eight of an output element in order
   const int ldm = hd + 2;
   {

@@ -2,18 +2,18 @@
 // its 64-wide K tiles.  fp32 operands run on v_mfma_f32_16x16x4_f32 (fp32 products, fp32 sums: the arithmetic of a chain of
 // fused multiply-adds), bf16 operands on v_mfma_f32_16x16x32_bf16.
 //
-// What bounds these shapes: with the 16 - 128 rows of a few states, the requests for weight and activation lines that a CU
-// keeps in flight, and the latency of the chain of loads along K; with several hundred rows the fp32 matrix pipes (256
-// flop per clock and CU).  Both operands are K-contiguous, and a 16x16 fragment of either type is one 16-byte load per lane
-// whose four lane groups read 64 contiguous bytes of a row, so nothing is staged in LDS: every wavefront loads fragments
-// straight into a ring of DEPTH register buffers.  Eight wavefronts share one output tile and split K (chunk c of 128
+// What bounds these shapes: with the 16 - 128 rows of a few states, the lines that a CU's L1 hands out; with several hundred
+// rows the fp32 matrix pipes (256 flop per clock and CU).  Eight wavefronts share one output tile and split K (chunk c of 128
 // bytes, a whole line of each row, goes to wavefront c % 8), which puts eight times as many loads in flight per tile;
 // their sums are added through LDS as a fixed tree.  The K order of an element depends on K alone, not on the tile or
 // on M, so a row's result does not depend on the rows computed with it.
 //
-// Measured, against a 64x64-tile kernel on vector FMAs with scalar loads (and, for the head, one workgroup per row that
-// streamed the whole vocabulary matrix): bf16, 128 rows, width 1024, FFN 2816: QKV 334 -> 9.8 us (three launches -> one),
-// gate/up 208 -> 14.6, output and down 8.2 on average.  fp32, 39 of 64 rows against 32000 tokens x 1024: 44 ms -> 62 us.
+// A 16x16 fragment of either type is one 16-byte load per lane whose four lane groups read 64 contiguous bytes of a row; loaded
+// so, straight into registers, half lines of sixteen rows an instruction, a CU gets 14 bytes a clock.  Each wavefront
+// therefore brings its chunk global -> LDS as whole lines (eight rows an instruction) into LDS of its own and reads the
+// fragments there.  Measured, registers -> LDS, us: fp32, 64 rows, QKV 1536 x 1024 8.5 -> 6.2, gate/up 2816 x 1024 18.4 -> 15.7,
+// down 1024 x 2816 17.8 -> 9.8; bf16, 128 rows, 8.4 -> 5.6, 13.8 -> 10.1, 17.3 -> 9.1.  (A kernel on vector FMAs with scalar loads
+// took 200 - 340 us for these.)
 #include <type_traits>
 
 #include "kernels.h"
@@ -43,87 +43,105 @@ __device__ __forceinline__ f32x4 mma(f32x4 c, bf16x8 a, bf16x8 b) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// One output tile: rows m0 .. m0+16*TM-1 (below m_max), weight rows given by `wrow` (TN fragments of 16).
-// On return wavefront 0's .. 7's sums are in acc; the caller reduces them.
-template <typename T, int TM, int TN, int DEPTH>
-__device__ __forceinline__ void tile_product(const T* const (&arow)[TM], const T* const (&wrow)[TN], int K, int wave, int lane,
+// LDS of one wavefront: a chunk of 128 bytes of TM * 16 activation rows and TN * 16 weight rows
+constexpr int stage_bytes(int tm, int tn) { return (tm + tn) * 2048; }
+
+__device__ __forceinline__ void wait_vmcnt0() {    // lgkmcnt / expcnt untouched
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  asm volatile("" ::: "memory");                   // no LDS read moves above it
+}
+__device__ __forceinline__ void wait_lgkm0() {     // vmcnt / expcnt untouched
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  asm volatile("" ::: "memory");
+}
+
+// Sources of a wavefront's transfers.  One transfer brings a chunk of eight rows as whole 128-byte lines, global -> LDS: lane
+// -> row 8 * q + lane / 8 and the 16 bytes that belong at LDS position lane % 8; position p of row r holds piece
+// p ^ (r / 2) % 8, so that the reads of one piece of sixteen rows are free of bank conflicts.  Transfers 0 .. 2*TM-1 are
+// activation rows, the rest weight rows; `row(i)` is the start of row i of the tile's TM*16 + TN*16.
+template <typename T, int TM, int TN, typename RowFn>
+__device__ __forceinline__ void tile_sources(const T* (&src)[2 * (TM + TN)], int lane, RowFn row) {
+#pragma unroll
+  for (int q = 0; q < 2 * (TM + TN); ++q) src[q] = row(8 * q + (lane >> 3));
+}
+
+// One output tile.  On return wavefront 0's .. 7's sums are in acc; the caller reduces them.  `stage` is this wavefront's LDS:
+// nobody else reads or writes it, so the loop has no barrier.  One chunk is in flight per wavefront, the next is asked for
+// as soon as the fragments are in registers; a second stage gained nothing, the workgroups it keeps off the compute unit
+// cost more (fp32, 64 rows, K = 2816: 9.7 us with one stage, 11.4 with two).
+template <typename T, int TM, int TN>
+__device__ __forceinline__ void tile_product(const T* const (&src)[2 * (TM + TN)], int K, int wave, int lane, unsigned stage,
                                              f32x4 (&acc)[TM][TN]) {
   typedef typename Frag<T>::type frag_t;
-  constexpr int KC = Frag<T>::KC, VEC = Frag<T>::VEC;
+  typedef const __attribute__((address_space(3))) frag_t* lds_frag_ptr;
+  constexpr int KC = Frag<T>::KC, VEC = Frag<T>::VEC, L = 2 * (TM + TN);
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  frag_t fa[DEPTH][2][TM], fw[DEPTH][2][TN];
-  const int k_lane = (lane >> 4) * VEC;
-  auto load_half = [&](int buf, int h, int k) {
+  // chunks of this wavefront; the last one of K may be cut short.  Every branch is wavefront-uniform.
+  const int whole = K / (2 * KC), n_whole = whole > wave ? (whole - wave + NW - 1) / NW : 0;
+  const bool cut = whole * 2 * KC < K && whole % NW == wave;
+  const int n = n_whole + (cut ? 1 : 0);
+  auto load = [&](int t) {                         // this wavefront's t-th chunk
+    const int k0 = (wave + t * NW) * 2 * KC;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fw[buf][h][j] = *reinterpret_cast<const frag_t*>(wrow[j] + k);
+    for (int q = 0; q < L; ++q) {
+      int k = k0 + (((lane & 7) ^ (4 * (q & 1) + (lane >> 4))) * VEC);
+      if (k0 + 2 * KC > K) k = min(k, K - VEC);    // (zeroed when it is read)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                   :: "s"(stage + q * 1024), "v"(src[q] + k) : "memory");
+    }
+  };
+  const int l16 = lane & 15, g = lane >> 4, swz = (l16 >> 1) & 7;
+  if (n > 0) load(0);
+  for (int t = 0; t < n; ++t) {
+    wait_vmcnt0();
+    const unsigned base = stage + l16 * 128;
+    frag_t fa[2][TM], fw[2][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa[buf][h][i] = *reinterpret_cast<const frag_t*>(arow[i] + k);
-  };
-  auto load = [&](int buf, int t) {                // this wavefront's t-th chunk
-    const int k = (wave + t * NW) * 2 * KC + k_lane;
-    load_half(buf, 0, k);
-    load_half(buf, 1, k + KC);
-  };
-  // fp32: a chunk's products are summed on their own and then added, so that the long sum along K is rounded once a chunk
-  // and wavefront (a layer of width 1024 against 64 bits: 5.0e-7 with one chain, 3.0e-7 so; no measurable time)
-  auto product = [&](int buf) {
+    for (int h = 0; h < 2; ++h) {
+      const unsigned p = base + (((h * 4 + g) ^ swz) * 16);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fw[h][j] = *(lds_frag_ptr)(size_t)(p + (TM + j) * 2048);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[h][i] = *(lds_frag_ptr)(size_t)(p + i * 2048);
+    }
+    wait_lgkm0();                                  // the fragments are in registers: the stage is free
+    if (t + 1 < n) load(t + 1);
+    if (cut && t == n - 1) {      // K is a multiple of 8, so a lane's values are all inside K or all beyond it
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if ((2 * whole + h) * KC + g * VEC >= K) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) fw[h][j] = frag_t{};
+#pragma unroll
+          for (int i = 0; i < TM; ++i) fa[h][i] = frag_t{};
+        }
+    }
+    // fp32: a chunk's products are summed on their own and then added, so that the long sum along K is rounded once a chunk
+    // and wavefront (a layer of width 1024 against 64 bits: 5.0e-7 with one chain, 3.0e-7 so; no measurable time)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         if constexpr (std::is_same<T, float>::value) {
-          f32x4 c = mma(f32x4{0.f, 0.f, 0.f, 0.f}, fa[buf][0][i], fw[buf][0][j]);
-          c = mma(c, fa[buf][1][i], fw[buf][1][j]);
+          f32x4 c = mma(f32x4{0.f, 0.f, 0.f, 0.f}, fa[0][i], fw[0][j]);
+          c = mma(c, fa[1][i], fw[1][j]);
 #pragma unroll
           for (int v = 0; v < 4; ++v) acc[i][j][v] += c[v];
         } else {
-          acc[i][j] = mma(acc[i][j], fa[buf][0][i], fw[buf][0][j]);
-          acc[i][j] = mma(acc[i][j], fa[buf][1][i], fw[buf][1][j]);
+          acc[i][j] = mma(acc[i][j], fa[0][i], fw[0][j]);
+          acc[i][j] = mma(acc[i][j], fa[1][i], fw[1][j]);
         }
       }
-  };
-  // whole chunks of this wavefront; every branch is wavefront-uniform
-  const int whole = K / (2 * KC), n = whole > wave ? (whole - wave + NW - 1) / NW : 0;
-#pragma unroll
-  for (int s = 0; s < DEPTH; ++s)
-    if (s < n) load(s, s);
-  __builtin_amdgcn_sched_barrier(0);
-  int t = 0;
-  for (; t + 2 * DEPTH <= n; t += DEPTH) {
-#pragma unroll
-    for (int s = 0; s < DEPTH; ++s) {
-      product(s);
-      load(s, t + s + DEPTH);
-      __builtin_amdgcn_sched_barrier(0);           // keep the ring: left alone, the scheduler gathers all loads at the end
-    }
   }
-#pragma unroll
-  for (int s = 0; s < DEPTH; ++s) {
-    if (t + s < n) product(s);
-    if (t + s + DEPTH < n) load(s, t + s + DEPTH);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-#pragma unroll
-  for (int s = 0; s < DEPTH - 1; ++s)
-    if (t + s + DEPTH < n) product(s);
-  // a last chunk that K cuts short: K is a multiple of 8, so a lane's values are all inside K or all beyond it
-  if (whole * 2 * KC < K && whole % NW == wave) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int k = (2 * whole + h) * KC + k_lane;
-      load_half(0, h, min(k, K - VEC));
-      if (k >= K) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fw[0][h][j] = frag_t{};
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[0][h][i] = frag_t{};
-      }
-    }
-    product(0);
-  }
+}
+
+// the wavefronts' stages; their sums take the same place afterwards
+constexpr int red_bytes(int tn) { return NW * tn * RSTRIDE * (int)sizeof(float); }
+constexpr int tile_lds(int tm, int tn) {
+  return NW * stage_bytes(tm, tn) > red_bytes(tn) ? NW * stage_bytes(tm, tn) : red_bytes(tn);
 }
 
 // the eight wavefronts' sums of one element, stride floats apart, added as a tree (fewer roundings at full size)
@@ -161,32 +179,30 @@ __device__ __forceinline__ void store_element(const GemmArgs& a, bool has_bias, 
 }
 
 // C tile of 16*TM rows x 16*TN columns (SWIGLU: TN/2 fragments of gate rows and the same rows of up)
-template <typename T, int EPI, int TM, int TN, int DEPTH>
+template <typename T, int EPI, int TM, int TN>
 __global__ __launch_bounds__(64 * NW) void tile_gemm_kernel(GemmArgs a) {
-  __shared__ float red[NW][TN][RSTRIDE];
+  extern __shared__ __align__(1024) unsigned char smem[];
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
+  float(*red)[TN][RSTRIDE] = reinterpret_cast<float(*)[TN][RSTRIDE]>(smem);
   constexpr int NO = EPI == EPI_SWIGLU ? TN / 2 : TN;      // output fragments along the columns
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int l16 = lane & 15;
   const int m_max = a.M_dev ? min(*a.M_dev, a.M) : a.M;
   const int m0 = blockIdx.y * 16 * TM, n0 = blockIdx.x * 16 * NO;
   if (m0 >= m_max) return;
   const int K = a.K;
-  const T* arow[TM];
-  const T* wrow[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) arow[i] = (const T*)a.A + (size_t)min(m0 + 16 * i + l16, m_max - 1) * a.lda;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    if (EPI == EPI_SWIGLU) wrow[j] = (const T*)a.W[j / NO] + (size_t)min(n0 + 16 * (j % NO) + l16, a.N - 1) * K;
-    else wrow[j] = weight_row<T, EPI>(a, n0 + 16 * j + l16);
-  }
+  const T* src[2 * (TM + TN)];
+  tile_sources<T, TM, TN>(src, lane, [&](int r) {
+    if (r < 16 * TM) return (const T*)a.A + (size_t)min(m0 + r, m_max - 1) * a.lda;
+    r -= 16 * TM;
+    if (EPI == EPI_SWIGLU) return (const T*)(r < 16 * NO ? a.W[0] : a.W[1]) + (size_t)min(n0 + r % (16 * NO), a.N - 1) * K;
+    return weight_row<T, EPI>(a, n0 + r);
+  });
   f32x4 acc[TM][TN];
-  tile_product<T, TM, TN, DEPTH>(arow, wrow, K, wave, lane, acc);
-
+  tile_product<T, TM, TN>(src, K, wave, lane, lds0 + wave * stage_bytes(TM, TN), acc);
   const bool has_bias = EPI == EPI_STORE && (a.bias[0] || a.bias[1] || a.bias[2]);
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    if (i) __syncthreads();
+    __syncthreads();                               // the sums go where the stages, or the last row's sums, were
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -310,22 +326,27 @@ __global__ __launch_bounds__(64 * SW) void tile_gemm_short_kernel(GemmArgs a, in
 // ..), blockIdx.y = group of 64 rows.  Every part leaves one (top, lowest index, runner-up, sum exp) summary per row.
 template <typename T, int TM>
 __device__ __forceinline__ void head_tiles(const T* n, const T* wv, int d, int V, float scale, int rows, int m0, int n_part,
-                                           int m_cap, TopPartial* part, float* red) {
+                                           int m_cap, TopPartial* part, unsigned char* smem) {
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
+  float* red = reinterpret_cast<float*>(smem);
   constexpr int TN = 4, PER = TM * 16 / NW;        // tokens rows of the tile whose summaries one wavefront keeps
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15;
-  const T* arow[TM];
+  float top_m[PER], top_m2[PER], top_s[PER];       // (an array of the structure ends up in scratch memory)
+  int top_i[PER];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) arow[i] = n + (size_t)min(m0 + 16 * i + l16, rows - 1) * d;
-  Top top[PER];
-#pragma unroll
-  for (int p = 0; p < PER; ++p) top[p] = top_empty();
+  for (int p = 0; p < PER; ++p) {
+    const Top e = top_empty();
+    top_m[p] = e.m; top_m2[p] = e.m2; top_s[p] = e.s; top_i[p] = e.idx;
+  }
   const int tiles = (V + 16 * TN - 1) / (16 * TN);
   for (int t = blockIdx.x; t < tiles; t += n_part) {
-    const T* wrow[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) wrow[j] = wv + (size_t)min(t * 16 * TN + 16 * j + l16, V - 1) * d;
+    const T* src[2 * (TM + TN)];
+    tile_sources<T, TM, TN>(src, lane, [&](int r) {
+      return r < 16 * TM ? n + (size_t)min(m0 + r, rows - 1) * d : wv + (size_t)min(t * 16 * TN + r - 16 * TM, V - 1) * d;
+    });
     f32x4 acc[TM][TN];
-    tile_product<T, TM, TN, 1>(arow, wrow, d, wave, lane, acc);
+    if (t != (int)blockIdx.x) __syncthreads();     // the sums of the last tile lie where the stages are
+    tile_product<T, TM, TN>(src, d, wave, lane, lds0 + wave * stage_bytes(TM, TN), acc);
     const int idx = t * 64 + lane;                 // this lane's token of the tile
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -349,7 +370,9 @@ __device__ __forceinline__ void head_tiles(const T* n, const T* wv, int d, int V
         one.idx = t * 64 + win;
         one.m2 = wave_max(lane == win ? -INFINITY : l);
         one.s = wave_sum(l == -INFINITY ? 0.f : __expf(l - mx));
-        top[i * 2 + p] = top_merge(top[i * 2 + p], one);
+        const int c = i * 2 + p;
+        one = top_merge(Top{top_m[c], top_m2[c], top_s[c], top_i[c]}, one);
+        top_m[c] = one.m; top_m2[c] = one.m2; top_s[c] = one.s; top_i[c] = one.idx;
       }
     }
   }
@@ -358,27 +381,36 @@ __device__ __forceinline__ void head_tiles(const T* n, const T* wv, int d, int V
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       const int r = m0 + 16 * i + wave * 2 + p;
-      const Top& o = top[i * 2 + p];
-      if (lane == 0 && r < rows) part[(size_t)blockIdx.x * m_cap + r] = TopPartial{o.m, o.m2, o.s, o.idx};
+      const int c = i * 2 + p;
+      if (lane == 0 && r < rows) part[(size_t)blockIdx.x * m_cap + r] = TopPartial{top_m[c], top_m2[c], top_s[c], top_i[c]};
     }
 }
 
-// One workgroup to a CU: 256 registers in fp32, 196 in bf16, for four row fragments, and the compiler keeps 160 bytes a lane in
-// scratch memory.  Measured, 39 of 64 rows, fp32, 32000 x 1024: 62 us, 2.1 TB/s, bound by 64-byte segments of weight rows in
-// flight from one workgroup.
+// One workgroup to a CU (112 KB of LDS for 48 rows).  39 of 64 rows, fp32, 32000 x 1024: 45 us, 62 with fragments loaded into
+// registers and the running summaries in scratch memory; the fp32 matrix pipes alone need 23 for the 48 rows computed.
 template <typename T>
 __global__ __launch_bounds__(64 * NW) void tile_head_kernel(const T* __restrict__ n, const T* __restrict__ wv, int d, int V,
                                                             float scale, const int32_t* __restrict__ count, int M, int m_cap,
                                                             TopPartial* __restrict__ part) {
-  __shared__ float red[NW * 4 * RSTRIDE];
+  extern __shared__ __align__(1024) unsigned char smem[];
   const int rows = min(*count, M), m0 = blockIdx.y * 64;
   if (m0 >= rows) return;
   const int left = rows - m0, n_part = gridDim.x;
   // as many 16-row fragments as there are rows
-  if (left > 48) head_tiles<T, 4>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, red);
-  else if (left > 32) head_tiles<T, 3>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, red);
-  else if (left > 16) head_tiles<T, 2>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, red);
-  else head_tiles<T, 1>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, red);
+  if (left > 48) head_tiles<T, 4>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, smem);
+  else if (left > 32) head_tiles<T, 3>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, smem);
+  else if (left > 16) head_tiles<T, 2>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, smem);
+  else head_tiles<T, 1>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, smem);
+}
+
+template <typename T, int EPI, int TM, int TN>
+hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
+  constexpr int NO = EPI == EPI_SWIGLU ? TN / 2 : TN, LDS = tile_lds(TM, TN);
+  static std::atomic<unsigned long long> lds_ok{0};
+  const hipError_t e = allow_dynamic_lds((const void*)tile_gemm_kernel<T, EPI, TM, TN>, LDS, lds_ok);
+  if (e != hipSuccess) return e;
+  tile_gemm_kernel<T, EPI, TM, TN><<<dim3(cdiv(a.N, 16 * NO), cdiv(a.M, 16 * TM)), 64 * NW, LDS, st>>>(a);
+  return hipGetLastError();
 }
 
 template <typename T, int EPI, int MAX_CHUNKS>
@@ -387,31 +419,37 @@ void launch_short(const GemmArgs& a, hipStream_t st) {
   tile_gemm_short_kernel<T, EPI, MAX_CHUNKS><<<cdiv(a.M, 32) * col_blocks, 64 * SW, 0, st>>>(a, col_blocks);
 }
 
-// Tiles of 64 x 64 (SWIGLU: 32 features) where they fill the chip: a quarter of the operand traffic per product.  Below
-// that 32 x 16 (16 x 16 with one fragment of rows): four to eight times the workgroups, each reading its operands once.
-// Measured around the line, fp32 / bf16, in us with 64 x 64 and with 32 x 16: 200 rows of 4104 columns (260 tiles of 64 x 64),
-// K = 1032: 45.4, 37.4 / 13.5, 17.9, SwiGLU 66, 58 / 22, 25; 1024 rows of 4104, 1040 tiles: 116, 150 / 46, 72; 4096 rows: 393,
-// 578 / 148, 271 (one line for both types: fp32 alone would gain from 32 x 16 tiles a little longer).
-// Where 64 x 64 tiles fill the chip and K has up to six chunks in fp32 (192), four in bf16 (256), a wavefront takes a tile: 4096 x
-// 4104 from K = 8 87 -> 23 / 59 -> 15, K = 136 127 -> 81 / 65 -> 32; with more chunks the shared tiles were as fast or faster
-// where they just fill the chip (1024 x 1032, SwiGLU: seven chunks fp32 23 against 25, five bf16 15 against 18).
+// Tile shapes, measured, us:
+// bf16 runs 64 x 64 tiles (SWIGLU: 32 features) where they fill the chip: a quarter of the operand traffic per product (4104
+// columns, K = 1032: 200 rows, 260 tiles, 13.7, with 32 x 32 14.3, with 32 x 16 15.4; 1024 rows 44.7, 48.4, 56.9; 4096 rows 148, 175,
+// 214).  fp32 does not: 32 x 32 tiles, two workgroups a CU, one adding sums while the other multiplies, were faster
+// throughout (200 rows 32.8, with 64 x 64 50.3; 1024 rows 108, 129; 4096 rows 387, 431).
+// Below that 32 x 32 or 32 x 16 (SWIGLU: 16 features either way), by rounds of 256 workgroups: one of 32 x 32 takes as long as 1.6 of
+// 32 x 16 in bf16, 1.9 in fp32, and starts sooner (K = 1024, 32 x 16 / 32 x 32: fp32 64 x 2048 6.3 / 8.6, 64 x 3072 9.8 / 8.9, 64 x 4104
+// 13.4 / 15.4; bf16 64 x 1544 3.7 / 4.1, 128 x 1032 4.6 / 4.2, 128 x 2056 5.4 / 5.9).  16 x 16 with one fragment of rows.
+// Where 64 x 64 tiles would fill the chip and K has up to six chunks in fp32 (192), four in bf16 (256), a wavefront takes a
+// tile: 4096 x 4104 from K = 8 78 -> 23 / 67 -> 14, K = 136 112 -> 82 / 70 -> 32; with more chunks the shared tiles were as fast
+// or faster where they just fill the chip (1024 x 1032, SwiGLU: seven chunks fp32 23 against 25, five bf16 15 against 18).
 template <typename T, int EPI>
 hipError_t launch_epi(const GemmArgs& a, hipStream_t st) {
   constexpr int CHUNK = 2 * Frag<T>::KC;
+  constexpr bool F32 = sizeof(T) == 4;
   const int big = cdiv(a.M, 64) * cdiv(a.N, EPI == EPI_SWIGLU ? 32 : 64);
   if (big >= 256 && a.K <= 4 * CHUNK) {
     launch_short<T, EPI, 4>(a, st);
-  } else if (big >= 256 && a.K <= 6 * CHUNK && sizeof(T) == 4) {
-    launch_short<float, EPI, 6>(a, st);
-  } else if (big >= 256) {
-    constexpr int NO = EPI == EPI_SWIGLU ? 2 : 4;
-    tile_gemm_kernel<T, EPI, 4, 4, 1><<<dim3(cdiv(a.N, 16 * NO), cdiv(a.M, 64)), 64 * NW, 0, st>>>(a);
-  } else if (a.M <= 16) {
-    tile_gemm_kernel<T, EPI, 1, EPI == EPI_SWIGLU ? 2 : 1, 2><<<dim3(cdiv(a.N, 16), 1), 64 * NW, 0, st>>>(a);
-  } else {
-    tile_gemm_kernel<T, EPI, 2, EPI == EPI_SWIGLU ? 2 : 1, 2><<<dim3(cdiv(a.N, 16), cdiv(a.M, 32)), 64 * NW, 0, st>>>(a);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  if (F32 && big >= 256 && a.K <= 6 * CHUNK) {
+    launch_short<float, EPI, 6>(a, st);
+    return hipGetLastError();
+  }
+  if constexpr (!F32)
+    if (big >= 256) return launch_tile<T, EPI, 4, 4>(a, st);
+  if (a.M <= 16) return launch_tile<T, EPI, 1, EPI == EPI_SWIGLU ? 2 : 1>(a, st);
+  const int rows = cdiv(a.M, 32), r16 = cdiv(rows * cdiv(a.N, 16), 256), r32 = cdiv(rows * cdiv(a.N, 32), 256);
+  if (EPI == EPI_SWIGLU || (F32 ? 19 * r32 - 2 < 10 * r16 : 16 * r32 < 10 * r16)) return launch_tile<T, EPI, 2, 2>(a, st);
+  if constexpr (EPI != EPI_SWIGLU) return launch_tile<T, EPI, 2, 1>(a, st);
+  return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -433,11 +471,17 @@ hipError_t launch_gemm_tile(int dtype, int epi, const GemmArgs& a, hipStream_t s
 hipError_t launch_lmhead_tile(int dtype, const void* n, const void* w_vocab, int d, int V, float scale, const int32_t* count,
                               int M, int m_cap, int n_part, TopPartial* part, hipStream_t st) {
   const dim3 grid(n_part, cdiv(M, 64));
-  if (dtype == SPIFFY_F32)
-    tile_head_kernel<float><<<grid, 64 * NW, 0, st>>>((const float*)n, (const float*)w_vocab, d, V, scale, count, M, m_cap, part);
-  else
-    tile_head_kernel<bf16_t><<<grid, 64 * NW, 0, st>>>((const bf16_t*)n, (const bf16_t*)w_vocab, d, V, scale, count, M, m_cap,
-                                                       part);
+  const int lds = tile_lds(M > 48 ? 4 : cdiv(M, 16), 4);      // for as many 16-row fragments as there can be
+  static std::atomic<unsigned long long> lds_ok[2];
+  hipError_t e;
+  if (dtype == SPIFFY_F32) {
+    if ((e = allow_dynamic_lds((const void*)tile_head_kernel<float>, tile_lds(4, 4), lds_ok[0])) != hipSuccess) return e;
+    tile_head_kernel<float><<<grid, 64 * NW, lds, st>>>((const float*)n, (const float*)w_vocab, d, V, scale, count, M, m_cap, part);
+  } else {
+    if ((e = allow_dynamic_lds((const void*)tile_head_kernel<bf16_t>, tile_lds(4, 4), lds_ok[1])) != hipSuccess) return e;
+    tile_head_kernel<bf16_t><<<grid, 64 * NW, lds, st>>>((const bf16_t*)n, (const bf16_t*)w_vocab, d, V, scale, count, M, m_cap,
+                                                          part);
+  }
   return hipGetLastError();
 }
 

@@ -137,3 +137,23 @@ def test_head_rows_from_the_last_reduction(sp, d, G, B, masked):
         outs.append({k: v.clone() for k, v in o.items() if k != "hidden" and torch.is_tensor(v)})
     for k in outs[0]:
         assert torch.equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K", [(40, 2056, 72), (33, 8200, 136), (200, 2056, 1032), (130, 3080, 264), (17, 24, 8), (260, 4104, 520)])
+def test_tile_gemm_shapes_by_rounds(sp, M, N, K, dtype):
+    """32 x 16, 32 x 32 and 64 x 64 tiles, chosen by rounds of workgroups, last chunks of K cut to 8 .. 56 values and wavefronts
+    without a chunk; rows do not depend on the tile (the first 16 rows alone run in 16 x 16 tiles).  Bounds as for the edges of
+    the tiles: |sum - exact| <= (K + 16) 2^-24 sum |a w|, in bf16 plus one rounding of the result, 2^-8 relative."""
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(M + N + K)
+    A, W0, W1 = ((torch.randn(s, generator=g) * f).to(td) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((N, K), 0.1)))
+    a, w0, w1 = to_np(A), to_np(W0), to_np(W1)
+    eps, out = 2.0 ** -24, 0.0 if dtype == "f32" else 1.02 * 2.0 ** -8
+    dev = [t.to(DEV) for t in (A, W0, W1)]
+    got = sp.gemm(sp.GEMM_STORE, dev[0], dev[1])
+    ref, d0 = a @ w0.T, (K + 16) * eps * (np.abs(a) @ np.abs(w0).T)
+    assert (np.abs(to_np(got) - ref) <= d0 + (out + eps) * np.abs(ref) + 1e-30).all()
+    assert torch.equal(sp.gemm(sp.GEMM_STORE, dev[0][:16].contiguous(), dev[1]), got[:16])
+    sw = sp.gemm(sp.GEMM_SWIGLU, *dev)
+    assert torch.equal(sp.gemm(sp.GEMM_SWIGLU, dev[0][:16].contiguous(), dev[1], dev[2]), sw[:16])
