@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspiffy.so")
 SOURCES = ["api.hip", "generic_kernels.hip", "tile_gemm.hip", "tile_attn.hip", "graph_accept.hip", "draft_prune.hip", "head_topk.hip", "subgraph_search.hip", "mfma_gemm.hip",
-           "mfma_gemm_swiglu.hip", "mfma_gemm_qkv.hip", "mfma_gemm_partial.hip", "mfma_gemm_store.hip", "mfma_attn.hip"]
+           "mfma_gemm_swiglu.hip", "mfma_gemm_qkv.hip", "mfma_gemm_partial.hip", "mfma_gemm_store.hip", "mfma_gemm_head.hip", "mfma_attn.hip"]
 PROBE_LIB = os.path.join(HERE, "libspiffy_probe.so")     # bench-only: measured peaks of the machine (csrc/probe.hip)
 # -ffp-contract=on: a multiply and an add are fused only where the source writes them in one expression, so the
 # rounding of a kernel does not depend on how the optimiser inlined or ordered it (different instantiations of one

@@ -138,6 +138,7 @@ struct TileShape { int bm, bn; };
 hipError_t launch_gemm_store(const GemmArgs& a, TileShape t, hipStream_t st);
 hipError_t launch_gemm_qkv(const GemmArgs& a, TileShape t, hipStream_t st);
 hipError_t launch_gemm_swiglu(const GemmArgs& a, TileShape t, hipStream_t st);
+hipError_t launch_gemm_head(const GemmArgs& a, hipStream_t st);
 hipError_t launch_gemm_partial(const GemmArgs& a, TileShape t, hipStream_t st);
 int mfma_lmhead_partials_per_row(int V);
 int mfma_ksplit(int N, int K);          // K slices used for a [M,K]x[N,K] projection with residual (depends on N, K only)

@@ -50,7 +50,7 @@
 // wavefront of a pair that takes the first key half, in groups of 32 rows that are counted the same way however many query
 // rows a workgroup owns, so a state's arithmetic does not depend on that; the mask is applied per element (any B works).
 // Queries and keys arrive rotated (positions pos0..pos0+B-1 for every state, Sec. 4.3), queries also scaled by
-// log2(e)/sqrt(128): the QKV projection's epilogue does both on its fp32 sums.
+// log2(e)/sqrt(128): the QKV projection's epilogue does both, in fp32 on the values rounded to bf16.
 #include <type_traits>
 
 #include "kernels.h"

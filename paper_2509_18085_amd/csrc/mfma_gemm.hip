@@ -1,6 +1,6 @@
-// Host side of the bf16 MFMA GEMM: which tile shapes a projection is launched with, the LM head's and the residual
-// epilogue's instantiations, and the reduction of the K slices.  The kernel is in mfma_gemm_kernel.h; the instantiations of
-// the other epilogues are in mfma_gemm_{store,qkv,swiglu,partial}.hip (one compilation each).
+// Host side of the bf16 MFMA GEMM: which tile shapes a projection is launched with, the residual epilogue's instantiations,
+// and the reduction of the K slices.  The kernel is in mfma_gemm_kernel.h; the instantiations of the other epilogues are in
+// mfma_gemm_{store,qkv,swiglu,partial,head}.hip (one compilation each).
 #include "mfma_gemm_kernel.h"
 
 namespace spiffy {
@@ -244,10 +244,6 @@ GemmPlan plan_gemm_mfma(int epi, int M, int N, int ksplit) {
       if (t.bn != 0 && !(t.bm == 256 && t.bn == 192)) try_main(t);
       break;
     }
-    case EPI_LMHEAD:      // vocabulary rows x token columns; the token tiles in use are only known on the device
-      p.n_parts = 1;
-      p.part[0] = {256, 192, 0, N, cdiv(N, BM) * cdiv(M, 192)};
-      break;
     default:
       break;
   }
@@ -348,6 +344,7 @@ GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_u
 hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
   GemmArgs a = a0;
   if (a.ksplit < 1) a.ksplit = 1;
+  if (epi == EPI_LMHEAD) return launch_gemm_head(a, st);     // the shape is chosen on the device
   const bool layer = a.layer && (epi == EPI_QKV || epi == EPI_PARTIAL || epi == EPI_SWIGLU);
   const GemmPlan p = layer ? plan_gemm_layer(epi, a.M, a.N, a.K, a.ksplit) : plan_gemm_mfma(epi, a.M, a.N, a.ksplit);
   if (p.n_parts < 1) return hipErrorInvalidValue;
@@ -375,8 +372,6 @@ hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
       }
       return hipSuccess;
     }
-    case EPI_LMHEAD:
-      return launch_t<EPI_LMHEAD, 192, 3>(a, cdiv(a.N, BM), cdiv(a.M, 192), st);
     default:
       return hipErrorInvalidValue;
   }

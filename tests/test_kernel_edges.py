@@ -157,3 +157,36 @@ def test_tile_gemm_shapes_by_rounds(sp, M, N, K, dtype):
     assert torch.equal(sp.gemm(sp.GEMM_STORE, dev[0][:16].contiguous(), dev[1]), got[:16])
     sw = sp.gemm(sp.GEMM_SWIGLU, *dev)
     assert torch.equal(sp.gemm(sp.GEMM_SWIGLU, dev[0][:16].contiguous(), dev[1], dev[2]), sw[:16])
+
+
+@pytest.mark.parametrize("V,d", [(31900, 192), (31874, 512), (66300, 256)])
+def test_head_rows_do_not_depend_on_the_tile_shape(sp, V, d):
+    """125 tiles of 256 vocabulary rows: 128 x 128 up to 128 rows, 128 x 256 up to 256, 256 x 192 up to 384, 256 x 256 up to 512,
+    256 x 192 again at 571; 259 tiles: 256 x 192 at 160 and 384 rows, 128 x 256 at 256 and 512.  The last tile ends
+    in its first or second half, K of three to eight steps.  Every output equals, bit for bit, that of the states alone, and the
+    top token that of the float64 logits."""
+    G, B = 18, 32
+    cfg = synth.CONFIGS["c1"].scaled(d=d, V=V, G=G, B=B, dtype="bf16")
+    g = torch.Generator().manual_seed(d)
+    x, w = torch.randn((G, B, d), generator=g).bfloat16().to(DEV), (torch.randn((V, d), generator=g) * 0.1).bfloat16().to(DEV)
+    gain = torch.ones(d).bfloat16().to(DEV)
+    tok = torch.full((G, B), cfg.mask_id, dtype=torch.int32)
+    tok[-1, 27:] = 1                                   # 571 rows
+    tok = tok.to(DEV)
+    scfg = sp.cfg_from_synth(cfg)
+    ws = sp.alloc_workspace(scfg, G, B, 0, DEV)
+    head = lambda a, b: sp.decode_head(scfg, x[a:b].contiguous(), gain, w, tok[a:b].contiguous(), 0.01, ws)
+    alone = [head(s, s + 1) for s in range(G)]
+    for n in (3, 5, 6, 8, 12, 16, 18):
+        got = head(0, n)
+        for s in range(n):
+            for k in got:
+                assert torch.equal(got[k][s], alone[s][k][0]), (n, s, k)
+    xd = x.double()
+    nf = (xd / (xd.square().mean(-1, keepdim=True) + cfg.rms_eps).sqrt()).bfloat16().double().view(G * B, d)
+    top = torch.topk((nf @ w.double().T), 2, dim=1)
+    # bf16 products, float32 sums: at most (d + 16) 2^-24 sum |n w| apart; a norm rounded the other way moves a logit by 2^-8 |n w|
+    safe = (top.values[:, 0] - top.values[:, 1]) > 2 * 2.0 ** -8 * (nf.abs() @ w.double().abs().T).amax(1)
+    m = (tok.view(-1) == cfg.mask_id) & safe
+    assert int(m.sum()) >= 100
+    assert torch.equal(torch.cat([a["argmax"].view(-1) for a in alone])[m].long(), top.indices[m, 0])
