@@ -293,7 +293,7 @@ def gemm(epilogue: int, A: torch.Tensor, W0: torch.Tensor, W1: Optional[torch.Te
 
 
 def gemm_plan(epilogue: int, M: int, N: int, K: int, with_workspace: bool = True) -> dict:
-    """The launches spiffy_gemm / verify_layer use for a bf16 projection of that shape (host arithmetic, no device)."""
+    """The launches spiffy_gemm uses for a bf16 projection of that shape (host arithmetic, no device)."""
     p = GemmPlan()
     _check(lib.spiffy_gemm_plan(epilogue, M, N, K, int(with_workspace), C.byref(p)), "spiffy_gemm_plan")
     return {"k_slices": p.k_slices,
