@@ -5,6 +5,7 @@ Usage: python -m paper_2509_18085_amd.build     (cross-compiles without a GPU)
 from __future__ import annotations
 
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -54,6 +55,16 @@ def build(verbose: bool = False) -> str:
     if verbose:
         print("\n".join(o for o in outs if o.strip()))
     return LIB
+
+
+def scratch_bytes(source: str) -> dict:
+    """Kernels of a source file -> bytes of scratch memory a lane, as the compiler reports them (nothing is written)."""
+    out = _run([_hipcc()] + FLAGS + ["--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage",
+                                     os.path.join(CSRC, source), "-o", os.devnull])
+    names = re.findall(r"Function Name: (\S+)", out)
+    sizes = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", out)]
+    assert names and len(names) == len(sizes), out[-2000:]
+    return dict(zip(names, sizes))
 
 
 def build_host_sanitized() -> tuple:
