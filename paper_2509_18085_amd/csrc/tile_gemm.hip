@@ -11,7 +11,7 @@
 // A 16x16 fragment of either type is one 16-byte load per lane whose four lane groups read 64 contiguous bytes of a row; loaded
 // so, straight into registers, half lines of sixteen rows an instruction, a CU gets 14 bytes a clock.  Each wavefront
 // therefore brings its chunk global -> LDS as whole lines (eight rows an instruction) into LDS of its own and reads the
-// fragments there.  Measured, registers -> LDS, us: fp32, 64 rows, QKV 1536 x 1024 8.5 -> 6.2, gate/up 2816 x 1024 18.4 -> 15.7,
+// fragments there (all but the fp32 tiles of 64 x 64).  Measured, registers -> LDS, us: fp32, 64 rows, QKV 1536 x 1024 8.5 -> 6.2, gate/up 2816 x 1024 18.4 -> 15.7,
 // down 1024 x 2816 17.8 -> 9.8; bf16, 128 rows, 8.4 -> 5.6, 13.8 -> 10.1, 17.3 -> 9.1.  (A kernel on vector FMAs with scalar loads
 // took 200 - 340 us for these.)
 #include <type_traits>
@@ -138,6 +138,66 @@ __device__ __forceinline__ void tile_product(const T* const (&src)[2 * (TM + TN)
   }
 }
 
+// The same sums in the same order with the fragments loaded straight into registers, one chunk at a time: `arow` and `wrow` are
+// the lane's rows.  For the fp32 tiles of 64 x 64 (launch_epi says where): one workgroup a CU either way, and without the trip
+// through LDS 1024 rows of 4104 columns, K = 1032, take 118 us instead of 129.
+template <typename T, int TM, int TN>
+__device__ __forceinline__ void tile_product_regs(const T* const (&arow)[TM], const T* const (&wrow)[TN], int K, int wave, int lane,
+                                                  f32x4 (&acc)[TM][TN]) {
+  typedef typename Frag<T>::type frag_t;
+  constexpr int KC = Frag<T>::KC, VEC = Frag<T>::VEC;
+  frag_t fa[2][TM], fw[2][TN];
+  const int k_lane = (lane >> 4) * VEC;
+  auto load_half = [&](int h, int k) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fw[h][j] = *reinterpret_cast<const frag_t*>(wrow[j] + k);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fa[h][i] = *reinterpret_cast<const frag_t*>(arow[i] + k);
+  };
+  auto load = [&](int t) {                         // this wavefront's t-th chunk
+    const int k = (wave + t * NW) * 2 * KC + k_lane;
+    load_half(0, k);
+    load_half(1, k + KC);
+  };
+  auto product = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const f32x4 c = mma(mma(f32x4{0.f, 0.f, 0.f, 0.f}, fa[0][i], fw[0][j]), fa[1][i], fw[1][j]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][j][v] += c[v];
+      }
+  };
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int whole = K / (2 * KC), n = whole > wave ? (whole - wave + NW - 1) / NW : 0;
+  if (n > 0) load(0);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int t = 1; t < n; ++t) {
+    product();
+    load(t);
+    __builtin_amdgcn_sched_barrier(0);             // (the loads stay behind the products: their registers are the same)
+  }
+  if (n > 0) product();
+  if (whole * 2 * KC < K && whole % NW == wave) {  // the chunk that K cuts short: a lane's values are all inside K or all beyond it
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = (2 * whole + h) * KC + k_lane;
+      load_half(h, min(k, K - VEC));
+      if (k >= K) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fw[h][j] = frag_t{};
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[h][i] = frag_t{};
+      }
+    }
+    product();
+  }
+}
+
 // the wavefronts' stages; their sums take the same place afterwards
 constexpr int red_bytes(int tn) { return NW * tn * RSTRIDE * (int)sizeof(float); }
 constexpr int tile_lds(int tm, int tn) {
@@ -179,7 +239,7 @@ __device__ __forceinline__ void store_element(const GemmArgs& a, bool has_bias, 
 }
 
 // C tile of 16*TM rows x 16*TN columns (SWIGLU: TN/2 fragments of gate rows and the same rows of up)
-template <typename T, int EPI, int TM, int TN>
+template <typename T, int EPI, int TM, int TN, bool REGS>
 __global__ __launch_bounds__(64 * NW) void tile_gemm_kernel(GemmArgs a) {
   extern __shared__ __align__(1024) unsigned char smem[];
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
@@ -190,15 +250,25 @@ __global__ __launch_bounds__(64 * NW) void tile_gemm_kernel(GemmArgs a) {
   const int m0 = blockIdx.y * 16 * TM, n0 = blockIdx.x * 16 * NO;
   if (m0 >= m_max) return;
   const int K = a.K;
-  const T* src[2 * (TM + TN)];
-  tile_sources<T, TM, TN>(src, lane, [&](int r) {
+  const auto tile_row = [&](int r) {               // row r of the tile's TM*16 activation and TN*16 weight rows
     if (r < 16 * TM) return (const T*)a.A + (size_t)min(m0 + r, m_max - 1) * a.lda;
     r -= 16 * TM;
     if (EPI == EPI_SWIGLU) return (const T*)(r < 16 * NO ? a.W[0] : a.W[1]) + (size_t)min(n0 + r % (16 * NO), a.N - 1) * K;
     return weight_row<T, EPI>(a, n0 + r);
-  });
+  };
   f32x4 acc[TM][TN];
-  tile_product<T, TM, TN>(src, K, wave, lane, lds0 + wave * stage_bytes(TM, TN), acc);
+  if constexpr (REGS) {
+    const T *arow[TM], *wrow[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) arow[i] = tile_row(16 * i + (lane & 15));
+#pragma unroll
+    for (int j = 0; j < TN; ++j) wrow[j] = tile_row(16 * (TM + j) + (lane & 15));
+    tile_product_regs<T, TM, TN>(arow, wrow, K, wave, lane, acc);
+  } else {
+    const T* src[2 * (TM + TN)];
+    tile_sources<T, TM, TN>(src, lane, tile_row);
+    tile_product<T, TM, TN>(src, K, wave, lane, lds0 + wave * stage_bytes(TM, TN), acc);
+  }
   const bool has_bias = EPI == EPI_STORE && (a.bias[0] || a.bias[1] || a.bias[2]);
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
@@ -403,13 +473,13 @@ __global__ __launch_bounds__(64 * NW) void tile_head_kernel(const T* __restrict_
   else head_tiles<T, 1>(n, wv, d, V, scale, rows, m0, n_part, m_cap, part, smem);
 }
 
-template <typename T, int EPI, int TM, int TN>
+template <typename T, int EPI, int TM, int TN, bool REGS = false>
 hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
-  constexpr int NO = EPI == EPI_SWIGLU ? TN / 2 : TN, LDS = tile_lds(TM, TN);
+  constexpr int NO = EPI == EPI_SWIGLU ? TN / 2 : TN, LDS = REGS ? red_bytes(TN) : tile_lds(TM, TN);
   static std::atomic<unsigned long long> lds_ok{0};
-  const hipError_t e = allow_dynamic_lds((const void*)tile_gemm_kernel<T, EPI, TM, TN>, LDS, lds_ok);
+  const hipError_t e = allow_dynamic_lds((const void*)tile_gemm_kernel<T, EPI, TM, TN, REGS>, LDS, lds_ok);
   if (e != hipSuccess) return e;
-  tile_gemm_kernel<T, EPI, TM, TN><<<dim3(cdiv(a.N, 16 * NO), cdiv(a.M, 16 * TM)), 64 * NW, LDS, st>>>(a);
+  tile_gemm_kernel<T, EPI, TM, TN, REGS><<<dim3(cdiv(a.N, 16 * NO), cdiv(a.M, 16 * TM)), 64 * NW, LDS, st>>>(a);
   return hipGetLastError();
 }
 
@@ -422,8 +492,11 @@ void launch_short(const GemmArgs& a, hipStream_t st) {
 // Tile shapes, measured, us:
 // bf16 runs 64 x 64 tiles (SWIGLU: 32 features) where they fill the chip: a quarter of the operand traffic per product (4104
 // columns, K = 1032: 200 rows, 260 tiles, 13.7, with 32 x 32 14.3, with 32 x 16 15.4; 1024 rows 44.7, 48.4, 56.9; 4096 rows 148, 175,
-// 214).  fp32 does not: 32 x 32 tiles, two workgroups a CU, one adding sums while the other multiplies, were faster
-// throughout (200 rows 32.8, with 64 x 64 50.3; 1024 rows 108, 129; 4096 rows 387, 431).
+// 214).  fp32 has 64 x 64 tiles with fragments in registers, and 32 x 32 tiles in LDS, two workgroups a CU, one adding sums while
+// the other multiplies.  The small ones win while K is short or the large ones leave a round of 256 workgroups half empty; with
+// longer K the large ones' quarter of the traffic does (1024 columns of 2816, 1000 rows: 57 us, small 68; 11008 x 4104, 1000 rows
+// 845, 1076, SwiGLU 3000 rows 5548, 7715; 1536 x 1024, 1000 rows 47, 39).  Of 1700 shapes measured (512 .. 11008 columns, K = 200 .. 8192,
+// 256 .. 3500 large tiles) the line below is 1.1% over the better of both on average, large tiles alone 9%, small ones alone 5%.
 // Below that 32 x 32 or 32 x 16 (SWIGLU: 16 features either way), by rounds of 256 workgroups: one of 32 x 32 takes as long as 1.6 of
 // 32 x 16 in bf16, 1.9 in fp32, and starts sooner (K = 1024, 32 x 16 / 32 x 32: fp32 64 x 2048 6.3 / 8.6, 64 x 3072 9.8 / 8.9, 64 x 4104
 // 13.4 / 15.4; bf16 64 x 1544 3.7 / 4.1, 128 x 1032 4.6 / 4.2, 128 x 2056 5.4 / 5.9).  16 x 16 with one fragment of rows.
@@ -445,8 +518,12 @@ hipError_t launch_epi(const GemmArgs& a, hipStream_t st) {
   }
   if constexpr (!F32)
     if (big >= 256) return launch_tile<T, EPI, 4, 4>(a, st);
-  if (a.M <= 16) return launch_tile<T, EPI, 1, EPI == EPI_SWIGLU ? 2 : 1>(a, st);
   const int rows = cdiv(a.M, 32), r16 = cdiv(rows * cdiv(a.N, 16), 256), r32 = cdiv(rows * cdiv(a.N, 32), 256);
+  if constexpr (F32) {
+    const long long r64 = cdiv(big, 256), small = EPI == EPI_SWIGLU ? r16 : r32;      // rounds of either tile
+    if (big >= 256 && 57 * r64 * (a.K + 500) <= 20 * small * (a.K + 300)) return launch_tile<T, EPI, 4, 4, true>(a, st);
+  }
+  if (a.M <= 16) return launch_tile<T, EPI, 1, EPI == EPI_SWIGLU ? 2 : 1>(a, st);
   if (EPI == EPI_SWIGLU || (F32 ? 19 * r32 - 2 < 10 * r16 : 16 * r32 < 10 * r16)) return launch_tile<T, EPI, 2, 2>(a, st);
   if constexpr (EPI != EPI_SWIGLU) return launch_tile<T, EPI, 2, 1>(a, st);
   return hipErrorInvalidValue;

@@ -159,6 +159,34 @@ def test_tile_gemm_shapes_by_rounds(sp, M, N, K, dtype):
     assert torch.equal(sp.gemm(sp.GEMM_SWIGLU, dev[0][:16].contiguous(), dev[1], dev[2]), sw[:16])
 
 
+@pytest.mark.parametrize("K", [200, 264, 2824])
+def test_large_fp32_tiles(sp, K):
+    """fp32 tiles of 64 x 64 with fragments in registers (16 x 16 of them, the last rows and columns ragged): a last chunk of 8
+    values, wavefronts without a chunk.  Bounds and row identity as for the other tiles; SwiGLU with both sums' errors
+    propagated: |silu'| <= 1.1, |silu(g)| <= |g|, its exponential and division within 2^-20 relative."""
+    M, N, F = 1000, 1016, 504
+    g = torch.Generator().manual_seed(K)
+    A, W0, W1, R = (torch.randn(s, generator=g) * f for s, f in (((M, K), 1.0), ((N, K), 0.1), ((F, K), 0.1), ((M, N), 1.0)))
+    a, w0, w1, r = (t.double().numpy() for t in (A, W0, W1, R))
+    eps = (K + 16) * 2.0 ** -24
+    dev = [t.to(DEV) for t in (A, W0, W1, R)]
+    ref, d0 = a @ w0.T, eps * (np.abs(a) @ np.abs(w0).T)
+    store, resid = sp.gemm(sp.GEMM_STORE, dev[0], dev[1]), sp.gemm(sp.GEMM_RESID, dev[0], dev[1], R=dev[3])
+    assert (np.abs(to_np(store) - ref) <= d0 + 2.0 ** -24 * np.abs(ref)).all()
+    assert (np.abs(to_np(resid) - ref - r) <= d0 + 2.0 ** -22 * (np.abs(ref) + np.abs(r))).all()
+    gate, up = ref[:, :F], a @ w1.T
+    silu = gate / (1 + np.exp(-gate))
+    d1 = eps * (np.abs(a) @ np.abs(w1).T)
+    wg = dev[1][:F].contiguous()
+    sw = sp.gemm(sp.GEMM_SWIGLU, dev[0], wg, dev[2])
+    assert (np.abs(to_np(sw) - silu * up) <= 1.1 * d0[:, :F] * (np.abs(up) + d1) + np.abs(silu) * d1 + 2.0 ** -19 * np.abs(silu * up) + 1e-30).all()
+    for lo, hi in ((0, 16), (990, 1000)):                # alone: 16 x 16 tiles
+        x = dev[0][lo:hi].contiguous()
+        assert torch.equal(sp.gemm(sp.GEMM_STORE, x, dev[1]), store[lo:hi])
+        assert torch.equal(sp.gemm(sp.GEMM_RESID, x, dev[1], R=dev[3][lo:hi].contiguous()), resid[lo:hi])
+        assert torch.equal(sp.gemm(sp.GEMM_SWIGLU, x, wg, dev[2]), sw[lo:hi])
+
+
 @pytest.mark.parametrize("V,d", [(31900, 192), (31874, 512), (66300, 256)])
 def test_head_rows_do_not_depend_on_the_tile_shape(sp, V, d):
     """125 tiles of 256 vocabulary rows: 128 x 128 up to 128 rows, 128 x 256 up to 256, 256 x 192 up to 384, 256 x 256 up to 512,
