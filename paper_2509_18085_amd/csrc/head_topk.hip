@@ -7,15 +7,15 @@
 // the K maxima; equal logits go to the lower token id and chunks are contiguous id ranges), so only those
 // K x 128 logits are recomputed - 1/250 of a second pass over the vocabulary matrix at V = 126k:
 //   topk_refine_kernel   workgroup (position b, k, slice): picks the k-th best chunk of the row and recomputes
-//                        kRefineRows of its 128 logits, four vocabulary rows a wavefront at a time
+//                        a part of its 128 logits, four vocabulary rows a wavefront at a time
 //   topk_full_kernel     path without chunk summaries (fp32 / shapes the MFMA head does not take): one
 //                        workgroup per position scans the whole vocabulary, K best candidates
-//   topk_merge_kernel    one wavefront per position: K best of the K x 128 logits (of the K candidates),
+//   topk_merge_kernel    one workgroup per position: K best of the K x 128 logits (of the K candidates),
 //                        probabilities from the row's (top logit, sum of exponentials); the row's argmax stays
 //                        first with exactly the confidence the head reported
 //
 // The refinement is bound by what a compute unit can fetch (25 - 50 GB/s: a chunk of 4096-wide bf16 rows is 1 MB), so a
-// chunk is shared by eight workgroups, each of which picks the chunk again (a few loads from L2).
+// chunk is shared by up to eight workgroups, each of which picks the chunk again (refine_slices).
 #include "kernels.h"
 
 namespace spiffy {
@@ -37,14 +37,30 @@ __device__ __forceinline__ int find_row(const int32_t* __restrict__ row_idx, int
 // (value, index) ordering of the drafting source: larger value first, equal values to the lower index
 __device__ __forceinline__ bool better(float v, int i, float v2, int i2) { return v > v2 || (v == v2 && i < i2); }
 
-// best (value, index) over the wavefront
+// best (value, index) over the wavefront, in the steps of wave_reduce
+__device__ __forceinline__ void keep_better(float& v, int& i, float v2, int i2) {
+  const bool b = better(v2, i2, v, i);
+  v = b ? v2 : v;
+  i = b ? i2 : i;
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true); }
 __device__ __forceinline__ void wave_best(float& v, int& i) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float v2 = __shfl_xor(v, o, 64);
-    const int i2 = __shfl_xor(i, o, 64);
-    if (better(v2, i2, v, i)) { v = v2; i = i2; }
-  }
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 rv = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  u32x2 ri = __builtin_amdgcn_permlane32_swap((unsigned)i, (unsigned)i, false, false);
+  v = __uint_as_float(rv[0]);
+  i = (int)ri[0];
+  keep_better(v, i, __uint_as_float(rv[1]), (int)ri[1]);
+  rv = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  ri = __builtin_amdgcn_permlane16_swap((unsigned)i, (unsigned)i, false, false);
+  v = __uint_as_float(rv[0]);
+  i = (int)ri[0];
+  keep_better(v, i, __uint_as_float(rv[1]), (int)ri[1]);
+  keep_better(v, i, spiffy::dpp_move<0x128>(v), dpp_move<0x128>(i));
+  keep_better(v, i, spiffy::dpp_move<0x1B>(spiffy::dpp_move<0x141>(v)), dpp_move<0x1B>(dpp_move<0x141>(i)));
+  keep_better(v, i, spiffy::dpp_move<0x4E>(v), dpp_move<0x4E>(i));
+  keep_better(v, i, spiffy::dpp_move<0xB1>(v), dpp_move<0xB1>(i));
 }
 
 template <typename T>
@@ -95,10 +111,17 @@ __device__ __forceinline__ void dot_rows4<float>(const float* __restrict__ x, co
   for (int u = 0; u < 4; ++u) out[u] = dot_row<float>(x, w + (size_t)u * d, d, lane);
 }
 
-// vocabulary rows of a chunk that one workgroup of the refinement takes: 16, four per wavefront.  24 positions, 2 chunks each
-// of 4096 bf16 columns (50 MB): 55.9 us with a workgroup a chunk (48 at work), 14.9 us with eight.
-constexpr int kRefineRows = 16;
-
+// Workgroups that share a chunk: enough to have 256 + d / 4 at work, at most eight.  Each picks the chunk again (K rounds over the
+// row's summaries), which the narrow widths notice and the wide ones do not.  24 positions, 2 chunks each of 4096 bf16 columns
+// (50 MB): 55.9 us with a workgroup a chunk, 14.9 us with eight.  32 positions of 126464 tokens, us with one, two, four,
+// eight: K = 8, width 4096 64.0, 48.1, 48.7, 51.6; width 512 25.0, 24.8, 27.6, 33.0; 128 positions, K = 8, width 512 35.6, 47.0, 51.7,
+// 70.4.  Over 152 shapes measured (V 130 .. 262144, width 256 .. 8192) this is 1.1% over the best, eight throughout 9%.
+inline int refine_slices(int B, int K, int d) {
+  const int limit = d < 7168 ? 256 + d / 4 : 2048;
+  int n = 8;
+  while (n > 1 && B * K * n > limit) n /= 2;
+  return n;
+}
 template <typename T>
 __global__ __launch_bounds__(256) void topk_refine_kernel(HeadTopkArgs a) {
   __shared__ float s_val[2][4];
@@ -147,7 +170,8 @@ __global__ __launch_bounds__(256) void topk_refine_kernel(HeadTopkArgs a) {
   // accumulation order: the logits are those of one row after the other)
   const T* x = reinterpret_cast<const T*>(a.nf) + (size_t)r * a.d;
   float* logits = a.logits + ((size_t)b * KMAX + k) * 128;
-  for (int i = blockIdx.z * kRefineRows + w * 4; i < (int)(blockIdx.z + 1) * kRefineRows; i += 16) {
+  const int rows = 128 / (int)gridDim.z;
+  for (int i = blockIdx.z * rows + w * 4; i < (int)(blockIdx.z + 1) * rows; i += 16) {
     const int v0 = chunk * 128 + i;
     float l[4];
     if (v0 + 3 < a.V) {
@@ -216,10 +240,14 @@ __global__ __launch_bounds__(256) void topk_full_kernel(HeadTopkArgs a) {
   }
 }
 
-// CHUNKS: the candidates are the logits of the row's K best chunks; otherwise the K best of the whole vocabulary
+// CHUNKS: the candidates are the logits of the row's K best chunks; otherwise the K best of the whole vocabulary.  A wavefront a
+// chunk finds the chunk's best, then the first takes the best of those: 2 (K - 1) rounds of a wavefront's best with one or two
+// candidates a lane.  (One wavefront with sixteen candidates a lane is a chain of comparisons: K = 8 13 - 19 us, 7 - 10 so.)
 template <bool CHUNKS>
-__global__ __launch_bounds__(64) void topk_merge_kernel(HeadTopkArgs a) {
-  const int b = blockIdx.x, lane = threadIdx.x;
+__global__ __launch_bounds__(64 * KMAX) void topk_merge_kernel(HeadTopkArgs a) {
+  __shared__ float s_v[KMAX][KMAX];
+  __shared__ int s_i[KMAX][KMAX];
+  const int b = blockIdx.x, lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int node = a.result ? a.result->node : a.node;
   int32_t* ot = a.out_tokens + (size_t)b * a.K;
   float* op = a.out_probs + (size_t)b * a.K;
@@ -227,7 +255,7 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(HeadTopkArgs a) {
   const int f = node_ok ? node * a.B + b : 0;
   const int r = node_ok ? find_row(a.row_idx, min(*a.count, a.G * a.B), f) : -1;
   if (r < 0) {                                      // not masked: nothing to draft here
-    if (lane < a.K) { ot[lane] = node_ok ? a.tokens[f] : -1; op[lane] = 0.f; }
+    if (w == 0 && lane < a.K) { ot[lane] = node_ok ? a.tokens[f] : -1; op[lane] = 0.f; }
     return;
   }
   const TopPartial top = a.row_top[r];
@@ -236,42 +264,50 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(HeadTopkArgs a) {
   // chunk's K best, or come second).  The other K-1 places go to the best candidates other than that token; a
   // candidate whose recomputed logit exceeds the head's top logit is held at it, so probabilities never increase
   // along a row.
-  if (lane == 0) { ot[0] = top.idx; op[0] = 1.0f / top.s; }
-  // the lane's candidates: elements lane and lane + 64 of every chunk, or element lane of the candidate list
-  constexpr int NC = CHUNKS ? 2 * KMAX : 1;
-  float cv[NC];
-  int ci[NC];
+  constexpr int NONE = 0x7fffffff;                  // of value -inf
+  float v = -INFINITY;
+  int i = NONE;
+  if (CHUNKS) {
+    float cv[2];
+    int ci[2];
+    const int chunk = a.chunk_id[b * KMAX + w];     // uniform
 #pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    cv[q] = -INFINITY;
-    ci[q] = -1;
-    if (CHUNKS) {
-      const int k = q >> 1, chunk = k < a.K ? a.chunk_id[b * KMAX + k] : -1, e = lane + 64 * (q & 1);
-      if (chunk >= 0) {
-        cv[q] = a.logits[((size_t)b * KMAX + k) * 128 + e];
-        ci[q] = chunk * 128 + e;
-      }
-    } else if (lane < a.K) {
-      cv[q] = a.cand_val[(size_t)b * KMAX * KMAX + lane];
-      ci[q] = a.cand_idx[(size_t)b * KMAX * KMAX + lane];
+    for (int q = 0; q < 2; ++q) {
+      const int e = lane + 64 * q;
+      cv[q] = chunk >= 0 ? a.logits[((size_t)b * KMAX + w) * 128 + e] : -INFINITY;
+      ci[q] = chunk * 128 + e;
+      if (chunk < 0 || ci[q] == top.idx) { cv[q] = -INFINITY; ci[q] = NONE; }
     }
-    if (ci[q] < 0 || ci[q] == top.idx) { cv[q] = -INFINITY; ci[q] = -1; }
-  }
-  for (int j = 1; j < a.K; ++j) {
-    float bk = -INFINITY;
-    int bi = 0x7fffffff;
+    for (int j = 1; j < a.K; ++j) {
+      float bv = cv[0];
+      int bi = ci[0];
+      keep_better(bv, bi, cv[1], ci[1]);
+      wave_best(bv, bi);
+      if (lane == 0) { s_v[w][j] = bv; s_i[w][j] = bv == -INFINITY ? NONE : bi; }
 #pragma unroll
-    for (int q = 0; q < NC; ++q)
-      if (ci[q] >= 0 && better(cv[q], ci[q], bk, bi)) { bk = cv[q]; bi = ci[q]; }
-    wave_best(bk, bi);
-    const bool any = bk != -INFINITY;               // -inf: no candidate is left
+      for (int q = 0; q < 2; ++q)
+        if (ci[q] == bi) { cv[q] = -INFINITY; ci[q] = NONE; }
+    }
+    __syncthreads();
+    if (w > 0) return;
+    const int k = lane / KMAX, j = lane % KMAX;
+    if (k < a.K && j > 0 && j < a.K) { v = s_v[k][j]; i = s_i[k][j]; }
+  } else if (lane < a.K) {
+    i = a.cand_idx[(size_t)b * KMAX * KMAX + lane];
+    v = a.cand_val[(size_t)b * KMAX * KMAX + lane];
+    if (i < 0 || i == top.idx) { v = -INFINITY; i = NONE; }
+  }
+  if (lane == 0) { ot[0] = top.idx; op[0] = 1.0f / top.s; }
+  for (int j = 1; j < a.K; ++j) {
+    float bv = v;
+    int bi = i;
+    wave_best(bv, bi);
+    const bool any = bv != -INFINITY;               // -inf: no candidate is left
     if (lane == 0) {
       ot[j] = any ? bi : -1;
-      op[j] = any ? __expf(fminf(bk, top.m) - top.m) / top.s : 0.f;
+      op[j] = any ? __expf(fminf(bv, top.m) - top.m) / top.s : 0.f;
     }
-#pragma unroll
-    for (int q = 0; q < NC; ++q)
-      if (ci[q] == bi) { cv[q] = -INFINITY; ci[q] = -1; }
+    if (i == bi) { v = -INFINITY; i = NONE; }
   }
 }
 
@@ -281,8 +317,8 @@ hipError_t launch_head_topk(const HeadTopkArgs& a, hipStream_t st) {
   if (a.K < 1 || a.K > KMAX || a.B < 1) return hipErrorInvalidValue;
   if (a.n_part > 0) {
     if (a.n_part > 2048 || a.dtype != SPIFFY_BF16 || a.d % 8 != 0) return hipErrorInvalidValue;
-    topk_refine_kernel<bf16_t><<<dim3(a.B, a.K, 128 / kRefineRows), 256, 0, st>>>(a);
-    topk_merge_kernel<true><<<a.B, 64, 0, st>>>(a);
+    topk_refine_kernel<bf16_t><<<dim3(a.B, a.K, refine_slices(a.B, a.K, a.d)), 256, 0, st>>>(a);
+    topk_merge_kernel<true><<<a.B, 64 * a.K, 0, st>>>(a);
     return hipGetLastError();
   }
   if (a.dtype == SPIFFY_F32) {

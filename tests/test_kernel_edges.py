@@ -27,6 +27,16 @@ def test_topk_slices_of_the_last_chunk(sp, V, K, B):
     check_head_topk(sp, cfg, st, synth.hidden_states(cfg), synth.head_weights(cfg), 6.0, K, (0, 1))
 
 
+@pytest.mark.parametrize("V,K,B", [(1003, 7, 10), (2049, 6, 24), (1003, 4, 76), (90, 8, 3)])
+def test_topk_shared_by_fewer_workgroups(sp, V, K, B):
+    """Four, two and one workgroup a chunk; fewer chunks than K, so that wavefronts of the merge have none."""
+    from test_gpu_parity import check_head_topk
+    cfg = synth.CONFIGS["c1"].scaled(dtype="bf16", d=192, V=V, B=B, G=2)
+    st = synth.random_states(cfg.G, cfg.B, cfg.V, 0.2, 0.9, 4)
+    st[1, :] = cfg.mask_id
+    check_head_topk(sp, cfg, st, synth.hidden_states(cfg), synth.head_weights(cfg), 6.0, K, (0, 1))
+
+
 @pytest.mark.parametrize("B,G,P,hq,hkv", [(24, 44, 130, 16, 8), (7, 150, 64, 16, 16), (40, 27, 0, 28, 4), (1, 1030, 65, 16, 2)])
 def test_attention_rows_of_any_block_do_not_depend_on_the_query_tile(sp, B, G, P, hq, hkv):
     """Blocks that neither divide 32 nor are multiples of it: the groups of own-block keys start anywhere, and 128-, 64- and
