@@ -10,15 +10,16 @@ namespace {
 //   vocabulary x tokens   time of a round, relative (products 1024 .. 4096 deep)
 //   256 x 192             50
 //   256 x 256             61      385 .. 512 rows: two token tiles instead of three
-//   128 x 256             34      half the vocabulary: fills rounds that 256 leave half empty
+//   128 x 256             35      half the vocabulary: fills rounds that 256 leave half empty
 //   128 x 128             25      the same up to 128 rows, where the weight stream is the bound
 // The times are the ones with the least regret over 76 measured launches (vocabularies of 32000, 126464 and 152064, 8 .. 1000
-// rows): 0.3% over the best shape of each launch, 256 x 192 alone 10.2%.  Whole heads, us, 256 x 192 alone -> this rule:
+// rows), 0.3% over the best shape of each launch, 256 x 192 alone 10.2%, and over 128 of 512 .. 6144 rows (1280 .. 200000
+// tokens), where a round of 128 x 256 at 34 was chosen at 1640 rows of 32000 (241 us, 256 x 256 229).  Whole heads, us, 256 x 192 alone -> this rule:
 // 152064 x 3584 at 24 rows 246 -> 223, at 250 rows 378 -> 308, at 440 rows 529 -> 470; 126464 x 4096 at 250 rows 358 -> 258, at
 // 1000 rows 958 -> 837; 32000 x 2048 at 24 rows 57 -> 49.  256 x 128 (250 rows of 126464 302, of 32000 59) is ahead of none of
 // them by more than 3%.
 // The summaries are per 128 vocabulary rows in every shape and added up in the same order: a row's bits do not depend on it.
-constexpr int T_256_192 = 50, T_256_256 = 61, T_128_256 = 34, T_128_128 = 25;
+constexpr int T_256_192 = 50, T_256_256 = 61, T_128_256 = 35, T_128_128 = 25;
 
 enum Shape { S_256_192, S_256_256, S_128_256, S_128_128 };
 __host__ __device__ __forceinline__ Shape head_shape(int rows, int tiles) {       // tiles of 256 vocabulary rows
