@@ -196,7 +196,7 @@ int spiffy_gemm(int32_t dtype, int32_t epilogue, const void *A, const void *W0, 
 
 /* How spiffy_gemm would launch a bf16 projection of M rows, N output columns (SPIFFY_GEMM_SWIGLU: N
  * features) and inner size K on the MFMA kernel: host arithmetic only, nothing is launched and no device is touched.
- * (tiles of 256, 128, 64 and 32 rows; verify_layer starts from this plan and also has heights in between)
+ * (tiles of 256, 128, 64 and 32 rows; spiffy_layer_gemm_plan says what verify_layer launches)
  * The choice is scheduling: the order of the K sum of an output element does not depend on it (Sec. 4.3: states of one
  * step are independent rows), only k_slices does, and k_slices depends on (N, K) alone.  with_workspace: as for
  * spiffy_gemm, SPIFFY_GEMM_RESID slices K only when scratch is given.  Returns SPIFFY_ESHAPE for shapes the MFMA
@@ -212,6 +212,20 @@ typedef struct {
 } spiffy_gemm_plan_t;
 int spiffy_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t with_workspace,
                      spiffy_gemm_plan_t *plan);
+
+/* How spiffy_verify_layer and the steps launch a bf16 projection on the MFMA kernel (tiles of 32 to 384 rows, chosen by
+ * measured costs): SPIFFY_GEMM_STORE the fused q | k | v projection (N = all its columns, heads of 128), SPIFFY_GEMM_RESID
+ * the output and down projections, SPIFFY_GEMM_SWIGLU gate and up (N features).  M = G*B rows and M_tail rows that ride
+ * along (suffix or finished block; 0 without): plans [2], *n_ranges = 1 for one launch sequence over all M + M_tail rows,
+ * 2 for one over either.  Host arithmetic only.  Status as for spiffy_gemm_plan. */
+int spiffy_layer_gemm_plan(int32_t epilogue, int32_t M, int32_t M_tail, int32_t N, int32_t K,
+                           spiffy_gemm_plan_t *plans, int32_t *n_ranges);
+
+/* spiffy_gemm (bf16, SPIFFY_GEMM_RESID or SPIFFY_GEMM_SWIGLU) in the tiles a layer's projection of that shape takes: the
+ * same bits as spiffy_gemm with scratch.  SPIFFY_ESHAPE for shapes the MFMA kernel does not take, SPIFFY_EINVAL for other
+ * epilogues or without the scratch that a sliced K needs. */
+int spiffy_layer_gemm(int32_t epilogue, const void *A, const void *W0, const void *W1, const void *R, void *C, int32_t M,
+                      int32_t N, int32_t K, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Acceptance walk (Alg. 1 step 5).  graph_edges [E,2] int32 (parent, child), E >= 0;
  * draft_states, target_states [G,B] int32; 0 <= root < G <= SPIFFY_MAX_G.  Starting at root, move

@@ -247,34 +247,22 @@ RopeArgs rope_args(const spiffy_model_cfg* cfg, void* tab, int M, int B, int S_s
   return RopeArgs{(float2*)tab, B + S_seq, B, cfg->head_dim / 2, pos0, tail_pos0, attn_on_mfma(cfg, M) ? 1 : 0, cfg->rope_base};
 }
 
-// The same product as two launches over the row ranges [0, rows_a) and [rows_a, rows_a + rows_b): each range gets the
-// tile shape that suits its height (a ragged total would otherwise pay a whole extra round of the tall tiles).
-// Rows are independent and the K order of an element does not depend on the shape, so nothing else changes.
-hipError_t launch_gemm_mfma_rows(int epi, GemmArgs g, int rows_a, int rows_b, int dtype, hipStream_t st) {
+// A projection of a layer over the rows [0, rows_a) and [rows_a, rows_a + rows_b), as `plan` says.
+hipError_t launch_gemm_rows(int epi, GemmArgs g, const RowsPlan& plan, int rows_a, int rows_b, int dtype, hipStream_t st) {
   const size_t es = esize(dtype), ces = epi == EPI_PARTIAL ? sizeof(float) : es;
-  g.Mz = rows_a + rows_b;
-  // one launch when there are few rows in all (weight streaming sets the time: stream them once, not twice) or when the
-  // measured costs of the tile shapes say that it is no longer than two
-  float one = 0.f, a_us = 0.f, b_us = 0.f;
-  const int ks = g.ksplit < 1 ? 1 : g.ksplit;
-  plan_gemm_layer(epi, rows_a + rows_b, g.N, g.K, ks, &one);
-  plan_gemm_layer(epi, rows_a, g.N, g.K, ks, &a_us);
-  plan_gemm_layer(epi, rows_b, g.N, g.K, ks, &b_us);
-  if (rows_a + rows_b <= 512 || one <= a_us + b_us) {
-    g.M = rows_a + rows_b;
-    return launch_gemm_mfma(epi, g, st);
-  }
+  g.Mz = g.M = rows_a + rows_b;
+  if (plan.n_ranges == 1) return launch_gemm_plan(epi, g, plan.range[0], st);
   GemmArgs a = g;
   a.M = rows_a;
-  hipError_t e = launch_gemm_mfma(epi, a, st);
-  if (e != hipSuccess || rows_b == 0) return e;
+  const hipError_t e = launch_gemm_plan(epi, a, plan.range[0], st);
+  if (e != hipSuccess) return e;
   GemmArgs b = g;
   b.M = rows_b;
   b.A = reinterpret_cast<const char*>(g.A) + (size_t)rows_a * g.lda * es;
   b.C = reinterpret_cast<char*>(g.C) + (size_t)rows_a * g.ldc * ces;
   if (g.R) b.R = reinterpret_cast<const char*>(g.R) + (size_t)rows_a * g.ldc * es;
   b.qkv.row0 += rows_a;
-  return launch_gemm_mfma(epi, b, st);
+  return launch_gemm_plan(epi, b, plan.range[1], st);
 }
 
 int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const spiffy_prefix_kv* prefix,
@@ -291,9 +279,8 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   const bool mf = layer_mfma(cfg);
   const LayerWs ws = carve_layer(cfg, G, B, prefix->P + prefix->S, workspace, S_seq);
   int rc;
-  auto mfma_rows = [&](int epi, GemmArgs ga) {
-    ga.layer = 1;
-    return S_seq ? launch_gemm_mfma_rows(epi, ga, G * B, S_seq, dt, st) : launch_gemm_mfma(epi, ga, st);
+  auto mfma_rows = [&](int epi, const GemmArgs& ga) {
+    return launch_gemm_rows(epi, ga, plan_gemm_rows(epi, G * B, S_seq, ga.N, ga.K, ga.ksplit), G * B, S_seq, dt, st);
   };
   if (chain) chain->normed_out = false;
   if (!(chain && chain->normed_in) &&
@@ -521,6 +508,62 @@ int check_accept_args(const int32_t* edges, int32_t E, const int32_t* draft, con
   return SPIFFY_OK;
 }
 
+// arguments of a projection alone, without pointers
+GemmArgs gemm_shape(int epilogue, int M, int N, int K) {
+  GemmArgs g;
+  std::memset(&g, 0, sizeof(g));
+  g.M = M; g.N = N; g.K = K; g.lda = K; g.ldc = N; g.scale = 1.f;
+  if (epilogue != SPIFFY_GEMM_SWIGLU) g.Nseg[0] = N;
+  return g;
+}
+
+// a projection alone; layer: in the tiles that a layer's projections take (the matrix-core kernel only)
+int gemm_call(int dtype, int epilogue, const void* A, const void* W0, const void* W1, const void* R, void* C, int M, int N, int K,
+              void* workspace, size_t workspace_bytes, hipStream_t st, bool layer) {
+  if (dtype != SPIFFY_BF16 && dtype != SPIFFY_F32) return SPIFFY_EINVAL;
+  if (epilogue < SPIFFY_GEMM_STORE || epilogue > SPIFFY_GEMM_SWIGLU) return SPIFFY_EINVAL;
+  if (!A || !W0 || !C || M < 1 || N < 1 || K < 1) return SPIFFY_EINVAL;
+  if (epilogue == SPIFFY_GEMM_SWIGLU && !W1) return SPIFFY_EINVAL;
+  if (epilogue == SPIFFY_GEMM_RESID && !R) return SPIFFY_EINVAL;
+  if (K % 8 != 0 || N % 8 != 0) return SPIFFY_ESHAPE;
+  if (!aligned16(A) || !aligned16(W0) || !aligned16(C) || (W1 && !aligned16(W1)) || (R && !aligned16(R)))
+    return SPIFFY_EALIGN;
+  GemmArgs g = gemm_shape(epilogue, M, N, K);
+  g.A = A; g.C = C; g.R = R; g.W[0] = W0;
+  if (epilogue == SPIFFY_GEMM_SWIGLU) g.W[1] = W1;
+  const bool mf = dtype == SPIFFY_BF16 && mfma_gemm_supported(epilogue, g);
+  if (layer && !mf) return SPIFFY_ESHAPE;
+  const auto launch = [&](int epi) {
+    return dev(layer ? launch_gemm_plan(epi, g, plan_gemm_layer(epi, M, N, K, g.ksplit), st) : launch_gemm_mfma(epi, g, st));
+  };
+  if (mf && epilogue == SPIFFY_GEMM_RESID) {     // same K slicing as verify_layer when scratch is given
+    const int ks = mfma_ksplit(N, K);
+    if (ks > 1 && layer && !workspace) return SPIFFY_EINVAL;
+    if (ks > 1 && workspace) {
+      if (reinterpret_cast<uintptr_t>(workspace) & 255u) return SPIFFY_EALIGN;
+      if (workspace_bytes < sizeof(float) * (size_t)ks * M * N) return SPIFFY_EWORKSPACE;
+      g.C = workspace; g.ksplit = ks;
+      const int rc = launch(EPI_PARTIAL);
+      if (rc) return rc;
+      return dev(launch_splitk_reduce((const float*)workspace, ks, R, C, nullptr, 0.f, nullptr, M, N, st));
+    }
+  }
+  return mf ? launch(epilogue) : dev(launch_gemm_tile(dtype, epilogue, g, st));
+}
+
+void put_plan(const GemmPlan& p, int k_slices, spiffy_gemm_plan_t* plan) {
+  std::memset(plan, 0, sizeof(*plan));
+  plan->n_launches = p.n_parts;
+  plan->k_slices = k_slices;
+  for (int i = 0; i < p.n_parts; ++i) {
+    plan->launch[i].tile_rows = p.part[i].bm;
+    plan->launch[i].tile_cols = p.part[i].bn;
+    plan->launch[i].col0 = p.part[i].col0;
+    plan->launch[i].n_cols = p.part[i].ncols;
+    plan->launch[i].workgroups = p.part[i].workgroups;
+  }
+}
+
 // Device address of `scratch` on the current device: looked up once per device, with that device current.
 int static_scratch_ptr(void** out) {
   static std::mutex mu;
@@ -647,56 +690,39 @@ int spiffy_decode_head_static(const spiffy_model_cfg* cfg, const void* hidden, c
 
 int spiffy_gemm(int32_t dtype, int32_t epilogue, const void* A, const void* W0, const void* W1, const void* R,
                 void* C, int32_t M, int32_t N, int32_t K, void* workspace, size_t workspace_bytes, void* stream) {
-  if (dtype != SPIFFY_BF16 && dtype != SPIFFY_F32) return SPIFFY_EINVAL;
-  if (epilogue < SPIFFY_GEMM_STORE || epilogue > SPIFFY_GEMM_SWIGLU) return SPIFFY_EINVAL;
-  if (!A || !W0 || !C || M < 1 || N < 1 || K < 1) return SPIFFY_EINVAL;
-  if (epilogue == SPIFFY_GEMM_SWIGLU && !W1) return SPIFFY_EINVAL;
-  if (epilogue == SPIFFY_GEMM_RESID && !R) return SPIFFY_EINVAL;
-  if (K % 8 != 0 || N % 8 != 0) return SPIFFY_ESHAPE;
-  if (!aligned16(A) || !aligned16(W0) || !aligned16(C) || (W1 && !aligned16(W1)) || (R && !aligned16(R)))
-    return SPIFFY_EALIGN;
-  GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.A = A; g.lda = K; g.M = M; g.K = K; g.N = N; g.C = C; g.ldc = N; g.R = R; g.scale = 1.f;
-  g.W[0] = W0;
-  if (epilogue == SPIFFY_GEMM_SWIGLU) g.W[1] = W1; else g.Nseg[0] = N;
-  const bool mf = dtype == SPIFFY_BF16 && mfma_gemm_supported(epilogue, g);
-  hipStream_t st = (hipStream_t)stream;
-  if (mf && epilogue == SPIFFY_GEMM_RESID) {     // same K slicing as verify_layer when scratch is given
-    const int ks = mfma_ksplit(N, K);
-    if (ks > 1 && workspace) {
-      if (reinterpret_cast<uintptr_t>(workspace) & 255u) return SPIFFY_EALIGN;
-      if (workspace_bytes < sizeof(float) * (size_t)ks * M * N) return SPIFFY_EWORKSPACE;
-      g.C = workspace; g.ksplit = ks;
-      int rc = dev(launch_gemm_mfma(EPI_PARTIAL, g, st));
-      if (rc) return rc;
-      return dev(launch_splitk_reduce((const float*)workspace, ks, R, C, nullptr, 0.f, nullptr, M, N, st));
-    }
-  }
-  return dev(mf ? launch_gemm_mfma(epilogue, g, st) : launch_gemm_tile(dtype, epilogue, g, st));
+  return gemm_call(dtype, epilogue, A, W0, W1, R, C, M, N, K, workspace, workspace_bytes, (hipStream_t)stream, false);
+}
+
+int spiffy_layer_gemm(int32_t epilogue, const void* A, const void* W0, const void* W1, const void* R, void* C, int32_t M,
+                      int32_t N, int32_t K, void* workspace, size_t workspace_bytes, void* stream) {
+  if (epilogue == SPIFFY_GEMM_STORE) return SPIFFY_EINVAL;
+  return gemm_call(SPIFFY_BF16, epilogue, A, W0, W1, R, C, M, N, K, workspace, workspace_bytes, (hipStream_t)stream, true);
 }
 
 int spiffy_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t with_workspace,
                      spiffy_gemm_plan_t* plan) {
   if (!plan || epilogue < SPIFFY_GEMM_STORE || epilogue > SPIFFY_GEMM_SWIGLU) return SPIFFY_EINVAL;
   if (M < 1 || N < 1 || K < 1) return SPIFFY_ESHAPE;
-  GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.M = M; g.N = N; g.K = K; g.lda = K; g.ldc = N;
-  if (epilogue != SPIFFY_GEMM_SWIGLU) g.Nseg[0] = N;
-  if (!mfma_gemm_supported(epilogue, g)) return SPIFFY_ESHAPE;
+  if (!mfma_gemm_supported(epilogue, gemm_shape(epilogue, M, N, K))) return SPIFFY_ESHAPE;
   int epi = epilogue, ks = 1;
   if (epilogue == SPIFFY_GEMM_RESID && with_workspace && mfma_ksplit(N, K) > 1) { epi = EPI_PARTIAL; ks = mfma_ksplit(N, K); }
-  const GemmPlan p = plan_gemm_mfma(epi, M, N, ks);
-  std::memset(plan, 0, sizeof(*plan));
-  plan->n_launches = p.n_parts;
-  plan->k_slices = ks;
-  for (int i = 0; i < p.n_parts; ++i) {
-    plan->launch[i].tile_rows = p.part[i].bm;
-    plan->launch[i].tile_cols = p.part[i].bn;
-    plan->launch[i].col0 = p.part[i].col0;
-    plan->launch[i].n_cols = p.part[i].ncols;
-    plan->launch[i].workgroups = p.part[i].workgroups;
+  put_plan(plan_gemm_mfma(epi, M, N, ks), ks, plan);
+  return SPIFFY_OK;
+}
+
+int spiffy_layer_gemm_plan(int32_t epilogue, int32_t M, int32_t M_tail, int32_t N, int32_t K, spiffy_gemm_plan_t* plans,
+                           int32_t* n_ranges) {
+  if (!plans || !n_ranges || epilogue < SPIFFY_GEMM_STORE || epilogue > SPIFFY_GEMM_SWIGLU) return SPIFFY_EINVAL;
+  if (M < 1 || M_tail < 0 || M > INT32_MAX - M_tail || N < 1 || K < 1) return SPIFFY_ESHAPE;
+  if (!mfma_gemm_supported(epilogue, gemm_shape(epilogue, M + M_tail, N, K))) return SPIFFY_ESHAPE;
+  if (epilogue == SPIFFY_GEMM_STORE && N % 128 != 0) return SPIFFY_ESHAPE;       // heads of 128 columns
+  int epi = epilogue == SPIFFY_GEMM_STORE ? EPI_QKV : epilogue, ks = 1;
+  if (epilogue == SPIFFY_GEMM_RESID && mfma_ksplit(N, K) > 1) { epi = EPI_PARTIAL; ks = mfma_ksplit(N, K); }
+  const RowsPlan p = plan_gemm_rows(epi, M, M_tail, N, K, ks);
+  *n_ranges = p.n_ranges;
+  for (int i = 0; i < p.n_ranges; ++i) {
+    if (!plan_has_kernels(epi, p.range[i])) return SPIFFY_EDEVICE;
+    put_plan(p.range[i], ks, &plans[i]);
   }
   return SPIFFY_OK;
 }

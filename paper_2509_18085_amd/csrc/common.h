@@ -129,7 +129,6 @@ struct GemmArgs {
   int ldw;              // row stride of the weight segments in elements (0 = K, i.e. dense rows)
   float scale;          // LMHEAD: logit scale
   int ksplit;           // PARTIAL: number of K slices (C = fp32 [ksplit][Mz][N]); otherwise 1
-  int layer;            // a projection of verify_layer: any tile height (spiffy_gemm keeps to 256, 128, 64 and 32 rows)
   QkvArgs qkv;          // QKV only
   int Mz;               // PARTIAL: rows per K slice of C when only some of them are computed by this launch (0 = M)
 };

@@ -132,8 +132,13 @@ struct GemmPlan {
   struct { int bm, bn, col0, ncols, workgroups; } part[2];
 };
 GemmPlan plan_gemm_mfma(int epi, int M, int N, int ksplit);
-// the same for the projections of a layer (GemmArgs::layer): more tile heights, chosen by measured costs
+// the same for the projections of a layer: more tile heights, chosen by measured costs
 GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_us = nullptr);
+// ... over rows_a rows and rows_b behind them, in one launch sequence or one for either
+struct RowsPlan { int n_ranges; GemmPlan range[2]; };
+RowsPlan plan_gemm_rows(int epi, int rows_a, int rows_b, int N, int K, int ksplit);
+bool plan_has_kernels(int epi, const GemmPlan& p);      // every tile shape of the plan is compiled for the epilogue
+hipError_t launch_gemm_plan(int epi, const GemmArgs& a, const GemmPlan& p, hipStream_t st);
 struct TileShape { int bm, bn; };
 hipError_t launch_gemm_store(const GemmArgs& a, TileShape t, hipStream_t st);
 hipError_t launch_gemm_qkv(const GemmArgs& a, TileShape t, hipStream_t st);
@@ -152,7 +157,6 @@ hipError_t launch_splitk_reduce(const float* P, int ksplit, const void* R, void*
                                 void* normed, int M, int N, hipStream_t st, const int32_t* n_rows_dev = nullptr,
                                 const int32_t* out_rows = nullptr, const int32_t* r_rows = nullptr,
                                 const HeadRows* head = nullptr);
-bool mfma_attn_supported(const AttnArgs& a);
 size_t mfma_attn_partial_bytes(int G, int B, int Hq, int hd, int P);
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t st);
 hipError_t launch_rope_table(const RopeArgs& a, hipStream_t st);

@@ -573,10 +573,6 @@ inline int n_splits(int P) { return P > 0 ? cdiv(P, SPLIT_KEYS) : 1; }
 
 }  // namespace
 
-bool mfma_attn_supported(const AttnArgs& a) {
-  return a.hd == HD && a.Hq % a.Hkv == 0 && a.B >= 1 && a.G >= 1;
-}
-
 // split partials; P = cached keys, prefix and suffix together
 size_t mfma_attn_partial_bytes(int G, int B, int Hq, int hd, int P) {
   const size_t M = (size_t)G * B;

@@ -278,12 +278,6 @@ static float shape_cost(const ShapeCost& s, int M, int n_cols, int unit, int k_t
   const float w = (float)tiles / 256.f, fill = (float)M / (float)(mt * s.bm), kt = (float)k_tiles / (float)ksplit;
   return 3.5f + (float)(r - 1) + kt * (s.c[0] * (float)r + s.c[1] * w + s.c[2] * w / (float)mt + s.c[3] * (float)r * fill);
 }
-static bool layer_shape(int epi, int bm, int bn) {      // the shapes launch_shape has for an epilogue
-  if (bn == 32) return epi == EPI_PARTIAL;
-  if (epi == EPI_PARTIAL) return bn != 192 && bn != 96 && bn != 256 && bm != 384;
-  return epi == EPI_SWIGLU || (bm != 384 && !(bm == 320 && bn == 192));
-}
-
 GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_us) {
   GemmPlan p = plan_gemm_mfma(epi, M, N, ksplit);
   if (ksplit < 1) ksplit = 1;
@@ -296,7 +290,7 @@ GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_u
   auto best_shape = [&](int n, TileShape& t) {
     float best = 1e30f;
     for (const ShapeCost& s : kShapeCost) {
-      if (n % (s.bn / unit) != 0 || !layer_shape(epi, s.bm, s.bn)) continue;
+      if (n % (s.bn / unit) != 0 || !has_shape(epi, s.bm, s.bn)) continue;
       // Tiles of 192 rows that are one full round of four slices take longer than the fit says: a layer of width 2048 with 608 .. 768
       // rows 133 - 138 us instead of 125 - 135.  With fewer or more of them they are the better ones (layers: 544 rows of width
       // 2048 122 -> 116 us, 1440 rows 231 -> 219, 1280 rows of width 1024 158 -> 145).
@@ -322,7 +316,7 @@ GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_u
   if (epi == EPI_SWIGLU) {
     best = best < 0.97f * whole ? best : 0.97f * whole;
     for (const ShapeCost& s : kShapeCost) {
-      if (!layer_shape(epi, s.bm, s.bn)) continue;
+      if (!has_shape(epi, s.bm, s.bn)) continue;
       const int per = s.bn / 2, mt = cdiv(M, s.bm);
       for (int r = 1; r <= (int)((long long)mt * (N / per) / 256); ++r) {
         const int main_tiles = 256 * r / mt, rest = N - per * main_tiles;
@@ -346,12 +340,36 @@ GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_u
   return p;
 }
 
-hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
+// The launches of a layer's projection over rows_a rows and the rows_b rows that ride along: one launch when there are few rows in
+// all (weight streaming sets the time: stream them once, not twice) or when the measured costs of the tile shapes say that it
+// is no longer than two, in which each range has the shape that suits its height (a ragged total would otherwise pay a
+// whole extra round of the tall tiles).  Rows are independent and the K order of an element does not depend on the shape.
+RowsPlan plan_gemm_rows(int epi, int rows_a, int rows_b, int N, int K, int ksplit) {
+  RowsPlan p = {1, {}};
+  float one = 0.f, a_us = 0.f, b_us = 0.f;
+  p.range[0] = plan_gemm_layer(epi, rows_a + rows_b, N, K, ksplit, &one);
+  if (rows_b == 0 || rows_a + rows_b <= 512) return p;
+  const GemmPlan a = plan_gemm_layer(epi, rows_a, N, K, ksplit, &a_us), b = plan_gemm_layer(epi, rows_b, N, K, ksplit, &b_us);
+  if (one > a_us + b_us) {
+    p.n_ranges = 2;
+    p.range[0] = a;
+    p.range[1] = b;
+  }
+  return p;
+}
+
+bool plan_has_kernels(int epi, const GemmPlan& p) {
+  if (p.n_parts < 1) return false;
+  for (int i = 0; i < p.n_parts; ++i) {
+    const int bm = p.part[i].bm, bn = p.part[i].bn;
+    if (epi == EPI_RESID ? bm != 256 || (bn != 128 && bn != 64) : !has_shape(epi, bm, bn)) return false;
+  }
+  return true;
+}
+
+hipError_t launch_gemm_plan(int epi, const GemmArgs& a0, const GemmPlan& p, hipStream_t st) {
   GemmArgs a = a0;
   if (a.ksplit < 1) a.ksplit = 1;
-  if (epi == EPI_LMHEAD) return launch_gemm_head(a, st);     // the shape is chosen on the device
-  const bool layer = a.layer && (epi == EPI_QKV || epi == EPI_PARTIAL || epi == EPI_SWIGLU);
-  const GemmPlan p = layer ? plan_gemm_layer(epi, a.M, a.N, a.K, a.ksplit) : plan_gemm_mfma(epi, a.M, a.N, a.ksplit);
   if (p.n_parts < 1) return hipErrorInvalidValue;
   const TileShape t = {p.part[0].bm, p.part[0].bn};
   switch (epi) {
@@ -380,6 +398,13 @@ hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
     default:
       return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_gemm_mfma(int epi, const GemmArgs& a0, hipStream_t st) {
+  GemmArgs a = a0;
+  if (a.ksplit < 1) a.ksplit = 1;
+  if (epi == EPI_LMHEAD) return launch_gemm_head(a, st);     // the shape is chosen on the device
+  return launch_gemm_plan(epi, a, plan_gemm_mfma(epi, a.M, a.N, a.ksplit), st);
 }
 
 hipError_t launch_splitk_reduce(const float* P, int ksplit, const void* R, void* out, const void* gain, float eps,

@@ -49,7 +49,6 @@ namespace {
 constexpr int BM = 256, BKK = 64;
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {   // vmcnt <= N; lgkmcnt / expcnt untouched
@@ -112,47 +111,48 @@ hipError_t launch_t(const GemmArgs& a, int tiles_i, int tiles_j, hipStream_t st)
   return hipGetLastError();
 }
 
+// The tile shapes of each epilogue: what launch_shape instantiates and the rules may pick.
+constexpr bool has_shape(int epi, int bm, int bn) {
+  switch (bm * 1000 + bn) {
+    case 256128: case 256064: case 128128: case 64128: case 64064: return true;
+    case 256192: case 128192: case 128096: case 64096: return epi != EPI_PARTIAL;      // the split-K projections are narrow
+    case 64032: case 32032: return epi == EPI_PARTIAL;
+    case 192128: case 128064: case 320128: return epi != EPI_STORE;                    // heights in between: a layer's own launches
+    case 192192: case 256256: return epi == EPI_QKV || epi == EPI_SWIGLU;
+    case 320192: case 384128: return epi == EPI_SWIGLU;
+    default: return false;
+  }
+}
+
+template <int EPI, int BN, int SD, int BMT, int SA = 0>
+bool launch_if(const GemmArgs& a, TileShape t, hipStream_t st, hipError_t& e) {
+  if constexpr (has_shape(EPI, BMT, BN)) {
+    if (t.bm == BMT && t.bn == BN) {
+      e = launch_t<EPI, BN, SD, BMT, SA>(a, cdiv(a.M, BMT), a.N / (BN / (EPI == EPI_SWIGLU ? 2 : 1)), st);
+      return true;
+    }
+  }
+  return false;
+}
+
 // One launch in tiles of shape t over all of a.N columns (SWIGLU: features).  The few-row shapes have weight rings as deep as
 // the LDS allows: bytes in flight are what sets the streaming rate.
 template <int EPI>
 hipError_t launch_shape(const GemmArgs& a, TileShape t, hipStream_t st) {
-  constexpr bool STORE = EPI == EPI_STORE, SWIGLU = EPI == EPI_SWIGLU, QKV = EPI == EPI_QKV, PARTIAL = EPI == EPI_PARTIAL;
-  constexpr int unit = SWIGLU ? 2 : 1;
-  const int mt = cdiv(a.M, t.bm), nt = a.N / (t.bn / unit);
-  const int shape = t.bm * 1000 + t.bn;
-  switch (shape) {
-    // 256 x 128: room for a third activation stage beside four weight stages (160 KB); in interleaved A/B runs 2-5%
-    // faster than two stages on every projection that takes this tile (down projection 95.9 -> 91.4 us at 1024 rows)
-    case 256128: return launch_t<EPI, 128, 4, 256, 3>(a, mt, nt, st);
-    case 256064: return launch_t<EPI, 64, 4>(a, mt, nt, st);
-    case 128128: return launch_t<EPI, 128, 4, 128>(a, mt, nt, st);
-    case 64128: return launch_t<EPI, 128, 6, 64>(a, mt, nt, st);
-    case 64064: return launch_t<EPI, 64, 8, 64>(a, mt, nt, st);
-    default: break;
-  }
-  if constexpr (!PARTIAL) {                        // the split-K projections are narrow
-    if (shape == 256192) return launch_t<EPI, 192, 3>(a, mt, nt, st);
-    if (shape == 128192) return launch_t<EPI, 192, 4, 128>(a, mt, nt, st);
-    if (shape == 128096) return launch_t<EPI, 96, SWIGLU ? 5 : 4, 128>(a, mt, nt, st);
-    if (shape == 64096) return launch_t<EPI, 96, SWIGLU ? 7 : 6, 64>(a, mt, nt, st);
-  } else {
-    if (shape == 64032) return launch_t<EPI, 32, 10, 64>(a, mt, nt, st);
-    if (shape == 32032) return launch_t<EPI, 32, 9, 32>(a, mt, nt, st);
-  }
-  if constexpr (!STORE) {                          // heights in between: the layers' own launches
-    if (shape == 192128) return launch_t<EPI, 128, 4, 192, 4>(a, mt, nt, st);
-    if (shape == 128064) return launch_t<EPI, 64, 6, 128>(a, mt, nt, st);
-    if (shape == 320128) return launch_t<EPI, 128, 4, 320, 2>(a, mt, nt, st);
-  }
-  if constexpr (QKV || SWIGLU) {
-    if (shape == 192192) return launch_t<EPI, 192, 3, 192, 3>(a, mt, nt, st);
-    if (shape == 256256) return launch_t<EPI, 256, 3>(a, mt, nt, st);
-  }
-  if constexpr (SWIGLU) {
-    if (shape == 320192) return launch_t<EPI, 192, 3, 320>(a, mt, nt, st);
-    if (shape == 384128) return launch_t<EPI, 128, 4, 384, 2>(a, mt, nt, st);
-  }
-  return hipErrorInvalidValue;
+  constexpr bool SWIGLU = EPI == EPI_SWIGLU;
+  hipError_t e = hipErrorInvalidValue;
+  // 256 x 128: room for a third activation stage beside four weight stages (160 KB); in interleaved A/B runs 2-5%
+  // faster than two stages on every projection that takes this tile (down projection 95.9 -> 91.4 us at 1024 rows)
+  (void)(launch_if<EPI, 128, 4, 256, 3>(a, t, st, e) || launch_if<EPI, 64, 4, 256>(a, t, st, e) ||
+         launch_if<EPI, 128, 4, 128>(a, t, st, e) || launch_if<EPI, 128, 6, 64>(a, t, st, e) ||
+         launch_if<EPI, 64, 8, 64>(a, t, st, e) || launch_if<EPI, 192, 3, 256>(a, t, st, e) ||
+         launch_if<EPI, 192, 4, 128>(a, t, st, e) || launch_if<EPI, 96, SWIGLU ? 5 : 4, 128>(a, t, st, e) ||
+         launch_if<EPI, 96, SWIGLU ? 7 : 6, 64>(a, t, st, e) || launch_if<EPI, 32, 10, 64>(a, t, st, e) ||
+         launch_if<EPI, 32, 9, 32>(a, t, st, e) || launch_if<EPI, 128, 4, 192, 4>(a, t, st, e) ||
+         launch_if<EPI, 64, 6, 128>(a, t, st, e) || launch_if<EPI, 128, 4, 320, 2>(a, t, st, e) ||
+         launch_if<EPI, 192, 3, 192, 3>(a, t, st, e) || launch_if<EPI, 256, 3, 256>(a, t, st, e) ||
+         launch_if<EPI, 192, 3, 320>(a, t, st, e) || launch_if<EPI, 128, 4, 384, 2>(a, t, st, e));
+  return e;
 }
 
 }  // namespace

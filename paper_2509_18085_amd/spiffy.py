@@ -27,7 +27,8 @@ EXPORTS = ["spiffy_status_str", "spiffy_uses_mfma", "spiffy_workspace_bytes", "s
            "spiffy_verify_layer", "spiffy_verify_layer_last", "spiffy_decode_head", "spiffy_gemm", "spiffy_graph_accept", "spiffy_draft_prune", "spiffy_head_topk", "spiffy_commit_block",
            "spiffy_subgraph_search_workspace_bytes", "spiffy_subgraph_search", "spiffy_verify_step",
            "spiffy_workspace_bytes_seq", "spiffy_verify_step_seq", "spiffy_workspace_bytes_commit",
-           "spiffy_verify_step_commit", "spiffy_decode_head_static", "spiffy_gemm_plan"]
+           "spiffy_verify_step_commit", "spiffy_decode_head_static", "spiffy_gemm_plan", "spiffy_layer_gemm_plan",
+           "spiffy_layer_gemm"]
 GEMM_STORE, GEMM_RESID, GEMM_SWIGLU = 0, 1, 2
 
 
@@ -94,6 +95,10 @@ def _load() -> C.CDLL:
     lib.spiffy_decode_head_static.argtypes = [cfgp, vp, vp, vp, vp, vp, i32, i32, f32, f32, i32, vp, vp, vp, vp, vp, vp]
     lib.spiffy_gemm_plan.restype = C.c_int
     lib.spiffy_gemm_plan.argtypes = [i32, i32, i32, i32, i32, C.POINTER(GemmPlan)]
+    lib.spiffy_layer_gemm_plan.restype = C.c_int
+    lib.spiffy_layer_gemm_plan.argtypes = [i32, i32, i32, i32, i32, C.POINTER(GemmPlan), C.POINTER(i32)]
+    lib.spiffy_layer_gemm.restype = C.c_int
+    lib.spiffy_layer_gemm.argtypes = [i32, vp, vp, vp, vp, vp, i32, i32, i32, vp, sz, vp]
     lib.spiffy_gemm.restype = C.c_int
     lib.spiffy_gemm.argtypes = [i32, i32, vp, vp, vp, vp, vp, i32, i32, i32, vp, sz, vp]
     lib.spiffy_graph_accept.restype = C.c_int
@@ -292,13 +297,41 @@ def gemm(epilogue: int, A: torch.Tensor, W0: torch.Tensor, W1: Optional[torch.Te
     return out
 
 
+def layer_gemm(epilogue: int, A: torch.Tensor, W0: torch.Tensor, W1: Optional[torch.Tensor] = None,
+               R: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None,
+               workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
+    """gemm (bf16; GEMM_RESID or GEMM_SWIGLU) in the tiles that verify_layer launches the projection in."""
+    M, K = A.shape
+    N = W0.shape[0]
+    if out is None:
+        out = torch.empty((M, N), dtype=A.dtype, device=A.device)
+    if A.dtype != torch.bfloat16:
+        raise ValueError("layer_gemm takes bfloat16")
+    wp, wn = _ws(workspace) if workspace is not None else (None, 0)
+    _check(lib.spiffy_layer_gemm(epilogue, _ptr(A), _ptr(W0), _ptr(W1), _ptr(R), _ptr(out), M, N, K, wp, wn,
+                                 _stream(stream)), "spiffy_layer_gemm")
+    return out
+
+
+def _plan_dict(p: GemmPlan) -> dict:
+    return {"k_slices": p.k_slices,
+            "launches": [{"tile": (l.tile_rows, l.tile_cols), "col0": l.col0, "n_cols": l.n_cols,
+                          "workgroups": l.workgroups} for l in p.launch[:p.n_launches]]}
+
+
 def gemm_plan(epilogue: int, M: int, N: int, K: int, with_workspace: bool = True) -> dict:
     """The launches spiffy_gemm uses for a bf16 projection of that shape (host arithmetic, no device)."""
     p = GemmPlan()
     _check(lib.spiffy_gemm_plan(epilogue, M, N, K, int(with_workspace), C.byref(p)), "spiffy_gemm_plan")
-    return {"k_slices": p.k_slices,
-            "launches": [{"tile": (l.tile_rows, l.tile_cols), "col0": l.col0, "n_cols": l.n_cols,
-                          "workgroups": l.workgroups} for l in p.launch[:p.n_launches]]}
+    return _plan_dict(p)
+
+
+def layer_gemm_plan(epilogue: int, M: int, N: int, K: int, M_tail: int = 0) -> List[dict]:
+    """The launches verify_layer and the steps use for that projection over M rows and M_tail rows that ride along: one plan
+    for all of them, or one for either (host arithmetic, no device)."""
+    p, n = (GemmPlan * 2)(), C.c_int32(0)
+    _check(lib.spiffy_layer_gemm_plan(epilogue, M, M_tail, N, K, p, C.byref(n)), "spiffy_layer_gemm_plan")
+    return [_plan_dict(x) for x in p[:n.value]]
 
 
 def graph_accept(graph_edges: torch.Tensor, draft_states: torch.Tensor, target_states: torch.Tensor,

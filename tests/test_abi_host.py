@@ -462,6 +462,64 @@ def test_gemm_plan_errors():
     assert sp.lib.spiffy_gemm_plan(sp.GEMM_STORE, 64, 128, 128, 1, None) == sp.SPIFFY_EINVAL
 
 
+LAYER_SHAPES = [(sp.GEMM_STORE, 12288, 4096), (sp.GEMM_STORE, 4608, 3584), (sp.GEMM_STORE, 4096, 2048), (sp.GEMM_STORE, 384, 128),
+                (sp.GEMM_RESID, 4096, 4096), (sp.GEMM_RESID, 4096, 12288), (sp.GEMM_RESID, 3584, 18944), (sp.GEMM_RESID, 2048, 5632),
+                (sp.GEMM_RESID, 1024, 4096), (sp.GEMM_RESID, 192, 512), (sp.GEMM_SWIGLU, 12288, 4096), (sp.GEMM_SWIGLU, 18944, 3584),
+                (sp.GEMM_SWIGLU, 5632, 2048), (sp.GEMM_SWIGLU, 64, 128)]
+
+
+def test_layer_gemm_plans_cover_rows_and_columns_in_compiled_tiles():
+    """What verify_layer launches: every plan covers its columns once, K slices go by (N, K) alone, and every tile shape is
+    compiled for the projection's epilogue (the query refuses a plan whose shape is not), alone and with rows that ride along."""
+    tiles = {(256, 256), (256, 192), (256, 128), (256, 64), (384, 128), (320, 192), (320, 128), (192, 192), (192, 128), (128, 192),
+             (128, 128), (128, 96), (128, 64), (64, 128), (64, 96), (64, 64), (64, 32), (32, 32)}
+    seen = set()
+    for epi, N, K in LAYER_SHAPES:
+        unit, slices = 2 if epi == sp.GEMM_SWIGLU else 1, set()
+        for M in list(range(1, 400, 9)) + list(range(400, 2200, 37)) + [1024, 1056, 3000, 4096, 8192, 16384]:
+            for tail in (0, 1, 224, 640):
+                if M + tail > 16384:
+                    continue
+                plans = sp.layer_gemm_plan(epi, M, N, K, tail)
+                rows = [M + tail] if len(plans) == 1 else [M, tail]
+                assert len(plans) <= 2 and (tail or len(plans) == 1)
+                for m, plan in zip(rows, plans):
+                    col = 0
+                    slices.add(plan["k_slices"])
+                    for l in plan["launches"]:
+                        bm, bn = l["tile"]
+                        assert (bm, bn) in tiles and l["n_cols"] % (bn // unit) == 0 and l["col0"] == col, (M, tail, l)
+                        assert l["workgroups"] == -(-m // bm) * (l["n_cols"] // (bn // unit)) * plan["k_slices"], (M, tail, l)
+                        col += l["n_cols"]
+                        seen.add((epi, bm, bn))
+                    assert col == N and plan["k_slices"] == sp.gemm_plan(epi, m, N, K)["k_slices"]
+        assert len(slices) == 1, (epi, N, K, slices)
+    assert {t[1:] for t in seen} == tiles
+
+
+def test_layer_gemm_plan_errors():
+    p, n = (sp.GemmPlan * 2)(), C.c_int32(0)
+    f = sp.lib.spiffy_layer_gemm_plan
+    assert f(sp.GEMM_STORE, 64, 0, 192, 256, p, C.byref(n)) == sp.SPIFFY_ESHAPE       # not whole heads
+    assert f(sp.GEMM_RESID, 64, 0, 128, 100, p, C.byref(n)) == sp.SPIFFY_ESHAPE       # K % 64
+    assert f(sp.GEMM_RESID, 0, 0, 128, 128, p, C.byref(n)) == sp.SPIFFY_ESHAPE
+    assert f(sp.GEMM_RESID, 64, -1, 128, 128, p, C.byref(n)) == sp.SPIFFY_ESHAPE
+    assert f(sp.GEMM_RESID, 2 ** 31 - 1, 2, 128, 128, p, C.byref(n)) == sp.SPIFFY_ESHAPE
+    assert f(5, 64, 0, 128, 128, p, C.byref(n)) == sp.SPIFFY_EINVAL
+    assert f(sp.GEMM_RESID, 64, 0, 128, 128, None, C.byref(n)) == sp.SPIFFY_EINVAL
+    assert f(sp.GEMM_RESID, 64, 0, 128, 128, p, None) == sp.SPIFFY_EINVAL
+
+
+def test_layer_gemm_argument_errors():
+    call = lambda epi=sp.GEMM_SWIGLU, a=DUMMY, w1=DUMMY, r=DUMMY, c=DUMMY, M=64, N=4096, K=4096, ws=DUMMY, nws=1 << 40: \
+        sp.lib.spiffy_layer_gemm(epi, a, DUMMY, w1, r, c, M, N, K, ws, nws, None)
+    assert call(epi=sp.GEMM_STORE) == sp.SPIFFY_EINVAL and call(epi=3) == sp.SPIFFY_EINVAL and call(a=None) == sp.SPIFFY_EINVAL
+    assert call(w1=None) == sp.SPIFFY_EINVAL and call(epi=sp.GEMM_RESID, r=None) == sp.SPIFFY_EINVAL
+    assert call(epi=sp.GEMM_RESID, ws=None) == sp.SPIFFY_EINVAL                       # K is sliced: scratch has to be there
+    assert call(epi=sp.GEMM_RESID, nws=100) == sp.SPIFFY_EWORKSPACE
+    assert call(K=4104) == sp.SPIFFY_ESHAPE and call(N=4104) == sp.SPIFFY_ESHAPE and call(N=4100) == sp.SPIFFY_ESHAPE
+
+
 def test_layer_width_limit_is_a_host_check():
     """A bf16 model wider than 16384 would need more than 64 KB of on-chip memory per row in the reduction behind the
     split-K projections: refused on the host, nothing is launched."""
