@@ -203,6 +203,7 @@ int check_layer_args(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w,
 // Chaining hints used by the whole-step driver: `normed_in` = ws.n already holds RMSNorm-1 of hidden_in
 // (written by the previous layer's last kernel); `next_norm1` = gain of the next layer's RMSNorm-1, to be
 // produced into ws.n by this layer's last kernel; `rope_ready` = the rotary table is already in place.
+enum Projection { QKV_PROJ, OUTPUT_PROJ, GATE_UP_PROJ, DOWN_PROJ };
 struct LayerChain {
   bool normed_in = false;
   const void* next_norm1 = nullptr;
@@ -228,6 +229,9 @@ struct LayerChain {
   void* head_nf = nullptr;
   HeadRows head = {nullptr, nullptr};
   bool head_ready = false;
+  // Launch plans of the projections, made by the pass's first layer (n_ranges = 0 before): a function of the rows and widths,
+  // which the layers of a pass share.
+  RowsPlan plans[4] = {};
 };
 
 // the arguments of the QKV projection that decide which path it and the attention take
@@ -279,8 +283,11 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   const bool mf = layer_mfma(cfg);
   const LayerWs ws = carve_layer(cfg, G, B, prefix->P + prefix->S, workspace, S_seq);
   int rc;
-  auto mfma_rows = [&](int epi, const GemmArgs& ga) {
-    return launch_gemm_rows(epi, ga, plan_gemm_rows(epi, G * B, S_seq, ga.N, ga.K, ga.ksplit), G * B, S_seq, dt, st);
+  auto mfma_rows = [&](Projection which, int epi, const GemmArgs& ga) {
+    RowsPlan alone = {};
+    RowsPlan& plan = chain ? chain->plans[which] : alone;
+    if (plan.n_ranges == 0) plan = plan_gemm_rows(epi, G * B, S_seq, ga.N, ga.K, ga.ksplit);
+    return launch_gemm_rows(epi, ga, plan, G * B, S_seq, dt, st);
   };
   if (chain) chain->normed_out = false;
   if (!(chain && chain->normed_in) &&
@@ -321,7 +328,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
     q.n_head = append || (S_seq && !prev) ? B : 0;               // the block itself, or the true block (state 0) ..
     q.dst_head = prefix->P;
     q.dst_tail = !S_seq ? -1 : prev ? prefix->P : prefix->P + B; // .. and the suffix behind it; or the finished block
-    if ((rc = dev(mfma_rows(EPI_QKV, g)))) return rc;
+    if ((rc = dev(mfma_rows(QKV_PROJ, EPI_QKV, g)))) return rc;
     a.partial = ws.attn_partial;
   } else {
     if ((rc = dev(launch_gemm_tile(dt, EPI_STORE, g, st)))) return rc;
@@ -394,12 +401,12 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   if (o_mfma) {
     if (o_slices > 1) {
       g.C = ws.splitk; g.ksplit = o_slices; g.a_rows = src_rows;
-      if ((rc = dev(mfma_rows(EPI_PARTIAL, g)))) return rc;
+      if ((rc = dev(mfma_rows(OUTPUT_PROJ, EPI_PARTIAL, g)))) return rc;
       if ((rc = dev(launch_splitk_reduce((const float*)ws.splitk, o_slices, resid, ws.h, w->norm2, cfg->rms_eps, ws.n, M,
                                          d, st, n_rows, nullptr, src_rows))))
         return rc;
       normed = true;
-    } else if ((rc = dev(mfma_rows(EPI_RESID, g)))) return rc;
+    } else if ((rc = dev(mfma_rows(OUTPUT_PROJ, EPI_RESID, g)))) return rc;
   } else if ((rc = dev(launch_gemm_tile(dt, EPI_RESID, g, st)))) return rc;
 
   if (!normed && (rc = dev(launch_rmsnorm(dt, ws.h, w->norm2, cfg->rms_eps, M, d, nullptr, n_rows, ws.n, st))))
@@ -408,7 +415,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   std::memset(&g, 0, sizeof(g));
   g.A = ws.n; g.lda = d; g.M = M; g.M_dev = n_rows; g.K = d; g.W[0] = w->w_gate; g.W[1] = w->w_up; g.N = cfg->ffn;
   g.C = ws.act; g.ldc = cfg->ffn; g.scale = 1.f;
-  if ((rc = dev(mf && mfma_gemm_supported(EPI_SWIGLU, g) ? mfma_rows(EPI_SWIGLU, g)
+  if ((rc = dev(mf && mfma_gemm_supported(EPI_SWIGLU, g) ? mfma_rows(GATE_UP_PROJ, EPI_SWIGLU, g)
                                                           : launch_gemm_tile(dt, EPI_SWIGLU, g, st))))
     return rc;
 
@@ -421,7 +428,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
     const int ks = mfma_ksplit(d, cfg->ffn);
     if (ks > 1) {
       g.C = ws.splitk; g.ksplit = ks;
-      if ((rc = dev(mfma_rows(EPI_PARTIAL, g)))) return rc;
+      if ((rc = dev(mfma_rows(DOWN_PROJ, EPI_PARTIAL, g)))) return rc;
       if (cm && chain->head_nf) {
         chain->head_ready = true;
         return dev(launch_splitk_reduce((const float*)ws.splitk, ks, ws.h, hidden_out, chain->final_norm, cfg->rms_eps,
@@ -432,7 +439,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
       return dev(launch_splitk_reduce((const float*)ws.splitk, ks, ws.h, hidden_out, ng, cfg->rms_eps,
                                       ng ? ws.n : nullptr, M, d, st, n_rows, cm ? ws.rows : nullptr));
     }
-    if ((rc = dev(mfma_rows(EPI_RESID, g)))) return rc;
+    if ((rc = dev(mfma_rows(DOWN_PROJ, EPI_RESID, g)))) return rc;
   } else if ((rc = dev(launch_gemm_tile(dt, EPI_RESID, g, st)))) return rc;
   if (cm) return dev(launch_scatter_rows(ws.gat_x, (size_t)d * esize(dt), ws.rows, ws.count, M, hidden_out, st));
   return SPIFFY_OK;
