@@ -134,13 +134,10 @@ bool mfma_gemm_supported(int epi, const GemmArgs& a) {
   if ((size_t)a.M * a.lda * 2 >= lim || (size_t)a.N * ldw * 2 >= lim) return false;
   if (epi == EPI_SWIGLU) return a.N % 32 == 0;
   if (epi == EPI_LMHEAD) return a.N >= 1;
-  if (a.N % 64 != 0) return false;
-  int n = 0;
-  for (int s = 0; s < 3; ++s) {
-    if (a.Nseg[s] < 0 || a.Nseg[s] % 8 != 0) return false;
-    n += a.Nseg[s];
-  }
-  return n == a.N && a.Nseg[0] > 0;
+  if (epi == EPI_QKV)      // whole heads of 128 columns: the epilogue pairs columns of a head
+    return a.Nseg[0] > 0 && a.Nseg[1] > 0 && a.Nseg[2] > 0 && (a.Nseg[0] | a.Nseg[1] | a.Nseg[2]) % 128 == 0 &&
+           a.Nseg[0] + a.Nseg[1] + a.Nseg[2] == a.N;
+  return a.N % 64 == 0 && a.Nseg[0] == a.N && !a.bias[0];      // one weight matrix
 }
 
 int mfma_lmhead_partials_per_row(int V) { return cdiv(V, BM) * 2; }

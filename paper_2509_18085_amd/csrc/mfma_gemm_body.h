@@ -100,14 +100,15 @@
           base = (row0 & 16) ? (const bf16_t*)a.W[1] : (const bf16_t*)a.W[0];
           r = tj * (BN / 2) + (row >> 5) * 16 + (row & 15);
         } else {
-          const int n0 = j0 + row0;   // column of the fused [seg0 | seg1 | seg2] output; 8-row groups never straddle
-          int seg0;
-          if (n0 < a.Nseg[0]) { base = (const bf16_t*)a.W[0]; seg0 = 0; }
-          else if (n0 < a.Nseg[0] + a.Nseg[1]) { base = (const bf16_t*)a.W[1]; seg0 = a.Nseg[0]; }
-          else { base = (const bf16_t*)a.W[2]; seg0 = a.Nseg[0] + a.Nseg[1]; }
-          r = j0 + row - seg0;
-          // rows of every 32-row MFMA tile: 16 columns of a head, then the 16 columns 64 further on that rotate with them
-          if (EPI == EPI_QKV) r = (r & ~127) + 16 * ((r >> 5) & 3) + 64 * ((r >> 4) & 1) + (r & 15);
+          base = (const bf16_t*)a.W[0];
+          r = j0 + row;
+          if (EPI == EPI_QKV) {
+            const int n0 = j0 + row0;   // column of the fused q | k | v output; 8-row groups never straddle
+            if (n0 >= a.Nseg[0] + a.Nseg[1]) { base = (const bf16_t*)a.W[2]; r -= a.Nseg[0] + a.Nseg[1]; }
+            else if (n0 >= a.Nseg[0]) { base = (const bf16_t*)a.W[1]; r -= a.Nseg[0]; }
+            // rows of every 32-row MFMA tile: 16 columns of a head, then the 16 columns 64 further on that rotate with them
+            r = (r & ~127) + 16 * ((r >> 5) & 3) + 64 * ((r >> 4) & 1) + (r & 15);
+          }
         }
         yoff[q] = (unsigned)r * (unsigned)(ldw * 2) + chunk * 16;
       }
@@ -461,15 +462,6 @@
         float x[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) x[v] = acc[i][j][v0 + v];
-        if (EPI == EPI_STORE) {
-          const int s0 = n < a.Nseg[0] ? 0 : (n < a.Nseg[0] + a.Nseg[1] ? a.Nseg[0] : a.Nseg[0] + a.Nseg[1]);
-          const void* bias = n < a.Nseg[0] ? a.bias[0] : (n < a.Nseg[0] + a.Nseg[1] ? a.bias[1] : a.bias[2]);
-          if (bias) {
-            const bf16_t* bp = (const bf16_t*)bias + (n - s0) + 4 * hh;
-#pragma unroll
-            for (int v = 0; v < 8; ++v) x[v] += static_cast<float>(bp[2 * (v & 4) + (v & 3)]);
-          }
-        }
         if (EPI == EPI_RESID && r < i_max) {
           const bf16_t* rp = R + (size_t)r * a.ldc + n + 4 * hh;
 #pragma unroll

@@ -23,10 +23,10 @@
 //   * workgroup ids are remapped so that the workgroups sharing a weight tile sit on one XCD.
 //
 // Epilogues:
-//   EPI_STORE    C = X W^T (+bias), W given as up to three row segments (q | k | v)
-//   EPI_QKV      the same for head_dim 128 with the rotary embedding on the q and k columns: a 32-column MFMA tile
-//                holds 16 columns c and the 16 columns c + 64 of a head, partner values are in one lane; k and v
-//                rows that extend the cache are stored there too
+//   EPI_STORE    C = X W^T
+//   EPI_QKV      C = X [Wq | Wk | Wv]^T (+ biases), heads of 128 columns, with the rotary embedding on the q and k
+//                columns: a 32-column MFMA tile holds 16 columns c and the 16 columns c + 64 of a head, partner
+//                values are in one lane; k and v rows that extend the cache are stored there too
 //   EPI_RESID    C = R + X W^T
 //   EPI_SWIGLU   C = silu(X Wg^T) * (X Wu^T); gate and up rows are interleaved 16/16 inside every
 //                32-column MFMA tile, partner values are in one lane
