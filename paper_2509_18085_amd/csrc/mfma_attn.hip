@@ -110,7 +110,9 @@ __device__ __forceinline__ float max_with_other_half(float x) {
 // 1 and the 64 multiplies are skipped).  The choice is made per query, so a row's arithmetic does not depend on the
 // rows that share its wavefront; (m, l, O) stay consistent and every later merge weighs partials by exp2(m - max m).
 // Returns the factor of l; O is rescaled here, in place (the multiplies are opaque to the compiler so that the rarely
-// taken branch around them does not cost a copy of the 64 accumulator registers on every tile).
+// taken branch around them does not cost a copy of the 64 accumulator registers on every tile).  The compiler does not see
+// what the assembly reads: each accumulator's first multiply waits out the matrix instruction that may have written it (at most
+// 19 wait states, here 24), and the last is followed by the two that a matrix instruction reading it could need.
 __device__ __forceinline__ float follow_maximum(WaveState& w, float tile_max) {
   const float m_cand = fmaxf(w.m_run, tile_max);
   const float m_new = (m_cand - w.m_run > 8.0f) ? m_cand : w.m_run;     // first tile: m_run = -inf, the difference is +inf
@@ -123,9 +125,11 @@ __device__ __forceinline__ float follow_maximum(WaveState& w, float tile_max) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         float x = w.o[n][v];
-        asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(alpha));
+        if (v == 0) asm volatile("s_nop 15\n\ts_nop 7\n\tv_mul_f32 %0, %1, %0" : "+v"(x) : "v"(alpha));
+        else asm volatile("v_mul_f32 %0, %1, %0" : "+v"(x) : "v"(alpha));
         w.o[n][v] = x;
       }
+    asm volatile("s_nop 1");
   }
   return alpha;
 }
