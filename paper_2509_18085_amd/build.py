@@ -67,6 +67,11 @@ def scratch_bytes(source: str) -> dict:
     return dict(zip(names, sizes))
 
 
+def assembly(source: str) -> str:
+    """The gfx950 assembly of a source file (nothing is written)."""
+    return _run([_hipcc()] + FLAGS + ["--cuda-device-only", "-S", os.path.join(CSRC, source), "-o", "-"])
+
+
 def build_host_sanitized() -> tuple:
     """The same library with the HOST code of the launcher (csrc/api.hip: argument checks, workspace carving, kernel
     selection) compiled under AddressSanitizer and UndefinedBehaviorSanitizer; device code and the kernel translation
