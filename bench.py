@@ -101,22 +101,22 @@ def time_steps(sp, w, steps, warmup):
 
 
 def time_dominant_kernel(sp, w, dev, iters):
-    """The gate/up SwiGLU GEMM alone: same shapes as in the step, weights rotating over the layers, HIP events on the
-    launch stream around back-to-back launches."""
+    """The gate/up SwiGLU GEMM alone, in the tiles that the step's layers launch it in (spiffy_layer_gemm): same shapes as in
+    the step, weights rotating over the layers, HIP events on the launch stream around back-to-back launches."""
     import torch
     cfg, layers = w["cfg"], w["layers"]
     M = cfg.G * cfg.B
     x = torch.randn((M, cfg.d), device=dev, dtype=torch.float32).to(torch.bfloat16)
     act = torch.empty((M, cfg.F), device=dev, dtype=torch.bfloat16)
     for lw in layers[:2]:
-        sp.gemm(sp.GEMM_SWIGLU, x, lw["w_gate"], lw["w_up"], out=act)
+        sp.layer_gemm(sp.GEMM_SWIGLU, x, lw["w_gate"], lw["w_up"], out=act)
     torch.cuda.synchronize()
     k0, k1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     n_launch = 0
     k0.record()
     for _ in range(iters):
         for lw in layers:
-            sp.gemm(sp.GEMM_SWIGLU, x, lw["w_gate"], lw["w_up"], out=act)
+            sp.layer_gemm(sp.GEMM_SWIGLU, x, lw["w_gate"], lw["w_up"], out=act)
             n_launch += 1
     k1.record()
     torch.cuda.synchronize()
@@ -124,8 +124,9 @@ def time_dominant_kernel(sp, w, dev, iters):
 
 
 def weight_stream_leg(sp, w, dev):
-    """The four projections of a layer alone, through spiffy_gemm with the step's shapes (QKV as one fused weight
-    matrix, output and down projections with their K slices and reduction), weights rotating over eight layers:
+    """The four projections of a layer alone, with the step's shapes and in the tiles its layers launch (spiffy_layer_gemm;
+    output and down projections with their K slices and reduction; QKV as the plain product of one fused weight matrix
+    through spiffy_gemm, without the rotary epilogue and the layer's own tiles), weights rotating over eight layers:
     algorithmic bytes over time against the HBM peak.  For the workloads whose projections are weight streams."""
     import torch
     cfg, layers = w["cfg"], w["layers"][:8]
@@ -138,12 +139,12 @@ def weight_stream_leg(sp, w, dev):
     ws = torch.empty(4 * M * d * 4 + 256, dtype=torch.uint8, device=dev)
     wqkv = [torch.cat([lw["wq"], lw["wk"], lw["wv"]]) for lw in layers]
     legs = {
-        "qkv": (lambda i: sp.gemm(sp.GEMM_STORE, x, wqkv[i], out=o_qkv), 2.0 * (wqkv[0].numel() + M * d + M * wqkv[0].shape[0])),
-        "output_projection_and_reduction": (lambda i: sp.gemm(sp.GEMM_RESID, xa, layers[i]["wo"], R=r, out=o_d, workspace=ws),
+        "qkv_plain_product": (lambda i: sp.gemm(sp.GEMM_STORE, x, wqkv[i], out=o_qkv), 2.0 * (wqkv[0].numel() + M * d + M * wqkv[0].shape[0])),
+        "output_projection_and_reduction": (lambda i: sp.layer_gemm(sp.GEMM_RESID, xa, layers[i]["wo"], R=r, out=o_d, workspace=ws),
                                             2.0 * (d * qd + M * qd + 2 * M * d)),
-        "gate_up": (lambda i: sp.gemm(sp.GEMM_SWIGLU, x, layers[i]["w_gate"], layers[i]["w_up"], out=o_f),
+        "gate_up": (lambda i: sp.layer_gemm(sp.GEMM_SWIGLU, x, layers[i]["w_gate"], layers[i]["w_up"], out=o_f),
                     2.0 * (2 * F * d + M * d + M * F)),
-        "down_projection_and_reduction": (lambda i: sp.gemm(sp.GEMM_RESID, xf, layers[i]["w_down"], R=r, out=o_d, workspace=ws),
+        "down_projection_and_reduction": (lambda i: sp.layer_gemm(sp.GEMM_RESID, xf, layers[i]["w_down"], R=r, out=o_d, workspace=ws),
                                           2.0 * (d * F + M * F + 2 * M * d)),
     }
     o_qkv = torch.empty((M, wqkv[0].shape[0]), device=dev, dtype=torch.bfloat16)
