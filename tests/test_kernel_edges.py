@@ -92,9 +92,10 @@ def test_projection_extends_the_cache(sp, B, S, P):
                                                     ("c4", 3584, 28, 4, 18944, (7, 8, 11, 14, 24)),
                                                     ("c4", 2048, 16, 8, 5632, (4, 11, 19, 24, 32))])
 def test_layer_rows_are_bit_identical_across_all_tile_heights(sp, name, d, hq, hkv, F, states):
-    """The row counts (192 .. 1024) run the projections in tiles of 192 x 128, 128 x 64, 320 x 128, 192 x 192, 256 x 256, 320 x 192
-    and 384 x 128 beside the others, gate/up in one and in two column ranges; every state equals what it gives alone, where
-    the layer runs in tiles of 32 and 64 rows.  Two row counts are not multiples of 32."""
+    """The row counts (192 .. 1024) run gate/up in tiles of 192 x 128, 128 x 64, 320 x 128, 192 x 192, 256 x 256, 320 x 192 and
+    384 x 128 beside the others, in one and in two column ranges, and the other projections in some of them (every shape of
+    every projection: test_layer_rows_in_every_tile_shape); every state equals what it gives alone, where the layer runs in
+    tiles of 32 and 64 rows.  Two row counts are not multiples of 32."""
     cfg = synth.CONFIGS[name].scaled(L=1, V=1280, P=64, d=d, Hq=hq, Hkv=hkv, F=F, G=max(states))
     g = torch.Generator(device=DEV).manual_seed(3)
     rn = lambda *s: (torch.randn(s, generator=g, device=DEV) * 0.02).to(torch.bfloat16)
@@ -115,6 +116,81 @@ def test_layer_rows_are_bit_identical_across_all_tile_heights(sp, name, d, hq, h
     full = run(x)                                        # fall into groups of 32, so states keep their places here)
     for n in (1, 3, 16):
         assert torch.equal(run(x[:n].contiguous()), full[:n]), n
+
+
+@pytest.mark.parametrize("name,d,hq,hkv,F", [("c3", 4096, 32, 32, 12288), ("c4", 3584, 28, 4, 18944), ("c4", 2048, 16, 8, 5632)])
+def test_layer_rows_in_every_tile_shape(sp, name, d, hq, hkv, F):
+    """Every tile shape that the rule picks for a projection of the model up to 2048 rows, each at the fewest rows it is picked
+    for: every state equals what it gives alone."""
+    todo = {}
+    for rows in range(32, 2049, 32):
+        for proj, (epi, N, K) in dict(qkv=(sp.GEMM_STORE, (hq + 2 * hkv) * 128, d), output=(sp.GEMM_RESID, d, hq * 128),
+                                      gate_up=(sp.GEMM_SWIGLU, F, d), down=(sp.GEMM_RESID, d, F)).items():
+            for launch in sp.layer_gemm_plan(epi, rows, N, K)[0]["launches"]:
+                todo.setdefault((proj, launch["tile"]), rows)
+    assert len(todo) >= 20
+    if d == 4096:
+        assert all(k in todo for k in (("qkv", (256, 256)), ("qkv", (320, 128)), ("output", (320, 128)), ("down", (320, 128))))
+    cfg = synth.CONFIGS[name].scaled(L=1, V=1280, P=64, d=d, Hq=hq, Hkv=hkv, F=F, G=64)
+    g = torch.Generator(device=DEV).manual_seed(4)
+    rn = lambda *s: (torch.randn(s, generator=g, device=DEV) * 0.02).to(torch.bfloat16)
+    w = dict(wq=rn(hq * 128, d), wk=rn(hkv * 128, d), wv=rn(hkv * 128, d), wo=rn(d, hq * 128), w_gate=rn(F, d), w_up=rn(F, d),
+             w_down=rn(d, F), norm1=1 + rn(d), norm2=1 + rn(d))
+    if name == "c4":
+        w.update(bq=rn(hq * 128), bk=rn(hkv * 128), bv=rn(hkv * 128))
+    pk, pv = rn(hkv, 64, 128) * 50, rn(hkv, 64, 128) * 50
+    scfg, lw, pf = sp.cfg_from_synth(cfg), sp.layer_weights(w), sp.prefix_kv(pk, pv)
+    ws = sp.alloc_workspace(scfg, 64, 32, 64, DEV)
+    x = rn(64, 32, d) * 50
+    alone = torch.cat([sp.verify_layer(scfg, lw, pf, x[i:i + 1].contiguous(), 64, ws).clone() for i in range(max(todo.values()) // 32)])
+    for rows in sorted(set(todo.values())):
+        n = rows // 32
+        assert torch.equal(sp.verify_layer(scfg, lw, pf, x[:n].contiguous(), 64, ws), alone[:n]), \
+            [k for k, v in todo.items() if v == rows]
+
+
+@pytest.mark.parametrize("epi,M,N,K", [("resid", 1056, 4096, 1024), ("resid", 33, 384, 128), ("resid", 300, 2048, 5632),
+                                       ("swiglu", 352, 12288, 256), ("swiglu", 1024, 9440, 192), ("swiglu", 17, 96, 128)])
+def test_layer_gemm_equals_gemm(sp, epi, M, N, K):
+    g = torch.Generator(device=DEV).manual_seed(M)
+    rn = lambda *s: torch.randn(s, generator=g, device=DEV).to(torch.bfloat16)
+    A, W0, W1, R = rn(M, K), rn(N, K), rn(N, K), rn(M, N)
+    ws = torch.empty(4 * M * N * 4 + 256, dtype=torch.uint8, device=DEV)
+    args = (sp.GEMM_RESID, A, W0, None, R, None, ws) if epi == "resid" else (sp.GEMM_SWIGLU, A, W0, W1)
+    assert torch.equal(sp.layer_gemm(*args), sp.gemm(*args))
+
+
+def test_projections_of_a_pass_in_two_row_ranges(sp):
+    """608 block rows and 1024 suffix rows at 12288 columns: the rule launches the QKV projection once for either range, so the second
+    launch's rows have table rows and cache rows of their own.  Hidden rows and cache rows equal those of passes with the
+    true block, one other state and the same suffix, which are one launch."""
+    G, B, S, P = 19, 32, 1024, 40
+    cfg = synth.CONFIGS["c3"].scaled(L=1, F=512, V=1280, P=P, B=B, G=G)
+    N = (cfg.Hq + 2 * cfg.Hkv) * cfg.hd
+    assert len(sp.layer_gemm_plan(sp.GEMM_STORE, G * B, N, cfg.d, S)) == 2
+    assert len(sp.layer_gemm_plan(sp.GEMM_STORE, 2 * B, N, cfg.d, S)) == 1
+    scfg = sp.cfg_from_synth(cfg)
+    lw = [sp.layer_weights({k: v.to(DEV) for k, v in synth.layer_weights(cfg, 0).items()})]
+    hw = {k: v.to(DEV) for k, v in synth.head_weights(cfg).items()}
+    emb = synth.embed_weights(cfg).to(DEV)
+    g = torch.Generator().manual_seed(6)
+    kv0 = [torch.randn((cfg.Hkv, P + B + S + 2, cfg.hd), generator=g).to(torch.bfloat16).to(DEV) for _ in range(2)]
+    st = torch.from_numpy(synth.random_states(G, B, cfg.V, 0.2, 0.9, 7)).to(DEV)
+    suffix = torch.randint(0, cfg.V - 1, (S,), generator=g, dtype=torch.int32).to(DEV)
+
+    def run(tokens):
+        k, v = kv0[0].clone(), kv0[1].clone()
+        plan = sp.SeqStepPlan(scfg, lw, [sp.prefix_kv(k, v, P, 0)], emb, hw["final_norm"], hw["w_vocab"], tokens.shape[0], B, S, P,
+                              0.9, logit_scale=1.0, device=DEV)
+        return plan.run(tokens.contiguous(), suffix, None)["hidden"], k, v
+
+    hid, k, v = run(st)
+    for i in (1, 7, G - 1):
+        h2, k2, v2 = run(st[[0, i]])
+        assert torch.equal(k, k2) and torch.equal(v, v2), i
+        assert torch.equal(h2[:B], hid[:B]) and torch.equal(h2[B:2 * B], hid[i * B:(i + 1) * B]), i
+        assert torch.equal(h2[2 * B:], hid[G * B:]), i
+    assert not torch.equal(k, kv0[0])
 
 
 @pytest.mark.parametrize("d,G,B,masked", [(4096, 2, 7, "some"), (4096, 20, 32, "some"), (2048, 3, 33, "none"), (2048, 5, 24, "all"),
@@ -153,8 +229,9 @@ def test_head_rows_from_the_last_reduction(sp, d, G, B, masked):
 @pytest.mark.parametrize("M,N,K", [(40, 2056, 72), (33, 8200, 136), (200, 2056, 1032), (130, 3080, 264), (17, 24, 8), (260, 4104, 520)])
 def test_tile_gemm_shapes_by_rounds(sp, M, N, K, dtype):
     """32 x 16, 32 x 32 and 64 x 64 tiles, chosen by rounds of workgroups, last chunks of K cut to 8 .. 56 values and wavefronts
-    without a chunk; rows do not depend on the tile (the first 16 rows alone run in 16 x 16 tiles).  Bounds as for the edges of
-    the tiles: |sum - exact| <= (K + 16) 2^-24 sum |a w|, in bf16 plus one rounding of the result, 2^-8 relative."""
+    without a chunk; rows do not depend on the tile (the first 16 rows alone run in 16 x 16 tiles, as do the last).  Bounds as for the edges of
+    the tiles: |sum - exact| <= (K + 16) 2^-24 sum |a w|, in bf16 plus one rounding of the result, 2^-8 relative; SwiGLU with both
+    sums' errors propagated: |silu'| <= 1.1, |silu(g)| <= |g|, its exponential and division within 2^-20 relative."""
     td = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator().manual_seed(M + N + K)
     A, W0, W1 = ((torch.randn(s, generator=g) * f).to(td) for s, f in (((M, K), 1.0), ((N, K), 0.1), ((N, K), 0.1)))
@@ -166,7 +243,14 @@ def test_tile_gemm_shapes_by_rounds(sp, M, N, K, dtype):
     assert (np.abs(to_np(got) - ref) <= d0 + (out + eps) * np.abs(ref) + 1e-30).all()
     assert torch.equal(sp.gemm(sp.GEMM_STORE, dev[0][:16].contiguous(), dev[1]), got[:16])
     sw = sp.gemm(sp.GEMM_SWIGLU, *dev)
-    assert torch.equal(sp.gemm(sp.GEMM_SWIGLU, dev[0][:16].contiguous(), dev[1], dev[2]), sw[:16])
+    up, d1 = a @ w1.T, (K + 16) * eps * (np.abs(a) @ np.abs(w1).T)
+    silu = ref / (1 + np.exp(-ref))
+    err = 1.1 * d0 * (np.abs(up) + d1) + np.abs(silu) * d1 + 2.0 ** -19 * np.abs(silu * up)
+    assert (np.abs(to_np(sw) - silu * up) <= err + out * (np.abs(silu * up) + err) + 1e-30).all()
+    for lo, hi in ((0, 16), (M - 16, M)):
+        x = dev[0][lo:hi].contiguous()
+        assert torch.equal(sp.gemm(sp.GEMM_SWIGLU, x, dev[1], dev[2]), sw[lo:hi])
+        assert torch.equal(sp.gemm(sp.GEMM_STORE, x, dev[1]), got[lo:hi])
 
 
 @pytest.mark.parametrize("K", [200, 264, 2824])
