@@ -496,7 +496,7 @@ void launch_short(const GemmArgs& a, hipStream_t st) {
 // the other multiplies.  The small ones win while K is short or the large ones leave a round of 256 workgroups half empty; with
 // longer K the large ones' quarter of the traffic does (1024 columns of 2816, 1000 rows: 57 us, small 68; 11008 x 4104, 1000 rows
 // 845, 1076, SwiGLU 3000 rows 5548, 7715; 1536 x 1024, 1000 rows 47, 39).  Of 1700 shapes measured (512 .. 11008 columns, K = 200 .. 8192,
-// 256 .. 3500 large tiles) the line below is 1.1% over the better of both on average, large tiles alone 9%, small ones alone 5%.
+// 256 .. 3500 large tiles) the line below is 0.3% over the better of both on average, large tiles alone 9%, small ones alone 5%.
 // Below that 32 x 32 or 32 x 16 (SWIGLU: 16 features either way), by rounds of 256 workgroups: one of 32 x 32 takes as long as 1.6 of
 // 32 x 16 in bf16, 1.9 in fp32, and starts sooner (K = 1024, 32 x 16 / 32 x 32: fp32 64 x 2048 6.3 / 8.6, 64 x 3072 9.8 / 8.9, 64 x 4104
 // 13.4 / 15.4; bf16 64 x 1544 3.7 / 4.1, 128 x 1032 4.6 / 4.2, 128 x 2056 5.4 / 5.9).  16 x 16 with one fragment of rows.
@@ -520,8 +520,8 @@ hipError_t launch_epi(const GemmArgs& a, hipStream_t st) {
     if (big >= 256) return launch_tile<T, EPI, 4, 4>(a, st);
   const int rows = cdiv(a.M, 32), r16 = cdiv(rows * cdiv(a.N, 16), 256), r32 = cdiv(rows * cdiv(a.N, 32), 256);
   if constexpr (F32) {
-    const long long r64 = cdiv(big, 256), small = EPI == EPI_SWIGLU ? r16 : r32;      // rounds of either tile
-    if (big >= 256 && 57 * r64 * (a.K + 500) <= 20 * small * (a.K + 300)) return launch_tile<T, EPI, 4, 4, true>(a, st);
+    const float large = 0.7f * cdiv(big, 256) + 0.3f * (big / 256.f), small = EPI == EPI_SWIGLU ? r16 : r32;    // rounds of either tile
+    if (big >= 256 && 3.05f * large * (a.K + 800.f) <= small * (a.K + 400.f)) return launch_tile<T, EPI, 4, 4, true>(a, st);
   }
   if (a.M <= 16) return launch_tile<T, EPI, 1, EPI == EPI_SWIGLU ? 2 : 1>(a, st);
   if (EPI == EPI_SWIGLU || (F32 ? 19 * r32 - 2 < 10 * r16 : 16 * r32 < 10 * r16)) return launch_tile<T, EPI, 2, 2>(a, st);
