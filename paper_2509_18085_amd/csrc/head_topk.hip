@@ -116,10 +116,14 @@ __device__ __forceinline__ void dot_rows4<float>(const float* __restrict__ x, co
 // (50 MB): 55.9 us with a workgroup a chunk, 14.9 us with eight.  32 positions of 126464 tokens, us with one, two, four,
 // eight: K = 8, width 4096 64.0, 48.1, 48.7, 51.6; width 512 25.0, 24.8, 27.6, 33.0; 128 positions, K = 8, width 512 35.6, 47.0, 51.7,
 // 70.4.  Over 152 shapes measured (V 130 .. 262144, width 256 .. 8192) this is 1.1% over the best, eight throughout 9%.
+// A workgroup a chunk where 400 .. 512 of them fill one round of two a CU, and for more than 640 (every position masked, us with one
+// and with two: 448 chunks of width 3584 72.6 and 75.7, 256 x 2 81.8 and 93.7; 80 x 5 of width 4096 77.4 and 83.0, of 5120 81.6 and 89.0;
+// 96 x 8 of 5120 147.0 and 151.7).
 inline int refine_slices(int B, int K, int d) {
-  const int limit = d < 7168 ? 256 + d / 4 : 2048;
+  const int chunks = B * K, limit = d < 7168 ? 256 + d / 4 : 2048;
+  if (d < 7168 && ((chunks >= 400 && chunks <= 512) || chunks > 640)) return 1;
   int n = 8;
-  while (n > 1 && B * K * n > limit) n /= 2;
+  while (n > 1 && chunks * n > limit) n /= 2;
   return n;
 }
 template <typename T>
