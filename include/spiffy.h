@@ -217,7 +217,9 @@ int spiffy_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t 
  * measured costs): SPIFFY_GEMM_STORE the fused q | k | v projection (N = all its columns, heads of 128), SPIFFY_GEMM_RESID
  * the output and down projections, SPIFFY_GEMM_SWIGLU gate and up (N features).  M = G*B rows and M_tail rows that ride
  * along (suffix or finished block; 0 without): plans [2], *n_ranges = 1 for one launch sequence over all M + M_tail rows,
- * 2 for one over either.  Host arithmetic only.  Status as for spiffy_gemm_plan. */
+ * 2 for one over either.  M_tail = SPIFFY_TAIL_MASKED: the projections behind the attention of a last layer that computes
+ * masked rows only, some of M rows.  Host arithmetic only.  Status as for spiffy_gemm_plan. */
+#define SPIFFY_TAIL_MASKED (-2)
 int spiffy_layer_gemm_plan(int32_t epilogue, int32_t M, int32_t M_tail, int32_t N, int32_t K,
                            spiffy_gemm_plan_t *plans, int32_t *n_ranges);
 

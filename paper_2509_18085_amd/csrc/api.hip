@@ -285,6 +285,7 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   int rc;
   auto mfma_rows = [&](Projection which, int epi, const GemmArgs& ga) {
     RowsPlan alone = {};
+    if (ga.M_dev) return launch_gemm_plan(epi, ga, plan_gemm_masked(epi, ga.M, ga.N, ga.K, ga.ksplit), st);
     RowsPlan& plan = chain ? chain->plans[which] : alone;
     if (plan.n_ranges == 0) plan = plan_gemm_rows(epi, G * B, S_seq, ga.N, ga.K, ga.ksplit);
     return launch_gemm_rows(epi, ga, plan, G * B, S_seq, dt, st);
@@ -720,12 +721,14 @@ int spiffy_gemm_plan(int32_t epilogue, int32_t M, int32_t N, int32_t K, int32_t 
 int spiffy_layer_gemm_plan(int32_t epilogue, int32_t M, int32_t M_tail, int32_t N, int32_t K, spiffy_gemm_plan_t* plans,
                            int32_t* n_ranges) {
   if (!plans || !n_ranges || epilogue < SPIFFY_GEMM_STORE || epilogue > SPIFFY_GEMM_SWIGLU) return SPIFFY_EINVAL;
+  const bool masked = M_tail == SPIFFY_TAIL_MASKED;
+  if (masked) M_tail = 0;
   if (M < 1 || M_tail < 0 || M > INT32_MAX - M_tail || N < 1 || K < 1) return SPIFFY_ESHAPE;
   if (!mfma_gemm_supported(epilogue, gemm_shape(epilogue, M + M_tail, N, K))) return SPIFFY_ESHAPE;
   if (epilogue == SPIFFY_GEMM_STORE && N % 128 != 0) return SPIFFY_ESHAPE;       // heads of 128 columns
   int epi = epilogue == SPIFFY_GEMM_STORE ? EPI_QKV : epilogue, ks = 1;
   if (epilogue == SPIFFY_GEMM_RESID && mfma_ksplit(N, K) > 1) { epi = EPI_PARTIAL; ks = mfma_ksplit(N, K); }
-  const RowsPlan p = plan_gemm_rows(epi, M, M_tail, N, K, ks);
+  const RowsPlan p = masked ? RowsPlan{1, {plan_gemm_masked(epi, M, N, K, ks)}} : plan_gemm_rows(epi, M, M_tail, N, K, ks);
   *n_ranges = p.n_ranges;
   for (int i = 0; i < p.n_ranges; ++i) {
     if (!plan_has_kernels(epi, p.range[i])) return SPIFFY_EDEVICE;

@@ -30,6 +30,7 @@ EXPORTS = ["spiffy_status_str", "spiffy_uses_mfma", "spiffy_workspace_bytes", "s
            "spiffy_verify_step_commit", "spiffy_decode_head_static", "spiffy_gemm_plan", "spiffy_layer_gemm_plan",
            "spiffy_layer_gemm"]
 GEMM_STORE, GEMM_RESID, GEMM_SWIGLU = 0, 1, 2
+TAIL_MASKED = -2
 
 
 class ModelCfg(C.Structure):
@@ -328,7 +329,8 @@ def gemm_plan(epilogue: int, M: int, N: int, K: int, with_workspace: bool = True
 
 def layer_gemm_plan(epilogue: int, M: int, N: int, K: int, M_tail: int = 0) -> List[dict]:
     """The launches verify_layer and the steps use for that projection over M rows and M_tail rows that ride along: one plan
-    for all of them, or one for either (host arithmetic, no device)."""
+    for all of them, or one for either (host arithmetic, no device).  M_tail = TAIL_MASKED: a last layer that computes the masked of
+    the M rows."""
     p, n = (GemmPlan * 2)(), C.c_int32(0)
     _check(lib.spiffy_layer_gemm_plan(epilogue, M, M_tail, N, K, p, C.byref(n)), "spiffy_layer_gemm_plan")
     return [_plan_dict(x) for x in p[:n.value]]

@@ -497,6 +497,27 @@ def test_layer_gemm_plans_cover_rows_and_columns_in_compiled_tiles():
     assert {t[1:] for t in seen} == tiles
 
 
+def test_plans_of_masked_rows_hold_for_few_of_them():
+    """A last layer that computes masked rows only: how many of its rows are in use is not known when it is launched.  Beyond 512
+    rows no tile is taller than the general rule's, which few rows would pay for in full, and any other plan is one launch."""
+    other = 0
+    for epi, N, K in LAYER_SHAPES:
+        if epi == sp.GEMM_STORE:
+            continue
+        for M in list(range(1, 400, 9)) + list(range(400, 2200, 37)) + [512, 513, 1024, 1280, 1536, 2048, 2049, 3000, 4096, 16384]:
+            plan, = sp.layer_gemm_plan(epi, M, N, K, sp.TAIL_MASKED)
+            layer, general = sp.layer_gemm_plan(epi, M, N, K)[0], sp.gemm_plan(epi, M, N, K)
+            assert plan["k_slices"] == general["k_slices"] and sum(l["n_cols"] for l in plan["launches"]) == N
+            if M <= 512:
+                assert plan == layer, (epi, M, N, K)
+                continue
+            tallest = lambda p: max(l["tile"][0] for l in p["launches"])
+            assert tallest(plan) <= tallest(general), (epi, M, N, K, plan, general)
+            assert plan == general or len(plan["launches"]) == 1
+            other += plan != layer
+    assert other > 0                      # the rule for all rows does take taller ones
+
+
 def test_layer_gemm_plan_errors():
     p, n = (sp.GemmPlan * 2)(), C.c_int32(0)
     f = sp.lib.spiffy_layer_gemm_plan
