@@ -374,8 +374,9 @@
 
   if (EPI == EPI_QKV) {
     // columns 0 .. 15 of a 32-column block are columns c of a head, 16 .. 31 the columns c + 64 that rotate with them.
-    // No more than the plain store took (1024 rows: 85 us, 256 rows: 41) and off the attention kernel, which rotated queries
-    // and own keys in front of its first product, one wavefront at a time (3 us), and a launch of its own for the cache (5).
+    // The launch takes 0.3 - 2.6 us more than with the plain store (1024 rows of 4096 88.0 -> 90.6, 768 rows of 3584 38.7 -> 40.9, 256
+    // rows 43.7 -> 44.0).  It pays through the attention kernel, which rotated queries and own keys in front of its first product,
+    // one wavefront at a time (3 us), and the launch of its own that extended the cache (5 us).
     const QkvArgs& q = a.qkv;
     auto seg_of = [&](int n0) { return n0 < a.Nseg[0] ? 0 : (n0 < a.Nseg[0] + a.Nseg[1] ? 1 : 2); };
     auto col_of = [&](int n0) { const int s = seg_of(n0); return n0 - (s == 0 ? 0 : (s == 1 ? a.Nseg[0] : a.Nseg[0] + a.Nseg[1])); };
