@@ -284,8 +284,8 @@ int run_layer(const spiffy_model_cfg* cfg, const spiffy_layer_weights* w, const 
   const LayerWs ws = carve_layer(cfg, G, B, prefix->P + prefix->S, workspace, S_seq);
   int rc;
   auto mfma_rows = [&](Projection which, int epi, const GemmArgs& ga) {
+    if (ga.M_dev && ga.M > kMaskedLikeLayerRows) return launch_gemm_plan(epi, ga, plan_gemm_masked(epi, ga.M, ga.N, ga.K, ga.ksplit), st);
     RowsPlan alone = {};
-    if (ga.M_dev) return launch_gemm_plan(epi, ga, plan_gemm_masked(epi, ga.M, ga.N, ga.K, ga.ksplit), st);
     RowsPlan& plan = chain ? chain->plans[which] : alone;
     if (plan.n_ranges == 0) plan = plan_gemm_rows(epi, G * B, S_seq, ga.N, ga.K, ga.ksplit);
     return launch_gemm_rows(epi, ga, plan, G * B, S_seq, dt, st);

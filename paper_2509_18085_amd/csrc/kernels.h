@@ -134,7 +134,9 @@ struct GemmPlan {
 GemmPlan plan_gemm_mfma(int epi, int M, int N, int ksplit);
 // the same for the projections of a layer: more tile heights, chosen by measured costs
 GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_us = nullptr);
-GemmPlan plan_gemm_masked(int epi, int M, int N, int K, int ksplit);      // ... of which M_dev rows are in use
+// ... of which M_dev rows are in use; up to kMaskedLikeLayerRows the same plan
+constexpr int kMaskedLikeLayerRows = 512;
+GemmPlan plan_gemm_masked(int epi, int M, int N, int K, int ksplit);
 // ... over rows_a rows and rows_b behind them, in one launch sequence or one for either
 struct RowsPlan { int n_ranges; GemmPlan range[2]; };
 RowsPlan plan_gemm_rows(int epi, int rows_a, int rows_b, int N, int K, int ksplit);

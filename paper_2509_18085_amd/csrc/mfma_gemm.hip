@@ -347,7 +347,7 @@ GemmPlan plan_gemm_layer(int epi, int M, int N, int K, int ksplit, float* cost_u
 // layers of 513 .. 2048 rows (five models, 5 .. 100% of the rows masked), against plan_gemm_mfma's: 2.1% less on average, 1.6% more at
 // most; plan_gemm_layer's 2.2% less, 32% more at most.  Up to 512 rows, 2,068 layers, that one is 2.9% less, 4.8% more at most.
 GemmPlan plan_gemm_masked(int epi, int M, int N, int K, int ksplit) {
-  if (M <= 512) return plan_gemm_layer(epi, M, N, K, ksplit);
+  if (M <= kMaskedLikeLayerRows) return plan_gemm_layer(epi, M, N, K, ksplit);
   const GemmPlan general = plan_gemm_mfma(epi, M, N, ksplit);
   if (epi != EPI_PARTIAL && epi != EPI_SWIGLU) return general;
   if (ksplit < 1) ksplit = 1;
